@@ -25,6 +25,7 @@ SOURCES = [
     "kernels_batch.hip",
     "surrogate.cpp",
     "kernels_surrogate.hip",
+    "kernels_surrogate_bwd.hip",
     "noalloc.hip",
     "kernels_eig.hip",
     "kernels_surrogate_bf16.hip",

@@ -1,277 +1,16 @@
-// Kernels of the spectral-convolution surrogate: one strided, batched GEMM
-// for every linear step (pointwise channel maps, truncated DFTs, per-mode
-// complex mixing, and their transposes in the backward pass), elementwise
-// bias / GELU / loss kernels, and the Adam update.
+// Kernels of the spectral-convolution surrogate: the lift, the fused halves of
+// a Fourier layer and its per-mode mixing, the head and the Adam update. The
+// FP32 backward pass runs the same kernels with the adjoint tables and
+// weights (the remaining backward kernels are in kernels_surrogate_bwd.hip).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 
 #include "scw_internal.h"
+#include "surrogate_device.h"
 
 namespace scw {
 namespace {
-
-struct f2 {
-  float x, y;
-};
-
-// C[b] = op(A[b]) . op(B[b]) (+ beta C[b]). Operands are real or complex
-// (interleaved); strides are in elements of the operand's type. The result is
-// complex, or its real part. Tile 32x32, 256 threads (2x2 outputs each),
-// K staged through LDS in steps of 16.
-constexpr int TM = 32, TN = 32, TK = 16;
-
-__global__ void __launch_bounds__(256) gemm_kernel(GemmOp op) {
-  __shared__ f2 As[TK][TM + 1];
-  __shared__ f2 Bs[TK][TN + 1];
-  const int b = blockIdx.y;
-  const int ntn = (op.N + TN - 1) / TN;
-  const int m0 = (blockIdx.x / ntn) * TM, n0 = (blockIdx.x % ntn) * TN;
-  const int tx = threadIdx.x % 16, ty = threadIdx.x / 16;
-  const float* A = op.A + (long long)b * op.a_bs * (op.a_cplx ? 2 : 1);
-  const float* B = op.B + (long long)b * op.b_bs * (op.b_cplx ? 2 : 1);
-  f2 acc[2][2] = {{{0.f, 0.f}, {0.f, 0.f}}, {{0.f, 0.f}, {0.f, 0.f}}};
-  const float ca = op.conj_a ? -1.f : 1.f, cb = op.conj_b ? -1.f : 1.f;
-  for (int k0 = 0; k0 < op.K; k0 += TK) {
-    for (int i = threadIdx.x; i < TM * TK; i += 256) {
-      const int r = i / TK, k = i % TK;
-      const int gm = m0 + r, gk = k0 + k;
-      f2 v = {0.f, 0.f};
-      if (gm < op.M && gk < op.K) {
-        const long long o = (long long)gm * op.a_rs + (long long)gk * op.a_cs;
-        if (op.a_cplx) v = {A[2 * o], ca * A[2 * o + 1]};
-        else v = {A[o], 0.f};
-      }
-      As[k][r] = v;
-    }
-    for (int i = threadIdx.x; i < TK * TN; i += 256) {
-      const int k = i / TN, c = i % TN;
-      const int gk = k0 + k, gn = n0 + c;
-      f2 v = {0.f, 0.f};
-      if (gk < op.K && gn < op.N) {
-        const long long o = (long long)gk * op.b_rs + (long long)gn * op.b_cs;
-        if (op.b_cplx) v = {B[2 * o], cb * B[2 * o + 1]};
-        else v = {B[o], 0.f};
-      }
-      Bs[k][c] = v;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < TK; ++k) {
-      const f2 a0 = As[k][ty], a1 = As[k][ty + 16];
-      const f2 b0 = Bs[k][tx], b1 = Bs[k][tx + 16];
-#define CMA(acc, a, bb)                                \
-  acc.x = fmaf(a.x, bb.x, fmaf(-a.y, bb.y, acc.x));     \
-  acc.y = fmaf(a.x, bb.y, fmaf(a.y, bb.x, acc.y));
-      CMA(acc[0][0], a0, b0) CMA(acc[0][1], a0, b1) CMA(acc[1][0], a1, b0) CMA(acc[1][1], a1, b1)
-#undef CMA
-    }
-    __syncthreads();
-  }
-  float* C = op.C + (long long)b * op.c_bs * (op.c_cplx ? 2 : 1);
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int gm = m0 + ty + 16 * i, gn = n0 + tx + 16 * j;
-      if (gm >= op.M || gn >= op.N) continue;
-      const long long o = (long long)gm * op.c_rs + (long long)gn * op.c_cs;
-      if (op.c_cplx) {
-        float re = acc[i][j].x, im = acc[i][j].y;
-        if (op.beta != 0.f) {
-          re += op.beta * C[2 * o];
-          im += op.beta * C[2 * o + 1];
-        }
-        C[2 * o] = re;
-        C[2 * o + 1] = im;
-      } else {
-        float re = acc[i][j].x;
-        if (op.beta != 0.f) re += op.beta * C[o];
-        C[o] = re;
-      }
-    }
-}
-
-// The same product on the matrix cores with BF16 operands and FP32
-// accumulation: every operand element is rounded to bf16 (nearest even) as it
-// is staged in LDS. Block tile 64 x 64, four waves of 32 x 32, K steps of 16
-// (v_mfma_f32_32x32x16_bf16). A complex product takes four MFMAs per step:
-//   Re C += Re A Re B + (-Im A) Im B,   Im C += Re A Im B + Im A Re B,
-// with conjugation applied to the imaginary parts as they are staged.
-// MFMA lane layout (one wave, 32 x 32 x 16): lane l holds A[l % 32][8 (l / 32)
-// + 0..7] and B[8 (l / 32) + 0..7][l % 32]; accumulator r of lane l is
-// D[8 (r / 4) + 4 (l / 32) + r % 4][l % 32].
-typedef float floatx16 __attribute__((ext_vector_type(16)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-
-constexpr int BM = 64, BN = 64, BK = 16, LROW = 24;  // LDS row: 16 k + 8 pad (bf16)
-
-__global__ void __launch_bounds__(256) gemm_bf16_kernel(GemmOp op) {
-  __shared__ __attribute__((aligned(16))) __bf16 As[2][BM * LROW];  // [re|im][row][k]
-  __shared__ __attribute__((aligned(16))) __bf16 Bs[2][BN * LROW];  // [re|im][col][k]
-  const int b = blockIdx.y;
-  const int ntn = (op.N + BN - 1) / BN;
-  const int m0 = (blockIdx.x / ntn) * BM, n0 = (blockIdx.x % ntn) * BN;
-  const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
-  const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
-  const float* A = op.A + (long long)b * op.a_bs * (op.a_cplx ? 2 : 1);
-  const float* B = op.B + (long long)b * op.b_bs * (op.b_cplx ? 2 : 1);
-  const float ca = op.conj_a ? -1.f : 1.f, cb = op.conj_b ? -1.f : 1.f;
-  floatx16 cre = {0}, cim = {0};
-  const int li = lane & 31, lk = 8 * (lane >> 5);
-  for (int k0 = 0; k0 < op.K; k0 += BK) {
-    // stage: 64 x 16 of A and 16 x 64 of B, four elements per thread each
-    // consecutive threads walk the operand's contiguous index where it has one
-    const bool a_kfast = op.a_cs == 1, b_kfast = op.b_rs == 1;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int i = t + 256 * e;
-      const int r = a_kfast ? i / BK : i % BM, k = a_kfast ? i % BK : i / BM;
-      const int gm = m0 + r, gk = k0 + k;
-      float re = 0.f, im = 0.f;
-      if (gm < op.M && gk < op.K) {
-        const long long o = (long long)gm * op.a_rs + (long long)gk * op.a_cs;
-        if (op.a_cplx) {
-          re = A[2 * o];
-          im = ca * A[2 * o + 1];
-        } else {
-          re = A[o];
-        }
-      }
-      As[0][r * LROW + k] = (__bf16)re;
-      As[1][r * LROW + k] = (__bf16)im;
-      const int c = b_kfast ? i / BK : i % BN, kb = b_kfast ? i % BK : i / BN;
-      const int gn = n0 + c, gkb = k0 + kb;
-      float bre = 0.f, bim = 0.f;
-      if (gn < op.N && gkb < op.K) {
-        const long long o = (long long)gkb * op.b_rs + (long long)gn * op.b_cs;
-        if (op.b_cplx) {
-          bre = B[2 * o];
-          bim = cb * B[2 * o + 1];
-        } else {
-          bre = B[o];
-        }
-      }
-      Bs[0][c * LROW + kb] = (__bf16)bre;
-      Bs[1][c * LROW + kb] = (__bf16)bim;
-    }
-    __syncthreads();
-    const u32x4 ar = *reinterpret_cast<const u32x4*>(&As[0][(wm + li) * LROW + lk]);
-    const u32x4 br = *reinterpret_cast<const u32x4*>(&Bs[0][(wn + li) * LROW + lk]);
-    cre = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ar),
-                                                  __builtin_bit_cast(bf16x8, br), cre, 0, 0, 0);
-    if (op.b_cplx) {
-      const u32x4 bi = *reinterpret_cast<const u32x4*>(&Bs[1][(wn + li) * LROW + lk]);
-      cim = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ar),
-                                                    __builtin_bit_cast(bf16x8, bi), cim, 0, 0, 0);
-      if (op.a_cplx) {
-        const u32x4 ai = *reinterpret_cast<const u32x4*>(&As[1][(wm + li) * LROW + lk]);
-        const u32x4 nai = ai ^ 0x80008000u;  // -Im A: flip every bf16 sign
-        cre = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, nai),
-                                                      __builtin_bit_cast(bf16x8, bi), cre, 0, 0, 0);
-        cim = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ai),
-                                                      __builtin_bit_cast(bf16x8, br), cim, 0, 0, 0);
-      }
-    } else if (op.a_cplx) {
-      const u32x4 ai = *reinterpret_cast<const u32x4*>(&As[1][(wm + li) * LROW + lk]);
-      cim = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ai),
-                                                    __builtin_bit_cast(bf16x8, br), cim, 0, 0, 0);
-    }
-    __syncthreads();
-  }
-  float* C = op.C + (long long)b * op.c_bs * (op.c_cplx ? 2 : 1);
-#pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const int gm = m0 + wm + 8 * (r / 4) + 4 * (lane >> 5) + (r % 4);
-    const int gn = n0 + wn + li;
-    if (gm >= op.M || gn >= op.N) continue;
-    const long long o = (long long)gm * op.c_rs + (long long)gn * op.c_cs;
-    if (op.c_cplx) {
-      float re = cre[r], im = cim[r];
-      if (op.beta != 0.f) {
-        re += op.beta * C[2 * o];
-        im += op.beta * C[2 * o + 1];
-      }
-      C[2 * o] = re;
-      C[2 * o + 1] = im;
-    } else {
-      float re = cre[r];
-      if (op.beta != 0.f) re += op.beta * C[o];
-      C[o] = re;
-    }
-  }
-}
-
-// d GELU / dz for the backward pass (exact erf)
-__device__ __forceinline__ float gelu_grad_f(float z) {
-  return 0.5f * (1.f + erff(z * 0.70710678118654752f)) +
-         z * expf(-0.5f * z * z) * 0.39894228040143268f;
-}
-
-__global__ void gelu_bwd(const float* z, float* g, long long n) {
-  long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) g[i] *= gelu_grad_f(z[i]);
-}
-
-// out[c][k] = sum_b in[b][c][k] (reduction over the batch index)
-__global__ void sum_batch(const float* in, float* out, int B, long long per) {
-  long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= per) return;
-  float s = 0.f;
-  for (int b = 0; b < B; ++b) s += in[(long long)b * per + i];
-  out[i] = s;
-}
-
-// bias gradient: out[c] = sum_{b,p} g[b][c][p]; one block per channel
-__global__ void bias_grad(const float* g, float* out, int B, int C, int P) {
-  __shared__ float red[256];
-  const int c = blockIdx.x;
-  float s = 0.f;
-  for (long long i = threadIdx.x; i < (long long)B * P; i += 256) {
-    const long long b = i / P, p = i % P;
-    s += g[(b * C + c) * P + p];
-  }
-  red[threadIdx.x] = s;
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) out[c] = red[0];
-}
-
-// sums[0] = sum |out - tgt|^2, sums[1] = sum |tgt|^2 (complex64 arrays of n)
-__global__ void loss_sums(const float* out, const float* tgt, long long n, float* sums) {
-  __shared__ float r0[256], r1[256];
-  float a = 0.f, b = 0.f;
-  for (long long i = threadIdx.x; i < n; i += 256) {
-    const float dx = out[2 * i] - tgt[2 * i], dy = out[2 * i + 1] - tgt[2 * i + 1];
-    a += dx * dx + dy * dy;
-    b += tgt[2 * i] * tgt[2 * i] + tgt[2 * i + 1] * tgt[2 * i + 1];
-  }
-  r0[threadIdx.x] = a;
-  r1[threadIdx.x] = b;
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if (threadIdx.x < w) {
-      r0[threadIdx.x] += r0[threadIdx.x + w];
-      r1[threadIdx.x] += r1[threadIdx.x + w];
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    sums[0] = r0[0];
-    sums[1] = r1[0];
-  }
-}
-
-// g = 2 (out - tgt) / sum |tgt|^2
-__global__ void loss_grad(const float* out, const float* tgt, const float* sums, float* g,
-                          long long n2) {
-  long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n2) g[i] = 2.f * (out[i] - tgt[i]) / sums[1];
-}
 
 __global__ void adam(float* p, const float* g, float* m, float* v, long long n, float lr,
                      float b1, float b2, float eps, float c1, float c2) {
@@ -296,18 +35,6 @@ __global__ void adam(float* p, const float* g, float* m, float* v, long long n, 
 // With BF16, both operands of every product are rounded to bf16 (nearest
 // even) first, as the matrix-core products of the unfused path round them;
 // sums stay FP32.
-constexpr int SN = 32, SKY = 17, SKX = 9, SNM = SKY * SKX, SW = 32;
-
-__device__ __forceinline__ float rbf(float x) {  // round to bf16, nearest even
-  unsigned u = __float_as_uint(x);
-  u = (u + 0x7FFFu + ((u >> 16) & 1u)) & 0xFFFF0000u;
-  return __uint_as_float(u);
-}
-template <bool BF16>
-__device__ __forceinline__ float op(float x) { return BF16 ? rbf(x) : x; }
-template <bool BF16>
-__device__ __forceinline__ f2 op(f2 x) { return BF16 ? f2{rbf(x.x), rbf(x.y)} : x; }
-
 // Truncated forward DFT of 8 channels of one patch per block:
 //   out[b][i][ky][kx] = sum_y fy[ky][y] sum_x h[b][i][y][x] fx[x][kx]
 // (KY x KX modes; fy is [KY][32], fx is [32][KX], both complex). Grid (4, B),
@@ -478,7 +205,19 @@ __device__ __forceinline__ float gelu_fwd_f(float z) {
 // conjugates of those of y.
 // One patch per block of 8 waves; wave w takes slot w of each group, and its
 // pixel loads for the next group are issued once the current ones are used.
-constexpr int INVM_T = 512, GYS = 19;  // gy row stride (floats), odd against bank conflicts
+// Grid (B, splits): a block runs 4 / splits of the four row groups, so that a
+// batch of few patches still reaches many CUs (each block stages G again).
+//
+// The same kernel is the adjoint of the forward half in the FP32 backward
+// pass, because the adjoint of a truncated DFT is an inverse transform with
+// conjugate tables:
+//   INV_ADJOINT  out[b][i] = (Re fy^H gH fx^H + sum_o pw[i][o] gz[b][o]) GELU'(zp)
+//                (G = gH, h = gz, the weights read transposed, no bias; zp is
+//                the previous layer's pre-activation, or null for the lift)
+//   INV_HEAD     out[b][i] = Re hy^H gF hx^H with gF[b][m][i] =
+//                sum_c gout[b][c][m] conj(head[i][c][m]) formed while staging
+constexpr int INVM_T = 512;
+enum { INV_LAYER = 0, INV_ADJOINT = 1, INV_HEAD = 2 };
 // The image rows of group k (0..3), slot w (0..7): conjugate pairs (y, 32 - y)
 // in slots w and w + 4, y = 4k + 1 + (w mod 4); the last group's slots 3 and
 // 7 hold the self-paired rows 0 and 16.
@@ -487,48 +226,73 @@ __device__ __forceinline__ int inv_row(int k, int w) {
   if (k == 3 && (w & 3) == 3) return w < 4 ? 0 : SN / 2;
   return w < 4 ? base : SN - base;
 }
-template <bool BF16>
+template <bool BF16, int MODE>
 __global__ void __launch_bounds__(INVM_T) __attribute__((amdgpu_waves_per_eu(4)))
 fused_dft_inv_mfma(
     const f2* __restrict__ G, const float* __restrict__ h, const f2* __restrict__ iy,
     const f2* __restrict__ ix, const float* __restrict__ pw, const float* __restrict__ pb,
-    float* __restrict__ z_out, float* __restrict__ h_out, int apply_gelu) {
-  __shared__ f2 gsm[SNM][SW];            // the patch's G, [mode][o]
-  __shared__ f2 iys[SN * SKY];           // [y][ky]
-  __shared__ float gyl[8][SW][GYS];      // [row of the group][o][kx re | kx im]
+    float* __restrict__ z_out, float* __restrict__ h_out, int apply_gelu,
+    const float* __restrict__ zp) {
+  constexpr int KY = MODE == INV_HEAD ? 15 : SKY, KX = MODE == INV_HEAD ? 15 : SKX;
+  constexpr int GYS = 2 * KX + 1;         // gy row stride (floats), odd against bank conflicts
+  constexpr int GS = MODE == INV_HEAD ? SW + 1 : SW;  // the head writes gsm along modes
+  __shared__ f2 gsm[KY * KX][GS];         // the patch's G, [mode][o]
+  __shared__ f2 iys[SN * KY];             // [y][ky]
+  __shared__ float gyl[8][SW][GYS];       // [row of the group][o][kx re | kx im]
   const int t = threadIdx.x, wave = t >> 6, lane = t & 63, li = lane & 31, lh = lane >> 5;
   const int b = blockIdx.x;
-  const f2* gb = G + (long long)b * SNM * SW;
-  for (int i = t; i < SNM * SW; i += INVM_T) (&gsm[0][0])[i] = op<BF16>(gb[i]);
-  for (int i = t; i < SN * SKY; i += INVM_T) iys[i] = op<BF16>(iy[i]);
+  const int groups = (SN / 8) / gridDim.y, g0 = blockIdx.y * groups;
+  if constexpr (MODE == INV_HEAD) {
+    constexpr int NMODE = KY * KX, OUT = 3;
+    const f2* go = G + (long long)b * OUT * NMODE;        // gout[b]
+    const f2* wh = reinterpret_cast<const f2*>(pw);       // head[i][c][m]
+    for (int i = t; i < NMODE * SW; i += INVM_T) {
+      const int m = i % NMODE, ch = i / NMODE;
+      f2 s = {0.f, 0.f};
+#pragma unroll
+      for (int c = 0; c < OUT; ++c) {
+        const f2 a = go[c * NMODE + m], w = wh[(ch * OUT + c) * NMODE + m];
+        s.x = fmaf(a.x, w.x, fmaf(a.y, w.y, s.x));
+        s.y = fmaf(a.y, w.x, fmaf(-a.x, w.y, s.y));
+      }
+      gsm[m][ch] = s;
+    }
+  } else {
+    const f2* gb = G + (long long)b * SNM * SW;
+    for (int i = t; i < SNM * SW; i += INVM_T) (&gsm[0][0])[i] = op<BF16>(gb[i]);
+  }
+  for (int i = t; i < SN * KY; i += INVM_T) iys[i] = op<BF16>(iy[i]);
   // fixed operands: A = pw^T (row o = li, k = i), B = row-transform twiddles
-  // (k' < 9: Re ix[k'][x], else -Im ix[k' - 9][x]; column x = li)
-  float pwa[SW / 2], ixb[SKX];
+  // (k' < KX: Re ix[k'][x], else -Im ix[k' - KX][x]; column x = li)
+  float pwa[SW / 2], ixb[KX];
+  if constexpr (MODE != INV_HEAD)
 #pragma unroll
-  for (int s = 0; s < SW / 2; ++s) pwa[s] = op<BF16>(pw[(2 * s + lh) * SW + li]);
+    for (int s = 0; s < SW / 2; ++s)
+      pwa[s] = op<BF16>(MODE == INV_LAYER ? pw[(2 * s + lh) * SW + li] : pw[li * SW + 2 * s + lh]);
 #pragma unroll
-  for (int s = 0; s < SKX; ++s) {
+  for (int s = 0; s < KX; ++s) {
     const int k = 2 * s + lh;
-    ixb[s] = k < SKX ? op<BF16>(ix[k * SN + li]).x : -op<BF16>(ix[(k - SKX) * SN + li]).y;
+    ixb[s] = k < KX ? op<BF16>(ix[k * SN + li]).x : -op<BF16>(ix[(k - KX) * SN + li]).y;
   }
   const float* hb = h + (long long)b * SW * SN * SN;
   // this wave's pixels of its row: B operand of the pointwise part (k = i);
   // the next row's are loaded as soon as the current ones are consumed
   float hv[SW / 2];
+  if constexpr (MODE != INV_HEAD)
 #pragma unroll
-  for (int s = 0; s < SW / 2; ++s) hv[s] = hb[((2 * s + lh) * SN + inv_row(0, wave)) * SN + li];
-  for (int yc = 0; yc < SN / 8; ++yc) {
+    for (int s = 0; s < SW / 2; ++s) hv[s] = hb[((2 * s + lh) * SN + inv_row(g0, wave)) * SN + li];
+  for (int yc = g0; yc < g0 + groups; ++yc) {
     const int y = inv_row(yc, wave);
     __syncthreads();  // G staged (first group) / the previous group's gy consumed
     // column transform of the group's 4 row pairs: items (pair, kx, o), o fastest
-    for (int it = t; it < 4 * SKX * SW; it += INVM_T) {
-      const int o = it % SW, kx = (it / SW) % SKX, pr = it / (SW * SKX);
+    for (int it = t; it < 4 * KX * SW; it += INVM_T) {
+      const int o = it % SW, kx = (it / SW) % KX, pr = it / (SW * KX);
       const int ya = inv_row(yc, pr), yb = inv_row(yc, pr + 4);
       float ra = 0.f, ia = 0.f, rb = 0.f, ib = 0.f;
       if (ya == 0) {  // rows 0 and 16
 #pragma unroll 4
-        for (int ky = 0; ky < SKY; ++ky) {
-          const f2 v = gsm[ky * SKX + kx][o], a = iys[ya * SKY + ky], c = iys[yb * SKY + ky];
+        for (int ky = 0; ky < KY; ++ky) {
+          const f2 v = gsm[ky * KX + kx][o], a = iys[ya * KY + ky], c = iys[yb * KY + ky];
           ra = fmaf(a.x, v.x, fmaf(-a.y, v.y, ra));
           ia = fmaf(a.x, v.y, fmaf(a.y, v.x, ia));
           rb = fmaf(c.x, v.x, fmaf(-c.y, v.y, rb));
@@ -537,8 +301,8 @@ fused_dft_inv_mfma(
       } else {
         float ar = 0.f, ai = 0.f, br = 0.f, bi = 0.f;
 #pragma unroll
-        for (int ky = 0; ky < SKY; ++ky) {
-          const f2 v = gsm[ky * SKX + kx][o], a = iys[ya * SKY + ky];
+        for (int ky = 0; ky < KY; ++ky) {
+          const f2 v = gsm[ky * KX + kx][o], a = iys[ya * KY + ky];
           ar = fmaf(a.x, v.x, ar);
           ai = fmaf(a.x, v.y, ai);
           br = fmaf(a.y, v.y, br);
@@ -550,30 +314,38 @@ fused_dft_inv_mfma(
         ib = ai - bi;
       }
       gyl[pr][o][kx] = op<BF16>(ra);
-      gyl[pr][o][SKX + kx] = op<BF16>(ia);
+      gyl[pr][o][KX + kx] = op<BF16>(ia);
       gyl[pr + 4][o][kx] = op<BF16>(rb);
-      gyl[pr + 4][o][SKX + kx] = op<BF16>(ib);
+      gyl[pr + 4][o][KX + kx] = op<BF16>(ib);
     }
     __syncthreads();
     floatx16 acc = {0};
-#pragma unroll
-    for (int s = 0; s < SW / 2; ++s)
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(pwa[s], op<BF16>(hv[s]), acc, 0, 0, 0);
-    if (yc + 1 < SN / 8)  // rounded (BF16) where used, so the loads stay in flight
+    if constexpr (MODE != INV_HEAD) {
 #pragma unroll
       for (int s = 0; s < SW / 2; ++s)
-        hv[s] = hb[((2 * s + lh) * SN + inv_row(yc + 1, wave)) * SN + li];
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(pwa[s], op<BF16>(hv[s]), acc, 0, 0, 0);
+      if (yc + 1 < g0 + groups)  // rounded (BF16) where used, so the loads stay in flight
 #pragma unroll
-    for (int s = 0; s < SKX; ++s)
+        for (int s = 0; s < SW / 2; ++s)
+          hv[s] = hb[((2 * s + lh) * SN + inv_row(yc + 1, wave)) * SN + li];
+    }
+#pragma unroll
+    for (int s = 0; s < KX; ++s)
       acc = __builtin_amdgcn_mfma_f32_32x32x2f32(gyl[wave][li][2 * s + lh], ixb[s], acc, 0, 0, 0);
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const int o = 8 * (r / 4) + 4 * lh + (r % 4);
-      const float z = acc[r] + pb[o];
       const long long off = (((long long)b * SW + o) * SN + y) * SN + li;
-      if (z_out) z_out[off] = z;
-      if (apply_gelu) h_out[off] = gelu_fwd_f(z);
-      else if (h_out != z_out) h_out[off] = z;
+      if constexpr (MODE == INV_LAYER) {
+        const float z = acc[r] + pb[o];
+        if (z_out) z_out[off] = z;
+        if (apply_gelu) h_out[off] = gelu_fwd_f(z);
+        else if (h_out != z_out) h_out[off] = z;
+      } else if (MODE == INV_ADJOINT && zp) {
+        h_out[off] = acc[r] * gelu_grad_f(zp[off]);
+      } else {
+        h_out[off] = acc[r];
+      }
     }
   }
 }
@@ -621,8 +393,11 @@ __global__ void __launch_bounds__(256) mode_mix_head(const f2* __restrict__ A,
 // outputs per half-wave) and uses them for both halves of K; each half-wave
 // writes the 32 outputs of one (patch, mode), one 256-byte run. With BF16 the operands are
 // rounded to bf16 as they are read (their products are exact in FP32).
+// ADJ is the adjoint, out[b][m][i] = sum_o A[m][b][o] conj(Wm[m][i][o]): a lane
+// then takes channels o = 16 half + s in product s, so that its sixteen
+// weights are one 128-byte run of its row i of Wm.
 constexpr int MM_G = 4;
-template <bool BF16>
+template <bool BF16, bool ADJ>
 __global__ void __launch_bounds__(256) mode_mix_mm(const f2* __restrict__ A,
                                                    const f2* __restrict__ Wm, int nmode, int B,
                                                    f2* __restrict__ out) {
@@ -638,20 +413,28 @@ __global__ void __launch_bounds__(256) mode_mix_mm(const f2* __restrict__ A,
   __syncthreads();
   const int m = m0 + wave;
   if (m >= nmode) return;  // no barrier follows
-  const f2* wm = Wm + (long long)m * SW * SW + li;
+  const f2* wm = Wm + (long long)m * SW * SW;
   f2 wv[SW / 2];
 #pragma unroll
-  for (int s = 0; s < SW / 2; ++s) wv[s] = op<BF16>(wm[(2 * s + lh) * SW]);
+  for (int s = 0; s < SW / 2; ++s) {
+    if (ADJ) {
+      const f2 w = wm[li * SW + 16 * lh + s];
+      wv[s] = op<BF16>(f2{w.x, -w.y});
+    } else {
+      wv[s] = op<BF16>(wm[(2 * s + lh) * SW + li]);
+    }
+  }
+  auto kidx = [&](int s) { return ADJ ? 16 * lh + s : 2 * s + lh; };
   floatx16 cre = {0}, cim = {0};
 #pragma unroll
   for (int s = 0; s < SW / 2; ++s) {  // real parts of A
-    const float a = as[wave][li][2 * s + lh].x;
+    const float a = as[wave][li][kidx(s)].x;
     cre = __builtin_amdgcn_mfma_f32_32x32x2f32(a, wv[s].x, cre, 0, 0, 0);
     cim = __builtin_amdgcn_mfma_f32_32x32x2f32(a, wv[s].y, cim, 0, 0, 0);
   }
 #pragma unroll
   for (int s = 0; s < SW / 2; ++s) {  // imaginary parts of A
-    const float a = as[wave][li][2 * s + lh].y;
+    const float a = as[wave][li][kidx(s)].y;
     cre = __builtin_amdgcn_mfma_f32_32x32x2f32(a, -wv[s].y, cre, 0, 0, 0);
     cim = __builtin_amdgcn_mfma_f32_32x32x2f32(a, wv[s].x, cim, 0, 0, 0);
   }
@@ -664,14 +447,20 @@ __global__ void __launch_bounds__(256) mode_mix_mm(const f2* __restrict__ A,
 }
 
 // Mode-major copy of the layers' spectral weights: Wm[k][m][i][o] from
-// W_k[i][o][m] (layer k at W + k * layer_stride complex values).
-__global__ void spec_mode_major(const f2* __restrict__ W, long long layer_stride, int nmode,
-                                f2* __restrict__ Wm) {
-  const long long q = (long long)blockIdx.x * blockDim.x + threadIdx.x;  // (m, i, o), o fastest
-  if (q >= (long long)nmode * SW * SW) return;
-  const int k = blockIdx.y;
-  const int o = (int)(q % SW), i = (int)((q / SW) % SW), m = (int)(q / (SW * SW));
-  Wm[(long long)k * nmode * SW * SW + q] = W[k * layer_stride + ((long long)i * SW + o) * nmode + m];
+// W_k[i][o][m] (layer k at W + k * layer_stride complex values). A block takes
+// one (i, k): 32 x nmode values that are one run of W, turned in LDS and
+// written as nmode runs of 256 bytes. Grid (32, layers).
+__global__ void __launch_bounds__(512) spec_mode_major(const f2* __restrict__ W,
+                                                       long long layer_stride,
+                                                       f2* __restrict__ Wm) {
+  __shared__ f2 tile[SNM][SW + 1];
+  const int t = threadIdx.x, i = blockIdx.x, k = blockIdx.y;
+  const f2* src = W + k * layer_stride + (long long)i * SW * SNM;
+  for (int q = t; q < SW * SNM; q += 512) tile[q % SNM][q / SNM] = src[q];
+  __syncthreads();
+  f2* dst = Wm + ((long long)k * SNM * SW + i) * SW;
+  for (int q = t; q < SW * SNM; q += 512)
+    dst[(long long)(q / SW) * SW * SW + q % SW] = tile[q / SW][q % SW];
 }
 
 // The lift: h[b][o][p] = sum_c lw[c][o] x[b][c][p] + lb[o], 16 input and 32
@@ -723,47 +512,6 @@ inline unsigned blocks(long long n, int bs = 256) { return (unsigned)((n + bs - 
 
 }  // namespace
 
-hipError_t launch_gemm(const GemmOp& op, hipStream_t s) {
-  if (op.M <= 0 || op.N <= 0 || op.K <= 0 || op.batch <= 0) return hipSuccess;
-  const int tm = op.bf16 ? BM : TM, tn = op.bf16 ? BN : TN;
-  const long long tiles = (long long)((op.M + tm - 1) / tm) * ((op.N + tn - 1) / tn);
-  if (tiles > 0x7fffffffLL) return hipErrorInvalidValue;
-  // the batch runs on grid.y in chunks of at most 65535
-  for (int b0 = 0; b0 < op.batch; b0 += 65535) {
-    GemmOp c = op;
-    c.batch = std::min(65535, op.batch - b0);
-    c.A += (long long)b0 * op.a_bs * (op.a_cplx ? 2 : 1);
-    c.B += (long long)b0 * op.b_bs * (op.b_cplx ? 2 : 1);
-    c.C += (long long)b0 * op.c_bs * (op.c_cplx ? 2 : 1);
-    dim3 grid((unsigned)tiles, c.batch);
-    if (op.bf16)
-      gemm_bf16_kernel<<<grid, 256, 0, s>>>(c);
-    else
-      gemm_kernel<<<grid, 256, 0, s>>>(c);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-  return hipSuccess;
-}
-
-hipError_t sur_gelu_bwd(const float* z, float* g, long long n, hipStream_t s) {
-  gelu_bwd<<<blocks(n), 256, 0, s>>>(z, g, n);
-  return hipGetLastError();
-}
-hipError_t sur_sum_batch(const float* in, float* out, int B, long long per, hipStream_t s) {
-  sum_batch<<<blocks(per), 256, 0, s>>>(in, out, B, per);
-  return hipGetLastError();
-}
-hipError_t sur_bias_grad(const float* g, float* out, int B, int C, int P, hipStream_t s) {
-  bias_grad<<<C, 256, 0, s>>>(g, out, B, C, P);
-  return hipGetLastError();
-}
-hipError_t sur_loss(const float* out, const float* tgt, long long n, float* sums, float* g,
-                    hipStream_t s) {
-  loss_sums<<<1, 256, 0, s>>>(out, tgt, n, sums);
-  if (g) loss_grad<<<blocks(2 * n), 256, 0, s>>>(out, tgt, sums, g, 2 * n);
-  return hipGetLastError();
-}
 hipError_t sur_adam(float* p, const float* g, float* m, float* v, long long n, float lr, int t,
                     hipStream_t s) {
   const float b1 = 0.9f, b2 = 0.999f;
@@ -787,15 +535,35 @@ hipError_t sur_fused_dft_fwd(const float* h, const float* fy, const float* fx, f
   }
   return hipGetLastError();
 }
+// Row-group splits of the inverse half: as many as keep the launch within two
+// blocks per CU (what its LDS allows), since every split stages G again.
+static int inv_splits(int B) { return B <= 128 ? 4 : B <= 256 ? 2 : 1; }
+
 hipError_t sur_fused_dft_inv(const float* G, const float* h, const float* iy, const float* ix,
                              const float* pw, const float* pb, float* z_out, float* h_out,
                              bool gelu, int B, bool bf16, hipStream_t s) {
   auto go = [&](auto kern) {
-    kern<<<B, INVM_T, 0, s>>>(reinterpret_cast<const f2*>(G), h, reinterpret_cast<const f2*>(iy),
-                            reinterpret_cast<const f2*>(ix), pw, pb, z_out, h_out, gelu ? 1 : 0);
+    kern<<<dim3(B, inv_splits(B)), INVM_T, 0, s>>>(
+        reinterpret_cast<const f2*>(G), h, reinterpret_cast<const f2*>(iy),
+        reinterpret_cast<const f2*>(ix), pw, pb, z_out, h_out, gelu ? 1 : 0, nullptr);
   };
-  if (bf16) go(fused_dft_inv_mfma<true>);
-  else go(fused_dft_inv_mfma<false>);
+  if (bf16) go(fused_dft_inv_mfma<true, INV_LAYER>);
+  else go(fused_dft_inv_mfma<false, INV_LAYER>);
+  return hipGetLastError();
+}
+hipError_t sur_fused_dft_adjoint(const float* gH, const float* gz, const float* fyh,
+                                 const float* fxh, const float* pw, const float* zp, float* out,
+                                 int B, hipStream_t s) {
+  fused_dft_inv_mfma<false, INV_ADJOINT><<<dim3(B, inv_splits(B)), INVM_T, 0, s>>>(
+      reinterpret_cast<const f2*>(gH), gz, reinterpret_cast<const f2*>(fyh),
+      reinterpret_cast<const f2*>(fxh), pw, nullptr, nullptr, out, 0, zp);
+  return hipGetLastError();
+}
+hipError_t sur_head_adjoint(const float* gout, const float* head, const float* hyh,
+                            const float* hxh, float* out, int B, hipStream_t s) {
+  fused_dft_inv_mfma<false, INV_HEAD><<<dim3(B, inv_splits(B)), INVM_T, 0, s>>>(
+      reinterpret_cast<const f2*>(gout), nullptr, reinterpret_cast<const f2*>(hyh),
+      reinterpret_cast<const f2*>(hxh), head, nullptr, nullptr, out, 0, nullptr);
   return hipGetLastError();
 }
 hipError_t sur_mode_mix(const float* A, const float* W, int nmode, int B, int O, float* out,
@@ -818,16 +586,24 @@ hipError_t sur_mode_mix_layer(const float* A, const float* Wm, int nmode, int B,
   const f2* a = reinterpret_cast<const f2*>(A);
   const f2* w = reinterpret_cast<const f2*>(Wm);
   f2* o = reinterpret_cast<f2*>(out);
-  if (bf16) mode_mix_mm<true><<<grid, 256, 0, s>>>(a, w, nmode, B, o);
-  else mode_mix_mm<false><<<grid, 256, 0, s>>>(a, w, nmode, B, o);
+  if (bf16) mode_mix_mm<true, false><<<grid, 256, 0, s>>>(a, w, nmode, B, o);
+  else mode_mix_mm<false, false><<<grid, 256, 0, s>>>(a, w, nmode, B, o);
+  return hipGetLastError();
+}
+hipError_t sur_mode_mix_adjoint(const float* A, const float* Wm, int nmode, int B, float* out,
+                                hipStream_t s) {
+  dim3 grid((B + 31) / 32, (nmode + MM_G - 1) / MM_G);
+  mode_mix_mm<false, true><<<grid, 256, 0, s>>>(reinterpret_cast<const f2*>(A),
+                                                reinterpret_cast<const f2*>(Wm), nmode, B,
+                                                reinterpret_cast<f2*>(out));
   return hipGetLastError();
 }
 hipError_t sur_spec_mode_major(const float* W, long long layer_stride_floats, int nmode,
                                int layers, float* Wm, hipStream_t s) {
-  if (layer_stride_floats % 2 != 0) return hipErrorInvalidValue;
-  dim3 grid(blocks((long long)nmode * SW * SW), layers);
-  spec_mode_major<<<grid, 256, 0, s>>>(reinterpret_cast<const f2*>(W), layer_stride_floats / 2,
-                                       nmode, reinterpret_cast<f2*>(Wm));
+  if (layer_stride_floats % 2 != 0 || nmode != SNM) return hipErrorInvalidValue;
+  spec_mode_major<<<dim3(SW, layers), 512, 0, s>>>(reinterpret_cast<const f2*>(W),
+                                                   layer_stride_floats / 2,
+                                                   reinterpret_cast<f2*>(Wm));
   return hipGetLastError();
 }
 hipError_t sur_lift(const float* x, const float* lw, const float* lb, float* h, int B, bool bf16,

@@ -409,27 +409,54 @@ BatchArgs batch_args(const scw_batch* b, void* E);
 std::string batch_key(const scw_grid& g);
 
 // ------------------------------------------------------------------ surrogate kernels
-// C[b] = op(A[b]) op(B[b]) + beta C[b]; strides in elements of each operand's
-// type (complex operands interleaved). c_cplx = 0 keeps the real part.
-struct GemmOp {
-  int M, N, K, batch;
-  int a_cplx, b_cplx, c_cplx;
-  int conj_a, conj_b;
-  const float* A;
-  long long a_rs, a_cs, a_bs;
-  const float* B;
-  long long b_rs, b_cs, b_bs;
-  float* C;
-  long long c_rs, c_cs, c_bs;
-  float beta;
-  int bf16;  // operands rounded to bf16, products on the matrix cores (FP32 accumulate)
-};
-hipError_t launch_gemm(const GemmOp& op, hipStream_t s);
-hipError_t sur_gelu_bwd(const float* z, float* g, long long n, hipStream_t s);
-hipError_t sur_sum_batch(const float* in, float* out, int B, long long per, hipStream_t s);
-hipError_t sur_bias_grad(const float* g, float* out, int B, int C, int P, hipStream_t s);
-hipError_t sur_loss(const float* out, const float* tgt, long long n, float* sums, float* g,
-                    hipStream_t s);
+// Backward kernels (kernels_surrogate_bwd.hip). Spectral gradients use the
+// forward pass's layouts: gG mode-major [mode][b][o], gH and gF [b][mode][i].
+constexpr int kSurPointwiseParts = 512, kSurHeadSlices = 16;
+// floats of the partial sums that sur_pointwise_grad and sur_head_grad need
+constexpr long long kSurPartFloats = 16LL * 2 * 32 * 3 * 225 > 512LL * 1056
+                                         ? 16LL * 2 * 32 * 3 * 225
+                                         : 512LL * 1056;
+// sums[0] = sum |out - tgt|^2, sums[1] = sum |tgt|^2 over n complex values,
+// g = 2 (out - tgt) / sums[1]; part: 512 floats of workspace.
+hipError_t sur_loss(const float* out, const float* tgt, long long n, float* part, float* sums,
+                    float* g, hipStream_t s);
+// out = [ci][32] weight gradient of a pointwise map from ci channels h, then
+// the 32 bias gradients.
+hipError_t sur_pointwise_grad(const float* h, const float* gz, int ci, int B, bool bf16,
+                              float* part, float* out, hipStream_t s);
+// gW[m][i][o] = sum_b conj(H[m][b][i]) gG[m][b][o], and its reordering into the
+// parameters' [i][o][m] for `layers` layers layer_stride_floats apart.
+hipError_t sur_spectral_grad(const float* H, const float* gG, int B, bool bf16, float* gW,
+                             hipStream_t s);
+hipError_t sur_spec_from_mode_major(const float* gW, long long layer_stride_floats, int layers,
+                                    float* G, hipStream_t s);
+// out[i][c][m] = sum_b conj(F[b][i][m]) gout[b][c][m]
+hipError_t sur_head_grad(const float* F, const float* gout, int B, bool bf16, float* part,
+                         float* out, hipStream_t s);
+// The adjoint in bf16 products: the head's mixing (gF), a layer's mixing (gH),
+// the inverse half's transforms (gG), and the forward half with the pointwise
+// map and, with zp, GELU' of the pre-activation zp (head: gF and the head's
+// tables, no pointwise map).
+hipError_t sur_head_mix_adjoint_bf16(const float* gout, const float* head, int B, float* gF,
+                                     hipStream_t s);
+hipError_t sur_mode_mix_adjoint_bf16(const float* gG, const float* Wm, int B, float* gH,
+                                     hipStream_t s);
+hipError_t sur_dft_adjoint_bf16(const float* gz, const float* iy, const float* ix, int B,
+                                float* gG, hipStream_t s);
+hipError_t sur_dft_fwd_adjoint_bf16(const float* gH, const float* gz, const float* fy,
+                                    const float* fx, const float* pw, const float* zp, bool head,
+                                    int B, float* out, hipStream_t s);
+// The same in FP32, on the forward kernels: gH from gG with Wm's adjoint; the
+// forward half's adjoint with the conjugate tables fyh [y][ky], fxh [kx][x];
+// and the head's, from gout. (The inverse half's transforms are
+// sur_fused_dft_fwd with the table conj(ix)^T.)
+hipError_t sur_mode_mix_adjoint(const float* A, const float* Wm, int nmode, int B, float* out,
+                                hipStream_t s);
+hipError_t sur_fused_dft_adjoint(const float* gH, const float* gz, const float* fyh,
+                                 const float* fxh, const float* pw, const float* zp, float* out,
+                                 int B, hipStream_t s);
+hipError_t sur_head_adjoint(const float* gout, const float* head, const float* hyh,
+                            const float* hxh, float* out, int B, hipStream_t s);
 hipError_t sur_adam(float* p, const float* g, float* m, float* v, long long n, float lr, int t,
                     hipStream_t s);
 hipError_t sur_encode(const float* n, float* x, int B, hipStream_t s);

@@ -56,10 +56,12 @@ struct SurNet {
   int step = 0;
   bool bf16 = false;  // GEMM operands in bf16 on the matrix cores (FP32 accumulate)
   DevBuf params, grads, adam_m, adam_v;
-  DevBuf dft;  // fy, fx, iy, ix, hy, hx (complex64)
-  long long o_fy, o_fx, o_iy, o_ix, o_hy, o_hx;
-  DevBuf x, h[NL + 1], z[NL], Hk[NL], G, Wm, F, out, gout, gF, T1, gh, gh2, T2, gG, gH,
-      tmp, sums, enc_in;
+  // fy, fx, iy, ix, hy, hx (complex64), then the adjoint tables that are not
+  // among them: conj(ix)^T, conj(fx)^T, conj(hy)^T, conj(hx)^T (conj(fy)^T is iy)
+  DevBuf dft;
+  long long o_fy, o_fx, o_iy, o_ix, o_hy, o_hx, o_ixh, o_fxh, o_hyh, o_hxh;
+  DevBuf x, h[NL + 1], z[NL], Hk[NL], G, Wm, F, out, gout, gF, gh, gh2, gG, gH, gWm, part, sums,
+      enc_in;
   DevBuf Wb;  // mixing weights as bf16 matrix-core operands (inference)
   // the parameters change only in sur_set_params and Adam steps; Wb is rebuilt
   // when its version lags behind theirs
@@ -69,47 +71,6 @@ struct SurNet {
 namespace {
 
 int alloc(DevBuf& b, long long floats) { return b.reserve((size_t)std::max(1LL, floats) * 4); }
-
-struct G {
-  GemmOp op{};
-  G(int M, int N, int K, int batch) {
-    op.M = M;
-    op.N = N;
-    op.K = K;
-    op.batch = batch;
-  }
-  G& a(const float* p, bool cplx, long long rs, long long cs, long long bs, bool conj = false) {
-    op.A = p;
-    op.a_cplx = cplx;
-    op.a_rs = rs;
-    op.a_cs = cs;
-    op.a_bs = bs;
-    op.conj_a = conj;
-    return *this;
-  }
-  G& b(const float* p, bool cplx, long long rs, long long cs, long long bs, bool conj = false) {
-    op.B = p;
-    op.b_cplx = cplx;
-    op.b_rs = rs;
-    op.b_cs = cs;
-    op.b_bs = bs;
-    op.conj_b = conj;
-    return *this;
-  }
-  G& c(float* p, bool cplx, long long rs, long long cs, long long bs, float beta = 0.f) {
-    op.C = p;
-    op.c_cplx = cplx;
-    op.c_rs = rs;
-    op.c_cs = cs;
-    op.c_bs = bs;
-    op.beta = beta;
-    return *this;
-  }
-  hipError_t run(hipStream_t s, bool bf16) {
-    op.bf16 = bf16 ? 1 : 0;
-    return launch_gemm(op, s);
-  }
-};
 
 #define SUR_HIP(x)                                                        \
   do {                                                                    \
@@ -141,6 +102,16 @@ int build_dft(SurNet& n) {
   n.o_hx = (long long)v.size();
   for (int x = 0; x < 32; ++x)
     for (int kx = -7; kx <= 7; ++kx) v.push_back(e(-tp * ((kx * x) % 32)) / 32.0);
+  auto adjoint = [&](long long from, int rows, int cols) {  // [rows][cols] -> conj, [cols][rows]
+    const long long at = (long long)v.size();
+    for (int c = 0; c < cols; ++c)
+      for (int r = 0; r < rows; ++r) v.push_back(std::conj(v[from + (long long)r * cols + c]));
+    return at;
+  };
+  n.o_ixh = adjoint(n.o_ix, KXN, 32);
+  n.o_fxh = adjoint(n.o_fx, 32, KXN);
+  n.o_hyh = adjoint(n.o_hy, HN, 32);
+  n.o_hxh = adjoint(n.o_hx, 32, HN);
   std::vector<float> f(2 * v.size());
   for (size_t i = 0; i < v.size(); ++i) {
     f[2 * i] = (float)v[i].real();
@@ -216,64 +187,50 @@ int infer(SurNet& n, const float* x, int B, hipStream_t s) {
   return n.bf16 ? forward_bf16(n, x, B, s) : forward(n, x, B, s, false);
 }
 
-// Backward pass from gout (= dL/dout) into grads.
+// Backward pass from gout (= dL/dout) into grads: per layer the adjoint of its
+// transforms and mixing and one pass for each weight gradient, with GELU' of
+// the layer below applied as the activations' gradient is written. The two
+// arithmetics run the same steps (in bf16 the operands of every product are
+// rounded).
 int backward(SurNet& n, int B, hipStream_t s) {
   const Off o;
   const float* P = n.params.as<float>();
   float* Gr = n.grads.as<float>();
-  const long long act = (long long)W * NP;
-  // head
-  SUR_HIP(G(W, OUT, B, HM).a(n.F.as<float>(), true, HM, (long long)W * HM, 1, true)
-              .b(n.gout.as<float>(), true, (long long)OUT * HM, HM, 1)
-              .c(Gr + o.head(), true, (long long)OUT * HM, HM, 1).run(s, n.bf16));
-  SUR_HIP(G(B, W, OUT, HM).a(n.gout.as<float>(), true, (long long)OUT * HM, HM, 1)
-              .b(P + o.head(), true, HM, (long long)OUT * HM, 1, true)
-              .c(n.gF.as<float>(), true, (long long)W * HM, HM, 1).run(s, n.bf16));
-  SUR_HIP(G(32, HN, HN, B * W).a(cx(n, n.o_hy), true, 1, 32, 0, true)
-              .b(n.gF.as<float>(), true, HN, 1, HM).c(n.T1.as<float>(), true, HN, 1, 32 * HN)
-              .run(s, n.bf16));
-  SUR_HIP(G(B * NP, 32, HN, 1).a(n.T1.as<float>(), true, HN, 1, 0)
-              .b(cx(n, n.o_hx), true, 1, HN, 0, true).c(n.gh.as<float>(), false, 32, 1, 0)
-              .run(s, n.bf16));
-  DevBuf* gh = &n.gh;
-  DevBuf* gh2 = &n.gh2;
-  for (int k = NL - 1; k >= 0; --k) {
-    float* gz = gh->as<float>();
-    if (k < NL - 1) SUR_HIP(sur_gelu_bwd(n.z[k].as<float>(), gz, (long long)B * act, s));
-    const float* hin = n.h[k].as<float>();
-    // pointwise weight and bias
-    SUR_HIP(G(W, W, NP, B).a(hin, false, NP, 1, act).b(gz, false, 1, NP, act)
-                .c(n.tmp.as<float>(), false, W, 1, W * W).run(s, n.bf16));
-    SUR_HIP(sur_sum_batch(n.tmp.as<float>(), Gr + o.pw(k), B, W * W, s));
-    SUR_HIP(sur_bias_grad(gz, Gr + o.pb(k), B, W, NP, s));
-    float* g2 = gh2->as<float>();
-    SUR_HIP(G(W, NP, W, B).a(P + o.pw(k), false, W, 1, 0).b(gz, false, NP, 1, act)
-                .c(g2, false, NP, 1, act).run(s, n.bf16));
-    // spectral branch
-    SUR_HIP(G(B * NP, KXN, 32, 1).a(gz, false, 32, 1, 0).b(cx(n, n.o_ix), true, 1, 32, 0, true)
-                .c(n.T2.as<float>(), true, KXN, 1, 0).run(s, n.bf16));
-    SUR_HIP(G(KYN, KXN, 32, B * W).a(cx(n, n.o_iy), true, 1, KYN, 0, true)
-                .b(n.T2.as<float>(), true, KXN, 1, 32 * KXN).c(n.gG.as<float>(), true, KXN, 1, NM)
-                .run(s, n.bf16));
-    SUR_HIP(G(W, W, B, NM).a(n.Hk[k].as<float>(), true, 1, W, (long long)B * W, true)
-                .b(n.gG.as<float>(), true, (long long)W * NM, NM, 1)
-                .c(Gr + o.spec(k), true, (long long)W * NM, NM, 1).run(s, n.bf16));
-    SUR_HIP(G(B, W, W, NM).a(n.gG.as<float>(), true, (long long)W * NM, NM, 1)
-                .b(P + o.spec(k), true, NM, (long long)W * NM, 1, true)
-                .c(n.gH.as<float>(), true, (long long)W * NM, NM, 1).run(s, n.bf16));
-    SUR_HIP(G(32, KXN, KYN, B * W).a(cx(n, n.o_fy), true, 1, 32, 0, true)
-                .b(n.gH.as<float>(), true, KXN, 1, NM).c(n.T2.as<float>(), true, KXN, 1, 32 * KXN)
-                .run(s, n.bf16));
-    SUR_HIP(G(B * NP, 32, KXN, 1).a(n.T2.as<float>(), true, KXN, 1, 0)
-                .b(cx(n, n.o_fx), true, 1, KXN, 0, true).c(g2, false, 32, 1, 0, 1.f).run(s, n.bf16));
-    std::swap(gh, gh2);
+  float* part = n.part.as<float>();
+  float *gG = n.gG.as<float>(), *gH = n.gH.as<float>(), *gout = n.gout.as<float>();
+  float *gz = n.gh.as<float>(), *gnext = n.gh2.as<float>();
+  SUR_HIP(sur_head_grad(n.F.as<float>(), gout, B, n.bf16, part, Gr + o.head(), s));
+  if (n.bf16) {
+    float* gF = n.gF.as<float>();
+    SUR_HIP(sur_head_mix_adjoint_bf16(gout, P + o.head(), B, gF, s));
+    SUR_HIP(sur_dft_fwd_adjoint_bf16(gF, nullptr, cx(n, n.o_hy), cx(n, n.o_hx), nullptr, nullptr,
+                                     true, B, gz, s));
+  } else {
+    SUR_HIP(sur_head_adjoint(gout, P + o.head(), cx(n, n.o_hyh), cx(n, n.o_hxh), gz, B, s));
   }
-  // lift
-  SUR_HIP(G(CIN, W, NP, B).a(n.x.as<float>(), false, NP, 1, (long long)CIN * NP)
-              .b(gh->as<float>(), false, 1, NP, act).c(n.tmp.as<float>(), false, W, 1, CIN * W)
-              .run(s, n.bf16));
-  SUR_HIP(sur_sum_batch(n.tmp.as<float>(), Gr + o.lw, B, CIN * W, s));
-  SUR_HIP(sur_bias_grad(gh->as<float>(), Gr + o.lb, B, W, NP, s));
+  for (int k = NL - 1; k >= 0; --k) {
+    const float* Wm = n.Wm.as<float>() + 2LL * k * NM * W * W;
+    const float* zp = k > 0 ? n.z[k - 1].as<float>() : nullptr;
+    SUR_HIP(sur_pointwise_grad(n.h[k].as<float>(), gz, W, B, n.bf16, part, Gr + o.pw(k), s));
+    if (n.bf16)
+      SUR_HIP(sur_dft_adjoint_bf16(gz, cx(n, n.o_iy), cx(n, n.o_ix), B, gG, s));
+    else
+      SUR_HIP(sur_fused_dft_fwd(gz, cx(n, n.o_fy), cx(n, n.o_ixh), gG, B, false, false, s));
+    SUR_HIP(sur_spectral_grad(n.Hk[k].as<float>(), gG, B, n.bf16,
+                              n.gWm.as<float>() + 2LL * k * NM * W * W, s));
+    if (n.bf16) {
+      SUR_HIP(sur_mode_mix_adjoint_bf16(gG, Wm, B, gH, s));
+      SUR_HIP(sur_dft_fwd_adjoint_bf16(gH, gz, cx(n, n.o_fy), cx(n, n.o_fx), P + o.pw(k), zp,
+                                       false, B, gnext, s));
+    } else {
+      SUR_HIP(sur_mode_mix_adjoint(gG, Wm, NM, B, gH, s));
+      SUR_HIP(sur_fused_dft_adjoint(gH, gz, cx(n, n.o_iy), cx(n, n.o_fxh), P + o.pw(k), zp, gnext,
+                                    B, s));
+    }
+    std::swap(gz, gnext);
+  }
+  SUR_HIP(sur_spec_from_mode_major(n.gWm.as<float>(), SZ_LAYER, NL, Gr + o.spec(0), s));
+  SUR_HIP(sur_pointwise_grad(n.x.as<float>(), gz, CIN, B, n.bf16, part, Gr + o.lw, s));
   return SCW_OK;
 }
 
@@ -302,10 +259,10 @@ int sur_create(Context& ctx, int max_batch, unsigned long long seed, SurNet** ou
       (rc = alloc(n->G, B * W * NM * 2)) || (rc = alloc(n->Wm, (long long)NL * NM * W * W * 2)) ||
       (rc = alloc(n->F, B * W * HM * 2)) || (rc = alloc(n->out, B * OUT * HM * 2)) ||
       (rc = alloc(n->gout, B * OUT * HM * 2)) || (rc = alloc(n->gF, B * W * HM * 2)) ||
-      (rc = alloc(n->T1, B * W * 32 * HN * 2)) || (rc = alloc(n->gh, act)) ||
-      (rc = alloc(n->gh2, act)) || (rc = alloc(n->T2, B * W * 32 * KXN * 2)) ||
+      (rc = alloc(n->gh, act)) || (rc = alloc(n->gh2, act)) ||
       (rc = alloc(n->gG, B * W * NM * 2)) || (rc = alloc(n->gH, B * W * NM * 2)) ||
-      (rc = alloc(n->tmp, B * W * W)) || (rc = alloc(n->sums, 16)) ||
+      (rc = alloc(n->gWm, (long long)NL * NM * W * W * 2)) ||
+      (rc = alloc(n->part, kSurPartFloats)) || (rc = alloc(n->sums, 16)) ||
       (rc = n->Wb.reserve(sur_mix_weights_bf16_bytes(NL))))
     return rc;
   for (int k = 0; k <= NL; ++k)
@@ -379,7 +336,8 @@ int sur_loss_grad(SurNet& n, const void* x_dev, const void* tgt_dev, int B, doub
   SCW_HIP(hipMemcpyAsync(n.x.p, x_dev, (size_t)B * CIN * NP * 4, hipMemcpyDeviceToDevice, s));
   if ((rc = forward(n, n.x.as<float>(), B, s, true))) return rc;
   SCW_HIP(sur_loss(n.out.as<float>(), reinterpret_cast<const float*>(tgt_dev),
-                   (long long)B * OUT * HM, n.sums.as<float>(), n.gout.as<float>(), s));
+                   (long long)B * OUT * HM, n.part.as<float>(), n.sums.as<float>(),
+                   n.gout.as<float>(), s));
   if ((rc = backward(n, B, s))) return rc;
   if (loss) {
     float sums[2];

@@ -1,0 +1,35 @@
+// Device helpers shared by the surrogate's FP32-storage kernels and its
+// backward pass.
+#pragma once
+#include <hip/hip_runtime.h>
+
+namespace scw {
+namespace {
+
+struct f2 {
+  float x, y;
+};
+
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+
+// a patch's side, the layers' spectral half plane and the channel count
+constexpr int SN = 32, SKY = 17, SKX = 9, SNM = SKY * SKX, SW = 32;
+
+__device__ __forceinline__ float rbf(float x) {  // round to bf16, nearest even
+  unsigned u = __float_as_uint(x);
+  u = (u + 0x7FFFu + ((u >> 16) & 1u)) & 0xFFFF0000u;
+  return __uint_as_float(u);
+}
+template <bool BF16>
+__device__ __forceinline__ float op(float x) { return BF16 ? rbf(x) : x; }
+template <bool BF16>
+__device__ __forceinline__ f2 op(f2 x) { return BF16 ? f2{rbf(x.x), rbf(x.y)} : x; }
+
+// d GELU / dz for the backward pass (exact erf)
+__device__ __forceinline__ float gelu_grad_f(float z) {
+  return 0.5f * (1.f + erff(z * 0.70710678118654752f)) +
+         z * expf(-0.5f * z * z) * 0.39894228040143268f;
+}
+
+}  // namespace
+}  // namespace scw
