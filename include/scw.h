@@ -192,8 +192,11 @@ int scw_solve(scw_ctx* ctx, const scw_problem* prob, scw_solution** out);
  * up to about 24 GB of device workspace. On success out[i] (caller-provided
  * array of n pointers) receives problem i's solution, each freed by
  * scw_solution_free. On failure every out[i] is NULL and the message names
- * the problem. The solutions' eig_seconds all report the shared batch time
- * of their round (plus any host part). */
+ * the problem. Neighbouring problems of equal truncation and layer count on
+ * SCW_ROUTE_STABLE_DEVICE also share their elimination's launches, in groups
+ * of up to about 4 GB of device workspace. The solutions' eig_seconds all
+ * report the shared batch time of their round (plus any host part), and
+ * boundary_seconds that of their group. */
 int scw_solve_batch(scw_ctx* ctx, const scw_problem* probs, int n, scw_solution** out);
 
 /* Batched FP64 eigendecomposition on the GPU (the step of Sec. 3.2 and

@@ -453,7 +453,14 @@ int scw_solve_batch(scw_ctx* ctx, const scw_problem* probs, int n, scw_solution*
     }
     sols[i] = &made[i]->s;
   }
-  const int rc = solve_problems(ctx->c, probs, n, sols.data());
+  int rc;
+  try {
+    rc = solve_problems(ctx->c, probs, n, sols.data());
+  } catch (const std::bad_alloc&) {
+    rc = fail(SCW_ENOMEM, "host allocation failed during setup");
+  } catch (const std::exception& e) {
+    rc = fail(SCW_EINVAL, std::string("setup failed: ") + e.what());
+  }
   if (rc) {
     for (scw_solution* m : made) delete m;
     return rc;

@@ -197,11 +197,25 @@ __global__ void to_fp32(const double* __restrict__ in, float* __restrict__ out, 
 
 inline unsigned blocks_for(long long n, int bs) { return (unsigned)((n + bs - 1) / bs); }
 
-// Elementwise steps of the device elimination (column-major n x n blocks).
+// Elementwise steps of the device elimination (column-major n x n blocks);
+// blockIdx.y is the problem of a batch.
 __global__ void eye_kernel(z2* __restrict__ A, int n) {
   const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= (long long)n * n) return;
-  A[i] = z2{i / n == i % n ? 1.0 : 0.0, 0.0};
+  A[(long long)blockIdx.y * n * n + i] = z2{i / n == i % n ? 1.0 : 0.0, 0.0};
+}
+
+// The 2M x 2M map whose four M x M blocks xx, xy, yx, yy are the diagonals
+// d[0..3] (E_xy of a half-space wave to its H_xy): entry (row, col).
+__device__ __forceinline__ z2 half_space_entry(const z2* __restrict__ d, int M, int row, int col) {
+  const int r = row % M, c = col % M;
+  return r == c ? d[(row / M * 2 + col / M) * M + r] : z2{0.0, 0.0};
+}
+__global__ void half_space_kernel(const z2* __restrict__ d, int n, z2* __restrict__ H) {
+  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= (long long)n * n) return;
+  H[(long long)blockIdx.y * n * n + i] =
+      half_space_entry(d + (long long)blockIdx.y * 2 * n, n / 2, (int)(i % n), (int)(i / n));
 }
 
 // A1 <- (A1 + A2) / 2, A2 <- (A1 - A2) / 2
@@ -219,10 +233,11 @@ __global__ void i_pm_ere(const z2* __restrict__ r, const z2* __restrict__ E, int
   const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= (long long)n * n) return;
   const int c = (int)(i / n), row = (int)(i % n);
-  const z2 x = zmul(zmul(E[row], r[i]), E[c]);
+  const long long g = blockIdx.y, o = g * n * n + i;
+  const z2 x = zmul(zmul(E[g * n + row], r[o]), E[g * n + c]);
   const double d = row == c ? 1.0 : 0.0;
-  P1[i] = z2{d + x.x, x.y};
-  P2[i] = z2{d - x.x, -x.y};
+  P1[o] = z2{d + x.x, x.y};
+  P2[o] = z2{d - x.x, -x.y};
 }
 
 // out[c][j] = E[j] A[c][j] for n rows and k columns
@@ -230,7 +245,8 @@ __global__ void scale_rows(const z2* __restrict__ E, const z2* __restrict__ A, i
                            z2* __restrict__ out) {
   const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= (long long)n * k) return;
-  out[i] = zmul(E[i % n], A[i]);
+  const long long g = blockIdx.y, o = g * n * k + i;
+  out[o] = zmul(E[g * n + i % n], A[o]);
 }
 
 // T_l = W diag(I, E) and B_l = W diag(E, I) of the connection route, with
@@ -263,21 +279,24 @@ hipError_t launch_build_tb(const double* X, const double* Y, const double* E, in
 
 // Top-surface system of the stable route, column-major n4 x n4 (n4 = 2 n2):
 // S = [[I, -Fe], [Hr, -Fh]] (incident + reflected = field at the top of layer 1).
-__global__ void top_system(const z2* __restrict__ Hr, const z2* __restrict__ Fe,
+// hd: the diagonals of Hr.
+__global__ void top_system(const z2* __restrict__ hd, const z2* __restrict__ Fe,
                            const z2* __restrict__ Fh, int n2, z2* __restrict__ S) {
   const int n4 = 2 * n2;
   const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= (long long)n4 * n4) return;
   const int col = (int)(i / n4), row = (int)(i % n4);
+  const long long g = blockIdx.y, o = g * n2 * n2;
   z2 v;
   if (col < n2)
-    v = row < n2 ? z2{row == col ? 1.0 : 0.0, 0.0} : Hr[(long long)col * n2 + row - n2];
+    v = row < n2 ? z2{row == col ? 1.0 : 0.0, 0.0}
+                 : half_space_entry(hd + g * 2 * n2, n2 / 2, row - n2, col);
   else {
-    const z2 f = row < n2 ? Fe[(long long)(col - n2) * n2 + row]
-                          : Fh[(long long)(col - n2) * n2 + row - n2];
+    const z2 f = row < n2 ? Fe[o + (long long)(col - n2) * n2 + row]
+                          : Fh[o + (long long)(col - n2) * n2 + row - n2];
     v = z2{-f.x, -f.y};
   }
-  S[i] = v;
+  S[g * n4 * n4 + i] = v;
 }
 
 // Connection system of Eq. 29, column-major n6 x n6 (n6 = 6M): rows 0 .. 4M-1
@@ -328,11 +347,17 @@ __global__ void col_abs_sum(const z2* __restrict__ A, int n, double* __restrict_
   if (lane == 0) out[c] = acc;
 }
 
-hipError_t launch_top_system(const double* Hr, const double* Fe, const double* Fh, int n2,
-                             double* S, hipStream_t s) {
-  top_system<<<blocks_for(4LL * n2 * n2, 256), 256, 0, s>>>(
-      reinterpret_cast<const z2*>(Hr), reinterpret_cast<const z2*>(Fe),
+hipError_t launch_top_system(const double* hd, const double* Fe, const double* Fh, int n2,
+                             int count, double* S, hipStream_t s) {
+  top_system<<<dim3(blocks_for(4LL * n2 * n2, 256), count), 256, 0, s>>>(
+      reinterpret_cast<const z2*>(hd), reinterpret_cast<const z2*>(Fe),
       reinterpret_cast<const z2*>(Fh), n2, reinterpret_cast<z2*>(S));
+  return hipGetLastError();
+}
+
+hipError_t launch_half_space(const double* hd, int n2, int count, double* H, hipStream_t s) {
+  half_space_kernel<<<dim3(blocks_for((long long)n2 * n2, 256), count), 256, 0, s>>>(
+      reinterpret_cast<const z2*>(hd), n2, reinterpret_cast<z2*>(H));
   return hipGetLastError();
 }
 
@@ -351,8 +376,9 @@ hipError_t launch_col_abs_sum(const double* A, int n, double* out, hipStream_t s
   return hipGetLastError();
 }
 
-hipError_t launch_eye(double* A, int n, hipStream_t s) {
-  eye_kernel<<<blocks_for((long long)n * n, 256), 256, 0, s>>>(reinterpret_cast<z2*>(A), n);
+hipError_t launch_eye(double* A, int n, hipStream_t s, int count) {
+  eye_kernel<<<dim3(blocks_for((long long)n * n, 256), count), 256, 0, s>>>(
+      reinterpret_cast<z2*>(A), n);
   return hipGetLastError();
 }
 
@@ -362,17 +388,17 @@ hipError_t launch_half_sum_diff(double* A1, double* A2, long long n, hipStream_t
   return hipGetLastError();
 }
 
-hipError_t launch_i_pm_ere(const double* r, const double* E, int n, double* P1, double* P2,
-                           hipStream_t s) {
-  i_pm_ere<<<blocks_for((long long)n * n, 256), 256, 0, s>>>(
+hipError_t launch_i_pm_ere(const double* r, const double* E, int n, int count, double* P1,
+                           double* P2, hipStream_t s) {
+  i_pm_ere<<<dim3(blocks_for((long long)n * n, 256), count), 256, 0, s>>>(
       reinterpret_cast<const z2*>(r), reinterpret_cast<const z2*>(E), n,
       reinterpret_cast<z2*>(P1), reinterpret_cast<z2*>(P2));
   return hipGetLastError();
 }
 
-hipError_t launch_scale_rows(const double* E, const double* A, int n, int k, double* out,
-                             hipStream_t s) {
-  scale_rows<<<blocks_for((long long)n * k, 256), 256, 0, s>>>(
+hipError_t launch_scale_rows(const double* E, const double* A, int n, int k, int count,
+                             double* out, hipStream_t s) {
+  scale_rows<<<dim3(blocks_for((long long)n * k, 256), count), 256, 0, s>>>(
       reinterpret_cast<const z2*>(E), reinterpret_cast<const z2*>(A), n, k,
       reinterpret_cast<z2*>(out));
   return hipGetLastError();

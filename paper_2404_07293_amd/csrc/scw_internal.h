@@ -222,17 +222,23 @@ int synthesize_illuminations(Context& ctx, Solution& s, const scw_grid& g, void*
 int solve_problem(Context& ctx, const scw_problem& prob, Solution& sol, int n_waves = 0,
                   const scw_plane_wave* waves = nullptr);
 // n problems solved together: their device eigendecompositions
-// (SCW_EIG_DEVICE) of equal truncation share launches; each other step runs
-// per problem as in solve_problem. sols[i] receives problem i.
+// (SCW_EIG_DEVICE) of equal truncation share launches, and so do the device
+// eliminations (SCW_ROUTE_STABLE_DEVICE) of neighbouring ones of equal
+// truncation and layer count; each other step runs per problem as in
+// solve_problem. sols[i] receives problem i.
 int solve_problems(Context& ctx, const scw_problem* probs, int n, Solution** sols);
 void release_blas(Context& ctx);
-// Elementwise steps of the device elimination, column-major complex128
-// n x n blocks: A = I; A1, A2 <- (A1 + A2)/2, (A1 - A2)/2 over n entries;
-// P1, P2 = I +- E r E with E diagonal; out = diag(E) A for n x k A.
-hipError_t launch_eye(double* A, int n, hipStream_t s);
-// Top-surface system [[I, -Fe], [Hr, -Fh]] (4M x 4M) of the stable route.
-hipError_t launch_top_system(const double* Hr, const double* Fe, const double* Fh, int n2,
-                             double* S, hipStream_t s);
+// Elementwise steps of the device elimination for `count` problems, one after
+// another in every array, column-major complex128 n x n blocks: A = I;
+// A1, A2 <- (A1 + A2)/2, (A1 - A2)/2 over n entries; P1, P2 = I +- E r E with
+// E diagonal; out = diag(E) A for n x k A; H = the half-space map from its
+// four diagonals (xx, xy, yx, yy of n/2 entries each).
+hipError_t launch_eye(double* A, int n, hipStream_t s, int count = 1);
+hipError_t launch_half_space(const double* hd, int n2, int count, double* H, hipStream_t s);
+// Top-surface system [[I, -Fe], [Hr, -Fh]] (4M x 4M) of the stable route,
+// from the diagonals hd of Hr.
+hipError_t launch_top_system(const double* hd, const double* Fe, const double* Fh, int n2,
+                             int count, double* S, hipStream_t s);
 // The 6M x 6M connection system of Eq. 29 from K C_r, C_t (4M x 3M) and the
 // Gauss rows (sx, sy real [M]; szt, szb complex [M]).
 hipError_t launch_connection_system(const double* KCr, const double* Ct, const double* sx,
@@ -241,10 +247,10 @@ hipError_t launch_connection_system(const double* KCr, const double* Ct, const d
 // Column sums of |A| of a column-major n x n complex matrix (its 1-norm is the largest).
 hipError_t launch_col_abs_sum(const double* A, int n, double* out, hipStream_t s);
 hipError_t launch_half_sum_diff(double* A1, double* A2, long long n, hipStream_t s);
-hipError_t launch_i_pm_ere(const double* r, const double* E, int n, double* P1, double* P2,
-                           hipStream_t s);
-hipError_t launch_scale_rows(const double* E, const double* A, int n, int k, double* out,
-                             hipStream_t s);
+hipError_t launch_i_pm_ere(const double* r, const double* E, int n, int count, double* P1,
+                           double* P2, hipStream_t s);
+hipError_t launch_scale_rows(const double* E, const double* A, int n, int k, int count,
+                             double* out, hipStream_t s);
 // T = W diag(I, E), B = W diag(E, I) with W = [[X, X], [Y, -Y]] (4M x 4M).
 hipError_t launch_build_tb(const double* X, const double* Y, const double* E, int n2, double* T,
                            double* B, hipStream_t s);

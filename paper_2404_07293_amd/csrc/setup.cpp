@@ -114,18 +114,31 @@ Mat identity(int n) {
 
 // Transverse plane-wave field map for a half-space wave with s = (sx, sy, sigma):
 // [px, py] -> [px, py, bx, by] with pz = -(sx px + sy py)/sigma (Eq. 14) and
-// b = s x p. Returns the 2M x 2M H block (the E block is the identity).
-Mat half_space_h(const Solution& s, const std::vector<zc>& sigma) {
-  const int M = s.M, n2 = 2 * M;
-  Mat H((size_t)n2 * n2, zc(0));
+// b = s x p. The 2M x 2M H block (the E block is the identity) couples only
+// the two components of one mode: its four diagonals xx, xy, yx, yy, M each.
+void half_space_diagonals(const Solution& s, const std::vector<zc>& sigma, zc* d) {
+  const int M = s.M;
   for (int m = 0; m < M; ++m) {
     const zc sg = sigma[m];
     const double sx = s.sx[m], sy = s.sy[m];
     // bx = -(sx sy / sg) px - (sy^2/sg + sg) py ; by = (sg + sx^2/sg) px + (sx sy/sg) py
-    H[(size_t)m * n2 + m] = -(sx * sy) / sg;
-    H[(size_t)(M + m) * n2 + m] = -(sy * sy / sg + sg);
-    H[(size_t)m * n2 + M + m] = sg + sx * sx / sg;
-    H[(size_t)(M + m) * n2 + M + m] = (sx * sy) / sg;
+    d[m] = -(sx * sy) / sg;
+    d[M + m] = -(sy * sy / sg + sg);
+    d[2 * M + m] = sg + sx * sx / sg;
+    d[3 * M + m] = (sx * sy) / sg;
+  }
+}
+
+Mat half_space_h(const Solution& s, const std::vector<zc>& sigma) {
+  const int M = s.M, n2 = 2 * M;
+  std::vector<zc> d(4 * (size_t)M);
+  half_space_diagonals(s, sigma, d.data());
+  Mat H((size_t)n2 * n2, zc(0));
+  for (int m = 0; m < M; ++m) {
+    H[(size_t)m * n2 + m] = d[m];
+    H[(size_t)(M + m) * n2 + m] = d[M + m];
+    H[(size_t)m * n2 + M + m] = d[2 * M + m];
+    H[(size_t)(M + m) * n2 + M + m] = d[3 * M + m];
   }
   return H;
 }
@@ -326,13 +339,17 @@ void top_surface_finish(Solution& s, const std::vector<zc>& x, std::vector<zc>& 
 // Right-hand sides -C_i p_inc of the top-surface system, 4M x K.
 std::vector<zc> top_surface_rhs(const Solution& s) {
   const int M = s.M, n4 = 4 * M, K = s.K;
-  Mat Ci = c_map(s, s.sz_top);
   std::vector<zc> rhs((size_t)n4 * K, zc(0));
   for (int kk = 0; kk < K; ++kk) {
     const zc* pin = s.p_inc.data() + (size_t)kk * 3 * M;
     zc* r = rhs.data() + (size_t)kk * n4;
-    for (int c = 0; c < 3 * M; ++c)
-      for (int rr = 0; rr < n4; ++rr) r[rr] -= Ci[(size_t)c * n4 + rr] * pin[c];
+    for (int m = 0; m < M; ++m) {
+      const zc sg = s.sz_top[m], px = pin[m], py = pin[M + m], pz = pin[2 * M + m];
+      r[m] = -px;
+      r[M + m] = -py;
+      r[2 * M + m] = sg * py - s.sy[m] * pz;  // the rows of c_map
+      r[3 * M + m] = s.sx[m] * pz - sg * px;
+    }
   }
   return rhs;
 }
@@ -373,9 +390,8 @@ int connection_system(const Lin& lin, Solution& s, const Mat& K, std::vector<zc>
 // A1 = X^-1 Fe, A2 = Y^-1 Fh, G_t = (A1 + A2)/2, G_b = (A1 - A2)/2,
 // t = G_t^-1, r = G_b t, Fe = X (I + E r E), Fh = Y (I - E r E). The LU
 // factors of every layer's X and Y do not depend on the recursion and are
-// computed first, in one batched call over the 2L matrices. The 4M x 4M
-// top-surface system is solved on the host (top_surface); the
-// back-substitution runs on the device for all illuminations at once.
+// computed first, in one batched call over the 2L matrices. Then the 4M x 4M
+// top-surface system, and the back-substitution of all illuminations at once.
 namespace {
 rocblas_double_complex* zp(const DevBuf& b, size_t off = 0) {
   return reinterpret_cast<rocblas_double_complex*>(b.as<zc>() + off);
@@ -388,40 +404,6 @@ rocblas_double_complex* zp(const DevBuf& b, size_t off = 0) {
     if (st_ != rocblas_status_success)                                                   \
       return fail(SCW_EHIP, std::string(#call) + ": " + rocblas_status_to_string(st_));  \
   } while (0)
-
-// The stable route's 4M x 4M top-surface system on the device: assembled from
-// the device F_1 (Fe, Fh), LU-factored by rocSOLVER, solved for every
-// illumination; p_ref and a_1 as top_surface leaves them.
-int top_surface_device(Context& ctx, Solution& s, const DevBuf& dFe, const DevBuf& dFh,
-                       std::vector<zc>& a1) {
-  const int M = s.M, n2 = 2 * M, n4 = 4 * M, K = s.K;
-  hipStream_t st = ctx.setup_stream;
-  void* hv = nullptr;
-  int rc;
-  if ((rc = blas_handle(ctx, st, &hv))) return rc;
-  rocblas_handle h = static_cast<rocblas_handle>(hv);
-  const Mat Hr = reflected_h(s);
-  std::vector<zc> x = top_surface_rhs(s);
-  DevBuf dHr, dS, drhs, dpiv, dinfo;
-  if ((rc = dHr.reserve((size_t)n2 * n2 * 16)) || (rc = dS.reserve((size_t)n4 * n4 * 16)) ||
-      (rc = drhs.reserve(x.size() * 16)) || (rc = dpiv.reserve((size_t)n4 * sizeof(rocblas_int))) ||
-      (rc = dinfo.reserve(sizeof(rocblas_int))))
-    return rc;
-  SCW_HIP(hipMemcpyAsync(dHr.p, Hr.data(), Hr.size() * 16, hipMemcpyHostToDevice, st));
-  SCW_HIP(hipMemcpyAsync(drhs.p, x.data(), x.size() * 16, hipMemcpyHostToDevice, st));
-  SCW_HIP(launch_top_system(dHr.as<double>(), dFe.as<double>(), dFh.as<double>(), n2,
-                            dS.as<double>(), st));
-  SCW_BLAS(rocsolver_zgetrf(h, n4, n4, zp(dS), n4, dpiv.as<rocblas_int>(), dinfo.as<rocblas_int>()));
-  SCW_BLAS(rocsolver_zgetrs(h, rocblas_operation_none, n4, K, zp(dS), n4, dpiv.as<rocblas_int>(),
-                            zp(drhs), n4));
-  rocblas_int info = 0;
-  SCW_HIP(hipMemcpyAsync(&info, dinfo.p, sizeof(info), hipMemcpyDeviceToHost, st));
-  SCW_HIP(hipMemcpyAsync(x.data(), drhs.p, x.size() * 16, hipMemcpyDeviceToHost, st));
-  SCW_HIP(hipStreamSynchronize(st));
-  if (info != 0) return fail(SCW_EILLCOND, "singular top-surface system in the device elimination");
-  top_surface_finish(s, x, a1);
-  return SCW_OK;
-}
 
 // The connection route's 6M x 6M system (Eq. 29) on the device, from the
 // device product K: assembled, LU-factored and solved by rocSOLVER. Its
@@ -499,134 +481,186 @@ int connection_system_device(Context& ctx, Solution& s, const DevBuf& dK,
   return SCW_OK;
 }
 
-int solve_stable_device(Context& ctx, const Lin& lin, Solution& s,
-                        std::vector<LayerHost>& layers) {
-  const int M = s.M, n2 = 2 * M, L = s.L, K = s.K;
-  const size_t nn = (size_t)n2 * n2;
+// G problems of one shape (M, L, K) together: every step below is one batched
+// call over them. The recursion of one problem is a chain of small LU
+// factorisations and triangular solves whose panel kernels take tens of
+// microseconds each on a few blocks (24 ms for 8 layers of 2M = 242), so
+// problems solved side by side cost little more than one. X and Y are on the
+// device, [G][L][2M x 2M]. On failure *bad is the problem at fault.
+int solve_stable_device(Context& ctx, int G, Solution* const* sols,
+                        std::vector<LayerHost>* const* layers, const zc* dX, const zc* dY,
+                        int* bad) {
+  const Solution& s0 = *sols[0];
+  const int M = s0.M, n2 = 2 * M, n4 = 4 * M, L = s0.L, K = s0.K;
+  const size_t nn = (size_t)n2 * n2, gn = (size_t)G * nn, nk = (size_t)n2 * K;
   hipStream_t st = ctx.setup_stream;
-  if (!ctx.blas) {
-    rocblas_handle h = nullptr;
-    SCW_BLAS(rocblas_create_handle(&h));
-    ctx.blas = h;
-  }
-  rocblas_handle h = static_cast<rocblas_handle>(ctx.blas);
-  SCW_BLAS(rocblas_set_stream(h, st));
-  // XY: X_l, Y_l of every layer at 2l, 2l + 1; XYlu: their LU factors
-  DevBuf dXY, dXYlu, dFe, dFh, dA1, dA2, dP1, dP2, dT, dR, dE, dpiv, dxypiv, dinfo;
+  *bad = 0;
+  void* hv = nullptr;
   int rc;
-  if ((rc = dXY.reserve(nn * 16 * 2 * L)) || (rc = dXYlu.reserve(nn * 16 * 2 * L)) ||
-      (rc = dFe.reserve(nn * 16)) || (rc = dFh.reserve(nn * 16)) ||
-      (rc = dA1.reserve(nn * 16)) || (rc = dA2.reserve(nn * 16)) || (rc = dP1.reserve(nn * 16)) ||
-      (rc = dP2.reserve(nn * 16)) || (rc = dT.reserve(nn * 16 * L)) ||
-      (rc = dR.reserve(nn * 16 * L)) || (rc = dE.reserve((size_t)L * n2 * 16)) ||
-      (rc = dpiv.reserve((size_t)n2 * sizeof(rocblas_int))) ||
-      (rc = dxypiv.reserve((size_t)2 * L * n2 * sizeof(rocblas_int))) ||
-      (rc = dinfo.reserve((size_t)3 * L * sizeof(rocblas_int))))
+  if ((rc = blas_handle(ctx, st, &hv))) return rc;
+  rocblas_handle h = static_cast<rocblas_handle>(hv);
+  // XYlu [L][2][G]: LU factors of X and Y; F, A [2][G]: F_l = [Fe; Fh] and its
+  // transformed copy; T, R [L][G]; E [L][G][n2]
+  DevBuf dXYlu, dF, dA, dP, dT, dR, dE, dhd, dpiv, dxypiv, dinfo;
+  if ((rc = dXYlu.reserve(gn * 16 * 2 * L)) || (rc = dF.reserve(gn * 16 * 2)) ||
+      (rc = dA.reserve(gn * 16 * 2)) || (rc = dP.reserve(gn * 16 * 2)) ||
+      (rc = dT.reserve(gn * 16 * L)) || (rc = dR.reserve(gn * 16 * L)) ||
+      (rc = dE.reserve((size_t)L * G * n2 * 16)) || (rc = dhd.reserve((size_t)G * 8 * M * 16)) ||
+      (rc = dpiv.reserve((size_t)G * n4 * sizeof(rocblas_int))) ||
+      (rc = dxypiv.reserve((size_t)2 * L * G * n2 * sizeof(rocblas_int))) ||
+      (rc = dinfo.reserve((size_t)(3 * L + 1) * G * sizeof(rocblas_int))))
     return rc;
-  for (int l = 0; l < L; ++l) {
-    SCW_HIP(hipMemcpyAsync(dE.as<zc>() + (size_t)l * n2, layers[l].E.data(), n2 * 16,
-                           hipMemcpyHostToDevice, st));
-    SCW_HIP(hipMemcpyAsync(dXY.as<zc>() + (size_t)(2 * l) * nn, layers[l].X.data(), nn * 16,
-                           hipMemcpyHostToDevice, st));
-    SCW_HIP(hipMemcpyAsync(dXY.as<zc>() + (size_t)(2 * l + 1) * nn, layers[l].Y.data(), nn * 16,
-                           hipMemcpyHostToDevice, st));
+  std::vector<zc> E((size_t)L * G * n2), hd((size_t)G * 8 * M);
+  for (int g = 0; g < G; ++g) {
+    for (int l = 0; l < L; ++l)
+      std::copy((*layers[g])[l].E.begin(), (*layers[g])[l].E.end(),
+                E.begin() + ((size_t)l * G + g) * n2);
+    const Solution& s = *sols[g];
+    std::vector<zc> msz(M);
+    for (int m = 0; m < M; ++m) msz[m] = -s.sz_top[m];
+    half_space_diagonals(s, s.sz_bot, hd.data() + (size_t)g * 4 * M);
+    half_space_diagonals(s, msz, hd.data() + (size_t)(G + g) * 4 * M);
+    for (int q = 0; q < 2; ++q)  // X, Y: layers L apart in their place of XYlu
+      SCW_HIP(hipMemcpy2DAsync(dXYlu.as<zc>() + ((size_t)q * G + g) * nn, 2 * gn * 16,
+                               (q ? dY : dX) + (size_t)g * L * nn, nn * 16, nn * 16, L,
+                               hipMemcpyDeviceToDevice, st));
   }
-  SCW_HIP(hipMemcpyAsync(dXYlu.p, dXY.p, nn * 16 * 2 * L, hipMemcpyDeviceToDevice, st));
-  SCW_HIP(launch_eye(dFe.as<double>(), n2, st));
-  const Mat Fh0 = half_space_h(s, s.sz_bot);
-  SCW_HIP(hipMemcpyAsync(dFh.p, Fh0.data(), nn * 16, hipMemcpyHostToDevice, st));
+  SCW_HIP(hipMemcpyAsync(dE.p, E.data(), E.size() * 16, hipMemcpyHostToDevice, st));
+  SCW_HIP(hipMemcpyAsync(dhd.p, hd.data(), hd.size() * 16, hipMemcpyHostToDevice, st));
+  SCW_HIP(launch_eye(dF.as<double>(), n2, st, G));
+  SCW_HIP(launch_half_space(dhd.as<double>(), n2, G, dF.as<double>() + 2 * gn, st));
   const rocblas_double_complex one = {1.0, 0.0}, zero = {0.0, 0.0};
-  rocblas_int* info = dinfo.as<rocblas_int>();  // [0, 2L): X, Y of each layer; [2L, 3L): G_t
+  // info: [0, 2 L G) X, Y of each layer; [2 L G, 3 L G) G_t; then the top system
+  rocblas_int* info = dinfo.as<rocblas_int>();
   rocblas_int* piv = dpiv.as<rocblas_int>();
   rocblas_int* xypiv = dxypiv.as<rocblas_int>();
   const rocblas_operation N = rocblas_operation_none;
-  SCW_BLAS(rocsolver_zgetrf_strided_batched(h, n2, n2, zp(dXYlu), n2, (rocblas_stride)nn, xypiv,
-                                            (rocblas_stride)n2, info, 2 * L));
+  const rocblas_stride snn = (rocblas_stride)nn, sl = (rocblas_stride)L * nn;
+  auto zx = [](const zc* p) {
+    return reinterpret_cast<rocblas_double_complex*>(const_cast<zc*>(p));
+  };
+  SCW_BLAS(rocsolver_zgetrf_strided_batched(h, n2, n2, zp(dXYlu), n2, snn, xypiv,
+                                            (rocblas_stride)n2, info, 2 * L * G));
   for (int l = L - 1; l >= 0; --l) {
-    rocblas_double_complex* Xl = zp(dXY, (size_t)(2 * l) * nn);
-    rocblas_double_complex* Yl = zp(dXY, (size_t)(2 * l + 1) * nn);
-    SCW_HIP(hipMemcpyAsync(dA1.p, dFe.p, nn * 16, hipMemcpyDeviceToDevice, st));
-    SCW_HIP(hipMemcpyAsync(dA2.p, dFh.p, nn * 16, hipMemcpyDeviceToDevice, st));
+    SCW_HIP(hipMemcpyAsync(dA.p, dF.p, gn * 16 * 2, hipMemcpyDeviceToDevice, st));
     // A1 = X^-1 Fe, A2 = Y^-1 Fh with the factors of the batched call
-    SCW_BLAS(rocsolver_zgetrs(h, N, n2, n2, zp(dXYlu, (size_t)(2 * l) * nn), n2,
-                              xypiv + (size_t)(2 * l) * n2, zp(dA1), n2));
-    SCW_BLAS(rocsolver_zgetrs(h, N, n2, n2, zp(dXYlu, (size_t)(2 * l + 1) * nn), n2,
-                              xypiv + (size_t)(2 * l + 1) * n2, zp(dA2), n2));
+    SCW_BLAS(rocsolver_zgetrs_strided_batched(
+        h, N, n2, n2, zp(dXYlu, (size_t)(2 * l) * gn), n2, snn,
+        xypiv + (size_t)(2 * l) * G * n2, (rocblas_stride)n2, zp(dA), n2, snn, 2 * G));
     // G_t, G_b in place; t = G_t^-1; r = G_b t
-    SCW_HIP(launch_half_sum_diff(dA1.as<double>(), dA2.as<double>(), (long long)nn, st));
-    zc* tl = dT.as<zc>() + (size_t)l * nn;
-    zc* rl = dR.as<zc>() + (size_t)l * nn;
-    SCW_HIP(launch_eye(reinterpret_cast<double*>(tl), n2, st));
-    SCW_BLAS(rocsolver_zgetrf(h, n2, n2, zp(dA1), n2, piv, info + 2 * L + l));
-    SCW_BLAS(rocsolver_zgetrs(h, N, n2, n2, zp(dA1), n2, piv,
-                              reinterpret_cast<rocblas_double_complex*>(tl), n2));
-    SCW_BLAS(rocblas_zgemm(h, N, N, n2, n2, n2, &one, zp(dA2), n2,
-                           reinterpret_cast<rocblas_double_complex*>(tl), n2, &zero,
-                           reinterpret_cast<rocblas_double_complex*>(rl), n2));
+    double* A2 = dA.as<double>() + 2 * gn;
+    SCW_HIP(launch_half_sum_diff(dA.as<double>(), A2, (long long)gn, st));
+    zc* tl = dT.as<zc>() + (size_t)l * gn;
+    zc* rl = dR.as<zc>() + (size_t)l * gn;
+    SCW_HIP(launch_eye(reinterpret_cast<double*>(tl), n2, st, G));
+    SCW_BLAS(rocsolver_zgetrf_strided_batched(h, n2, n2, zp(dA), n2, snn, piv, (rocblas_stride)n2,
+                                              info + (size_t)(2 * L + l) * G, G));
+    SCW_BLAS(rocsolver_zgetrs_strided_batched(h, N, n2, n2, zp(dA), n2, snn, piv,
+                                              (rocblas_stride)n2, zx(tl), n2, snn, G));
+    SCW_BLAS(rocblas_zgemm_strided_batched(h, N, N, n2, n2, n2, &one, zp(dA, gn), n2, snn, zx(tl),
+                                           n2, snn, &zero, zx(rl), n2, snn, G));
     // F_l = [X (I + E r E); Y (I - E r E)]
-    SCW_HIP(launch_i_pm_ere(reinterpret_cast<double*>(rl), dE.as<double>() + (size_t)l * n2 * 2,
-                            n2, dP1.as<double>(), dP2.as<double>(), st));
-    SCW_BLAS(rocblas_zgemm(h, N, N, n2, n2, n2, &one, Xl, n2, zp(dP1), n2, &zero, zp(dFe), n2));
-    SCW_BLAS(rocblas_zgemm(h, N, N, n2, n2, n2, &one, Yl, n2, zp(dP2), n2, &zero, zp(dFh), n2));
+    SCW_HIP(launch_i_pm_ere(reinterpret_cast<double*>(rl),
+                            dE.as<double>() + (size_t)l * G * n2 * 2, n2, G, dP.as<double>(),
+                            dP.as<double>() + 2 * gn, st));
+    SCW_BLAS(rocblas_zgemm_strided_batched(h, N, N, n2, n2, n2, &one, zx(dX + (size_t)l * nn), n2,
+                                           sl, zp(dP), n2, snn, &zero, zp(dF), n2, snn, G));
+    SCW_BLAS(rocblas_zgemm_strided_batched(h, N, N, n2, n2, n2, &one, zx(dY + (size_t)l * nn), n2,
+                                           sl, zp(dP, gn), n2, snn, &zero, zp(dF, gn), n2, snn,
+                                           G));
   }
-  std::vector<rocblas_int> hinfo(3 * L);
+  // The 4M x 4M top-surface system of every problem: p_ref and a_1 as
+  // top_surface leaves them, for every illumination.
+  const size_t n4k = (size_t)n4 * K;
+  dXYlu.release();
+  DevBuf dS, drhs;
+  if ((rc = dS.reserve((size_t)G * n4 * n4 * 16)) || (rc = drhs.reserve((size_t)G * n4k * 16)))
+    return rc;
+  std::vector<zc> x((size_t)G * n4k);
+  for (int g = 0; g < G; ++g) {
+    const std::vector<zc> r = top_surface_rhs(*sols[g]);
+    std::copy(r.begin(), r.end(), x.begin() + (size_t)g * n4k);
+  }
+  SCW_HIP(hipMemcpyAsync(drhs.p, x.data(), x.size() * 16, hipMemcpyHostToDevice, st));
+  SCW_HIP(launch_top_system(dhd.as<double>() + (size_t)G * 8 * M, dF.as<double>(),
+                            dF.as<double>() + 2 * gn, n2, G, dS.as<double>(), st));
+  SCW_BLAS(rocsolver_zgetrf_strided_batched(h, n4, n4, zp(dS), n4, (rocblas_stride)n4 * n4, piv,
+                                            (rocblas_stride)n4, info + (size_t)3 * L * G, G));
+  SCW_BLAS(rocsolver_zgetrs_strided_batched(h, N, n4, K, zp(dS), n4, (rocblas_stride)n4 * n4, piv,
+                                            (rocblas_stride)n4, zp(drhs), n4,
+                                            (rocblas_stride)n4k, G));
+  std::vector<rocblas_int> hinfo((size_t)(3 * L + 1) * G);
   SCW_HIP(hipMemcpyAsync(hinfo.data(), info, hinfo.size() * sizeof(rocblas_int),
                          hipMemcpyDeviceToHost, st));
+  SCW_HIP(hipMemcpyAsync(x.data(), drhs.p, x.size() * 16, hipMemcpyDeviceToHost, st));
   SCW_HIP(hipStreamSynchronize(st));
-  for (int i = 0; i < 3 * L; ++i)
-    if (hinfo[i] != 0)
-      return fail(i >= 2 * L ? SCW_EILLCOND : SCW_EDEFECTIVE,
-                  i >= 2 * L ? "singular interface matrix in the device elimination (layer " +
-                                   std::to_string(i - 2 * L) + ")"
-                             : "eigenvector matrix is singular (layer " + std::to_string(i / 2) +
-                                   ")");
-  std::vector<zc> a1;
-  if ((rc = top_surface_device(ctx, s, dFe, dFh, a1))) return rc;
-  // back-substitution of all illuminations: columns of n2 x K blocks
-  DevBuf dAc, dEA, dAs, dBs;
-  const size_t nk = (size_t)n2 * K;
-  if ((rc = dAc.reserve(nk * 16)) || (rc = dEA.reserve(nk * 16)) ||
-      (rc = dAs.reserve(nk * 16 * L)) || (rc = dBs.reserve(nk * 16 * L)))
-    return rc;
-  SCW_HIP(hipMemcpyAsync(dAc.p, a1.data(), nk * 16, hipMemcpyHostToDevice, st));
-  for (int l = 0; l < L; ++l) {
-    SCW_HIP(hipMemcpyAsync(dAs.as<zc>() + (size_t)l * nk, dAc.p, nk * 16, hipMemcpyDeviceToDevice,
-                           st));
-    SCW_HIP(launch_scale_rows(dE.as<double>() + (size_t)l * n2 * 2, dAc.as<double>(), n2, K,
-                              dEA.as<double>(), st));
-    SCW_BLAS(rocblas_zgemm(h, N, N, n2, K, n2, &one,
-                           reinterpret_cast<rocblas_double_complex*>(dR.as<zc>() + (size_t)l * nn),
-                           n2, zp(dEA), n2, &zero, zp(dBs, (size_t)l * nk), n2));
-    SCW_BLAS(rocblas_zgemm(h, N, N, n2, K, n2, &one,
-                           reinterpret_cast<rocblas_double_complex*>(dT.as<zc>() + (size_t)l * nn),
-                           n2, zp(dEA), n2, &zero, zp(dAc), n2));
+  for (int g = 0; g < G; ++g) {
+    *bad = g;
+    for (int l = 0; l < L; ++l)
+      for (int q = 0; q < 2; ++q)
+        if (hinfo[((size_t)2 * l + q) * G + g] != 0)
+          return fail(SCW_EDEFECTIVE,
+                      "eigenvector matrix is singular (layer " + std::to_string(l) + ")");
+    for (int l = 0; l < L; ++l)
+      if (hinfo[(size_t)(2 * L + l) * G + g] != 0)
+        return fail(SCW_EILLCOND, "singular interface matrix in the device elimination (layer " +
+                                      std::to_string(l) + ")");
+    if (hinfo[(size_t)3 * L * G + g] != 0)
+      return fail(SCW_EILLCOND, "singular top-surface system in the device elimination");
   }
-  std::vector<zc> As(nk * L), Bs(nk * L), last(nk);
+  *bad = 0;
+  // back-substitution of all illuminations: columns of n2 x K blocks per problem
+  dS.release();
+  DevBuf dEA, dAs, dBs;  // As, Bs [L + 1][G][n2 K]
+  if ((rc = dEA.reserve(G * nk * 16)) || (rc = dAs.reserve(G * nk * 16 * (L + 1))) ||
+      (rc = dBs.reserve(G * nk * 16 * L)))
+    return rc;
+  std::vector<zc> As(G * nk * (L + 1)), Bs(G * nk * L);
+  for (int g = 0; g < G; ++g) {
+    std::vector<zc> a1;
+    top_surface_finish(*sols[g],
+                       std::vector<zc>(x.begin() + (size_t)g * n4k, x.begin() + (size_t)(g + 1) * n4k),
+                       a1);
+    std::copy(a1.begin(), a1.end(), As.begin() + (size_t)g * nk);
+  }
+  SCW_HIP(hipMemcpyAsync(dAs.p, As.data(), G * nk * 16, hipMemcpyHostToDevice, st));
+  for (int l = 0; l < L; ++l) {
+    SCW_HIP(launch_scale_rows(dE.as<double>() + (size_t)l * G * n2 * 2,
+                              dAs.as<double>() + (size_t)l * G * nk * 2, n2, K, G,
+                              dEA.as<double>(), st));
+    SCW_BLAS(rocblas_zgemm_strided_batched(h, N, N, n2, K, n2, &one, zp(dR, (size_t)l * gn), n2,
+                                           snn, zp(dEA), n2, (rocblas_stride)nk, &zero,
+                                           zp(dBs, (size_t)l * G * nk), n2, (rocblas_stride)nk, G));
+    SCW_BLAS(rocblas_zgemm_strided_batched(
+        h, N, N, n2, K, n2, &one, zp(dT, (size_t)l * gn), n2, snn, zp(dEA), n2,
+        (rocblas_stride)nk, &zero, zp(dAs, (size_t)(l + 1) * G * nk), n2, (rocblas_stride)nk, G));
+  }
   SCW_HIP(hipMemcpyAsync(As.data(), dAs.p, As.size() * 16, hipMemcpyDeviceToHost, st));
   SCW_HIP(hipMemcpyAsync(Bs.data(), dBs.p, Bs.size() * 16, hipMemcpyDeviceToHost, st));
-  SCW_HIP(hipMemcpyAsync(last.data(), dAc.p, nk * 16, hipMemcpyDeviceToHost, st));
   SCW_HIP(hipStreamSynchronize(st));
-  // [L][K][n2] on the device -> [K][L][n2]
-  s.a.assign((size_t)K * L * n2, zc(0));
-  s.b.assign((size_t)K * L * n2, zc(0));
-  for (int l = 0; l < L; ++l)
-    for (int kk = 0; kk < K; ++kk) {
-      std::copy(As.begin() + (size_t)l * nk + (size_t)kk * n2,
-                As.begin() + (size_t)l * nk + (size_t)(kk + 1) * n2,
-                s.a.begin() + ((size_t)kk * L + l) * n2);
-      std::copy(Bs.begin() + (size_t)l * nk + (size_t)kk * n2,
-                Bs.begin() + (size_t)l * nk + (size_t)(kk + 1) * n2,
-                s.b.begin() + ((size_t)kk * L + l) * n2);
-    }
-  for (int kk = 0; kk < K; ++kk) transmitted(s, kk, last.data() + (size_t)kk * n2);
+  for (int g = 0; g < G; ++g) {  // [L][G][K][n2] -> [K][L][n2] per problem
+    Solution& s = *sols[g];
+    s.a.assign((size_t)K * L * n2, zc(0));
+    s.b.assign((size_t)K * L * n2, zc(0));
+    for (int l = 0; l < L; ++l)
+      for (int kk = 0; kk < K; ++kk) {
+        const size_t src = ((size_t)l * G + g) * nk + (size_t)kk * n2;
+        const size_t dst = ((size_t)kk * L + l) * n2;
+        std::copy(As.begin() + src, As.begin() + src + n2, s.a.begin() + dst);
+        std::copy(Bs.begin() + src, Bs.begin() + src + n2, s.b.begin() + dst);
+      }
+    for (int kk = 0; kk < K; ++kk)
+      transmitted(s, kk, As.data() + ((size_t)L * G + g) * nk + (size_t)kk * n2);
+  }
   return SCW_OK;
 }
+
 // The connection route with its per-layer work on the device: T_l and B_l
 // from X, Y, E, T_l = LU (kept per layer with its pivots), M_l = B_l T_l^-1,
 // K = M_L ... M_1; the 6M x 6M system on the host (connection_system); then
 // alpha_l = T_l^-1 B_{l-1} alpha_{l-1} for all illuminations on the device.
-int solve_connection_device(Context& ctx, const Lin& lin, Solution& s,
-                            std::vector<LayerHost>& layers) {
+int solve_connection_device(Context& ctx, Solution& s, const std::vector<LayerHost>& layers,
+                            const zc* dX, const zc* dY) {
   const int M = s.M, n2 = 2 * M, n4 = 4 * M, L = s.L, nk = s.K;
   const size_t nn = (size_t)n2 * n2, nn4 = (size_t)n4 * n4;
   hipStream_t st = ctx.setup_stream;
@@ -637,10 +671,9 @@ int solve_connection_device(Context& ctx, const Lin& lin, Solution& s,
   }
   rocblas_handle h = static_cast<rocblas_handle>(ctx.blas);
   SCW_BLAS(rocblas_set_stream(h, st));
-  DevBuf dX, dY, dE, dT, dB, dTi, dMk, dK, dK2, dpiv, dinfo;
+  DevBuf dE, dT, dB, dTi, dMk, dK, dK2, dpiv, dinfo;
   int rc;
-  if ((rc = dX.reserve(nn * 16)) || (rc = dY.reserve(nn * 16)) ||
-      (rc = dE.reserve((size_t)L * n2 * 16)) || (rc = dT.reserve(nn4 * 16 * L)) ||
+  if ((rc = dE.reserve((size_t)L * n2 * 16)) || (rc = dT.reserve(nn4 * 16 * L)) ||
       (rc = dB.reserve(nn4 * 16 * L)) || (rc = dTi.reserve(nn4 * 16)) ||
       (rc = dMk.reserve(nn4 * 16)) || (rc = dK.reserve(nn4 * 16)) || (rc = dK2.reserve(nn4 * 16)) ||
       (rc = dpiv.reserve((size_t)L * n4 * sizeof(rocblas_int))) ||
@@ -657,10 +690,10 @@ int solve_connection_device(Context& ctx, const Lin& lin, Solution& s,
   auto Bl = [&](int l) { return zp(dB, (size_t)l * nn4); };
   SCW_HIP(launch_eye(dK.as<double>(), n4, st));
   for (int l = 0; l < L; ++l) {
-    SCW_HIP(hipMemcpyAsync(dX.p, layers[l].X.data(), nn * 16, hipMemcpyHostToDevice, st));
-    SCW_HIP(hipMemcpyAsync(dY.p, layers[l].Y.data(), nn * 16, hipMemcpyHostToDevice, st));
-    SCW_HIP(launch_build_tb(dX.as<double>(), dY.as<double>(), dE.as<double>() + (size_t)l * n2 * 2,
-                            n2, reinterpret_cast<double*>(Tl(l)),
+    SCW_HIP(launch_build_tb(reinterpret_cast<const double*>(dX + (size_t)l * nn),
+                            reinterpret_cast<const double*>(dY + (size_t)l * nn),
+                            dE.as<double>() + (size_t)l * n2 * 2, n2,
+                            reinterpret_cast<double*>(Tl(l)),
                             reinterpret_cast<double*>(Bl(l)), st));
     SCW_BLAS(rocsolver_zgetrf(h, n4, n4, Tl(l), n4, piv(l), info + l));
     SCW_HIP(launch_eye(dTi.as<double>(), n4, st));
@@ -878,6 +911,15 @@ struct PendingSolve {
   double device_eig_seconds = 0;
   std::vector<LayerHost> layers;
   DevBuf d_A, d_C;  // property blocks of every layer (device eigensolver only)
+  // X, Y of every layer on the device, [L][2M x 2M], in buffers that the
+  // problems of one eigensolver batch share (null: only in `layers`)
+  std::shared_ptr<DevBuf> own_X, own_Y;
+  const zc *dX = nullptr, *dY = nullptr;
+  void release_xy() {
+    dX = dY = nullptr;
+    own_X.reset();
+    own_Y.reset();
+  }
   DevBuf d_psi, d_u, d_v, d_sx, d_sy;
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
   PendingSolve() = default;
@@ -893,16 +935,20 @@ struct PendingSolve {
 // The layers of n problems of one truncation (2M x 2M products): every A C
 // by one strided-batched GEMM, all of them eigendecomposed by the batched
 // device eigensolver at once, gamma on the host, Y = C X diag(1/gamma) on the
-// device; X, Y, gamma and E of every layer end in each problem's `layers` as
-// layer_eig leaves them.
-static int device_eig_group(Context& ctx, Solution** sols, PendingSolve** ps, int n) {
+// device. gamma and E of every layer end in each problem's `layers` as
+// layer_eig leaves them; X and Y stay on the device (dX, dY), and are copied
+// to `layers` for the problems whose boundary solve runs on the host.
+static int device_eig_group(Context& ctx, const scw_problem* const* probs, Solution** sols,
+                            PendingSolve** ps, int n) {
   const int n2 = 2 * sols[0]->M;
   const size_t nn = (size_t)n2 * n2;
   int total = 0;
   for (int i = 0; i < n; ++i) total += sols[i]->L;
   hipStream_t st = ctx.setup_stream;
   const double t0 = now_s();
-  DevBuf cat_A, cat_C, d_AC, d_X, d_w, d_f;
+  DevBuf cat_A, cat_C, d_w, d_f;
+  auto own_X = std::make_shared<DevBuf>(), own_Y = std::make_shared<DevBuf>();
+  DevBuf &d_X = *own_X, &d_AC = *own_Y;  // (A C, then Y)
   int rc;
   const DevBuf* A = &ps[0]->d_A;
   const DevBuf* C = &ps[0]->d_C;
@@ -935,22 +981,32 @@ static int device_eig_group(Context& ctx, Solution** sols, PendingSolve** ps, in
   std::vector<zc> lam((size_t)n2 * total), f((size_t)n2 * total);
   SCW_HIP(hipMemcpyAsync(lam.data(), d_w.p, lam.size() * 16, hipMemcpyDeviceToHost, st));
   SCW_HIP(hipStreamSynchronize(st));
-  size_t g = 0;  // global layer index
+  std::vector<std::pair<int, int>> at;  // (problem, layer) of each matrix
   for (int i = 0; i < n; ++i)
-    for (int l = 0; l < sols[i]->L; ++l, ++g) {
-      LayerHost& lh = ps[i]->layers[l];
-      if ((rc = layer_gamma(*sols[i], lam.data() + g * n2, lh))) return rc;
-      for (int j = 0; j < n2; ++j) f[g * n2 + j] = 1.0 / lh.gamma[j];
-    }
+    for (int l = 0; l < sols[i]->L; ++l) at.emplace_back(i, l);
+  rc = parallel_for(total, ctx.host_threads, [&](int q) -> int {
+    LayerHost& lh = ps[at[q].first]->layers[at[q].second];
+    const int r = layer_gamma(*sols[at[q].first], lam.data() + (size_t)q * n2, lh);
+    if (r) return r;
+    for (int j = 0; j < n2; ++j) f[(size_t)q * n2 + j] = 1.0 / lh.gamma[j];
+    return 0;
+  });
+  if (rc) return rc;
   SCW_HIP(hipMemcpyAsync(d_f.p, f.data(), f.size() * 16, hipMemcpyHostToDevice, st));
   SCW_BLAS(rocblas_zgemm_strided_batched(h, N, N, n2, n2, n2, &one, zp(*C), n2,
                                          (rocblas_stride)nn, zp(d_X), n2, (rocblas_stride)nn,
                                          &zero, zp(d_AC), n2, (rocblas_stride)nn, total));
   SCW_HIP(launch_eig_scale_cols(n2, (long long)n2 * total, d_f.as<double>(), d_AC.as<double>(),
                                 st));
-  g = 0;
-  for (int i = 0; i < n; ++i)
+  size_t g = 0;  // global layer index
+  for (int i = 0; i < n; ++i) {
+    ps[i]->own_X = own_X;
+    ps[i]->own_Y = own_Y;
+    ps[i]->dX = d_X.as<zc>() + g * nn;
+    ps[i]->dY = d_AC.as<zc>() + g * nn;
+    const bool host = probs[i]->route == SCW_ROUTE_STABLE || probs[i]->route == SCW_ROUTE_CONNECTION;
     for (int l = 0; l < sols[i]->L; ++l, ++g) {
+      if (!host) continue;
       LayerHost& lh = ps[i]->layers[l];
       lh.X.resize(nn);
       lh.Y.resize(nn);
@@ -959,6 +1015,7 @@ static int device_eig_group(Context& ctx, Solution** sols, PendingSolve** ps, in
       SCW_HIP(hipMemcpyAsync(lh.Y.data(), d_AC.as<zc>() + g * nn, nn * 16, hipMemcpyDeviceToHost,
                              st));
     }
+  }
   SCW_HIP(hipStreamSynchronize(st));
   const double dt = now_s() - t0;
   for (int i = 0; i < n; ++i) {
@@ -1160,18 +1217,16 @@ int solve_begin(Context& ctx, const scw_problem& p, Solution& s, int n_waves,
   return SCW_OK;
 }
 
-// Steps after the eigendecompositions' device part: host eigendecompositions
-// (SCW_EIG_HOST), LU of the eigenvector blocks for the host stable route,
-// growth exponent, boundary solve, synthesis matrices and device uploads.
-int solve_finish(Context& ctx, const scw_problem& p, Solution& s, PendingSolve& ps) {
+// After the eigendecompositions' device part: host eigendecompositions
+// (SCW_EIG_HOST), LU of the eigenvector blocks for the host stable route, the
+// growth exponent, and X, Y on the device for the device routes.
+int solve_modes(Context& ctx, const scw_problem& p, Solution& s, PendingSolve& ps) {
   const Lapack& lp = lapack();
   const Lin lin{lp};
-  const int M = s.M, n2 = 2 * M, L = s.L, U = s.U, V = s.V;
-  const int nbu = 2 * U - 1, nbv = 2 * V - 1;
+  const int n2 = 2 * s.M, L = s.L;
   const size_t blk = (size_t)n2 * n2;
   const bool dev_eig = ps.dev_eig;
   std::vector<LayerHost>& layers = ps.layers;
-  DevBuf &d_psi = ps.d_psi, &d_u = ps.d_u, &d_v = ps.d_v, &d_sx = ps.d_sx, &d_sy = ps.d_sy;
   hipStream_t st = ctx.setup_stream;
   int rc;
   // ---- eigendecompositions (Sec. 3.2, Sec. 4.2): on the host, one layer per
@@ -1213,7 +1268,6 @@ int solve_finish(Context& ctx, const scw_problem& p, Solution& s, PendingSolve& 
   s.info.min_abs_gamma_rel = gmin_rel;
   s.info.growth_exponent = growth;
 
-  // ---- host: boundary solve (Sec. 2.5.4, Sec. 3.3-3.4)
   // The connection product K holds exp(growth_exponent) next to O(1) terms;
   // past e^25 (about 7e10) its system keeps fewer digits than the field needs,
   // so a forced connection route fails instead of returning degraded values.
@@ -1222,31 +1276,100 @@ int solve_finish(Context& ctx, const scw_problem& p, Solution& s, PendingSolve& 
     return fail(SCW_EILLCOND, "connection route: growth exponent " + std::to_string(growth) +
                                   " above 25 (use SCW_ROUTE_STABLE)");
   if (lp.set_threads) lp.set_threads(ctx.host_threads);
+  const bool device_route =
+      p.route == SCW_ROUTE_STABLE_DEVICE || p.route == SCW_ROUTE_CONNECTION_DEVICE;
+  if (device_route && !ps.dX) {
+    ps.own_X = std::make_shared<DevBuf>();
+    ps.own_Y = std::make_shared<DevBuf>();
+    if ((rc = ps.own_X->reserve(blk * 16 * L)) || (rc = ps.own_Y->reserve(blk * 16 * L))) return rc;
+    for (int l = 0; l < L; ++l) {
+      SCW_HIP(hipMemcpyAsync(ps.own_X->as<zc>() + (size_t)l * blk, layers[l].X.data(), blk * 16,
+                             hipMemcpyHostToDevice, st));
+      SCW_HIP(hipMemcpyAsync(ps.own_Y->as<zc>() + (size_t)l * blk, layers[l].Y.data(), blk * 16,
+                             hipMemcpyHostToDevice, st));
+    }
+    SCW_HIP(hipStreamSynchronize(st));
+    ps.dX = ps.own_X->as<zc>();
+    ps.dY = ps.own_Y->as<zc>();
+  }
+  return SCW_OK;
+}
+
+// Boundary solve (Sec. 2.5.4, Sec. 3.3-3.4) of `n` problems: one, or problems
+// on the stable device route whose X, Y follow each other on the device
+// (boundary_group). On failure *bad is the problem at fault.
+int solve_boundary(Context& ctx, const scw_problem* const* probs, Solution** sols,
+                   PendingSolve** ps, int n, int* bad) {
+  const Lin lin{lapack()};
   const double t_bnd = now_s();
-  switch (p.route) {
+  Solution& s = *sols[0];
+  std::vector<LayerHost>& layers = ps[0]->layers;
+  int rc;
+  *bad = 0;
+  switch (probs[0]->route) {
     case SCW_ROUTE_STABLE: rc = solve_stable(lin, s, layers); break;
-    case SCW_ROUTE_STABLE_DEVICE: rc = solve_stable_device(ctx, lin, s, layers); break;
-    case SCW_ROUTE_CONNECTION_DEVICE: rc = solve_connection_device(ctx, lin, s, layers); break;
+    case SCW_ROUTE_STABLE_DEVICE: {
+      std::vector<std::vector<LayerHost>*> lay(n);
+      for (int i = 0; i < n; ++i) lay[i] = &ps[i]->layers;
+      rc = solve_stable_device(ctx, n, sols, lay.data(), ps[0]->dX, ps[0]->dY, bad);
+      break;
+    }
+    case SCW_ROUTE_CONNECTION_DEVICE:
+      rc = solve_connection_device(ctx, s, layers, ps[0]->dX, ps[0]->dY);
+      break;
     default: rc = solve_connection(lin, s, layers, ctx.host_threads); break;
   }
   if (rc) return rc;
-  s.info.boundary_seconds = now_s() - t_bnd;
+  for (int i = 0; i < n; ++i) sols[i]->info.boundary_seconds = now_s() - t_bnd;
+  return SCW_OK;
+}
 
+// How many problems from the first of `n` can share the device elimination:
+// the same shape, one after another on the device, in about 4 GB of
+// workspace (6 blocks per layer and 2 x 2 for the top system).
+int boundary_group(const scw_problem* const* probs, Solution** sols, PendingSolve** ps, int n) {
+  if (probs[0]->route != SCW_ROUTE_STABLE_DEVICE) return 1;
+  const size_t nn = 4 * (size_t)sols[0]->M * sols[0]->M;
+  const size_t each = nn * 16 * (4 * (size_t)sols[0]->L + 10);
+  int g = 1;
+  while (g < n && (size_t)(g + 1) * each <= ((size_t)4 << 30) &&
+         probs[g]->route == SCW_ROUTE_STABLE_DEVICE && sols[g]->M == sols[0]->M &&
+         sols[g]->L == sols[0]->L && sols[g]->K == sols[0]->K && ps[g]->dX && ps[0]->dX &&
+         ps[g]->dX == ps[0]->dX + (size_t)g * sols[0]->L * nn &&
+         ps[g]->dY == ps[0]->dY + (size_t)g * sols[0]->L * nn)
+    ++g;
+  return g;
+}
+
+// Last steps of a solve: synthesis matrices and device uploads.
+int solve_finish(Context& ctx, Solution& s, PendingSolve& ps) {
+  const int M = s.M, n2 = 2 * M, L = s.L, U = s.U, V = s.V;
+  const int nbu = 2 * U - 1, nbv = 2 * V - 1;
+  const size_t blk = (size_t)n2 * n2;
+  std::vector<LayerHost>& layers = ps.layers;
+  DevBuf &d_psi = ps.d_psi, &d_u = ps.d_u, &d_v = ps.d_v, &d_sx = ps.d_sx, &d_sy = ps.d_sy;
+  hipStream_t st = ctx.setup_stream;
+  int rc;
   // ---- device: synthesis matrices P_l = [X; Psi (S_y Y_x - S_x Y_y)] (Sec. 4.1)
   const size_t pl = (size_t)3 * M * n2;
   if ((rc = s.d_P64.reserve(pl * 16 * L))) return rc;
   DevBuf d_X, d_Y;
-  const int pchunk = std::max(1, std::min(L, (int)((size_t)(1u << 30) / (blk * 32))));
-  if ((rc = d_X.reserve(blk * 16 * pchunk)) || (rc = d_Y.reserve(blk * 16 * pchunk))) return rc;
+  const bool on_device = ps.dX != nullptr;  // else uploaded in chunks
+  const int pchunk =
+      on_device ? L : std::max(1, std::min(L, (int)((size_t)(1u << 30) / (blk * 32))));
+  if (!on_device &&
+      ((rc = d_X.reserve(blk * 16 * pchunk)) || (rc = d_Y.reserve(blk * 16 * pchunk))))
+    return rc;
   for (int l0 = 0; l0 < L; l0 += pchunk) {
     const int nl = std::min(pchunk, L - l0);
-    for (int l = l0; l < l0 + nl; ++l) {
+    for (int l = l0; l < l0 + nl && !on_device; ++l) {
       SCW_HIP(hipMemcpyAsync(d_X.as<char>() + (size_t)(l - l0) * blk * 16, layers[l].X.data(),
                              blk * 16, hipMemcpyHostToDevice, st));
       SCW_HIP(hipMemcpyAsync(d_Y.as<char>() + (size_t)(l - l0) * blk * 16, layers[l].Y.data(),
                              blk * 16, hipMemcpyHostToDevice, st));
     }
-    SCW_HIP(launch_build_p(d_X.as<double>(), d_Y.as<double>(),
+    SCW_HIP(launch_build_p(on_device ? reinterpret_cast<const double*>(ps.dX) : d_X.as<double>(),
+                           on_device ? reinterpret_cast<const double*>(ps.dY) : d_Y.as<double>(),
                            d_psi.as<double>() + (size_t)l0 * nbv * nbu * 2, d_u.as<int>(),
                            d_v.as<int>(), d_sx.as<double>(), d_sy.as<double>(), U, V, nl,
                            s.d_P64.as<double>() + (size_t)l0 * pl * 2, st));
@@ -1306,6 +1429,7 @@ int solve_finish(Context& ctx, const scw_problem& p, Solution& s, PendingSolve& 
   SCW_HIP(hipMemcpyAsync(s.d_ext.p, ext.data(), ext.size() * 16, hipMemcpyHostToDevice, st));
   SCW_HIP(hipMemcpyAsync(s.d_ksz.p, ksz.data(), ksz.size() * 16, hipMemcpyHostToDevice, st));
   SCW_HIP(hipStreamSynchronize(st));
+  ps.release_xy();
   s.device = ctx.device;
   s.info.setup_seconds = now_s() - ps.t_start;
   return SCW_OK;
@@ -1316,12 +1440,14 @@ int solve_problem(Context& ctx, const scw_problem& p, Solution& s, int n_waves,
   PendingSolve ps;
   int rc = solve_begin(ctx, p, s, n_waves, waves, ps);
   if (rc) return rc;
-  if (ps.dev_eig) {
-    PendingSolve* one[1] = {&ps};
-    Solution* sol[1] = {&s};
-    if ((rc = device_eig_group(ctx, sol, one, 1))) return rc;
-  }
-  return solve_finish(ctx, p, s, ps);
+  PendingSolve* one[1] = {&ps};
+  Solution* sol[1] = {&s};
+  const scw_problem* prob[1] = {&p};
+  int bad;
+  if (ps.dev_eig && (rc = device_eig_group(ctx, prob, sol, one, 1))) return rc;
+  if ((rc = solve_modes(ctx, p, s, ps)) || (rc = solve_boundary(ctx, prob, sol, one, 1, &bad)))
+    return rc;
+  return solve_finish(ctx, s, ps);
 }
 
 int solve_problems(Context& ctx, const scw_problem* probs, int n, Solution** sols) {
@@ -1353,22 +1479,45 @@ int solve_problems(Context& ctx, const scw_problem* probs, int n, Solution** sol
       if (done[i - i0] || !ps[i - i0]->dev_eig) continue;
       std::vector<PendingSolve*> grp;
       std::vector<Solution*> gs;
+      std::vector<const scw_problem*> gp;
       for (int j = i; j < i1; ++j)
         if (!done[j - i0] && ps[j - i0]->dev_eig && sols[j]->M == sols[i]->M) {
           grp.push_back(ps[j - i0].get());
           gs.push_back(sols[j]);
+          gp.push_back(&probs[j]);
           done[j - i0] = 1;
         }
-      if ((rc = device_eig_group(ctx, gs.data(), grp.data(), (int)grp.size()))) {
+      if ((rc = device_eig_group(ctx, gp.data(), gs.data(), grp.data(), (int)grp.size()))) {
         set_error(rc, "problems from " + std::to_string(i) + ": " + scw_last_error());
         return rc;
       }
     }
-    for (int i = i0; i < i1; ++i)
-      if ((rc = solve_finish(ctx, probs[i], *sols[i], *ps[i - i0]))) {
-        set_error(rc, "problem " + std::to_string(i) + ": " + scw_last_error());
+    std::vector<const scw_problem*> pp(i1 - i0);
+    std::vector<PendingSolve*> pps(i1 - i0);
+    for (int i = i0; i < i1; ++i) {
+      pp[i - i0] = &probs[i];
+      pps[i - i0] = ps[i - i0].get();
+    }
+    for (int i = i0; i < i1;) {
+      const int q = i - i0;
+      int g = boundary_group(&pp[q], sols + i, &pps[q], i1 - i), at = 0;
+      rc = SCW_OK;
+      for (at = 0; at < g && !rc; ++at) rc = solve_modes(ctx, probs[i + at], *sols[i + at], *pps[q + at]);
+      if (rc) --at;
+      else
+        // the group's workspace may not fit where a smaller one's does
+        while ((rc = solve_boundary(ctx, &pp[q], sols + i, &pps[q], g, &at)) == SCW_ENOMEM && g > 1)
+          g = (g + 1) / 2;
+      if (!rc) {
+        for (at = 0; at < g && !rc; ++at) rc = solve_finish(ctx, *sols[i + at], *pps[q + at]);
+        if (rc) --at;
+      }
+      if (rc) {
+        set_error(rc, "problem " + std::to_string(i + at) + ": " + scw_last_error());
         return rc;
       }
+      i += g;
+    }
     i0 = i1;
   }
   return SCW_OK;
