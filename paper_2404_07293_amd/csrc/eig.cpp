@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 #include <rocblas/rocblas.h>
 
+#include <algorithm>
 #include <string>
 #include <vector>
 
@@ -36,13 +37,42 @@ int device_eig_batched(Context& ctx, int n, int count, double* A, double* w, dou
   if (!A || !w || !X) return fail(SCW_EINVAL, "batched eigensolver: null pointer");
   SCW_HIP(hipSetDevice(ctx.device));
   const size_t nn = (size_t)n * n;
-  DevBuf dZ, dTt, dinfo;
+  DevBuf dZ, dTt, dstate, drot, dhdr;
   int rc;
+  // A usual iteration has about 1.25 n^2 rotations per matrix and takes three
+  // launches with this record; another launch costs tens of microseconds, so
+  // less is taken where memory is short.
+  EigRecord rec{};
+  size_t capr = nn / 2 + n;
+  rec.caps = 4 * n + 64;
   if ((rc = dZ.reserve(nn * 16 * count)) || (rc = dTt.reserve(nn * 16 * count)) ||
-      (rc = dinfo.reserve(sizeof(int) * count)))
+      (rc = dstate.reserve(sizeof(int) * 8 * count)) ||
+      (rc = dhdr.reserve((size_t)rec.caps * 16 * count)))
     return rc;
+  while ((rc = drot.reserve(capr * 24 * count)) == SCW_ENOMEM && capr > (size_t)n)
+    capr = std::max<size_t>(n, capr / 4);
+  if (rc) return rc;
+  rec.capr = (int)capr;
+  rec.state = dstate.as<int>();
+  rec.rots = drot.as<double>();
+  rec.rotc = drot.as<double>() + 2 * capr * count;
+  rec.hdr = dhdr.as<int>();
   SCW_HIP(launch_eig_hessenberg(n, count, A, dZ.as<double>(), st));
-  SCW_HIP(launch_eig_schur(n, count, A, dZ.as<double>(), w, dinfo.as<int>(), st));
+  SCW_HIP(launch_eig_schur_begin(n, count, rec.state, st));
+  std::vector<int> state(8 * (size_t)count);
+  for (bool done = false; !done;) {
+    SCW_HIP(launch_eig_schur(n, count, A, dZ.as<double>(), w, rec, st));
+    SCW_HIP(hipMemcpyAsync(state.data(), rec.state, state.size() * sizeof(int),
+                           hipMemcpyDeviceToHost, st));
+    SCW_HIP(hipStreamSynchronize(st));
+    done = true;
+    for (int b = 0; b < count; ++b) done = done && state[8 * (size_t)b + 2] != 0;
+  }
+  for (int b = 0; b < count; ++b)
+    if (state[8 * (size_t)b + 3])
+      return fail(SCW_ELAPACK, "batched eigensolver: QR iteration of matrix " +
+                                   std::to_string(b) + " did not converge at eigenvalue " +
+                                   std::to_string(state[8 * (size_t)b + 3] - 1));
   // the Schur factor's eigenvectors overwrite A once it is copied row-major
   SCW_HIP(launch_eig_vectors(n, count, A, dTt.as<double>(), w, A, st));
   void* hv = nullptr;
@@ -58,14 +88,7 @@ int device_eig_batched(Context& ctx, int n, int count, double* A, double* w, dou
     return fail(SCW_EHIP, std::string("rocblas_zgemm_strided_batched: ") +
                               rocblas_status_to_string(bs));
   SCW_HIP(launch_eig_normalize(n, (long long)count * n, X, st));
-  std::vector<int> info(count);
-  SCW_HIP(hipMemcpyAsync(info.data(), dinfo.p, sizeof(int) * count, hipMemcpyDeviceToHost, st));
   SCW_HIP(hipStreamSynchronize(st));
-  for (int b = 0; b < count; ++b)
-    if (info[b])
-      return fail(SCW_ELAPACK, "batched eigensolver: QR iteration of matrix " +
-                                   std::to_string(b) + " did not converge at eigenvalue " +
-                                   std::to_string(info[b] - 1));
   return SCW_OK;
 }
 

@@ -10,9 +10,10 @@
 //      Computations, Alg. 7.4.2).
 //   2. Complex Schur form T = Z^H A Z by the implicitly shifted single-shift
 //      QR algorithm on H: Wilkinson shifts with exceptional shifts after 10
-//      and 20 stalled iterations, deflation on negligible subdiagonals, every
-//      Givens rotation applied to the whole rows and columns of H and to Z
-//      (Golub & Van Loan, Sec. 7.5; the complex form of LAPACK's xLAHQR).
+//      and 20 stalled iterations, deflation on negligible subdiagonals
+//      (Golub & Van Loan, Sec. 7.5; the complex form of LAPACK's xLAHQR). The
+//      iteration works on the active diagonal block; its rotations are
+//      recorded and then applied to the rest of H and to Z.
 //   3. Eigenvectors of T by back-substitution, (T - t_jj I) y_j = 0 with
 //      y_j(j) = 1, perturbing a vanishing pivot to eps |t_jj| as xTREVC does.
 //      The eigenvectors of A are Z y_j (a batched matrix product done by the
@@ -28,7 +29,8 @@ namespace scw {
 namespace {
 
 constexpr int kMaxSweepsPerEigenvalue = 300;
-constexpr int kEigWindow = 16;  // rotations per window of the QR sweep
+constexpr int kEigWindow = 24;  // rotations per window of the QR sweep
+constexpr int kEigInner = 64;   // active blocks up to this order stay in LDS
 
 __device__ inline double2 cmul(double2 a, double2 b) {
   return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
@@ -177,7 +179,8 @@ eig_hessenberg_kernel(int n, double2* __restrict__ A, double2* __restrict__ Z) {
 }
 
 // Rotation G = [[c, s], [-conj(s), c]] with G [x; y] = [r; 0], c real.
-__device__ inline void givens(double2 x, double2 y, double& c, double2& s, double2& r) {
+__device__ inline void givens_scaled(double2 x, double2 y, double& c, double2& s,
+                                           double2& r) {
   const double ax = cabs(x), ay = cabs(y);
   if (ay == 0.0) {
     c = 1.0;
@@ -197,56 +200,228 @@ __device__ inline void givens(double2 x, double2 y, double& c, double2& s, doubl
   s = cscale(cmul(ph, cconj(y)), 1.0 / nrm);
   r = cscale(ph, nrm);
 }
+// The same from two reciprocal square roots where no square leaves the normal
+// range (the chase waits for this result at every rotation).
+__device__ inline void givens(double2 x, double2 y, double& c, double2& s, double2& r) {
+  const double ax2 = x.x * x.x + x.y * x.y, ay2 = y.x * y.x + y.y * y.y, n2 = ax2 + ay2;
+  if (ax2 > 1e-250 && ay2 > 1e-250 && n2 < 1e250) {
+    const double rx = rsqrt(ax2), rn = rsqrt(n2), f = rx * rn;
+    c = ax2 * f;
+    s = cscale(cmul(x, cconj(y)), f);
+    r = cscale(x, n2 * f);
+  } else {
+    givens_scaled(x, y, c, s, r);
+  }
+}
 
 __device__ inline double2& at(double2* M, int n, int i, int j) { return M[(size_t)j * n + i]; }
 
-// Step 2. One workgroup of TPB threads per matrix: H (upper Hessenberg, from
-// step 1) becomes the upper triangular Schur factor T, Z accumulates the
-// rotations, w gets the eigenvalues t_jj. info[b] = 0, or j + 1 when
-// eigenvalue j did not converge in kMaxSweepsPerEigenvalue sweeps.
+__device__ inline double read_lane(double v, int l) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l),
+                          __builtin_amdgcn_readlane(__double2loint(v), l));
+}
+__device__ inline double2 read_lane(double2 v, int l) {
+  return make_double2(read_lane(v.x, l), read_lane(v.y, l));
+}
+__device__ inline int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+// Orders one wave's LDS accesses between phases that pass values across lanes.
+__device__ inline void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// Step 2. H (upper Hessenberg, from step 1) becomes the upper triangular Schur
+// factor T, Z accumulates the rotations, w gets the eigenvalues t_jj.
 //
-// Each sweep runs in windows of W rotations (delayed updates): the diagonal
-// block the window's rotations touch (rows and columns b0 .. be, at most
-// W + 3) is chased in LDS, the rotations are kept, and then applied in one
-// pass to the three regions outside the block that they change: rows
-// k0 .. k1 right of the block (row rotations), columns k0 .. k1 above it and
-// in Z (column rotations). A thread takes one column or row of a region and
-// applies the whole window's rotations to its W + 1 values in registers, so a
-// window costs one read and one write of those regions and no barrier per
-// rotation outside the small block. Within a window the column entries a
-// rotation produces (its r and the zeroed bulge) are written by thread 0 one
-// rotation later, once every thread has read them.
-template <int TPB, int W>
-__global__ void __launch_bounds__(TPB)
-eig_schur_kernel(int n, double2* __restrict__ Hall, double2* __restrict__ Zall,
-                 double2* __restrict__ wall, int* __restrict__ info) {
-  constexpr int LB = W + 3;  // leading dimension of the LDS block (column-major)
-  __shared__ double2 blk[LB * LB];
-  __shared__ double s_c[W];
-  __shared__ double2 s_s[W];
-  __shared__ int s_l;
-  const size_t nn = (size_t)n * n;
-  double2* H = Hall + blockIdx.x * nn;
-  double2* Z = Zall + blockIdx.x * nn;
+// eig_schur_kernel (one workgroup per matrix) iterates on the active diagonal
+// block [l, ihi] alone and records every sweep's rotations; eig_apply_kernel
+// then applies the records to what the iteration never reads: Z, the rows
+// above the active blocks and the columns right of them. The iteration is one
+// dependent chain, so a matrix cannot fill more than a CU with it: with the
+// whole of H and Z updated inside it (2 MB moved per sweep at n = 242, and two
+// barriers per rotation), 96 matrices of order 242 took 142 ms. Only a sixth of
+// that traffic belongs to the active blocks; the rest has no chain at all.
+//
+// A record: sweep q of a matrix is hdr[q] = {l, ihi, offset}, rotation k of it
+// (rows and columns k, k + 1; l <= k < ihi) at offset + k - l of rotc / rots.
+// A matrix whose record is full stops with its state saved (kState ints:
+// ihi, its, done, info, sweeps, rotations) and goes on in the next launch.
+//
+// chase: one wave, rotations k0 .. k1 - 1 of a sweep on the block of rows and
+// columns b0 .. b0 + bn - 1 (bn <= 64) in LDS, lane j on column j. A lane
+// carries its column's value in the row that the next rotation takes, so a
+// rotation is applied to all columns in two complex products; the three entries
+// that decide the next rotation (rows k + 1, k + 2 of columns k, k + 1) are
+// broadcast and turned at once by every lane. The column rotations of row r
+// with index k >= r are left to apply_block_columns: no later rotation of the
+// window reads them.
+constexpr int kState = 8;
+__device__ void chase(double2* __restrict__ blk, int ld, int bn, int b0, int k0, int k1, int l,
+                      int ihi, double2 mu, double* __restrict__ rc, double2* __restrict__ rs) {
+  const int lane = threadIdx.x & 63;
+  int kk = k0 - b0;
+  double2 x, y;
+  if (k0 == l) {
+    x = csub(blk[kk * ld + kk], mu);
+    y = blk[kk * ld + kk + 1];
+  } else {
+    x = blk[(kk - 1) * ld + kk];
+    y = blk[(kk - 1) * ld + kk + 1];
+  }
+  const bool live = lane < bn;
+  double2* col = blk + min(lane, bn - 1) * ld;
+  double2 cur = col[kk], nxt = col[kk + 1];
+  for (int k = k0; k < k1; ++k, ++kk) {
+    double2 nn = col[min(kk + 2, bn - 1)];
+    double c;
+    double2 s, r;
+    givens(x, y, c, s, r);
+    const double2 cs = cconj(s);
+    if (lane == 0) {
+      rc[k - k0] = c;
+      rs[k - k0] = s;
+      if (k > l) {
+        blk[(kk - 1) * ld + kk] = r;
+        blk[(kk - 1) * ld + kk + 1] = make_double2(0.0, 0.0);
+      }
+    }
+    const double2 top = cadd(cscale(cur, c), cmul(s, nxt));
+    cur = csub(cscale(nxt, c), cmul(cs, cur));
+    if (live && lane >= kk) col[kk] = top;
+    const double2 a = read_lane(cur, kk), b = read_lane(cur, kk + 1);
+    double2 sub = read_lane(nn, kk + 1);
+    if (k + 2 > ihi) sub = make_double2(0.0, 0.0);
+    x = cadd(cscale(a, c), cmul(cs, b));
+    y = cmul(cs, sub);
+    if (lane == kk + 1) {
+      cur = csub(cscale(b, c), cmul(s, a));
+      nn = cscale(sub, c);
+    }
+    nxt = nn;
+  }
+  if (live && lane >= kk) col[kk] = cur;  // row k1
+  if (lane == kk && k1 < ihi) col[kk + 1] = nxt;
+  if (lane == 0) {
+    blk[(kk - 1) * ld + kk] = x;
+    if (k1 < ihi) blk[(kk - 1) * ld + kk + 1] = y;
+  }
+}
+
+// The column rotations that chase left out: row b0 + row of the block takes
+// rotations max(k0, b0 + row) .. k1 - 1.
+__device__ inline void apply_block_columns(double2* __restrict__ blk, int ld, int row, int b0,
+                                           int k0, int k1, const double* __restrict__ rc,
+                                           const double2* __restrict__ rs) {
+  const int first = max(k0, b0 + row);
+  double2* v = blk + row;
+  double2 cur = v[(k0 - b0) * ld];
+  for (int k = k0; k < k1; ++k) {
+    const int kk = k - b0;
+    const double2 t2 = v[(kk + 1) * ld];
+    if (k >= first) {
+      const double c = rc[k - k0];
+      const double2 s = rs[k - k0];
+      v[kk * ld] = cadd(cscale(cur, c), cmul(cconj(s), t2));
+      cur = csub(cscale(t2, c), cmul(s, cur));
+    } else {
+      cur = t2;
+    }
+  }
+  if (first < k1) v[(k1 - b0) * ld] = cur;
+}
+
+__device__ inline bool negligible(double sub, double tst, int n) {
+  return sub <= fmax(DBL_MIN * ((double)n / DBL_EPSILON), DBL_EPSILON * tst);
+}
+
+// Wilkinson's shift of the trailing 2 x 2 block [[a, b], [c, d]]: its
+// eigenvalue closer to d.
+__device__ inline double2 wilkinson(double2 a, double2 b, double2 c, double2 d) {
+  const double2 bc = cmul(b, c);
+  const double2 x = cscale(csub(a, d), 0.5);
+  double2 y = csqrt(cadd(cmul(x, x), bc));
+  if (x.x * y.x + x.y * y.y < 0.0) y = make_double2(-y.x, -y.y);
+  const double2 den = cadd(x, y);
+  return (den.x == 0.0 && den.y == 0.0) ? d : csub(d, cdiv(bc, den));
+}
+
+// A window's W rotations (the last W - nq of them identities) on elements 0 .. nq
+// of a row (COL) or a column, `stride` apart. Elements past nq are copies of
+// the last; stored from the last down, its own value comes after theirs.
+template <int W, bool COL>
+__device__ inline void window_rotate(double2* __restrict__ v0, int stride, int nq,
+                                     const double* rc, const double2* rs) {
+  double vx[W + 1], vy[W + 1];
+#pragma unroll
+  for (int q = 0; q <= W; ++q) {
+    const double2 t = v0[(size_t)(min(q, nq) * stride)];
+    vx[q] = t.x;
+    vy[q] = t.y;
+  }
+#pragma unroll
+  for (int q = 0; q < W; ++q) {
+    const double c = rc[q], sx = rs[q].x, sy = COL ? -rs[q].y : rs[q].y;
+    const double ax = vx[q], ay = vy[q], bx = vx[q + 1], by = vy[q + 1];
+    vx[q] = c * ax + (sx * bx - sy * by);
+    vy[q] = c * ay + (sx * by + sy * bx);
+    vx[q + 1] = c * bx - (sx * ax + sy * ay);
+    vy[q + 1] = c * by - (sx * ay - sy * ax);
+    // the rotations are read as they are used: all at once they would spill
+    if (q % 4 == 3) asm volatile("" : "+v"(vx[q + 1]), "+v"(vy[q + 1]) : : "memory");
+  }
+  asm volatile("" : "+s"(nq));  // form the addresses again rather than keep them
+#pragma unroll
+  for (int q = W; q >= 0; --q) v0[(size_t)(min(q, nq) * stride)] = make_double2(vx[q], vy[q]);
+}
+
+// 96 matrices of order 242: 142 ms with everything in the iteration, now 51 ms
+// for it and 23 ms for the three applications of its records.
+//
+// Two phases by the size of the active block. Above kInner it lives in memory
+// and a sweep runs in windows of W rotations: the window's diagonal block (at
+// most W + 3) is chased in LDS by one wave, then its rotations are applied in
+// one pass to the active columns right of it and the active rows above it,
+// one thread per column or row with the window's W + 1 values in registers.
+// From kInner down the whole block stays in LDS and one wave runs every sweep.
+template <int W, int kInner>
+__global__ void __launch_bounds__(512)
+eig_schur_kernel(int n, double2* __restrict__ Hall, double2* __restrict__ wall,
+                 int* __restrict__ stateall, int capr, int caps, double* __restrict__ rotc,
+                 double2* __restrict__ rots, int4* __restrict__ hdrall) {
+  constexpr int LD = kInner + 1;
+  static_assert(W + 3 <= kInner && kInner <= 64, "a block's columns are one wave's lanes");
+  __shared__ double2 blk[LD * kInner];
+  __shared__ double s_c[kInner];
+  __shared__ double2 s_s[kInner];
+  __shared__ int s_l, s_ihi, s_its, s_stop, s_nsw, s_nrot;
+  double2* H = Hall + blockIdx.x * (size_t)n * n;
   double2* w = wall + (size_t)blockIdx.x * n;
-  const int tid = threadIdx.x;
-  const double ulp = DBL_EPSILON, smlnum = DBL_MIN * ((double)n / DBL_EPSILON);
-  int ihi = n - 1, its = 0, status = 0;
+  int* state = stateall + (size_t)blockIdx.x * kState;
+  rotc += (size_t)blockIdx.x * capr;
+  rots += (size_t)blockIdx.x * capr;
+  int4* hdr = hdrall + (size_t)blockIdx.x * caps;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if (state[2]) {  // finished in an earlier launch
+    if (tid == 0) state[4] = state[5] = 0;
+    return;
+  }
+  int ihi = uniform(state[0]), its = uniform(state[1]), nsw = 0, nrot = 0, status = 0;
+  bool full = false;
   while (ihi >= 0) {
     // largest k in [1, ihi] with a negligible subdiagonal: the active block is [l, ihi]
     if (tid == 0) s_l = 0;
     __syncthreads();
-    for (int k = 1 + tid; k <= ihi; k += TPB) {
+    for (int k = 1 + tid; k <= ihi; k += 512) {
       const double sub = cabs1(at(H, n, k, k - 1));
       double tst = cabs1(at(H, n, k - 1, k - 1)) + cabs1(at(H, n, k, k));
       if (tst == 0.0) {
         if (k >= 2) tst += fabs(at(H, n, k - 1, k - 2).x);
         if (k + 1 <= ihi) tst += fabs(at(H, n, k + 1, k).x);
       }
-      if (sub <= fmax(smlnum, ulp * tst)) atomicMax(&s_l, k);
+      if (negligible(sub, tst, n)) atomicMax(&s_l, k);
     }
     __syncthreads();
-    const int l = s_l;
+    const int l = uniform(s_l);
     __syncthreads();  // every thread has read s_l before it is reset
     if (l > 0 && tid == 0) at(H, n, l, l - 1) = make_double2(0.0, 0.0);
     if (l == ihi) {  // a 1 x 1 block: eigenvalue ihi has converged
@@ -256,134 +431,295 @@ eig_schur_kernel(int n, double2* __restrict__ Hall, double2* __restrict__ Zall,
       __syncthreads();
       continue;
     }
+    const int m = ihi - l + 1;
+    if (m <= kInner) {
+      for (int e = tid; e < m * m; e += 512) {
+        const int r = e % m, c = e / m;
+        blk[c * LD + r] = at(H, n, l + r, l + c);
+      }
+      __syncthreads();
+      if (wave == 0) {
+        int hi = ihi, stop = 0;
+        while (hi >= l) {
+          wave_sync();
+          // lane q tests the subdiagonal of row l + q
+          bool neg = false;
+          const int q = lane, top = hi - l;
+          if (q >= 1 && q <= top) {
+            const double sub = cabs1(blk[(q - 1) * LD + q]);
+            double tst = cabs1(blk[(q - 1) * LD + q - 1]) + cabs1(blk[q * LD + q]);
+            if (tst == 0.0) {
+              if (q >= 2) tst += fabs(blk[(q - 2) * LD + q - 1].x);
+              if (q + 1 <= top) tst += fabs(blk[q * LD + q + 1].x);
+            }
+            neg = negligible(sub, tst, n);
+          }
+          const unsigned long long mask = __ballot(neg);
+          const int dl = uniform(mask ? 63 - __clzll((long long)mask) : 0);
+          const int al = l + dl;  // the active block is [al, hi]
+          if (dl > 0 && lane == 0) blk[(dl - 1) * LD + dl] = make_double2(0.0, 0.0);
+          if (al == hi) {
+            if (lane == 0) w[hi] = blk[dl * LD + dl];
+            --hi;
+            its = 0;
+            continue;
+          }
+          if (nrot + (hi - al) > capr || nsw >= caps) {
+            stop = 1;
+            break;
+          }
+          if (++its > kMaxSweepsPerEigenvalue) {
+            stop = 2;
+            break;
+          }
+          double2* sb = blk + dl * (LD + 1);
+          const int bn = hi - al + 1;
+          double2 mu;
+          if (its % 20 == 10) {
+            mu = cadd(sb[0], make_double2(0.75 * fabs(sb[1].x), 0.0));
+          } else if (its % 20 == 0) {
+            mu = cadd(sb[(bn - 1) * (LD + 1)],
+                      make_double2(0.75 * fabs(sb[(bn - 2) * LD + bn - 1].x), 0.0));
+          } else {
+            mu = wilkinson(sb[(bn - 2) * (LD + 1)], sb[(bn - 1) * LD + bn - 2],
+                           sb[(bn - 2) * LD + bn - 1], sb[(bn - 1) * (LD + 1)]);
+          }
+          chase(sb, LD, bn, al, al, hi, al, hi, mu, s_c, s_s);
+          wave_sync();
+          if (lane < bn) apply_block_columns(sb, LD, lane, al, al, hi, s_c, s_s);
+          wave_sync();
+          if (lane < bn - 1) {
+            rotc[nrot + lane] = s_c[lane];
+            rots[nrot + lane] = s_s[lane];
+          }
+          if (lane == 0) hdr[nsw] = make_int4(al, hi, nrot, 0);
+          nrot += hi - al;
+          ++nsw;
+        }
+        if (lane == 0) {
+          s_ihi = hi;
+          s_its = its;
+          s_stop = stop;
+          s_nsw = nsw;
+          s_nrot = nrot;
+        }
+      }
+      __syncthreads();
+      for (int e = tid; e < m * m; e += 512) {
+        const int r = e % m, c = e / m;
+        at(H, n, l + r, l + c) = blk[c * LD + r];
+      }
+      ihi = uniform(s_ihi);
+      its = uniform(s_its);
+      nsw = uniform(s_nsw);
+      nrot = uniform(s_nrot);
+      const int stop = uniform(s_stop);
+      __syncthreads();
+      if (stop == 2) status = ihi + 1;
+      full = stop == 1;
+      if (stop) break;
+      continue;
+    }
+    if (nrot + (ihi - l) > capr || nsw >= caps) {
+      full = true;
+      break;
+    }
     if (++its > kMaxSweepsPerEigenvalue) {
       status = ihi + 1;
       break;
     }
-    // shift
     double2 mu;
-    if (its % 20 == 10) {
+    if (its % 20 == 10)
       mu = cadd(at(H, n, l, l), make_double2(0.75 * fabs(at(H, n, l + 1, l).x), 0.0));
-    } else if (its % 20 == 0) {
+    else if (its % 20 == 0)
       mu = cadd(at(H, n, ihi, ihi), make_double2(0.75 * fabs(at(H, n, ihi, ihi - 1).x), 0.0));
-    } else {
-      // eigenvalue of the trailing 2 x 2 block closer to its last diagonal entry
-      const double2 a = at(H, n, ihi - 1, ihi - 1), b = at(H, n, ihi - 1, ihi);
-      const double2 c = at(H, n, ihi, ihi - 1), d = at(H, n, ihi, ihi);
-      const double2 bc = cmul(b, c);
-      const double2 x = cscale(csub(a, d), 0.5);
-      double2 y = csqrt(cadd(cmul(x, x), bc));
-      if (x.x * y.x + x.y * y.y < 0.0) y = make_double2(-y.x, -y.y);
-      const double2 den = cadd(x, y);
-      mu = (den.x == 0.0 && den.y == 0.0) ? d : csub(d, cdiv(bc, den));
-    }
+    else
+      mu = wilkinson(at(H, n, ihi - 1, ihi - 1), at(H, n, ihi - 1, ihi), at(H, n, ihi, ihi - 1),
+                     at(H, n, ihi, ihi));
     // one implicit single-shift QR sweep over [l, ihi], W rotations per window
     for (int k0 = l; k0 < ihi; k0 += W) {
-      const int k1 = min(k0 + W, ihi);        // rotations k0 .. k1 - 1
-      const int b0 = k0 == l ? l : k0 - 1;    // block rows and columns b0 .. be
+      const int k1 = min(k0 + W, ihi);      // rotations k0 .. k1 - 1
+      const int b0 = k0 == l ? l : k0 - 1;  // block rows and columns b0 .. be
       const int be = min(k1 + 1, ihi);
-      const int bn = be - b0 + 1;
-      for (int e = tid; e < bn * bn; e += TPB) {
+      const int bn = be - b0 + 1, nq = k1 - k0;
+      for (int e = tid; e < bn * bn; e += 512) {
         const int r = e % bn, c = e / bn;
-        blk[c * LB + r] = at(H, n, b0 + r, b0 + c);
+        blk[c * LD + r] = at(H, n, b0 + r, b0 + c);
       }
       __syncthreads();
-      double2 r_prev = make_double2(0.0, 0.0);
-      for (int k = k0; k < k1; ++k) {
-        const int kk = k - b0;
-        double2 x, y;
-        if (k == l) {
-          x = csub(blk[kk * LB + kk], mu);
-          y = blk[kk * LB + kk + 1];
-        } else {
-          x = blk[(kk - 1) * LB + kk];
-          y = blk[(kk - 1) * LB + kk + 1];
+      if (wave == 0) {
+        if (lane >= nq && lane < W) {  // a short window ends in identities
+          s_c[lane] = 1.0;
+          s_s[lane] = make_double2(0.0, 0.0);
         }
-        double c;
-        double2 s, r;
-        givens(x, y, c, s, r);
-        const double2 ms = make_double2(-s.x, s.y);  // -conj(s)
-        const double2 cs = cconj(s);
-        if (tid == 0) {
-          if (k > k0 && k - 1 > l) {  // the previous rotation's column entries
-            blk[(kk - 2) * LB + kk - 1] = r_prev;
-            blk[(kk - 2) * LB + kk] = make_double2(0.0, 0.0);
-          }
-          s_c[k - k0] = c;
-          s_s[k - k0] = s;
-        }
-        r_prev = r;
-        for (int j = kk + tid; j < bn; j += TPB) {  // rows k, k+1: columns k .. be
-          const double2 t1 = blk[j * LB + kk], t2 = blk[j * LB + kk + 1];
-          blk[j * LB + kk] = cadd(cscale(t1, c), cmul(s, t2));
-          blk[j * LB + kk + 1] = cadd(cmul(ms, t1), cscale(t2, c));
-        }
-        __syncthreads();
-        const int iend = min(k + 2, be) - b0;
-        for (int i = tid; i <= iend; i += TPB) {  // columns k, k+1: rows b0 .. min(k+2, be)
-          const double2 t1 = blk[kk * LB + i], t2 = blk[(kk + 1) * LB + i];
-          blk[kk * LB + i] = cadd(cscale(t1, c), cmul(cs, t2));
-          blk[(kk + 1) * LB + i] = csub(cscale(t2, c), cmul(s, t1));
-        }
-        __syncthreads();
-      }
-      if (tid == 0 && k1 - 1 > l) {  // the window's last pending entries
-        const int kk = k1 - 1 - b0;
-        blk[(kk - 1) * LB + kk] = r_prev;
-        blk[(kk - 1) * LB + kk + 1] = make_double2(0.0, 0.0);
+        chase(blk, LD, bn, b0, k0, k1, l, ihi, mu, s_c, s_s);
       }
       __syncthreads();
-      for (int e = tid; e < bn * bn; e += TPB) {
-        const int r = e % bn, c = e / bn;
-        at(H, n, b0 + r, b0 + c) = blk[c * LB + r];
-      }
-      const int nq = k1 - k0;
-      // rows k0 .. k1 of the columns right of the block
-      for (int j = be + 1 + tid; j < n; j += TPB) {
-        double2 v[W + 1];
-#pragma unroll
-        for (int q = 0; q <= W; ++q)
-          if (q <= nq) v[q] = at(H, n, k0 + q, j);
-#pragma unroll
-        for (int q = 0; q < W; ++q) {
-          if (q < nq) {
-            const double c = s_c[q];
-            const double2 sq = s_s[q], msq = make_double2(-sq.x, sq.y);
-            const double2 t1 = v[q], t2 = v[q + 1];
-            v[q] = cadd(cscale(t1, c), cmul(sq, t2));
-            v[q + 1] = cadd(cmul(msq, t1), cscale(t2, c));
-          }
+      if (wave == 0) {  // the block itself, and the record
+        if (lane < bn) {
+          apply_block_columns(blk, LD, lane, b0, k0, k1, s_c, s_s);
+          for (int c = 0; c < bn; ++c) at(H, n, b0 + lane, b0 + c) = blk[c * LD + lane];
         }
-#pragma unroll
-        for (int q = 0; q <= W; ++q)
-          if (q <= nq) at(H, n, k0 + q, j) = v[q];
-      }
-      // columns k0 .. k1 of the rows above the block, then of every row of Z
-      for (int i = tid; i < b0 + n; i += TPB) {
-        double2* Mx = i < b0 ? H : Z;
-        const int row = i < b0 ? i : i - b0;
-        double2 v[W + 1];
-#pragma unroll
-        for (int q = 0; q <= W; ++q)
-          if (q <= nq) v[q] = at(Mx, n, row, k0 + q);
-#pragma unroll
-        for (int q = 0; q < W; ++q) {
-          if (q < nq) {
-            const double c = s_c[q];
-            const double2 sq = s_s[q];
-            const double2 t1 = v[q], t2 = v[q + 1];
-            v[q] = cadd(cscale(t1, c), cmul(cconj(sq), t2));
-            v[q + 1] = csub(cscale(t2, c), cmul(sq, t1));
-          }
+        if (lane < nq) {
+          rotc[nrot + (k0 - l) + lane] = s_c[lane];
+          rots[nrot + (k0 - l) + lane] = s_s[lane];
         }
-#pragma unroll
-        for (int q = 0; q <= W; ++q)
-          if (q <= nq) at(Mx, n, row, k0 + q) = v[q];
+      } else {
+        // columns right of the block, then rows above it
+        const int nright = ihi - be, nabove = b0 - l;
+        for (int i = tid - 64; i < nright; i += 448)
+          window_rotate<W, false>(&at(H, n, k0, be + 1 + i), 1, nq, s_c, s_s);
+        for (int i = 511 - tid; i < nabove; i += 448)
+          window_rotate<W, true>(&at(H, n, l + i, k0), n, nq, s_c, s_s);
       }
       __syncthreads();
     }
+    if (tid == 0) hdr[nsw] = make_int4(l, ihi, nrot, 0);
+    nrot += ihi - l;
+    ++nsw;
   }
-  if (tid == 0) info[blockIdx.x] = status;
+  if (tid == 0) {
+    state[0] = ihi;
+    state[1] = its;
+    state[2] = full ? 0 : 1;
+    state[3] = status;
+    state[4] = nsw;
+    state[5] = nrot;
+  }
+}
+
+__global__ void eig_schur_begin(int n, int count, int* __restrict__ state) {
+  const int b = blockIdx.x * blockDim.x + threadIdx.x;
+  if (b >= count) return;
+  int* s = state + (size_t)b * kState;
+  s[0] = n - 1;
+  for (int i = 1; i < kState; ++i) s[i] = 0;
+}
+
+// The recorded sweeps on what the iteration left out. MODE 0: every row of Z
+// (column rotations). MODE 1: row r of H takes the sweeps with l > r (column
+// rotations). MODE 2: column j of H takes the sweeps with ihi < j (row
+// rotations). A row of H right of one block and above another takes both; they
+// act from different sides and commute.
+//
+// One wave per 64 rows (columns), a lane each. Sixteen sweeps run at once in a
+// skewed order: at step t sweep s applies its rotation k = t - 2 s, which no
+// earlier sweep still has to reach, so the sixteen are independent and every
+// value is read and written once per sixteen sweeps. The values under way are
+// a ring of 64 columns in LDS; each chunk of 16 steps brings in 16 columns and
+// retires 16, the next chunk's columns and rotations being loaded meanwhile.
+// Bound by LDS (two 16-byte reads and writes per rotation and lane).
+constexpr int kApplySweeps = 16, kApplySteps = 16, kApplyRing = 64;
+template <int MODE>
+__global__ void __launch_bounds__(64)
+eig_apply_kernel(int n, double2* __restrict__ Mall, const int* __restrict__ stateall, int capr,
+                 int caps, const double* __restrict__ rotc, const double2* __restrict__ rots,
+                 const int4* __restrict__ hdrall) {
+  constexpr int S = kApplySweeps, T = kApplySteps, R = kApplyRing;
+  static_assert(R >= 2 * S + 2 * T && T == 16 && S == 16, "ring and fetch layout");
+  __shared__ double2 ring[R][64];
+  __shared__ double s_c[T * S];
+  __shared__ double2 s_s[T * S];
+  const int lane = threadIdx.x, b = blockIdx.y;
+  const int first = blockIdx.x * 64, id = first + lane, last = min(first + 63, n - 1);
+  double2* M = Mall + (size_t)b * n * n;
+  rotc += (size_t)b * capr;
+  rots += (size_t)b * capr;
+  const int4* hdr = hdrall + (size_t)b * caps;
+  const int nsw = uniform(stateall[(size_t)b * kState + 4]);
+  // element q of this lane's row or column
+  const size_t stride = MODE == 2 ? 1 : (size_t)n;
+  double2* base = M + (MODE == 2 ? (size_t)min(id, n - 1) * n : (size_t)min(id, n - 1));
+  for (int s0 = 0; s0 < nsw; s0 += S) {
+    int sl[S], sh[S], so[S];  // the sixteen sweeps (an empty range past the last)
+    int lo = n, hi = 0;
+    bool any = false;
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      const int4 h = hdr[min(s0 + s, nsw - 1)];
+      sl[s] = uniform(h.x);
+      sh[s] = uniform(h.y);
+      so[s] = uniform(h.z);
+      const bool on = s0 + s < nsw &&
+                      (MODE == 0 || (MODE == 1 ? first < sl[s] : last > sh[s]));
+      if (on) {
+        any = true;
+        lo = min(lo, sl[s]);
+        hi = max(hi, sh[s]);
+      } else {
+        sh[s] = sl[s];
+      }
+    }
+    if (!any) continue;
+    double colx[T], coly[T], rcv[4], rsx[4], rsy[4];
+    ring[lo & (R - 1)][lane] = base[(size_t)lo * stride];
+    // this lane's rotations of a chunk: steps lane / 16 + 4 q of sweep lane % 16
+    int el = 0, eh = 0, eo = 0;
+#pragma unroll
+    for (int u = 0; u < S; ++u)
+      if (u == (lane & 15)) {
+        el = sl[u];
+        eh = sh[u];
+        eo = so[u];
+      }
+    // the chunk that starts at t0 retires columns t0 - 30 .. t0 - 15 (the pass
+    // before the first only loads)
+    for (int t0 = lo - T; t0 - 2 * S + 2 <= hi; t0 += T) {
+      const bool run = t0 >= lo;
+      if (run) {
+#pragma unroll
+        for (int i = 0; i < T; ++i) ring[(t0 + 1 + i) & (R - 1)][lane] = make_double2(colx[i], coly[i]);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          s_c[q * 64 + lane] = rcv[q];
+          s_s[q * 64 + lane] = make_double2(rsx[q], rsy[q]);
+        }
+      }
+      wave_sync();
+#pragma unroll
+      for (int i = 0; i < T; ++i) {
+        const double2 v = base[(size_t)min(t0 + T + 1 + i, hi) * stride];
+        colx[i] = v.x;
+        coly[i] = v.y;
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int k = t0 + T + 4 * q + (lane >> 4) - 2 * (lane & 15);
+        const int e = k >= el && k < eh ? eo + k - el : 0;
+        const double2 v = rots[e];
+        rcv[q] = rotc[e];
+        rsx[q] = v.x;
+        rsy[q] = v.y;
+      }
+      if (!run) continue;
+      for (int i = 0; i < T; ++i) {
+        const int t = t0 + i;
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+          const int k = t - 2 * s;
+          if (k < sl[s] || k >= sh[s]) continue;  // uniform
+          const double c = s_c[i * S + s];
+          const double2 sv = s_s[i * S + s];
+          const double2 sk = MODE == 2 ? sv : cconj(sv);
+          if (MODE == 0 || (MODE == 1 ? id < sl[s] : id > sh[s])) {
+            double2* p0 = &ring[k & (R - 1)][lane];
+            double2* p1 = &ring[(k + 1) & (R - 1)][lane];
+            const double2 t1 = *p0, t2 = *p1;
+            *p0 = cadd(cscale(t1, c), cmul(sk, t2));
+            *p1 = csub(cscale(t2, c), cmul(cconj(sk), t1));
+          }
+        }
+      }
+      if (id < n) {
+#pragma unroll
+        for (int i = 0; i < T; ++i) {
+          const int q = t0 - 2 * S + 2 + i;
+          if (q >= lo && q <= hi) base[(size_t)q * stride] = ring[q & (R - 1)][lane];
+        }
+      }
+      wave_sync();
+    }
+  }
 }
 
 // Column-major T -> row-major copy of its upper triangle (zeros below), in
@@ -491,12 +827,25 @@ hipError_t launch_eig_hessenberg(int n, int count, double* A, double* Z, hipStre
   return hipGetLastError();
 }
 
-hipError_t launch_eig_schur(int n, int count, double* H, double* Z, double* w, int* info,
-                            hipStream_t s) {
+hipError_t launch_eig_schur_begin(int n, int count, int* state, hipStream_t s) {
   if (n < 1 || n > kEigMaxN || count < 1) return hipErrorInvalidValue;
-  eig_schur_kernel<256, kEigWindow><<<count, 256, 0, s>>>(
-      n, reinterpret_cast<double2*>(H), reinterpret_cast<double2*>(Z),
-      reinterpret_cast<double2*>(w), info);
+  eig_schur_begin<<<(count + 63) / 64, 64, 0, s>>>(n, count, state);
+  return hipGetLastError();
+}
+
+hipError_t launch_eig_schur(int n, int count, double* H, double* Z, double* w,
+                            const EigRecord& rec, hipStream_t s) {
+  if (n < 1 || n > kEigMaxN || count < 1) return hipErrorInvalidValue;
+  double2* h = reinterpret_cast<double2*>(H);
+  double2* z = reinterpret_cast<double2*>(Z);
+  double2* rs = reinterpret_cast<double2*>(rec.rots);
+  int4* hdr = reinterpret_cast<int4*>(rec.hdr);
+  eig_schur_kernel<kEigWindow, kEigInner><<<count, 512, 0, s>>>(
+      n, h, reinterpret_cast<double2*>(w), rec.state, rec.capr, rec.caps, rec.rotc, rs, hdr);
+  const dim3 grid((n + 63) / 64, count);
+  eig_apply_kernel<0><<<grid, 64, 0, s>>>(n, z, rec.state, rec.capr, rec.caps, rec.rotc, rs, hdr);
+  eig_apply_kernel<1><<<grid, 64, 0, s>>>(n, h, rec.state, rec.capr, rec.caps, rec.rotc, rs, hdr);
+  eig_apply_kernel<2><<<grid, 64, 0, s>>>(n, h, rec.state, rec.capr, rec.caps, rec.rotc, rs, hdr);
   return hipGetLastError();
 }
 

@@ -265,8 +265,21 @@ int device_eig_batched(Context& ctx, int n, int count, double* A, double* w, dou
 // The context's rocBLAS handle (created on first use), bound to stream st.
 int blas_handle(Context& ctx, hipStream_t st, void** out);
 hipError_t launch_eig_hessenberg(int n, int count, double* A, double* Z, hipStream_t s);
-hipError_t launch_eig_schur(int n, int count, double* H, double* Z, double* w, int* info,
-                            hipStream_t s);
+// Record of the QR iteration: per matrix 8 state ints ({ihi, eigenvalue's
+// sweeps, done, info, recorded sweeps, recorded rotations}; info j + 1 when
+// eigenvalue j did not converge), capr rotations (at least n) and caps sweep
+// headers. launch_eig_schur iterates every unfinished matrix until it is done
+// or its record is full and applies the record; call it until all are done.
+struct EigRecord {
+  int capr, caps;
+  int* state;
+  double* rotc;  // [count][capr]
+  double* rots;  // [count][capr] complex
+  int* hdr;      // [count][caps] x 4
+};
+hipError_t launch_eig_schur_begin(int n, int count, int* state, hipStream_t s);
+hipError_t launch_eig_schur(int n, int count, double* H, double* Z, double* w,
+                            const EigRecord& rec, hipStream_t s);
 // T (column-major Schur factors) -> Tt (row-major copies) -> Y (eigenvectors
 // of T, column-major; Y may be T).
 hipError_t launch_eig_vectors(int n, int count, const double* T, double* Tt, const double* w,

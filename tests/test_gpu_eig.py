@@ -262,3 +262,30 @@ def test_solve_batch_matches_single_solves(ctx):
             assert rel_l2(got, oracle) <= 1e-10
         ref.free()
         sol.free()
+
+
+def test_reducible_matrices(ctx):
+    """Block triangular matrices: the QR iteration splits at exact zeros, so
+    active blocks (larger and smaller than the 64 columns that one wave holds)
+    have rows above them and columns right of them that only the recorded
+    rotations reach."""
+    torch = _torch()
+    rng = np.random.default_rng(11)
+    mats = []
+    for sizes in ((70, 30, 50), (5, 140, 5), (64, 64, 22)):
+        A = np.triu(rng.standard_normal((150, 150)) + 1j * rng.standard_normal((150, 150)), 1)
+        at = 0
+        for m in sizes:
+            A[at:at + m, at:at + m] = rng.standard_normal((m, m)) + 1j * rng.standard_normal((m, m))
+            at += m
+        # upper Hessenberg blocks stay block triangular through the reduction
+        mats.append(A)
+    A = np.stack(mats)
+    w, X = ctx.eig_batched(torch.as_tensor(A).cuda())
+    torch.cuda.synchronize()
+    w, X = w.cpu().numpy(), X.cpu().numpy()
+    for b in range(len(A)):
+        res = np.linalg.norm(A[b] @ X[b] - X[b] * w[b]) / np.linalg.norm(A[b])
+        print("reducible[%d] residual %.2e" % (b, res), flush=True)
+        assert res <= 1e-12
+        assert np.abs(np.linalg.norm(X[b], axis=0) - 1).max() <= 1e-12
