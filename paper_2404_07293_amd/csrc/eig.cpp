@@ -57,7 +57,15 @@ int device_eig_batched(Context& ctx, int n, int count, double* A, double* w, dou
   rec.rots = drot.as<double>();
   rec.rotc = drot.as<double>() + 2 * capr * count;
   rec.hdr = dhdr.as<int>();
-  SCW_HIP(launch_eig_hessenberg(n, count, A, dZ.as<double>(), st));
+  // the row-major copy's buffer is free until the iteration is done; small
+  // matrices need more for the reduction's panels than it holds
+  DevBuf dhess;
+  double* hwork = dTt.as<double>();
+  if (eig_hessenberg_work(n) > nn * 16) {
+    if ((rc = dhess.reserve(eig_hessenberg_work(n) * count))) return rc;
+    hwork = dhess.as<double>();
+  }
+  SCW_HIP(launch_eig_hessenberg(n, count, A, dZ.as<double>(), hwork, st));
   SCW_HIP(launch_eig_schur_begin(n, count, rec.state, st));
   std::vector<int> state(8 * (size_t)count);
   for (bool done = false; !done;) {

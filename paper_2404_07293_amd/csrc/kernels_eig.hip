@@ -5,9 +5,10 @@
 // layers, wavelengths or patches fills the chip.
 //
 // Steps, each a published method restated for this layout:
-//   1. Householder reduction to upper Hessenberg form H = Q^H A Q, with the
-//      reflectors accumulated into Z = Q (Golub & Van Loan, Matrix
-//      Computations, Alg. 7.4.2).
+//   1. Householder reduction to upper Hessenberg form H = Q^H A Q in panels of
+//      reflectors, which are then accumulated into Z = Q (Golub & Van Loan,
+//      Matrix Computations, Sec. 7.4; the compact form Q = I - V T V^H of
+//      Schreiber and Van Loan).
 //   2. Complex Schur form T = Z^H A Z by the implicitly shifted single-shift
 //      QR algorithm on H: Wilkinson shifts with exceptional shifts after 10
 //      and 20 stalled iterations, deflation on negligible subdiagonals
@@ -74,108 +75,401 @@ __device__ inline double2 wave_sum(double2 v) {
   return v;
 }
 
-template <int TPB>
-__device__ double block_sum(double v, double* red) {
-  const int tid = threadIdx.x;
-  for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m, 64);
-  if ((tid & 63) == 0) red[tid >> 6] = v;
-  __syncthreads();
-  double s = 0.0;
-  for (int w = 0; w < TPB / 64; ++w) s += red[w];
-  __syncthreads();
-  return s;
+typedef double dx4 __attribute__((ext_vector_type(4)));
+// D += A B on 16 x 16 x 4 (v_mfma_f64_16x16x4_f64): lane l holds A[l % 16][l / 16]
+// and B[l / 16][l % 16]; entry i of lane l is D[4 i + l / 16][l % 16].
+__device__ inline dx4 mm4(double a, double b, dx4 c) {
+  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
-// M[:, k+1:n] -= tau (M[:, k+1:n] v) v^H on all n rows, one thread per row
-// (NR rows per thread).
-template <int TPB, int NR>
-__device__ void reflect_right(double2* __restrict__ Mx, int n, int k, const double2* v,
-                              double2 tau) {
-  const int tid = threadIdx.x, m = n - k - 1;
-  double2 acc[NR];
-#pragma unroll
-  for (int t = 0; t < NR; ++t) acc[t] = make_double2(0.0, 0.0);
-  for (int i = 0; i < m; ++i) {
-    const double2 vi = v[i];
-    const double2* col = Mx + (size_t)(k + 1 + i) * n;
-#pragma unroll
-    for (int t = 0; t < NR; ++t) {
-      const int r = tid + t * TPB;
-      if (r < n) acc[t] = cadd(acc[t], cmul(col[r], vi));
-    }
-  }
-#pragma unroll
-  for (int t = 0; t < NR; ++t) acc[t] = cmul(acc[t], tau);
-  for (int i = 0; i < m; ++i) {
-    const double2 vc = cconj(v[i]);
-    double2* col = Mx + (size_t)(k + 1 + i) * n;
-#pragma unroll
-    for (int t = 0; t < NR; ++t) {
-      const int r = tid + t * TPB;
-      if (r < n) col[r] = csub(col[r], cmul(acc[t], vc));
-    }
-  }
+// Step 1. Householder reduction in panels of kPanel columns (the blocked form of
+// LAPACK's xGEHRD / xLAHR2). With the panel's reflectors Q = I - V T V^H
+// (T upper triangular), the rows k0 + 1 .. n - 1 of the columns right of the
+// panel become
+//   C <- (I - V T^H V^H) (C - Y V^H),   Y = A V T,
+// where A V needs only the trailing matrix as it was before the panel: one
+// reading per column (the product with the newest reflector), instead of six
+// and three writings of H and Q when each reflector was applied at once.
+// Rows 0 .. k0 of H and all of Q see the panel only from the right, row by row;
+// eig_hess_apply_kernel does them afterwards, many workgroups to a matrix.
+//
+// One workgroup of 16 waves per matrix. Per column: update it by the panel so
+// far (a thread per row), V^H a (a wave per reflector), the reflector, then
+// A v with the rows over the threads and the columns over what groups of
+// threads are left. The trailing update runs on the matrix cores in 16 x 16
+// tiles. The reflectors are left below H's subdiagonal (with their leading 1
+// implied) for the second kernel, which clears them, the T factors in Tall.
+//
+// 96 matrices of order 242: 46.2 ms with unblocked reflections (20 GB/s per
+// workgroup).
+constexpr int kPanel = 16;
+// Workspace per matrix, in complex values: V, Y, W (kPanel x n each, column
+// major, ld n) and the T factors of ceil(n / kPanel) panels.
+__host__ __device__ inline size_t hess_work(int n) {
+  return (size_t)3 * kPanel * n + (size_t)((n + kPanel - 1) / kPanel) * kPanel * kPanel;
 }
-
-// Step 1. One workgroup of TPB threads per matrix; n <= NR * TPB and the
-// reflector vector (n - 1 entries) in LDS.
-template <int TPB, int NR>
-__global__ void __launch_bounds__(TPB)
-eig_hessenberg_kernel(int n, double2* __restrict__ A, double2* __restrict__ Z) {
-  extern __shared__ double2 v[];
-  __shared__ double red[TPB / 64];
-  __shared__ double2 s_tau, s_scale;
-  __shared__ int s_skip;
-  const size_t nn = (size_t)n * n;
-  double2* H = A + blockIdx.x * nn;
-  double2* Q = Z + blockIdx.x * nn;
+__global__ void __launch_bounds__(1024)
+eig_hessenberg_kernel(int n, double2* __restrict__ Aall, double2* __restrict__ work) {
+  constexpr int NB = kPanel;
+  extern __shared__ double2 lds[];  // acol [n], part [1024]
+  double2* acol = lds;
+  double2* part = lds + n;
+  __shared__ double2 s_T[NB][NB];  // T[p][q]
+  __shared__ double2 s_S[NB][NB];  // V^H Y, then T^H V^H Y
+  __shared__ double2 s_row[NB], s_w[NB], s_u[NB];
+  __shared__ double s_red[16];
+  double2* A = Aall + (size_t)blockIdx.x * n * n;
+  double2* V = work + (size_t)blockIdx.x * hess_work(n);
+  double2* Y = V + (size_t)NB * n;
+  double2* Wb = Y + (size_t)NB * n;
+  double2* Tg = Wb + (size_t)NB * n;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  for (size_t e = tid; e < nn; e += TPB)
-    Q[e] = make_double2(e % (size_t)(n + 1) == 0 ? 1.0 : 0.0, 0.0);
-  for (int k = 0; k + 2 < n; ++k) {
-    const int m = n - k - 1;  // x = H[k+1 .. n-1, k]
-    double2* x = H + (size_t)k * n + k + 1;
-    double part = 0.0;
-    for (int i = 1 + tid; i < m; i += TPB) part += x[i].x * x[i].x + x[i].y * x[i].y;
-    const double xnorm2 = block_sum<TPB>(part, red);
-    if (tid == 0) {
-      const double2 alpha = x[0];
-      if (xnorm2 == 0.0 && alpha.y == 0.0) {
-        s_skip = 1;
-      } else {
-        // beta = -sign(Re alpha) ||(alpha, x)||, tau = (beta - alpha) / beta,
-        // v = [1; x / (alpha - beta)]: (I - tau v v^H)^H [alpha; x] = [beta; 0]
-        const double beta =
-            -copysign(sqrt(alpha.x * alpha.x + alpha.y * alpha.y + xnorm2), alpha.x);
-        s_tau = make_double2((beta - alpha.x) / beta, -alpha.y / beta);
-        s_scale = cdiv(make_double2(1.0, 0.0), make_double2(alpha.x - beta, alpha.y));
-        s_skip = 0;
-        v[0] = make_double2(1.0, 0.0);
-        x[0] = make_double2(beta, 0.0);
+  const double2 zero = make_double2(0.0, 0.0);
+  const int nref = n - 2;  // reflectors, one per column 0 .. n - 3
+  for (int k0 = 0; k0 < nref; k0 += NB) {
+    const int jn = min(NB, nref - k0), r0 = k0 + 1, m = n - r0;
+    // A v: rows over rt threads, columns over ng groups of them
+    const int rt = min(1024, (m + 63) / 64 * 64), ng = 1024 / rt;
+    const int grp = tid / rt, rid = tid - grp * rt;
+    if (tid < NB * NB) {
+      s_T[tid / NB][tid % NB] = zero;
+      s_S[tid / NB][tid % NB] = zero;
+    }
+    for (int q = jn; q < NB; ++q)  // a short panel ends in empty columns
+      for (int r = r0 + tid; r < n; r += 1024) V[(size_t)q * n + r] = Y[(size_t)q * n + r] = zero;
+    for (int j = 0; j < jn; ++j) {
+      const int c = k0 + j;
+      double2* ac = A + (size_t)c * n;
+      // column c by the panel so far, from the right: - Y V[c, :]^H
+      if (tid < j) s_row[tid] = cconj(V[(size_t)tid * n + c]);
+      __syncthreads();
+      for (int r = r0 + tid; r < n; r += 1024) {
+        double2 a = ac[r];
+        for (int q = 0; q < j; ++q) a = csub(a, cmul(Y[(size_t)q * n + r], s_row[q]));
+        acol[r] = a;
+      }
+      __syncthreads();
+      // and from the left: - V T^H (V^H a)
+      if (wave < j) {
+        double2 acc = zero;
+        for (int r = r0 + lane; r < n; r += 64)
+          acc = cadd(acc, cmulcj(V[(size_t)wave * n + r], acol[r]));
+        acc = wave_sum(acc);
+        if (lane == 0) s_w[wave] = acc;
+      }
+      __syncthreads();
+      if (tid < j) {
+        double2 acc = zero;
+        for (int p = 0; p <= tid; ++p) acc = cadd(acc, cmulcj(s_T[p][tid], s_w[p]));
+        s_u[tid] = acc;
+      }
+      __syncthreads();
+      double norm2 = 0.0;
+      for (int r = r0 + tid; r < n; r += 1024) {
+        double2 a = acol[r];
+        for (int q = 0; q < j; ++q) a = csub(a, cmul(V[(size_t)q * n + r], s_u[q]));
+        acol[r] = a;
+        if (r > c + 1) norm2 += a.x * a.x + a.y * a.y;
+      }
+      for (int o = 32; o >= 1; o >>= 1) norm2 += __shfl_xor(norm2, o, 64);
+      if (lane == 0) s_red[wave] = norm2;
+      __syncthreads();
+      // the reflector: beta = -sign(Re alpha) ||(alpha, x)||, tau = (beta - alpha)
+      // / beta, v = [1; x / (alpha - beta)]: (I - tau v v^H)^H [alpha; x] = [beta; 0]
+      double x2 = 0.0;
+#pragma unroll
+      for (int q = 0; q < 16; ++q) x2 += s_red[q];
+      const double2 alpha = acol[c + 1];
+      double beta = alpha.x;
+      double2 tau = zero, scale = zero;
+      if (x2 != 0.0 || alpha.y != 0.0) {
+        beta = -copysign(sqrt(alpha.x * alpha.x + alpha.y * alpha.y + x2), alpha.x);
+        tau = make_double2((beta - alpha.x) / beta, -alpha.y / beta);
+        scale = cdiv(make_double2(1.0, 0.0), make_double2(alpha.x - beta, alpha.y));
+      }
+      __syncthreads();  // every thread has read alpha
+      for (int r = r0 + tid; r < n; r += 1024) {
+        const double2 a = acol[r];
+        const double2 v = r > c + 1 ? cmul(a, scale) : make_double2(r == c + 1 ? 1.0 : 0.0, 0.0);
+        ac[r] = r > c + 1 ? v : (r == c + 1 ? make_double2(beta, 0.0) : a);
+        acol[r] = v;
+        V[(size_t)j * n + r] = v;
+      }
+      __syncthreads();
+      // u = V^H v over the earlier reflectors, and A v in parts
+      if (wave < j) {
+        double2 acc = zero;
+        for (int r = c + 1 + lane; r < n; r += 64)
+          acc = cadd(acc, cmulcj(V[(size_t)wave * n + r], acol[r]));
+        acc = wave_sum(acc);
+        if (lane == 0) s_w[wave] = acc;
+      }
+      for (int rb = 0; rb < m; rb += rt) {
+        const int r = min(r0 + rb + rid, n - 1);
+        double2 acc = zero, acc2 = zero;
+        if (grp < ng) {
+          const double2* ap = A + r;
+          int cc = c + 1 + grp;
+          for (; cc + 7 * ng < n; cc += 8 * ng) {
+            double2 x[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) x[u] = ap[(size_t)(cc + u * ng) * n];
+#pragma unroll
+            for (int u = 0; u < 8; u += 2) {
+              acc = cadd(acc, cmul(x[u], acol[cc + u * ng]));
+              acc2 = cadd(acc2, cmul(x[u + 1], acol[cc + (u + 1) * ng]));
+            }
+          }
+          for (; cc < n; cc += ng) acc = cadd(acc, cmul(ap[(size_t)cc * n], acol[cc]));
+        }
+        part[tid] = cadd(acc, acc2);
+        __syncthreads();
+        if (tid < rt && r0 + rb + tid < n) {
+          double2 y = part[tid];
+          for (int g = 1; g < ng; ++g) y = cadd(y, part[g * rt + tid]);
+          for (int q = 0; q < j; ++q) y = csub(y, cmul(Y[(size_t)q * n + r0 + rb + tid], s_w[q]));
+          Y[(size_t)j * n + r0 + rb + tid] = cmul(y, tau);
+        }
+        __syncthreads();
+      }
+      // T[:, j] = -tau T u, T[j][j] = tau
+      if (tid <= j) {
+        double2 t = zero;
+        for (int q = tid; q < j; ++q) t = cadd(t, cmul(s_T[tid][q], s_w[q]));
+        t = cmul(make_double2(-t.x, -t.y), tau);
+        s_T[tid][j] = tid == j ? tau : t;
+      }
+      __syncthreads();
+    }
+    if (tid < NB * NB) Tg[(size_t)(k0 / NB) * NB * NB + tid] = s_T[tid / NB][tid % NB];
+    // ---- the columns right of the panel
+    const int c1 = k0 + jn, mc = n - c1;
+    {  // S = V^H Y, a wave per row
+      double2 acc[NB];
+#pragma unroll
+      for (int p = 0; p < NB; ++p) acc[p] = zero;
+      for (int r = r0 + lane; r < n; r += 64) {
+        const double2 v = V[(size_t)wave * n + r];
+#pragma unroll
+        for (int p = 0; p < NB; ++p) acc[p] = cadd(acc[p], cmulcj(v, Y[(size_t)p * n + r]));
+      }
+#pragma unroll
+      for (int p = 0; p < NB; ++p) {
+        const double2 t = wave_sum(acc[p]);
+        if (lane == 0) s_S[wave][p] = t;
+      }
+    }
+    const int lr = lane & 15, lk = lane >> 4;
+    // W0 = V^H C: 16 x 16 tiles, K = the rows, four consecutive ones per lane
+    for (int ct = wave * 16; ct < mc; ct += 256) {
+      const int cc = min(c1 + ct + lr, n - 1);
+      const double2* cp = A + (size_t)cc * n;
+      const double2* vp = V + (size_t)lr * n;
+      dx4 wr = {0.0, 0.0, 0.0, 0.0}, wi = wr;
+#pragma unroll 2
+      for (int rb = r0; rb < n; rb += 16) {
+        double2 a[4], b[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int r = rb + 4 * lk + u, rc = min(r, n - 1);
+          a[u] = vp[rc];
+          b[u] = cp[rc];
+          if (r >= n) a[u] = zero;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {  // conj(V) C
+          wr = mm4(a[u].x, b[u].x, wr);
+          wr = mm4(a[u].y, b[u].y, wr);
+          wi = mm4(a[u].x, b[u].y, wi);
+          wi = mm4(-a[u].y, b[u].x, wi);
+        }
+      }
+      if (c1 + ct + lr < n)
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          Wb[(size_t)(4 * u + lk) * n + c1 + ct + lr] = make_double2(wr[u], wi[u]);
+    }
+    __syncthreads();
+    // W = T^H (W0 - S V[c, :]^H), a thread per column and four of its rows
+    for (int e = tid; e < 4 * mc; e += 1024) {
+      const int c = c1 + e / 4, q0 = (e % 4) * 4;
+      double2 w[NB];
+#pragma unroll
+      for (int p = 0; p < NB; ++p) w[p] = Wb[(size_t)p * n + c];
+#pragma unroll 1
+      for (int q = 0; q < NB; ++q) {
+        const double2 vc = cconj(V[(size_t)q * n + c]);
+#pragma unroll
+        for (int p = 0; p < NB; ++p) w[p] = csub(w[p], cmul(s_S[p][q], vc));
+      }
+      double2 o[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        o[u] = zero;
+#pragma unroll
+        for (int p = 0; p < NB; ++p) o[u] = cadd(o[u], cmulcj(s_T[p][q0 + u], w[p]));
+      }
+      // the four threads of a column are neighbours in one wave: all have read
+      // W0 before any writes
+#pragma unroll
+      for (int u = 0; u < 4; ++u) Wb[(size_t)(q0 + u) * n + c] = o[u];
+    }
+    __syncthreads();
+    // C -= Y V[c, :]^H + V W: tiles of 16 x 16, a wave per strip of rows
+    const int tr = (m + 15) / 16, tc = (mc + 15) / 16;
+    const int strips = min(16, tr), share = 16 / strips;  // waves per strip of rows
+    for (int t = wave / share; t < tr; t += strips) {
+      if (wave / share >= strips) break;
+      const int rr = r0 + 16 * t;
+      double2 ya[4], va[4];
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const int r = min(rr + lr, n - 1);
+        ya[s] = Y[(size_t)(4 * s + lk) * n + r];
+        va[s] = V[(size_t)(4 * s + lk) * n + r];
+      }
+      for (int u = wave % share; u < tc; u += share) {
+        const int c = c1 + 16 * u + lr, cl = min(c, n - 1);
+        dx4 cr, ci;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const double2 x = A[(size_t)cl * n + min(rr + 4 * i + lk, n - 1)];
+          cr[i] = x.x;
+          ci[i] = x.y;
+        }
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          const double2 vb = V[(size_t)(4 * s + lk) * n + cl];
+          const double2 wb = Wb[(size_t)(4 * s + lk) * n + cl];
+          // - Y conj(V)
+          cr = mm4(-ya[s].x, vb.x, cr);
+          cr = mm4(-ya[s].y, vb.y, cr);
+          ci = mm4(ya[s].x, vb.y, ci);
+          ci = mm4(-ya[s].y, vb.x, ci);
+          // - V W
+          cr = mm4(-va[s].x, wb.x, cr);
+          cr = mm4(va[s].y, wb.y, cr);
+          ci = mm4(-va[s].x, wb.y, ci);
+          ci = mm4(-va[s].y, wb.x, ci);
+        }
+        if (c < n)
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if (rr + 4 * i + lk < n)
+              A[(size_t)c * n + rr + 4 * i + lk] = make_double2(cr[i], ci[i]);
       }
     }
     __syncthreads();
-    if (s_skip) continue;
-    const double2 tau = s_tau, scale = s_scale;
-    for (int i = 1 + tid; i < m; i += TPB) {
-      v[i] = cmul(x[i], scale);
-      x[i] = make_double2(0.0, 0.0);
-    }
-    __syncthreads();
-    reflect_right<TPB, NR>(H, n, k, v, tau);
-    reflect_right<TPB, NR>(Q, n, k, v, tau);
-    __syncthreads();
-    // left: H[k+1:, c] -= conj(tau) v (v^H H[k+1:, c]) for c > k, a wave per column
-    const double2 ctau = cconj(tau);
-    for (int c = k + 1 + wave; c < n; c += TPB / 64) {
-      double2* hc = H + (size_t)c * n + k + 1;
-      double2 acc = make_double2(0.0, 0.0);
-      for (int i = lane; i < m; i += 64) acc = cadd(acc, cmulcj(v[i], hc[i]));
-      const double2 y = cmul(ctau, wave_sum(acc));
-      for (int i = lane; i < m; i += 64) hc[i] = csub(hc[i], cmul(v[i], y));
-    }
-    __syncthreads();
   }
+}
+
+// The panels from the right, x <- x - ((x V) T) V^H, on the rows of Q (from the
+// identity; z = 0) and on the rows of H that a panel's columns had left behind
+// (row r <= k0; z = 1). A workgroup takes 64 rows, a lane each, its four waves
+// a quarter of the columns each; V comes through LDS in chunks of 64 columns.
+__global__ void __launch_bounds__(256)
+eig_hess_apply_kernel(int n, double2* __restrict__ Hall, double2* __restrict__ Zall,
+                      const double2* __restrict__ work) {
+  constexpr int NB = kPanel, CH = 64;
+  __shared__ double2 s_V[CH][NB];
+  __shared__ double2 s_T[NB][NB];
+  __shared__ double2 s_w[4][NB][64];
+  const bool q_rows = blockIdx.z == 0;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int first = blockIdx.x * 64, row = first + lane;
+  const double2* H = Hall + (size_t)blockIdx.y * n * n;
+  double2* X = (q_rows ? Zall : Hall) + (size_t)blockIdx.y * n * n + min(row, n - 1);
+  const double2* Tg = work + (size_t)blockIdx.y * hess_work(n) + (size_t)3 * NB * n;
+  const double2 zero = make_double2(0.0, 0.0);
+  if (q_rows && row < n)
+    for (int c = wave; c < n; c += 4) X[(size_t)c * n] = make_double2(c == row ? 1.0 : 0.0, 0.0);
+  const int nref = n - 2;
+  for (int k0 = 0; k0 < nref; k0 += NB) {
+    const int jn = min(NB, nref - k0);
+    if (!q_rows && first > k0) continue;
+    const bool on = row < n && (q_rows || row <= k0);
+    __syncthreads();
+    s_T[tid / NB][tid % NB] = Tg[(size_t)(k0 / NB) * NB * NB + tid];
+    auto stage = [&](int c0) {  // V[c0 .. c0 + 63][:]
+#pragma unroll
+      for (int q = 0; q < CH * NB / 256; ++q) {
+        const int e = tid + 256 * q, c = c0 + (e & 63), j = e >> 6, lead = k0 + j + 1;
+        double2 v = zero;
+        if (j < jn && c < n) {
+          if (c > lead) v = H[(size_t)(k0 + j) * n + c];
+          else if (c == lead) v = make_double2(1.0, 0.0);
+        }
+        s_V[e & 63][j] = v;
+      }
+    };
+    double wx[NB], wy[NB];
+#pragma unroll
+    for (int j = 0; j < NB; ++j) wx[j] = wy[j] = 0.0;
+    for (int c0 = k0 + 1; c0 < n; c0 += CH) {
+      __syncthreads();
+      stage(c0);
+      __syncthreads();
+#pragma unroll 4
+      for (int i = 0; i < CH / 4; ++i) {
+        const int cl = 4 * i + wave, c = c0 + cl;
+        if (c >= n) break;
+        const double2 x = X[(size_t)c * n];
+#pragma unroll
+        for (int j = 0; j < NB; ++j) {
+          const double2 v = s_V[cl][j];
+          wx[j] += x.x * v.x - x.y * v.y;
+          wy[j] += x.x * v.y + x.y * v.x;
+        }
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < NB; ++j) s_w[wave][j][lane] = make_double2(wx[j], wy[j]);
+    __syncthreads();
+    // w = (x V) T: the four partial sums, then the triangular factor
+    double ux[NB], uy[NB];
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      const double2 a = cadd(cadd(s_w[0][j][lane], s_w[1][j][lane]),
+                             cadd(s_w[2][j][lane], s_w[3][j][lane]));
+      wx[j] = a.x;
+      wy[j] = a.y;
+    }
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      ux[j] = uy[j] = 0.0;
+#pragma unroll
+      for (int p = 0; p <= j; ++p) {
+        const double2 t = s_T[p][j];
+        ux[j] += wx[p] * t.x - wy[p] * t.y;
+        uy[j] += wx[p] * t.y + wy[p] * t.x;
+      }
+    }
+    for (int c0 = k0 + 1; c0 < n; c0 += CH) {
+      __syncthreads();
+      stage(c0);
+      __syncthreads();
+#pragma unroll 4
+      for (int i = 0; i < CH / 4; ++i) {
+        const int cl = 4 * i + wave, c = c0 + cl;
+        if (c >= n) break;
+        double2 x = X[(size_t)c * n];
+#pragma unroll
+        for (int j = 0; j < NB; ++j) {  // - w conj(V)
+          const double2 v = s_V[cl][j];
+          x.x -= ux[j] * v.x + uy[j] * v.y;
+          x.y -= uy[j] * v.x - ux[j] * v.y;
+        }
+        if (on) X[(size_t)c * n] = x;
+      }
+    }
+  }
+}
+
+// Zeros below the subdiagonal, where the reflectors were.
+__global__ void __launch_bounds__(256) eig_hess_clear_kernel(int n, double2* __restrict__ Hall) {
+  double2* H = Hall + (size_t)blockIdx.y * n * n;
+  const int c = blockIdx.x;
+  for (int r = c + 2 + threadIdx.x; r < n; r += 256) H[(size_t)c * n + r] = make_double2(0.0, 0.0);
 }
 
 // Rotation G = [[c, s], [-conj(s), c]] with G [x; y] = [r; 0], c real.
@@ -814,16 +1108,18 @@ eig_scale_cols_kernel(int n, long long ncols, const double2* __restrict__ f,
 
 }  // namespace
 
-hipError_t launch_eig_hessenberg(int n, int count, double* A, double* Z, hipStream_t s) {
+size_t eig_hessenberg_work(int n) { return hess_work(n) * sizeof(double2); }
+
+hipError_t launch_eig_hessenberg(int n, int count, double* A, double* Z, double* work,
+                                 hipStream_t s) {
   if (n < 1 || n > kEigMaxN || count < 1) return hipErrorInvalidValue;
-  const size_t lds = (size_t)n * sizeof(double2);
+  const size_t lds = ((size_t)n + 1024) * sizeof(double2);
   double2* a = reinterpret_cast<double2*>(A);
   double2* z = reinterpret_cast<double2*>(Z);
-  const int nr = (n + 255) / 256;
-  if (nr <= 1) eig_hessenberg_kernel<256, 1><<<count, 256, lds, s>>>(n, a, z);
-  else if (nr <= 2) eig_hessenberg_kernel<256, 2><<<count, 256, lds, s>>>(n, a, z);
-  else if (nr <= 4) eig_hessenberg_kernel<256, 4><<<count, 256, lds, s>>>(n, a, z);
-  else eig_hessenberg_kernel<256, 8><<<count, 256, lds, s>>>(n, a, z);
+  double2* w = reinterpret_cast<double2*>(work);
+  eig_hessenberg_kernel<<<count, 1024, lds, s>>>(n, a, w);
+  eig_hess_apply_kernel<<<dim3((n + 63) / 64, count, 2), 256, 0, s>>>(n, a, z, w);
+  eig_hess_clear_kernel<<<dim3(n, count), 256, 0, s>>>(n, a);
   return hipGetLastError();
 }
 

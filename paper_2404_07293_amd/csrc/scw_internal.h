@@ -264,7 +264,9 @@ int device_eig_batched(Context& ctx, int n, int count, double* A, double* w, dou
                        hipStream_t st);
 // The context's rocBLAS handle (created on first use), bound to stream st.
 int blas_handle(Context& ctx, hipStream_t st, void** out);
-hipError_t launch_eig_hessenberg(int n, int count, double* A, double* Z, hipStream_t s);
+size_t eig_hessenberg_work(int n);  // bytes of workspace per matrix
+hipError_t launch_eig_hessenberg(int n, int count, double* A, double* Z, double* work,
+                                 hipStream_t s);
 // Record of the QR iteration: per matrix 8 state ints ({ihi, eigenvalue's
 // sweeps, done, info, recorded sweeps, recorded rotations}; info j + 1 when
 // eigenvalue j did not converge), capr rotations (at least n) and caps sweep

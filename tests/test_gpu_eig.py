@@ -289,3 +289,24 @@ def test_reducible_matrices(ctx):
         print("reducible[%d] residual %.2e" % (b, res), flush=True)
         assert res <= 1e-12
         assert np.abs(np.linalg.norm(X[b], axis=0) - 1).max() <= 1e-12
+
+
+@pytest.mark.parametrize("n", [16, 18, 19, 34, 35, 50, 88, 89, 1100])
+def test_panel_and_window_edges(ctx, n):
+    """Orders around the reduction's panels (16 reflectors after two columns), the
+    QR windows, and above 1024 rows, where a thread takes two. Backward stable
+    steps leave a residual of a small multiple of n eps; the eigenvalue sum is
+    the trace to the same level."""
+    torch = _torch()
+    rng = np.random.default_rng(1000 + n)
+    A = rng.standard_normal((2, n, n)) + 1j * rng.standard_normal((2, n, n))
+    A[1] = np.triu(A[1], -1) + 1e-9 * A[1]  # nearly Hessenberg: tiny reflectors
+    Ad = torch.as_tensor(A).cuda()
+    w, X = ctx.eig_batched(Ad)
+    for b in range(2):
+        na = float(torch.linalg.norm(Ad[b]))
+        res = float(torch.linalg.norm(Ad[b] @ X[b] - X[b] * w[b][None, :])) / na
+        tr = abs(complex(w[b].sum()) - np.trace(A[b])) / na
+        print("edge[%d] n=%d residual %.2e trace %.2e" % (b, n, res, tr), flush=True)
+        assert res <= 1e-12 and tr <= 1e-12
+        assert float((torch.linalg.norm(X[b], dim=0) - 1).abs().max()) <= 1e-12
