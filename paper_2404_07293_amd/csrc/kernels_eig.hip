@@ -30,7 +30,7 @@ namespace scw {
 namespace {
 
 constexpr int kMaxSweepsPerEigenvalue = 300;
-constexpr int kEigWindow = 24;  // rotations per window of the QR sweep
+constexpr int kEigWindow = 16;  // rotations per window of the QR sweep (20 and 24 spill registers: 1.15x)
 constexpr int kEigInner = 64;   // active blocks up to this order stay in LDS
 
 __device__ inline double2 cmul(double2 a, double2 b) {
@@ -494,18 +494,21 @@ __device__ inline void givens_scaled(double2 x, double2 y, double& c, double2& s
   s = cscale(cmul(ph, cconj(y)), 1.0 / nrm);
   r = cscale(ph, nrm);
 }
+// 1 / sqrt(x) of a normal x: the hardware's estimate and one third-order step.
+__device__ inline double rsqrt_normal(double x) {
+  const double y = __builtin_amdgcn_rsq(x);
+  const double e = fma(-x * y, y, 1.0);
+  return fma(y * e, fma(e, 0.375, 0.5), y);
+}
 // The same from two reciprocal square roots where no square leaves the normal
 // range (the chase waits for this result at every rotation).
 __device__ inline void givens(double2 x, double2 y, double& c, double2& s, double2& r) {
   const double ax2 = x.x * x.x + x.y * x.y, ay2 = y.x * y.x + y.y * y.y, n2 = ax2 + ay2;
-  if (ax2 > 1e-250 && ay2 > 1e-250 && n2 < 1e250) {
-    const double rx = rsqrt(ax2), rn = rsqrt(n2), f = rx * rn;
-    c = ax2 * f;
-    s = cscale(cmul(x, cconj(y)), f);
-    r = cscale(x, n2 * f);
-  } else {
-    givens_scaled(x, y, c, s, r);
-  }
+  const double rx = rsqrt_normal(ax2), rn = rsqrt_normal(n2), f = rx * rn;
+  c = ax2 * f;
+  s = cscale(cmul(x, cconj(y)), f);
+  r = cscale(x, n2 * f);
+  if (!(fmin(ax2, ay2) > 1e-250 && n2 < 1e250)) givens_scaled(x, y, c, s, r);
 }
 
 __device__ inline double2& at(double2* M, int n, int i, int j) { return M[(size_t)j * n + i]; }
@@ -565,34 +568,40 @@ __device__ void chase(double2* __restrict__ blk, int ld, int bn, int b0, int k0,
   const bool live = lane < bn;
   double2* col = blk + min(lane, bn - 1) * ld;
   double2 cur = col[kk], nxt = col[kk + 1];
+  double mc = 1.0;  // lane q keeps rotation k0 + q
+  double2 ms = make_double2(0.0, 0.0);
   for (int k = k0; k < k1; ++k, ++kk) {
     double2 nn = col[min(kk + 2, bn - 1)];
     double c;
     double2 s, r;
     givens(x, y, c, s, r);
     const double2 cs = cconj(s);
-    if (lane == 0) {
-      rc[k - k0] = c;
-      rs[k - k0] = s;
-      if (k > l) {
-        blk[(kk - 1) * ld + kk] = r;
-        blk[(kk - 1) * ld + kk + 1] = make_double2(0.0, 0.0);
-      }
-    }
-    const double2 top = cadd(cscale(cur, c), cmul(s, nxt));
+    const bool keep = lane == k - k0;
+    mc = keep ? c : mc;
+    ms.x = keep ? s.x : ms.x;
+    ms.y = keep ? s.y : ms.y;
+    // row k, and r in the column before it (what the bulge leaves below the
+    // subdiagonal is never read)
+    double2 top = cadd(cscale(cur, c), cmul(s, nxt));
+    const bool sub_col = lane == kk - 1;
+    top.x = sub_col ? r.x : top.x;
+    top.y = sub_col ? r.y : top.y;
     cur = csub(cscale(nxt, c), cmul(cs, cur));
-    if (live && lane >= kk) col[kk] = top;
+    if (live && lane >= kk - 1 && (k > l || lane >= kk)) col[kk] = top;
     const double2 a = read_lane(cur, kk), b = read_lane(cur, kk + 1);
     double2 sub = read_lane(nn, kk + 1);
     if (k + 2 > ihi) sub = make_double2(0.0, 0.0);
     x = cadd(cscale(a, c), cmul(cs, b));
     y = cmul(cs, sub);
-    if (lane == kk + 1) {
-      cur = csub(cscale(b, c), cmul(s, a));
-      nn = cscale(sub, c);
-    }
-    nxt = nn;
+    const bool next = lane == kk + 1;
+    const double2 nb = csub(cscale(b, c), cmul(s, a));
+    cur.x = next ? nb.x : cur.x;
+    cur.y = next ? nb.y : cur.y;
+    nxt.x = next ? sub.x * c : nn.x;
+    nxt.y = next ? sub.y * c : nn.y;
   }
+  rc[lane] = mc;
+  rs[lane] = ms;
   if (live && lane >= kk) col[kk] = cur;  // row k1
   if (lane == kk && k1 < ihi) col[kk + 1] = nxt;
   if (lane == 0) {
@@ -606,22 +615,34 @@ __device__ void chase(double2* __restrict__ blk, int ld, int bn, int b0, int k0,
 __device__ inline void apply_block_columns(double2* __restrict__ blk, int ld, int row, int b0,
                                            int k0, int k1, const double* __restrict__ rc,
                                            const double2* __restrict__ rs) {
-  const int first = max(k0, b0 + row);
-  double2* v = blk + row;
-  double2 cur = v[(k0 - b0) * ld];
-  for (int k = k0; k < k1; ++k) {
-    const int kk = k - b0;
-    const double2 t2 = v[(kk + 1) * ld];
-    if (k >= first) {
-      const double c = rc[k - k0];
-      const double2 s = rs[k - k0];
-      v[kk * ld] = cadd(cscale(cur, c), cmul(cconj(s), t2));
-      cur = csub(cscale(t2, c), cmul(s, cur));
-    } else {
-      cur = t2;
+  constexpr int N = 4;  // rotations read ahead
+  const int first = max(k0, b0 + row) - k0, nq = k1 - k0;
+  double2* v = blk + (k0 - b0) * ld + row;  // v[q * ld]: column k0 + q
+  double2 cur = v[0];
+  for (int q0 = 0; q0 < nq; q0 += N) {
+    double cx[N], cy[N], c[N], sx[N], sy[N];
+#pragma unroll
+    for (int u = 0; u < N; ++u) {  // rotations nq and above are identities
+      const int q = min(q0 + u, nq - 1);
+      const double2 t = v[(q + 1) * ld], sv = rs[q0 + u];
+      const bool on = q0 + u >= first;
+      cx[u] = t.x;
+      cy[u] = t.y;
+      c[u] = on ? rc[q0 + u] : 1.0;
+      sx[u] = on ? sv.x : 0.0;
+      sy[u] = on ? sv.y : 0.0;
+    }
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+      if (q0 + u >= nq) break;
+      const double2 o = make_double2(c[u] * cur.x + (sx[u] * cx[u] + sy[u] * cy[u]),
+                                     c[u] * cur.y + (sx[u] * cy[u] - sy[u] * cx[u]));
+      cur = make_double2(c[u] * cx[u] - (sx[u] * cur.x - sy[u] * cur.y),
+                         c[u] * cy[u] - (sx[u] * cur.y + sy[u] * cur.x));
+      v[(q0 + u) * ld] = o;
     }
   }
-  if (first < k1) v[(k1 - b0) * ld] = cur;
+  v[nq * ld] = cur;
 }
 
 __device__ inline bool negligible(double sub, double tst, int n) {
@@ -668,8 +689,8 @@ __device__ inline void window_rotate(double2* __restrict__ v0, int stride, int n
   for (int q = W; q >= 0; --q) v0[(size_t)(min(q, nq) * stride)] = make_double2(vx[q], vy[q]);
 }
 
-// 96 matrices of order 242: 142 ms with everything in the iteration, now 51 ms
-// for it and 23 ms for the three applications of its records.
+// 96 matrices of order 242: 142 ms with everything in the iteration, now 42 ms
+// for it and 11 ms for the three applications of its records.
 //
 // Two phases by the size of the active block. Above kInner it lives in memory
 // and a sweep runs in windows of W rotations: the window's diagonal block (at
@@ -685,8 +706,8 @@ eig_schur_kernel(int n, double2* __restrict__ Hall, double2* __restrict__ wall,
   constexpr int LD = kInner + 1;
   static_assert(W + 3 <= kInner && kInner <= 64, "a block's columns are one wave's lanes");
   __shared__ double2 blk[LD * kInner];
-  __shared__ double s_c[kInner];
-  __shared__ double2 s_s[kInner];
+  __shared__ double s_c[64];  // a lane each: identities past the last rotation
+  __shared__ double2 s_s[64];
   __shared__ int s_l, s_ihi, s_its, s_stop, s_nsw, s_nrot;
   double2* H = Hall + blockIdx.x * (size_t)n * n;
   double2* w = wall + (size_t)blockIdx.x * n;
@@ -841,13 +862,7 @@ eig_schur_kernel(int n, double2* __restrict__ Hall, double2* __restrict__ wall,
         blk[c * LD + r] = at(H, n, b0 + r, b0 + c);
       }
       __syncthreads();
-      if (wave == 0) {
-        if (lane >= nq && lane < W) {  // a short window ends in identities
-          s_c[lane] = 1.0;
-          s_s[lane] = make_double2(0.0, 0.0);
-        }
-        chase(blk, LD, bn, b0, k0, k1, l, ihi, mu, s_c, s_s);
-      }
+      if (wave == 0) chase(blk, LD, bn, b0, k0, k1, l, ihi, mu, s_c, s_s);
       __syncthreads();
       if (wave == 0) {  // the block itself, and the record
         if (lane < bn) {
@@ -897,21 +912,25 @@ __global__ void eig_schur_begin(int n, int count, int* __restrict__ state) {
 // act from different sides and commute.
 //
 // One wave per 64 rows (columns), a lane each. Sixteen sweeps run at once in a
-// skewed order: at step t sweep s applies its rotation k = t - 2 s, which no
-// earlier sweep still has to reach, so the sixteen are independent and every
-// value is read and written once per sixteen sweeps. The values under way are
-// a ring of 64 columns in LDS; each chunk of 16 steps brings in 16 columns and
-// retires 16, the next chunk's columns and rotations being loaded meanwhile.
-// Bound by LDS (two 16-byte reads and writes per rotation and lane).
-constexpr int kApplySweeps = 16, kApplySteps = 16, kApplyRing = 64;
+// skewed order: at step t sweep s applies its rotation k = t - s to the elements
+// k and k + 1. Of its two results the one at k is the second element of sweep
+// s + 1, next in the same step, the one at k + 1 its own first element at the
+// next step; so the sixteen form a pipeline held in registers, into which one
+// element enters per step and from which one leaves. An element is read and written once per sixteen
+// sweeps. A rotation outside its sweep's range is an identity. The next
+// chunk's elements and rotations are fetched during a chunk of 16 steps.
+// Bound by the FP64 units: 12 operations per rotation and lane. (With the
+// elements in an LDS ring, each rotation reading and writing two: 23.5 ms
+// instead of 10.9 for the three kernels on 96 matrices of order 242.)
+constexpr int kApplySweeps = 16, kApplySteps = 16;
 template <int MODE>
 __global__ void __launch_bounds__(64)
 eig_apply_kernel(int n, double2* __restrict__ Mall, const int* __restrict__ stateall, int capr,
                  int caps, const double* __restrict__ rotc, const double2* __restrict__ rots,
                  const int4* __restrict__ hdrall) {
-  constexpr int S = kApplySweeps, T = kApplySteps, R = kApplyRing;
-  static_assert(R >= 2 * S + 2 * T && T == 16 && S == 16, "ring and fetch layout");
-  __shared__ double2 ring[R][64];
+  constexpr int S = kApplySweeps, T = kApplySteps;
+  static_assert(T == 16 && S == 16, "fetch layout");
+  __shared__ double2 s_in[T][64];
   __shared__ double s_c[T * S];
   __shared__ double2 s_s[T * S];
   const int lane = threadIdx.x, b = blockIdx.y;
@@ -925,44 +944,43 @@ eig_apply_kernel(int n, double2* __restrict__ Mall, const int* __restrict__ stat
   const size_t stride = MODE == 2 ? 1 : (size_t)n;
   double2* base = M + (MODE == 2 ? (size_t)min(id, n - 1) * n : (size_t)min(id, n - 1));
   for (int s0 = 0; s0 < nsw; s0 += S) {
-    int sl[S], sh[S], so[S];  // the sixteen sweeps (an empty range past the last)
-    int lo = n, hi = 0;
-    bool any = false;
+    // lane u of each 16 holds sweep s0 + u (an empty range past the last)
+    const int4 h = hdr[min(s0 + (lane & 15), nsw - 1)];
+    int el = h.x, eh = h.y;
+    const bool on = s0 + (lane & 15) < nsw && (MODE == 0 || (MODE == 1 ? first < el : last > eh));
+    if (!__ballot(on)) continue;
+    if (!on) eh = el;
+    // the group's range, and this lane's sweeps (bit s: it takes part in sweep s)
+    int lo = on ? el : n, hi = on ? eh : 0;
 #pragma unroll
-    for (int s = 0; s < S; ++s) {
-      const int4 h = hdr[min(s0 + s, nsw - 1)];
-      sl[s] = uniform(h.x);
-      sh[s] = uniform(h.y);
-      so[s] = uniform(h.z);
-      const bool on = s0 + s < nsw &&
-                      (MODE == 0 || (MODE == 1 ? first < sl[s] : last > sh[s]));
-      if (on) {
-        any = true;
-        lo = min(lo, sl[s]);
-        hi = max(hi, sh[s]);
-      } else {
-        sh[s] = sl[s];
-      }
+    for (int o = 8; o >= 1; o >>= 1) {
+      lo = min(lo, __shfl_xor(lo, o, 64));
+      hi = max(hi, __shfl_xor(hi, o, 64));
     }
-    if (!any) continue;
-    double colx[T], coly[T], rcv[4], rsx[4], rsy[4];
-    ring[lo & (R - 1)][lane] = base[(size_t)lo * stride];
-    // this lane's rotations of a chunk: steps lane / 16 + 4 q of sweep lane % 16
-    int el = 0, eh = 0, eo = 0;
+    lo = uniform(lo);
+    hi = uniform(hi);
+    unsigned takes = 0xffffu;
+    if (MODE != 0) {
+      takes = 0;
 #pragma unroll
-    for (int u = 0; u < S; ++u)
-      if (u == (lane & 15)) {
-        el = sl[u];
-        eh = sh[u];
-        eo = so[u];
-      }
-    // the chunk that starts at t0 retires columns t0 - 30 .. t0 - 15 (the pass
-    // before the first only loads)
-    for (int t0 = lo - T; t0 - 2 * S + 2 <= hi; t0 += T) {
+      for (int s = 0; s < S; ++s)
+        if (MODE == 1 ? id < __shfl(h.x, s, 64) : id > __shfl(h.y, s, 64)) takes |= 1u << s;
+    }
+    double colx[T], coly[T], rcv[4], rsx[4], rsy[4];
+    double px[S], py[S];  // sweep s's first element at step t: t - s
+#pragma unroll
+    for (int s = 0; s < S; ++s) px[s] = py[s] = 0.0;
+    {
+      const double2 v = base[(size_t)lo * stride];
+      px[0] = v.x;
+      py[0] = v.y;
+    }
+    // the pass before the first only loads
+    for (int t0 = lo - T; t0 - S + 1 <= hi; t0 += T) {
       const bool run = t0 >= lo;
       if (run) {
 #pragma unroll
-        for (int i = 0; i < T; ++i) ring[(t0 + 1 + i) & (R - 1)][lane] = make_double2(colx[i], coly[i]);
+        for (int i = 0; i < T; ++i) s_in[i][lane] = make_double2(colx[i], coly[i]);
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           s_c[q * 64 + lane] = rcv[q];
@@ -970,6 +988,8 @@ eig_apply_kernel(int n, double2* __restrict__ Mall, const int* __restrict__ stat
         }
       }
       wave_sync();
+      // elements t + 1 of the next chunk's steps, and its rotations: step
+      // 4 q + lane / 16 of sweep lane % 16 at q * 64 + lane
 #pragma unroll
       for (int i = 0; i < T; ++i) {
         const double2 v = base[(size_t)min(t0 + T + 1 + i, hi) * stride];
@@ -978,38 +998,41 @@ eig_apply_kernel(int n, double2* __restrict__ Mall, const int* __restrict__ stat
       }
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const int k = t0 + T + 4 * q + (lane >> 4) - 2 * (lane & 15);
-        const int e = k >= el && k < eh ? eo + k - el : 0;
+        const int k = t0 + T + 4 * q + (lane >> 4) - (lane & 15);
+        const bool in = k >= el && k < eh;
+        const int e = in ? h.z + k - el : 0;
         const double2 v = rots[e];
-        rcv[q] = rotc[e];
-        rsx[q] = v.x;
-        rsy[q] = v.y;
+        const double c = rotc[e];
+        rcv[q] = in ? c : 1.0;
+        rsx[q] = in ? v.x : 0.0;
+        rsy[q] = in ? (MODE == 2 ? v.y : -v.y) : 0.0;
       }
       if (!run) continue;
+#pragma unroll 1
       for (int i = 0; i < T; ++i) {
-        const int t = t0 + i;
+        const double2 in = s_in[i][lane];
+        double fx = in.x, fy = in.y;  // the element handed down: sweep s's second
 #pragma unroll
         for (int s = 0; s < S; ++s) {
-          const int k = t - 2 * s;
-          if (k < sl[s] || k >= sh[s]) continue;  // uniform
-          const double c = s_c[i * S + s];
+          double c = s_c[i * S + s];
           const double2 sv = s_s[i * S + s];
-          const double2 sk = MODE == 2 ? sv : cconj(sv);
-          if (MODE == 0 || (MODE == 1 ? id < sl[s] : id > sh[s])) {
-            double2* p0 = &ring[k & (R - 1)][lane];
-            double2* p1 = &ring[(k + 1) & (R - 1)][lane];
-            const double2 t1 = *p0, t2 = *p1;
-            *p0 = cadd(cscale(t1, c), cmul(sk, t2));
-            *p1 = csub(cscale(t2, c), cmul(cconj(sk), t1));
+          double sx = sv.x, sy = sv.y;
+          if (MODE != 0) {
+            const bool mine = (takes >> s) & 1;
+            c = mine ? c : 1.0;
+            sx = mine ? sx : 0.0;
+            sy = mine ? sy : 0.0;
           }
+          const double ax = px[s], ay = py[s];
+          // first: c a + s f; second: c f - conj(s) a
+          const double ox = c * ax + (sx * fx - sy * fy), oy = c * ay + (sx * fy + sy * fx);
+          px[s] = c * fx - (sx * ax + sy * ay);
+          py[s] = c * fy - (sx * ay - sy * ax);
+          fx = ox;
+          fy = oy;
         }
-      }
-      if (id < n) {
-#pragma unroll
-        for (int i = 0; i < T; ++i) {
-          const int q = t0 - 2 * S + 2 + i;
-          if (q >= lo && q <= hi) base[(size_t)q * stride] = ring[q & (R - 1)][lane];
-        }
+        const int q = t0 + i - S + 1;  // the element that leaves the last sweep
+        if (q >= lo && q <= hi && id < n) base[(size_t)q * stride] = make_double2(fx, fy);
       }
       wave_sync();
     }
