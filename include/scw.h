@@ -335,8 +335,10 @@ int scw_synthesize_composed(scw_ctx* ctx, scw_solution* const* patches, int px, 
  *   transform   how Eq. 10 is evaluated: SCW_XFORM_FFT (Horner x pass and a
  *               factored y pass fy = R * P; FP64/FP32, fy a power of two,
  *               V <= 32), SCW_XFORM_MFMA (y pass as a GEMM on the matrix
- *               cores; the only transform of the split modes), or
- *               SCW_XFORM_DIRECT (Horner in x and y);
+ *               cores; the only transform of the split modes),
+ *               SCW_XFORM_DIRECT (Horner in x and y), or SCW_XFORM_AUTO: by
+ *               conjugate pairs in FP64 and FP32 where fft_radix and tiles are
+ *               0 and its tables fit (V <= 33), else the best of the others;
  *   fft_radix   P of the factored y pass (2 .. 32, a power of two);
  *   tiles       row tiles per plane (DIRECT), plane-components per block
  *               (MFMA) or columns per block, 32 or 64 (FFT); 0 = automatic.

@@ -21,6 +21,7 @@ SOURCES = [
     "tune.cpp",
     "kernels_setup.hip",
     "kernels_synth.hip",
+    "kernels_transform.hip",
     "kernels_mfma.hip",
     "kernels_batch.hip",
     "surrogate.cpp",

@@ -3,7 +3,6 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <functional>
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
@@ -215,12 +214,26 @@ int choose_shape(const Solution& s, const scw_grid& g, int precision,
   const bool fft_ok = !split && s.V <= 32 && g.fy >= 2 && is_pow2(g.fy) && is_pow2(P) &&
                       P >= 2 && P <= 32 && P <= g.fy &&
                       fft_lds_bytes(s, g, precision, P) <= 64 * 1024;
+  // FP32 and FP64 transform by conjugate pairs wherever its tables fit: a quarter
+  // to an eighth of the direct sum's work for any fy, and no operand through
+  // memory. Transforms alone, pairs against the factored pass: 8 x 128 x 128 x
+  // 64 points, V = 15: 40 us, 72; 256 x 256 x 128, V = 21: 44.6 us, 45; against
+  // the direct sums, 150 x 90 x 45, V = 9: 8.0 us, 19.1.
+  // The tables grow with fx and fy, the field also with fz: grids so thin that
+  // the tables would be the larger keep the other transforms.
   int kind = cfg.transform;
+  out->pair = kind == SCW_XFORM_AUTO && !split && !cfg.fft_radix && !cfg.tiles &&
+              g.fx < (1 << 30) &&
+              pair_transform_fits(s.U, s.V, precision == SCW_FP64, 1) &&
+              pair_layout(s.U, s.V, g.fx, g.fy).size <=
+                  std::max(1LL << 16, 3LL * g.fx * g.fy * g.fz);
   if (kind == SCW_XFORM_AUTO)
     kind = split ? SCW_XFORM_MFMA
-                 : (fft_ok ? SCW_XFORM_FFT
-                           : (precision == SCW_FP32 && s.V <= 32 ? SCW_XFORM_MFMA
-                                                                 : SCW_XFORM_DIRECT));
+                 : (out->pair ? SCW_XFORM_DIRECT
+                              : (fft_ok ? SCW_XFORM_FFT
+                                        : (precision == SCW_FP32 && s.V <= 32
+                                               ? SCW_XFORM_MFMA
+                                               : SCW_XFORM_DIRECT)));
   if (split && kind != SCW_XFORM_MFMA)
     return fail(SCW_EINVAL, "split-precision synthesis evaluates the transform on the matrix cores");
   if (kind == SCW_XFORM_FFT && !fft_ok)
@@ -287,31 +300,6 @@ int build_plan(Solution& s, Plan& pl, const scw_grid& g, int precision,
   if ((rc = pl.d_w.reserve(std::max<size_t>(16, pl.tasks.size() * 2 * zt * n2 * eb))) ||
       (rc = pl.d_spec.reserve((size_t)g.fz * 3 * s.M * eb)))
     return rc;
-  // inverse-transform factors: wx[0][f] = e^{2 pi i f/fx}, wx[1][f] = e^{-2 pi i (U/2) f/fx}
-  std::vector<zc> twx(2 * (size_t)g.fx), twy(2 * (size_t)g.fy);
-  for (int f = 0; f < g.fx; ++f) {
-    twx[f] = twiddle_inv(f, g.fx);
-    twx[g.fx + f] = twiddle_inv(-(long long)(s.U / 2) * f, g.fx);
-  }
-  for (int gg = 0; gg < g.fy; ++gg) {
-    twy[gg] = twiddle_inv(gg, g.fy);
-    twy[g.fy + gg] = twiddle_inv(-(long long)(s.V / 2) * gg, g.fy);
-  }
-  if (precision == SCW_FP64) {
-    std::vector<double> a, b;
-    pack(twx, a);
-    pack(twy, b);
-    if ((rc = upload(pl.d_twx, a.data(), a.size() * 8)) ||
-        (rc = upload(pl.d_twy, b.data(), b.size() * 8)))
-      return rc;
-  } else {
-    std::vector<float> a, b;
-    pack(twx, a);
-    pack(twy, b);
-    if ((rc = upload(pl.d_twx, a.data(), a.size() * 4)) ||
-        (rc = upload(pl.d_twy, b.data(), b.size() * 4)))
-      return rc;
-  }
   // kernel configuration: explicit, tuned, or the built-in default
   pl.cfg = cfg;
   KernelShape ks;
@@ -321,6 +309,53 @@ int build_plan(Solution& s, Plan& pl, const scw_grid& g, int precision,
   const int kind = ks.kind, P = ks.fft_p;
   pl.fft_p = 0;
   pl.mfma = false;
+  pl.pair = ks.pair;
+  // Inverse-transform factors, in one upload: twx and twy, with wx[0][f] =
+  // e^{2 pi i f/fx}, wx[1][f] = e^{-2 pi i (U/2) f/fx}, then the pair tables.
+  // Every factor is a root of unity of order fx or fy (2 fx, 2 fy in the pair
+  // tables), so each order's sines are taken once.
+  const int order = ks.pair ? 2 : 1;
+  std::vector<zc> rx((size_t)order * g.fx), ry((size_t)order * g.fy);
+  for (size_t k = 0; k < rx.size(); ++k) rx[k] = twiddle_inv((long long)k, order * g.fx);
+  for (size_t k = 0; k < ry.size(); ++k) ry[k] = twiddle_inv((long long)k, order * g.fy);
+  auto root = [](const std::vector<zc>& r, long long k) {
+    const long long n = (long long)r.size(), i = k % n;
+    return r[(size_t)(i < 0 ? i + n : i)];
+  };
+  const PairLayout lay = ks.pair ? pair_layout(s.U, s.V, g.fx, g.fy) : PairLayout{};
+  const size_t o_y = 2 * (size_t)g.fx, o_pair = o_y + 2 * (size_t)g.fy;
+  std::vector<zc> tab(o_pair + (size_t)lay.size);
+  for (int f = 0; f < g.fx; ++f) {
+    tab[f] = rx[(size_t)order * f];
+    tab[g.fx + f] = root(rx, -(long long)order * (s.U / 2) * f);
+  }
+  for (int gg = 0; gg < g.fy; ++gg) {
+    tab[o_y + gg] = ry[(size_t)order * gg];
+    tab[o_y + g.fy + gg] = root(ry, -(long long)order * (s.V / 2) * gg);
+  }
+  if (ks.pair) {
+    // pair p lies (2 p + e) / 2 from the axis' middle, e = 1 for an even axis
+    const int ex = 1 - g.fx % 2, ey = 1 - g.fy % 2;
+    zc* w = tab.data() + o_pair;
+    for (int u = 1; u <= s.U / 2; ++u)
+      for (int p = 0; p < lay.npx; ++p) *w++ = root(rx, (long long)u * (2 * p + ex));
+    for (int u = 0; u <= s.U / 2; ++u) *w++ = root(rx, (long long)u * (g.fx - 1));
+    for (int p = 0; p < lay.npy; ++p, w += lay.hv)
+      for (int v = 1; v <= s.V / 2; ++v) w[v - 1] = root(ry, (long long)v * (2 * p + ey));
+    for (int v = 0; v < s.V; ++v) *w++ = root(ry, (long long)(v - s.V / 2) * (g.fy - 1));
+  }
+  if (precision == SCW_FP64) {
+    std::vector<double> b;
+    pack(tab, b);
+    if ((rc = upload(pl.d_tw, b.data(), b.size() * 8))) return rc;
+  } else {
+    std::vector<float> b;
+    pack(tab, b);
+    if ((rc = upload(pl.d_tw, b.data(), b.size() * 4))) return rc;
+  }
+  pl.twx = pl.d_tw.p;
+  pl.twy = static_cast<const char*>(pl.d_tw.p) + o_y * eb;
+  pl.pair_tab = ks.pair ? static_cast<const char*>(pl.d_tw.p) + o_pair * eb : nullptr;
   if (kind == SCW_XFORM_FFT) {
     const int R = g.fy / P;
     pl.fft_p = P;
@@ -572,8 +607,8 @@ static SynthArgs synth_args(const Solution& s, const Plan& pl, const scw_grid& g
   a.ext_planes = pl.d_ext.p;
   a.w = pl.d_w.p;
   a.spec = pl.d_spec.p;
-  a.twx = pl.d_twx.p;
-  a.twy = pl.d_twy.p;
+  a.twx = pl.twx;
+  a.twy = pl.twy;
   a.E = E;
   a.kgab32 = s.d_kgab32.p;
   a.task_dz32 = pl.d_task_dz32.p;
@@ -588,6 +623,8 @@ static SynthArgs synth_args(const Solution& s, const Plan& pl, const scw_grid& g
   a.idft_gtiles = pl.tiles;
   a.modal_rw = pl.modal_rw;
   a.stages = stages;
+  a.pair_tab = pl.pair_tab;
+  a.nvol = 1;
   return a;
 }
 
@@ -627,6 +664,13 @@ int synthesize_illuminations(Context& c, Solution& s, const scw_grid& g, void* E
                                k0, std::min(group, s.K - k0), pl.d_wmulti.p,
                                pl.d_spec_multi.p, st));
   const size_t vol = (size_t)3 * g.fz * g.fy * g.fx;
+  if (pl.pair && s.K <= 65535) {  // every illumination's exterior planes and transform in one launch each
+    SynthArgs a = synth_args(s, pl, g, SCW_FP32, E, kStageExterior | kStageTransform);
+    a.spec = pl.d_spec_multi.p;
+    a.nvol = s.K;
+    SCW_HIP(launch_synthesis_fp32(a, st, nullptr));
+    return SCW_OK;
+  }
   for (int k = 0; k < s.K; ++k) {
     SynthArgs a = synth_args(s, pl, g, SCW_FP32, static_cast<char*>(E) + k * vol * 8,
                              kStageExterior | kStageTransform);
@@ -748,7 +792,7 @@ int scw_synthesize_slice(scw_ctx* ctx, scw_solution* sol, const scw_slice* slice
   const Plan& pl = *plp;
   SliceArgs a{};
   a.spec = pl.d_spec.p;
-  a.tw = slice->axis == SCW_SLICE_XZ ? pl.d_twx.p : pl.d_twy.p;
+  a.tw = slice->axis == SCW_SLICE_XZ ? pl.twx : pl.twy;
   a.U = s.U;
   a.V = s.V;
   a.n = slice->n;
@@ -760,11 +804,13 @@ int scw_synthesize_slice(scw_ctx* ctx, scw_solution* sol, const scw_slice* slice
   return SCW_OK;
 }
 
-// The spectra of the grid's planes, `op` on them, then Eq. 10 and (when I_dev
-// is not null) the intensity.
+// The spectra of the grid's planes, then an objective's aperture (na >= 0) or a
+// transfer function H on them, Eq. 10 and (when I_dev is not null) the
+// intensity. The pair transform takes the aperture as it reads the spectra
+// and, in FP32, writes the intensity with the field.
 static int synthesize_with(scw_ctx* ctx, scw_solution* sol, const scw_grid* grid, int precision,
-                           void* E_dev, void* I_dev, void* hip_stream,
-                           const std::function<hipError_t(Solution&, Plan&, hipStream_t)>& op) {
+                           void* E_dev, void* I_dev, void* hip_stream, double na,
+                           const void* H) {
   if (!ctx || !sol || !E_dev) return fail(SCW_EINVAL, "null argument");
   int rc = check_grid(grid);
   if (rc) return rc;
@@ -775,39 +821,42 @@ static int synthesize_with(scw_ctx* ctx, scw_solution* sol, const scw_grid* grid
   Context& c = ctx->c;
   Solution& s = sol->s;
   const hipStream_t st = reinterpret_cast<hipStream_t>(hip_stream);
+  const bool fp64 = precision == SCW_FP64;
   Plan* pl = nullptr;
   if ((rc = synthesize(c, s, *grid, precision, E_dev, st, kStageModal | kStageExterior, nullptr,
                        false, &pl)))
     return rc;
-  SCW_HIP(op(s, *pl, st));
-  if ((rc = synthesize(c, s, *grid, precision, E_dev, st, kStageTransform, nullptr))) return rc;
-  if (I_dev)
-    SCW_HIP(launch_intensity(E_dev, I_dev, (long long)grid->fz * grid->fy * grid->fx,
-                             precision == SCW_FP64, st));
+  SynthArgs a = synth_args(s, *pl, *grid, precision, E_dev, kStageTransform);
+  const double sx_step = s.lam / s.X, sy_step = s.lam / s.Y;
+  const long long nspec = (long long)grid->fz * 3 * s.M;
+  if (H) {
+    SCW_HIP(launch_transfer(pl->d_spec.p, nspec, s.M, H, fp64, st));
+  } else if (pl->pair) {
+    a.objective = 1;
+    a.sx_step = sx_step;
+    a.sy_step = sy_step;
+    a.na2 = na * na;
+  } else {
+    SCW_HIP(launch_objective(pl->d_spec.p, nspec, s.M, s.U, s.V, sx_step, sy_step, na, fp64, st));
+  }
+  const bool fused = I_dev && pl->pair && !fp64 && pair_transform_fits(s.U, s.V, false, 3);
+  if (fused) a.I = I_dev;
+  SCW_HIP(fp64 ? launch_synthesis_fp64(a, st, nullptr) : launch_synthesis_fp32(a, st, nullptr));
+  if (I_dev && !fused)
+    SCW_HIP(launch_intensity(E_dev, I_dev, (long long)grid->fz * grid->fy * grid->fx, fp64, st));
   return SCW_OK;
 }
 
 int scw_synthesize_image(scw_ctx* ctx, scw_solution* sol, const scw_grid* grid, int precision,
                          double na, void* E_dev, void* I_dev, void* hip_stream) {
   if (!(na >= 0.0) || !std::isfinite(na)) return fail(SCW_EINVAL, "na must be finite and >= 0");
-  return synthesize_with(ctx, sol, grid, precision, E_dev, I_dev, hip_stream,
-                         [&](Solution& s, Plan& pl, hipStream_t st) {
-                           return launch_objective(pl.d_spec.p,
-                                                   (long long)grid->fz * 3 * s.M, s.M, s.U, s.V,
-                                                   s.lam / s.X, s.lam / s.Y, na,
-                                                   precision == SCW_FP64, st);
-                         });
+  return synthesize_with(ctx, sol, grid, precision, E_dev, I_dev, hip_stream, na, nullptr);
 }
 
 int scw_synthesize_filtered(scw_ctx* ctx, scw_solution* sol, const scw_grid* grid, int precision,
                             const void* H_dev, void* E_dev, void* I_dev, void* hip_stream) {
   if (!H_dev) return fail(SCW_EINVAL, "null transfer function");
-  return synthesize_with(ctx, sol, grid, precision, E_dev, I_dev, hip_stream,
-                         [&](Solution& s, Plan& pl, hipStream_t st) {
-                           return launch_transfer(pl.d_spec.p,
-                                                  (long long)grid->fz * 3 * s.M, s.M, H_dev,
-                                                  precision == SCW_FP64, st);
-                         });
+  return synthesize_with(ctx, sol, grid, precision, E_dev, I_dev, hip_stream, 0.0, H_dev);
 }
 
 int scw_synthesis_configure(scw_solution* sol, const scw_synth_config* cfg) {

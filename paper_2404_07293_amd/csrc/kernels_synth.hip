@@ -521,10 +521,12 @@ modal_multi_kernel(
 template <typename T>
 __global__ void exterior_kernel(const ExtPlane* __restrict__ ext, int n_ext, int M,
                                 const zd* __restrict__ coef, const zd* __restrict__ ksz,
-                                cx<T>* __restrict__ spec) {
+                                long long spec_stride, cx<T>* __restrict__ spec) {
   const int n3 = 3 * M;
   long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= (long long)n_ext * n3) return;
+  coef += (long long)blockIdx.y * 3 * n3;  // one volume (illumination) per blockIdx.y
+  spec += blockIdx.y * spec_stride;
   const int r = (int)(t % n3);
   const ExtPlane e = ext[t / n3];
   const int m = r % M;
@@ -965,15 +967,19 @@ hipError_t launch_synthesis(const SynthArgs& a, hipStream_t s, hipEvent_t* ev) {
   }
   if ((e = mark(2)) != hipSuccess) return e;
   if (a.n_ext > 0 && (a.stages & kStageExterior)) {
-    exterior_kernel<T><<<blocks_for((long long)a.n_ext * 3 * a.M, 256), 256, 0, s>>>(
+    exterior_kernel<T><<<dim3(blocks_for((long long)a.n_ext * 3 * a.M, 256), a.nvol), 256, 0,
+                         s>>>(
         reinterpret_cast<const ExtPlane*>(a.ext_planes), a.n_ext, a.M,
         reinterpret_cast<const zd*>(a.ext), reinterpret_cast<const zd*>(a.ksz),
+        (long long)a.fz * 3 * a.M,
         reinterpret_cast<cx<T>*>(a.spec));
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   if ((e = mark(3)) != hipSuccess) return e;
   if (!(a.stages & kStageTransform)) {
     // transform not requested
+  } else if (a.pair_tab) {
+    if ((e = launch_idft_pair(a, s)) != hipSuccess) return e;
   } else if (a.fft_p > 0) {
     if ((e = launch_idft_fft<T>(a, s)) != hipSuccess) return e;
   } else if (sizeof(T) == 4 && a.mfma) {

@@ -138,6 +138,28 @@ __device__ double2 dev_twiddle(long long idx, int n) {
   return make_double2(cs, sn);
 }
 
+// The pair transform's tables (pair_layout), as build_plan makes them.
+template <typename T>
+__global__ void noalloc_pair_kernel(PairLayout l, int fx, int fy, int U, int V,
+                                    T* __restrict__ tab) {
+  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= l.size) return;
+  const int ex = 1 - fx % 2, ey = 1 - fy % 2;
+  double2 w = make_double2(0.0, 0.0);
+  if (i < l.xph) {
+    w = dev_twiddle((i / l.npx + 1) * (2 * (i % l.npx) + ex), 2 * fx);
+  } else if (i < l.yw) {
+    w = dev_twiddle((i - l.xph) * (fx - 1), 2 * fx);
+  } else if (i < l.yph) {
+    const long long p = (i - l.yw) / l.hv, v = (i - l.yw) % l.hv + 1;
+    if (v <= V / 2) w = dev_twiddle(v * (2 * p + ey), 2 * fy);
+  } else {
+    w = dev_twiddle((i - l.yph - V / 2) * (fy - 1), 2 * fy);
+  }
+  tab[2 * i] = (T)w.x;
+  tab[2 * i + 1] = (T)w.y;
+}
+
 // twx [2][fx], twy [2][fy] and, when R > 0, the factored transform's [R][32].
 template <typename T>
 __global__ void noalloc_twiddles_kernel(int fx, int fy, int U, int V, int R, T* __restrict__ twx,
@@ -215,23 +237,40 @@ extern "C" int scw_synthesize_noalloc(scw_ctx* ctx, scw_solution* sol, const scw
   }
   const size_t eb = precision == SCW_FP64 ? 16 : 8;
   const size_t n2 = 2 * (size_t)s.M;
-  const int R = ks.fft_p > 0 ? g.fy / ks.fft_p : 0;
+  PairLayout lay{};
+  int R = 0;
+  size_t off, o_first, o_count, o_tasks, o_dz, o_dz32, o_ext, o_w, o_spec, o_twx, o_twy, o_fft,
+      o_pair;
   // layout of the scratch array, every region 256-byte aligned
-  size_t off = 0;
-  auto take = [&](size_t bytes) {
-    const size_t o = off;
-    off += align256(std::max<size_t>(bytes, 16));
-    return o;
+  auto plan_scratch = [&]() {
+    off = 0;
+    auto take = [&](size_t bytes) {
+      const size_t o = off;
+      off += align256(std::max<size_t>(bytes, 16));
+      return o;
+    };
+    R = ks.fft_p > 0 ? g.fy / ks.fft_p : 0;
+    lay = ks.pair ? pair_layout(s.U, s.V, g.fx, g.fy) : PairLayout{};
+    o_first = take((size_t)s.L * 4);
+    o_count = take((size_t)s.L * 4);
+    o_tasks = take((size_t)pg.ntasks * sizeof(Task));
+    o_dz = take((size_t)pg.ntasks * pg.zt * 2 * sizeof(double));
+    o_dz32 = take((size_t)pg.ntasks * pg.zt * 2 * sizeof(float));
+    o_ext = take((size_t)pg.n_ext * sizeof(ExtPlane));
+    o_w = take(precision == SCW_FP64 ? (size_t)pg.ntasks * 2 * pg.zt * n2 * eb : 0);
+    o_spec = take((size_t)g.fz * 3 * s.M * eb);
+    o_twx = take(2 * (size_t)g.fx * eb);
+    o_twy = take(2 * (size_t)g.fy * eb);
+    o_fft = take(32 * (size_t)R * eb);
+    o_pair = take((size_t)lay.size * eb);
   };
-  const size_t o_first = take((size_t)s.L * 4), o_count = take((size_t)s.L * 4);
-  const size_t o_tasks = take((size_t)pg.ntasks * sizeof(Task));
-  const size_t o_dz = take((size_t)pg.ntasks * pg.zt * 2 * sizeof(double));
-  const size_t o_dz32 = take((size_t)pg.ntasks * pg.zt * 2 * sizeof(float));
-  const size_t o_ext = take((size_t)pg.n_ext * sizeof(ExtPlane));
-  const size_t o_w = take(precision == SCW_FP64 ? (size_t)pg.ntasks * 2 * pg.zt * n2 * eb : 0);
-  const size_t o_spec = take((size_t)g.fz * 3 * s.M * eb);
-  const size_t o_twx = take(2 * (size_t)g.fx * eb), o_twy = take(2 * (size_t)g.fy * eb);
-  const size_t o_fft = take(32 * (size_t)R * eb);
+  plan_scratch();
+  if (off > SCW_NOALLOC_SCRATCH_BYTES && ks.pair) {  // the other transforms' tables are smaller
+    cfg.transform = ks.fft_ok ? SCW_XFORM_FFT : SCW_XFORM_DIRECT;
+    cfg.tiles = 0;
+    if ((rc = choose_shape(s, g, precision, cfg, pg.zt, &ks))) return rc;
+    plan_scratch();
+  }
   if (off > SCW_NOALLOC_SCRATCH_BYTES)
     return fail(SCW_EINVAL, "allocation-free synthesis needs " + std::to_string(off) +
                                 " bytes of scratch, above its limit of " +
@@ -257,6 +296,16 @@ extern "C" int scw_synthesize_noalloc(scw_ctx* ctx, scw_solution* sol, const scw
         g.fx, g.fy, s.U, s.V, R, reinterpret_cast<float*>(b + o_twx),
         reinterpret_cast<float*>(b + o_twy), reinterpret_cast<float*>(b + o_fft));
   SCW_HIP(hipGetLastError());
+  if (ks.pair) {
+    const unsigned nb = (unsigned)((lay.size + 255) / 256);
+    if (precision == SCW_FP64)
+      noalloc_pair_kernel<double><<<nb, 256, 0, st>>>(lay, g.fx, g.fy, s.U, s.V,
+                                                      reinterpret_cast<double*>(b + o_pair));
+    else
+      noalloc_pair_kernel<float><<<nb, 256, 0, st>>>(lay, g.fx, g.fy, s.U, s.V,
+                                                     reinterpret_cast<float*>(b + o_pair));
+    SCW_HIP(hipGetLastError());
+  }
   SynthArgs a{};
   a.M = s.M;
   a.U = s.U;
@@ -292,6 +341,8 @@ extern "C" int scw_synthesize_noalloc(scw_ctx* ctx, scw_solution* sol, const scw
   a.idft_gtiles = ks.tiles;
   a.modal_rw = ks.modal_rw;
   a.stages = kStageAll;
+  a.pair_tab = ks.pair ? b + o_pair : nullptr;
+  a.nvol = 1;
   SCW_HIP(precision == SCW_FP64 ? launch_synthesis_fp64(a, st, nullptr)
                                 : launch_synthesis_fp32(a, st, nullptr));
   return SCW_OK;

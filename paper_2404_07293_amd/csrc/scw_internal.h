@@ -104,13 +104,16 @@ struct Plan {
   int kp = 0;                       // padded K of the y-pass GEMM
   int fft_p = 0;                    // factored y pass (fy = R * P) when > 0
   DevBuf d_fft_tw;                  // its twiddles
+  bool pair = false;                // transform by conjugate pairs
   bool mfma = false;                // inverse transform on the matrix cores
   int modal_rw = 0;                 // rows per wave of the FP32 modal sum
   int tiles = 0;                    // DIRECT row tiles / MFMA plane-components per block
   scw_synth_config cfg{};           // the configuration the plan was built for
   bool direct_only = false;         // built for the direct-sum transform (slices)
-  DevBuf d_twx;                     // [2][fx] complex<T>: e^{2 pi i f/fx}, e^{-2 pi i (U/2) f/fx}
-  DevBuf d_twy;                     // [2][fy] complex<T>: same for g, V
+  DevBuf d_tw;                      // the transform's factors, complex<T>:
+  const void* twx = nullptr;        //   [2][fx]: e^{2 pi i f/fx}, e^{-2 pi i (U/2) f/fx}
+  const void* twy = nullptr;        //   [2][fy]: same for g, V
+  const void* pair_tab = nullptr;   //   pair_layout (pair)
   DevBuf d_spec_multi;              // [K][fz][3M] complex64: spectra of every illumination
   DevBuf d_wmulti;                  // phase table of one illumination group
   DevBuf d_tile;                    // [3][fz][fy][fx]: one period, for tiled / composed fields
@@ -204,6 +207,7 @@ scw_synth_config resolve_config(const Context& ctx, const Solution& s, const scw
 struct KernelShape {
   int modal_rw, kind, fft_p, tiles;
   bool fft_ok;
+  bool pair;  // DIRECT by conjugate pairs (the automatic choice where it fits)
 };
 int choose_shape(const Solution& s, const scw_grid& g, int precision,
                  const scw_synth_config& cfg, int zt, KernelShape* out);
@@ -354,7 +358,22 @@ struct SynthArgs {
   void* bmat;
   float* bscale;
   const void* amat;
+  const void* pair_tab;    // not null: transform by conjugate pairs, with these tables
+  int nvol;                // volumes (illuminations) of spec, E and ext, one after another
+  void* I;                 // pair transform, FP32: intensity [fz][fy][fx], or null
+  int objective;           // pair transform: remove the modes with sx^2 + sy^2 > na2
+  double sx_step, sy_step, na2;
 };
+
+// Tables of the transform by conjugate pairs (kernels_transform.hip): offsets
+// in complex values and their total.
+struct PairLayout {
+  int hv, npx, npy;
+  long long xph, yw, yph, size;
+};
+PairLayout pair_layout(int U, int V, int fx, int fy);
+bool pair_transform_fits(int U, int V, bool fp64, int components);
+hipError_t launch_idft_pair(const SynthArgs& a, hipStream_t s);
 
 struct MfmaArgs {
   int U, V, fx, fy, fz, Kp;

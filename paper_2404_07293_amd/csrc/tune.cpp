@@ -151,6 +151,7 @@ int tune_synthesis(Context& c, Solution& s, const scw_grid& g, int precision, vo
     if (rc) return bail(rc);
     const bool split = precision == SCW_BF16X3 || precision == SCW_FP16X3;
     std::vector<scw_synth_config> cands;
+    if (!split) cands.push_back({best.modal_rows, SCW_XFORM_AUTO, 0, 0});
     if (!split)
       for (int P = 2; P <= 32; P *= 2)
         for (int cols : {64, 32}) cands.push_back({best.modal_rows, SCW_XFORM_FFT, P, cols});
@@ -200,7 +201,9 @@ int tune_synthesis(Context& c, Solution& s, const scw_grid& g, int precision, vo
     rep->best_ms = best_ms;
     const Plan& pl = *chosen;
     rep->config.modal_rows = precision == SCW_FP64 ? 0 : pl.modal_rw;
-    rep->config.transform = pl.fft_p ? SCW_XFORM_FFT : (pl.mfma ? SCW_XFORM_MFMA : SCW_XFORM_DIRECT);
+    rep->config.transform = pl.pair ? SCW_XFORM_AUTO
+                            : pl.fft_p ? SCW_XFORM_FFT
+                            : pl.mfma ? SCW_XFORM_MFMA : SCW_XFORM_DIRECT;
     rep->config.fft_radix = pl.fft_p;
     rep->config.tiles = pl.tiles;
   }
