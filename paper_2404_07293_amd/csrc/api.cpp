@@ -196,7 +196,7 @@ PlaneGroups plane_group_shape(const scw_grid& g, int L, double d) {
 }
 
 int choose_shape(const Solution& s, const scw_grid& g, int precision,
-                 const scw_synth_config& cfg, int zt, KernelShape* out) {
+                 const scw_synth_config& cfg, int zt, int ntasks, KernelShape* out) {
   const bool split = precision == SCW_BF16X3 || precision == SCW_FP16X3;
   if (cfg.transform < SCW_XFORM_AUTO || cfg.transform > SCW_XFORM_DIRECT)
     return fail(SCW_EINVAL, "unknown transform kind " + std::to_string(cfg.transform));
@@ -206,6 +206,13 @@ int choose_shape(const Solution& s, const scw_grid& g, int precision,
   // FP32 modal sum: rows per wave, so that rows x planes stays <= 32
   int rw = cfg.modal_rows ? cfg.modal_rows : (zt >= 8 ? 4 : (zt == 4 ? 8 : 16));
   while (rw > 2 && rw * zt > 32) rw /= 2;
+  // blocks of fewer rows (each makes its own phases) while there are less than
+  // two per CU: 16 tasks at M = 225 take 10.3 us with 4 rows per wave, 704
+  // blocks, against 11.4 with 8, 368 blocks (and 11.3 with 2)
+  auto blocks = [&](int r) {
+    return (long long)ntasks * ((2 * s.M + 4 * r - 1) / (4 * r) + (s.M + 4 * r - 1) / (4 * r));
+  };
+  while (!cfg.modal_rows && rw > 4 && blocks(rw) < 512) rw /= 2;
   out->modal_rw = rw;
   out->tiles = cfg.tiles;
   // factored y pass: fy = R * P, P <= 32 a power of two, spectra V <= 32 rows
@@ -303,7 +310,7 @@ int build_plan(Solution& s, Plan& pl, const scw_grid& g, int precision,
   // kernel configuration: explicit, tuned, or the built-in default
   pl.cfg = cfg;
   KernelShape ks;
-  if ((rc = choose_shape(s, g, precision, cfg, pl.zt, &ks))) return rc;
+  if ((rc = choose_shape(s, g, precision, cfg, pl.zt, (int)pl.tasks.size(), &ks))) return rc;
   pl.modal_rw = ks.modal_rw;
   pl.tiles = ks.tiles;
   const int kind = ks.kind, P = ks.fft_p;

@@ -157,6 +157,10 @@ __global__ void __launch_bounds__(256) modal_kernel(
 // read P two complex at a time (16-byte loads); every lane accumulates
 // RW rows x ZT planes, and a recursive-halving butterfly leaves the complete
 // sum of value index i in lane i (NV = 2 RW ZT values, NV - 1 shuffles).
+// Bound by the read of P where there are many layers: 300 MB (32 layers, M = 441)
+// take 52.6 us (5.7 TB/s; a plain read of them 43.4), 56 with the loads one step
+// ahead and begun after the phases; by its prologue (phases, first loads) where
+// there are few: 39 MB (16 layers, M = 225) take 10.3 us, 12.5 before.
 template <int N>
 __device__ __forceinline__ void halve(float* v, int lane) {
   if constexpr (N > 1) {
@@ -205,95 +209,130 @@ __global__ void __launch_bounds__(256) modal_f32_kernel(
   const int rows_per_block = 4 * RW;
   const int row_begin = zrows ? n2 + (rb - nb_xy) * rows_per_block : rb * rows_per_block;
   const int row_end = zrows ? n3 : n2;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int r0 = row_begin + wave * RW;
   const float4* Pl = P + (long long)tk.layer * n3 * h2;
   const float2* kg = kgab + (long long)tk.layer * n2;
   const float2* av = kgab + ((long long)L + tk.layer) * n2;
   const float2* bv = kgab + (2LL * L + tk.layer) * n2;
   const float sgn = zrows ? -1.f : 1.f;
-  const float4* prow[RW];
+  const char* prow[RW];  // wave-uniform: loads take a scalar base and a 32-bit offset
 #pragma unroll
-  for (int r = 0; r < RW; ++r) prow[r] = Pl + (long long)min(r0 + r, row_end - 1) * h2;
+  for (int r = 0; r < RW; ++r)
+    prow[r] = reinterpret_cast<const char*>(Pl + (long long)min(r0 + r, row_end - 1) * h2);
   float2 dzp[ZT];
 #pragma unroll
   for (int p = 0; p < ZT; ++p) dzp[p] = tdz[task * ZT + p];
-
-  float acc[NV];
-#pragma unroll
-  for (int i = 0; i < NV; ++i) acc[i] = 0.f;
 
   // The phase table holds jq float4 per plane, jq = jc / 2 rounded up to a
   // multiple of 64, with zeros past the chunk. Every lane then runs the same
   // ceil(qn / 64) steps: a lane past the chunk reads a valid element of its
   // row (the index clamped to the row) and adds its product with a zero
-  // weight, which leaves its sums unchanged. Each step first issues its RW
-  // loads for the next step unconditionally, into the other of two register
-  // sets, so the wait before its products leaves those loads in flight.
+  // weight, which leaves its sums unchanged. The loads run two steps ahead, in
+  // two register sets: both are filled before the phases are computed, and a
+  // step loads its successor's successor into each row's registers as soon as
+  // that row's products are done. Loads return in order, so those of the first
+  // phases go out before the rows', and the rows' in the order of their use
+  // (the barriers of the scheduler keep both).
   const int jq = (jc / 2 + 63) / 64 * 64;
+  constexpr int KG = 4;  // phase arguments loaded ahead: the first 1024
+  float2 kgr[KG], avr[KG], bvr[KG];
+#pragma unroll
+  for (int k = 0; k < KG; ++k) {
+    const int j = min((int)threadIdx.x + 256 * k, n2 - 1);
+    kgr[k] = kg[j];
+    avr[k] = av[j];
+    bvr[k] = bv[j];
+  }
+  auto phases = [&](int jj, int jn, float2 g, float2 a, float2 b) {
+    if (jj < jn) {
+#pragma unroll
+      for (int p = 0; p < ZT; ++p) {
+        const float2 gf = cexpi_f(g.x * dzp[p].x, g.y * dzp[p].x);
+        const float2 gb = cexpi_f(-g.x * dzp[p].y, -g.y * dzp[p].y);
+        const float fx = a.x * gf.x - a.y * gf.y, fy = a.x * gf.y + a.y * gf.x;
+        const float bx = b.x * gb.x - b.y * gb.y, by = b.x * gb.y + b.y * gb.x;
+        sw[p * 2 * jq + jj] = make_float2(fx + sgn * bx, fy + sgn * by);
+      }
+    } else if (jj < 2 * jq) {
+#pragma unroll
+      for (int p = 0; p < ZT; ++p) sw[p * 2 * jq + jj] = make_float2(0.f, 0.f);
+    }
+  };
+  auto load = [&](int r, int q) {
+    return *reinterpret_cast<const float4*>(prow[r] + 16u * (unsigned)min(q, h2 - 1));
+  };
+  __builtin_amdgcn_sched_barrier(0);
   float4 pa[RW], pb[RW];
 #pragma unroll
-  for (int r = 0; r < RW; ++r) pa[r] = prow[r][min(lane, h2 - 1)];
-  auto step = [&](const float4 (&cur)[RW], float4 (&nxt)[RW], int q, int qg) {
-#pragma unroll
-    for (int r = 0; r < RW; ++r) nxt[r] = prow[r][qg];
-    // keep the loads ahead of this step's products (the scheduler would
-    // otherwise sink them to the end of the step)
+  for (int r = 0; r < RW; ++r) {
+    pa[r] = load(r, lane);
     __builtin_amdgcn_sched_barrier(0);
+  }
 #pragma unroll
-    for (int p = 0; p < ZT; ++p) {
-      const float4 w = sw4[p * jq + q];
+  for (int r = 0; r < RW; ++r) {
+    pb[r] = load(r, lane + 64);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  auto more_phases = [&](int j0, int jn, int from) {
+    for (int jj = threadIdx.x + from; jj < 2 * jq; jj += 256) {
+      const int j = min(j0 + jj, n2 - 1);
+      phases(jj, jn, kg[j], av[j], bv[j]);
+    }
+  };
 #pragma unroll
-      for (int r = 0; r < RW; ++r) {
+  for (int k = 0; k < KG; ++k)  // a use here: the loads above stay above
+    asm volatile("" : "+v"(kgr[k].x), "+v"(kgr[k].y), "+v"(avr[k].x), "+v"(avr[k].y),
+                      "+v"(bvr[k].x), "+v"(bvr[k].y));
+#pragma unroll
+  for (int k = 0; k < KG; ++k)
+    phases(threadIdx.x + 256 * k, min(jc, n2), kgr[k], avr[k], bvr[k]);
+  more_phases(0, min(jc, n2), 256 * KG);
+  float acc[NV];
+#pragma unroll
+  for (int i = 0; i < NV; ++i) acc[i] = 0.f;
+  auto step = [&](float4 (&cur)[RW], int q, int qg) {
+    float4 w[ZT];
+#pragma unroll
+    for (int p = 0; p < ZT; ++p) w[p] = sw4[p * jq + q];
+#pragma unroll
+    for (int r = 0; r < RW; ++r) {
+#pragma unroll
+      for (int p = 0; p < ZT; ++p) {
         float& re = acc[(r * ZT + p) * 2];
         float& im = acc[(r * ZT + p) * 2 + 1];
-        re = fmaf(cur[r].x, w.x, re);
-        re = fmaf(-cur[r].y, w.y, re);
-        im = fmaf(cur[r].x, w.y, im);
-        im = fmaf(cur[r].y, w.x, im);
-        re = fmaf(cur[r].z, w.z, re);
-        re = fmaf(-cur[r].w, w.w, re);
-        im = fmaf(cur[r].z, w.w, im);
-        im = fmaf(cur[r].w, w.z, im);
+        re = fmaf(cur[r].x, w[p].x, re);
+        re = fmaf(-cur[r].y, w[p].y, re);
+        im = fmaf(cur[r].x, w[p].y, im);
+        im = fmaf(cur[r].y, w[p].x, im);
+        re = fmaf(cur[r].z, w[p].z, re);
+        re = fmaf(-cur[r].w, w[p].w, re);
+        im = fmaf(cur[r].z, w[p].w, im);
+        im = fmaf(cur[r].w, w[p].z, im);
       }
+      cur[r] = load(r, qg);
+      // keep the load here (the scheduler would otherwise sink it)
+      __builtin_amdgcn_sched_barrier(0);
     }
   };
   for (int j0 = 0; j0 < n2; j0 += jc) {
     const int jn = min(jc, n2 - j0);
-    __syncthreads();
-    for (int jj = threadIdx.x; jj < 2 * jq; jj += 256) {
-      if (jj < jn) {
-        const float2 g = kg[j0 + jj], a = av[j0 + jj], b = bv[j0 + jj];
-#pragma unroll
-        for (int p = 0; p < ZT; ++p) {
-          const float2 gf = cexpi_f(g.x * dzp[p].x, g.y * dzp[p].x);
-          const float2 gb = cexpi_f(-g.x * dzp[p].y, -g.y * dzp[p].y);
-          const float fx = a.x * gf.x - a.y * gf.y, fy = a.x * gf.y + a.y * gf.x;
-          const float bx = b.x * gb.x - b.y * gb.y, by = b.x * gb.y + b.y * gb.x;
-          sw[p * 2 * jq + jj] = make_float2(fx + sgn * bx, fy + sgn * by);
-        }
-      } else {
-#pragma unroll
-        for (int p = 0; p < ZT; ++p) sw[p * 2 * jq + jj] = make_float2(0.f, 0.f);
-      }
+    if (j0 > 0) {
+      __syncthreads();
+      more_phases(j0, jn, 0);
     }
     __syncthreads();
-    // step i covers q = lane + 64 i of the chunk and loads element q + 64 of
-    // the rows: the next step's, or for the last step the first of the next
-    // chunk (chunks before the last hold a multiple of 64 float4)
+    // step i covers q = lane + 64 i of the chunk and loads element q + 128 of
+    // the rows, which may belong to the next chunk: a chunk before the last has
+    // jc / 128 steps, an even number, so the sets keep their turns
     const int q0 = j0 / 2, ns = (jn / 2 + 63) / 64;
     int i = 0;
     for (; i + 2 <= ns; i += 2) {
       const int q = lane + 64 * i;
-      step(pa, pb, q, min(q0 + q + 64, h2 - 1));
-      step(pb, pa, q + 64, min(q0 + q + 128, h2 - 1));
+      step(pa, q, q0 + q + 128);
+      step(pb, q + 64, q0 + q + 192);
     }
-    if (i < ns) {
-      const int q = lane + 64 * i;
-      step(pa, pb, q, min(q0 + q + 64, h2 - 1));
-#pragma unroll
-      for (int r = 0; r < RW; ++r) pa[r] = pb[r];
-    }
+    if (i < ns) step(pa, lane + 64 * i, h2 - 1);
   }
   halve<NV>(acc, lane);
 #pragma unroll

@@ -229,11 +229,11 @@ extern "C" int scw_synthesize_noalloc(scw_ctx* ctx, scw_solution* sol, const scw
   const PlaneGroups pg = plane_group_shape(g, s.L, s.d);
   scw_synth_config cfg = resolve_config(c, s, g, precision);
   KernelShape ks{};
-  if ((rc = choose_shape(s, g, precision, cfg, pg.zt, &ks))) return rc;
+  if ((rc = choose_shape(s, g, precision, cfg, pg.zt, pg.ntasks, &ks))) return rc;
   if (ks.kind == SCW_XFORM_MFMA) {  // its operands are host-built: factored or direct instead
     cfg.transform = ks.fft_ok ? SCW_XFORM_FFT : SCW_XFORM_DIRECT;
     cfg.tiles = 0;
-    if ((rc = choose_shape(s, g, precision, cfg, pg.zt, &ks))) return rc;
+    if ((rc = choose_shape(s, g, precision, cfg, pg.zt, pg.ntasks, &ks))) return rc;
   }
   const size_t eb = precision == SCW_FP64 ? 16 : 8;
   const size_t n2 = 2 * (size_t)s.M;
@@ -268,7 +268,7 @@ extern "C" int scw_synthesize_noalloc(scw_ctx* ctx, scw_solution* sol, const scw
   if (off > SCW_NOALLOC_SCRATCH_BYTES && ks.pair) {  // the other transforms' tables are smaller
     cfg.transform = ks.fft_ok ? SCW_XFORM_FFT : SCW_XFORM_DIRECT;
     cfg.tiles = 0;
-    if ((rc = choose_shape(s, g, precision, cfg, pg.zt, &ks))) return rc;
+    if ((rc = choose_shape(s, g, precision, cfg, pg.zt, pg.ntasks, &ks))) return rc;
     plan_scratch();
   }
   if (off > SCW_NOALLOC_SCRATCH_BYTES)

@@ -210,7 +210,7 @@ struct KernelShape {
   bool pair;  // DIRECT by conjugate pairs (the automatic choice where it fits)
 };
 int choose_shape(const Solution& s, const scw_grid& g, int precision,
-                 const scw_synth_config& cfg, int zt, KernelShape* out);
+                 const scw_synth_config& cfg, int zt, int ntasks, KernelShape* out);
 // SCW_OK for a grid every synthesis accepts, else SCW_EINVAL with a message.
 int check_grid(const scw_grid* g);
 // Allocation-free synthesis: attach the device's static scratch array (once
