@@ -234,6 +234,36 @@ int backward(SurNet& n, int B, hipStream_t s) {
   return SCW_OK;
 }
 
+// Standard normal values by Marsaglia's polar method. The values, to the bit, of
+// std::normal_distribution<double> over std::mt19937_64, which spends two extended
+// logarithms per uniform on the generator's range: 1.2 million take 18 ms, not 87.
+struct Normal {
+  std::mt19937_64 rng;
+  double saved = 0.0;
+  bool has = false;
+  explicit Normal(unsigned long long seed) : rng(seed) {}
+  double uniform() {  // [0, 1)
+    const double r = (double)rng() * 0x1p-64;
+    return r < 1.0 ? r : std::nextafter(1.0, 0.0);
+  }
+  double operator()() {
+    if (has) {
+      has = false;
+      return saved;
+    }
+    double x, y, r2;
+    do {
+      x = 2.0 * uniform() - 1.0;
+      y = 2.0 * uniform() - 1.0;
+      r2 = x * x + y * y;
+    } while (r2 > 1.0 || r2 == 0.0);
+    const double m = std::sqrt(-2.0 * std::log(r2) / r2);
+    saved = x * m;
+    has = true;
+    return y * m;
+  }
+};
+
 int check_batch(const SurNet& n, int B) {
   if (B < 1 || B > n.max_batch)
     return fail(SCW_EINVAL, "surrogate batch must be in [1, " + std::to_string(n.max_batch) + "]");
@@ -273,11 +303,10 @@ int sur_create(Context& ctx, int max_batch, unsigned long long seed, SurNet** ou
   // initial weights: N(0, 1/fan_in) for real maps, complex with the same total
   // variance (spectral mixing scaled down by 4), zero biases
   std::vector<float> p(N_PARAMS, 0.f);
-  std::mt19937_64 rng(seed);
-  std::normal_distribution<double> nd(0.0, 1.0);
+  Normal nd(seed);
   const Off o;
   auto fill = [&](long long off, long long cnt, double sd) {
-    for (long long i = 0; i < cnt; ++i) p[off + i] = (float)(sd * nd(rng));
+    for (long long i = 0; i < cnt; ++i) p[off + i] = (float)(sd * nd());
   };
   fill(o.lw, SZ_LW, 1.0 / std::sqrt((double)CIN));
   for (int k = 0; k < NL; ++k) {
