@@ -45,43 +45,68 @@ __device__ __forceinline__ zd zmul(zd a, zd b) {
 }
 
 // ---------------------------------------------------------------- phase
+// f = a g_f(z_p) and bk = b g_b(z_p) of plane p of a task.
+__device__ __forceinline__ void phase_pair(zd g, zd a, zd b, const double* __restrict__ dzp, zd& f,
+                                           zd& bk) {
+  const zd gf = zexp_i({g.x * dzp[0], g.y * dzp[0]});
+  const zd gb = zexp_i({-g.x * dzp[1], -g.y * dzp[1]});
+  f = zmul(a, gf);
+  bk = zmul(b, gb);
+}
+
+// One thread per (task, plane, column): the exponentials of a plane are a chain
+// of some 300 dependent operations, so planes go side by side.
 template <typename T>
 __global__ void phase_kernel(const Task* __restrict__ tasks, const double* __restrict__ dz,
                              const zd* __restrict__ kg, const zd* __restrict__ a,
                              const zd* __restrict__ b, int n2, int zt, int ntasks,
                              cx<T>* __restrict__ w) {
-  long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= (long long)ntasks * n2) return;
-  const int j = (int)(t % n2);
-  const int task = (int)(t / n2);
+  const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+  if (t >= (long long)ntasks * zt * n2) return;
+  const int j = (int)(t % n2), p = (int)(t / n2 % zt), task = (int)(t / n2 / zt);
   const Task tk = tasks[task];
-  const long long lj = (long long)tk.layer * n2 + j;
-  const zd g = kg[lj], aj = a[lj], bj = b[lj];
-  for (int p = 0; p < zt; ++p) {
-    cx<T> wp = {0, 0}, wm = {0, 0};
-    if (p < tk.count) {
-      const double dt = dz[((long long)task * zt + p) * 2 + 0];
-      const double db = dz[((long long)task * zt + p) * 2 + 1];
-      const zd gf = zexp_i({g.x * dt, g.y * dt});
-      const zd gb = zexp_i({-g.x * db, -g.y * db});
-      const zd f = zmul(aj, gf), bk = zmul(bj, gb);
-      wp = {(T)(f.x + bk.x), (T)(f.y + bk.y)};
-      wm = {(T)(f.x - bk.x), (T)(f.y - bk.y)};
-    }
-    w[(((long long)task * 2 + 0) * zt + p) * n2 + j] = wp;
-    w[(((long long)task * 2 + 1) * zt + p) * n2 + j] = wm;
+  cx<T> wp = {0, 0}, wm = {0, 0};
+  if (p < tk.count) {
+    const long long lj = (long long)tk.layer * n2 + j;
+    zd f, bk;
+    phase_pair(kg[lj], a[lj], b[lj], dz + ((long long)task * zt + p) * 2, f, bk);
+    wp = {(T)(f.x + bk.x), (T)(f.y + bk.y)};
+    wm = {(T)(f.x - bk.x), (T)(f.y - bk.y)};
   }
+  w[(((long long)task * 2 + 0) * zt + p) * n2 + j] = wp;
+  w[(((long long)task * 2 + 1) * zt + p) * n2 + j] = wm;
 }
 
 // ---------------------------------------------------------------- modal sum
+// Sums over the lanes by recursive halving: v[i] of every lane summed in lane i
+// (N - 1 shuffles for N values).
+template <int N, typename T>
+__device__ __forceinline__ void halve(T* v, int lane) {
+  if constexpr (N > 1) {
+    constexpr int H = N / 2;
+    const bool up = (lane & H) != 0;
+#pragma unroll
+    for (int i = 0; i < H; ++i) {
+      const T send = up ? v[i] : v[i + H];
+      const T keep = up ? v[i + H] : v[i];
+      v[i] = keep + __shfl_xor(send, H, 64);
+    }
+    halve<H>(v, lane);
+  }
+}
+
 // One block = 4 waves; each wave owns RW consecutive rows of one category
 // (x/y rows or z rows) of one task. The task's W table for that category is
-// staged in LDS in chunks of jc columns; lanes stride over j, every lane keeps
-// RW x ZT partial sums, and a butterfly reduction finishes each row.
-template <typename T, int ZT, int RW>
+// staged in LDS in chunks of jc columns (PH: computed there); lanes stride over
+// j, every lane keeps RW x ZT partial sums, and halving over the lanes finishes
+// them.
+template <typename T, int ZT, int RW, bool PH>
 __global__ void __launch_bounds__(256) modal_kernel(
-    const cx<T>* __restrict__ P, const cx<T>* __restrict__ w, const Task* __restrict__ tasks,
-    int M, int nb_xy, int nb_z, int jc, cx<T>* __restrict__ spec) {
+    const cx<T>* __restrict__ P, const cx<T>* __restrict__ w, const zd* __restrict__ kg,
+    const zd* __restrict__ a, const zd* __restrict__ b, const double* __restrict__ dz,
+    const Task* __restrict__ tasks, int M, int nb_xy, int nb_z, int jc, cx<T>* __restrict__ spec) {
+  constexpr int NV = 2 * RW * ZT;
+  static_assert(NV <= 64 && (NV & (NV - 1)) == 0, "value count must be a power of two <= 64");
   extern __shared__ unsigned char smem_raw[];
   cx<T>* sw = reinterpret_cast<cx<T>*>(smem_raw);  // [ZT][jc]
   const int n2 = 2 * M, n3 = 3 * M;
@@ -96,58 +121,70 @@ __global__ void __launch_bounds__(256) modal_kernel(
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int r0 = row_begin + wave * RW;
   const cx<T>* Pl = P + (long long)tk.layer * n3 * n2;
-  const cx<T>* wt = w + ((long long)task * 2 + sign) * ZT * n2;
+  const cx<T>* wt = PH ? nullptr : w + ((long long)task * 2 + sign) * ZT * n2;
 
-  cx<T> acc[RW][ZT];
+  T acc[NV];  // [r][p][re, im]
 #pragma unroll
-  for (int r = 0; r < RW; ++r)
+  for (int i = 0; i < NV; ++i) acc[i] = 0;
+
+  // rows one step ahead, the first step's while the table is filled (indices
+  // past the last row or column are clamped; their sums are not used)
+  const cx<T>* prow[RW];
 #pragma unroll
-    for (int p = 0; p < ZT; ++p) acc[r][p] = {0, 0};
+  for (int r = 0; r < RW; ++r) prow[r] = Pl + (long long)min(r0 + r, row_end - 1) * n2;
+  cx<T> nxt[RW];
+#pragma unroll
+  for (int r = 0; r < RW; ++r) nxt[r] = prow[r][min(lane, n2 - 1)];
 
   for (int j0 = 0; j0 < n2; j0 += jc) {
     const int jn = min(jc, n2 - j0);
-    __syncthreads();
+    if (j0 > 0) __syncthreads();
     for (int i = threadIdx.x; i < ZT * jn; i += blockDim.x) {
       const int p = i / jn, jj = i % jn;
-      sw[p * jc + jj] = wt[(long long)p * n2 + j0 + jj];
+      if constexpr (PH) {
+        cx<T> v = {0, 0};
+        if (p < tk.count) {
+          const long long lj = (long long)tk.layer * n2 + j0 + jj;
+          zd f, bk;
+          phase_pair(kg[lj], a[lj], b[lj], dz + ((long long)task * ZT + p) * 2, f, bk);
+          v = sign == 0 ? cx<T>{(T)(f.x + bk.x), (T)(f.y + bk.y)}
+                        : cx<T>{(T)(f.x - bk.x), (T)(f.y - bk.y)};
+        }
+        sw[p * jc + jj] = v;
+      } else {
+        sw[p * jc + jj] = wt[(long long)p * n2 + j0 + jj];
+      }
     }
     __syncthreads();
     for (int jj = lane; jj < jn; jj += 64) {
-      cx<T> wv[ZT];
+      // the next step of this chunk, or the first of the next one
+      const int jq = jj + 64 < jn ? j0 + jj + 64 : j0 + jn + lane;
+      cx<T> wv[ZT], cur[RW];
+#pragma unroll
+      for (int r = 0; r < RW; ++r) {
+        cur[r] = nxt[r];
+        nxt[r] = prow[r][min(jq, n2 - 1)];
+      }
 #pragma unroll
       for (int p = 0; p < ZT; ++p) wv[p] = sw[p * jc + jj];
 #pragma unroll
-      for (int r = 0; r < RW; ++r) {
-        const int row = r0 + r;
-        if (row < row_end) {
-          const cx<T> pv = Pl[(long long)row * n2 + j0 + jj];
+      for (int r = 0; r < RW; ++r)
 #pragma unroll
-          for (int p = 0; p < ZT; ++p) cfma(acc[r][p], pv, wv[p]);
+        for (int p = 0; p < ZT; ++p) {
+          cx<T> s = {acc[(r * ZT + p) * 2], acc[(r * ZT + p) * 2 + 1]};
+          cfma(s, cur[r], wv[p]);
+          acc[(r * ZT + p) * 2] = s.x;
+          acc[(r * ZT + p) * 2 + 1] = s.y;
         }
-      }
     }
   }
+  halve<NV>(acc, lane);
 #pragma unroll
-  for (int r = 0; r < RW; ++r)
-#pragma unroll
-    for (int p = 0; p < ZT; ++p) {
-      T x = acc[r][p].x, y = acc[r][p].y;
-#pragma unroll
-      for (int off = 32; off > 0; off >>= 1) {
-        x += __shfl_xor(x, off, 64);
-        y += __shfl_xor(y, off, 64);
-      }
-      acc[r][p] = {x, y};
-    }
-  if (lane == 0) {
-#pragma unroll
-    for (int r = 0; r < RW; ++r) {
-      const int row = r0 + r;
-      if (row >= row_end) continue;
-#pragma unroll
-      for (int p = 0; p < ZT; ++p)
-        if (p < tk.count) spec[(long long)(tk.plane0 + p) * n3 + row] = acc[r][p];
-    }
+  for (int off = NV; off < 64; off <<= 1) acc[0] += __shfl_xor(acc[0], off, 64);
+  if (lane < NV) {
+    const int p = (lane >> 1) % ZT, row = r0 + (lane >> 1) / ZT;
+    if (row < row_end && p < tk.count)
+      reinterpret_cast<T*>(spec)[((long long)(tk.plane0 + p) * n3 + row) * 2 + (lane & 1)] = acc[0];
   }
 }
 
@@ -161,21 +198,6 @@ __global__ void __launch_bounds__(256) modal_kernel(
 // take 52.6 us (5.7 TB/s; a plain read of them 43.4), 56 with the loads one step
 // ahead and begun after the phases; by its prologue (phases, first loads) where
 // there are few: 39 MB (16 layers, M = 225) take 10.3 us, 12.5 before.
-template <int N>
-__device__ __forceinline__ void halve(float* v, int lane) {
-  if constexpr (N > 1) {
-    constexpr int H = N / 2;
-    const bool up = (lane & H) != 0;
-#pragma unroll
-    for (int i = 0; i < H; ++i) {
-      const float send = up ? v[i] : v[i + H];
-      const float keep = up ? v[i + H] : v[i];
-      v[i] = keep + __shfl_xor(send, H, 64);
-    }
-    halve<H>(v, lane);
-  }
-}
-
 // exp(i (re + i im)) for the phase factors of the FP32 modal sum. The angle is
 // first reduced to [-pi, pi] by Cody and Waite's two-constant subtraction of
 // the nearest multiple of 2 pi, then passed to the hardware sine and cosine;
@@ -949,7 +971,7 @@ hipError_t launch_idft(const SynthArgs& a, hipStream_t s) {
 inline unsigned blocks_for(long long n, int bs) { return (unsigned)((n + bs - 1) / bs); }
 
 template <typename T, int ZT>
-hipError_t launch_modal(const SynthArgs& a, hipStream_t s) {
+hipError_t launch_modal(const SynthArgs& a, hipStream_t s, bool phases) {
   constexpr int RW = (sizeof(T) == 4) ? (ZT <= 4 ? 8 : 4) : (ZT <= 2 ? 4 : 2);
   const int n2 = 2 * a.M;
   const int rows_per_block = 4 * RW;
@@ -961,10 +983,15 @@ hipError_t launch_modal(const SynthArgs& a, hipStream_t s) {
   const size_t lds = (size_t)ZT * jc * sizeof(cx<T>);
   const long long nblocks = (long long)a.ntasks * (nb_xy + nb_z);
   if (nblocks == 0) return hipSuccess;
-  modal_kernel<T, ZT, RW><<<(unsigned)nblocks, 256, lds, s>>>(
-      reinterpret_cast<const cx<T>*>(a.P), reinterpret_cast<const cx<T>*>(a.w), a.tasks, a.M,
-      nb_xy, nb_z, jc, reinterpret_cast<cx<T>*>(a.spec));
-  return hipGetLastError();
+  auto go = [&](auto kern) {
+    kern<<<(unsigned)nblocks, 256, lds, s>>>(
+        reinterpret_cast<const cx<T>*>(a.P), reinterpret_cast<const cx<T>*>(a.w),
+        reinterpret_cast<const zd*>(a.kg), reinterpret_cast<const zd*>(a.a),
+        reinterpret_cast<const zd*>(a.b), a.task_dz, a.tasks, a.M, nb_xy, nb_z, jc,
+        reinterpret_cast<cx<T>*>(a.spec));
+    return hipGetLastError();
+  };
+  return phases ? go(modal_kernel<T, ZT, RW, true>) : go(modal_kernel<T, ZT, RW, false>);
 }
 
 template <typename T>
@@ -977,17 +1004,25 @@ hipError_t launch_synthesis(const SynthArgs& a, hipStream_t s, hipEvent_t* ev) {
   if (!modal) {
     if ((e = mark(1)) != hipSuccess) return e;
   } else if (a.ntasks > 0 && sizeof(T) == 8) {
-    phase_kernel<T><<<blocks_for((long long)a.ntasks * n2, 256), 256, 0, s>>>(
-        a.tasks, a.task_dz, reinterpret_cast<const zd*>(a.kg),
-        reinterpret_cast<const zd*>(a.a), reinterpret_cast<const zd*>(a.b), n2, a.zt,
-        a.ntasks, reinterpret_cast<cx<T>*>(a.w));
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+    // The phases of a task are made in the modal sum's blocks where a thread
+    // makes at most six (each block repeats them), in a launch before it
+    // otherwise. 4 tasks of 8 planes: M = 25 12.8 us a call fused, 18.2 with the
+    // launch; M = 81 15.9 and 16.5; M = 121 16.9 and 16.5; 8 tasks at M = 225
+    // 28.2 and 22.2.
+    const bool fused = (long long)a.zt * n2 <= 1536;
+    if (!fused) {
+      phase_kernel<T><<<blocks_for((long long)a.ntasks * a.zt * n2, 256), 256, 0, s>>>(
+          a.tasks, a.task_dz, reinterpret_cast<const zd*>(a.kg),
+          reinterpret_cast<const zd*>(a.a), reinterpret_cast<const zd*>(a.b), n2, a.zt,
+          a.ntasks, reinterpret_cast<cx<T>*>(a.w));
+      if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
     if ((e = mark(1)) != hipSuccess) return e;
     switch (a.zt) {
-      case 1: e = launch_modal<T, 1>(a, s); break;
-      case 2: e = launch_modal<T, 2>(a, s); break;
-      case 4: e = launch_modal<T, 4>(a, s); break;
-      case 8: e = launch_modal<T, 8>(a, s); break;
+      case 1: e = launch_modal<T, 1>(a, s, fused); break;
+      case 2: e = launch_modal<T, 2>(a, s, fused); break;
+      case 4: e = launch_modal<T, 4>(a, s, fused); break;
+      case 8: e = launch_modal<T, 8>(a, s, fused); break;
       default: return hipErrorInvalidValue;
     }
     if (e != hipSuccess) return e;
