@@ -408,32 +408,38 @@ hipError_t launch_modal_f32(const SynthArgs& a, hipStream_t s) {
 // With several illuminations the columns of a task are (illumination, plane)
 // pairs c = ki * zt + p, 32 per launch group, and the product P_l W becomes a
 // real GEMM pair on the matrix cores: spec_re = P_re W_re - P_im W_im and
-// spec_im = P_re W_im + P_im W_re, four v_mfma_f32_32x32x2f32 per pair of j.
+// spec_im = P_re W_im + P_im W_re, in v_mfma_f32_16x16x4f32 (lane l holds row
+// or column l % 16 of K slot l / 16; accumulator i is D[4 (l / 16) + i][l % 16]).
 //
-// multi_phase_kernel writes the group's phase table once,
-// W[task][sign][c][j] = a_kj g_f(z_p) +- b_kj g_b(z_p), zero for j >= 2M
-// (rows padded to n2p, a multiple of 16) and for columns past the group.
-// modal_multi_kernel: one block = four waves on the same 32 rows of one sign
-// category of one task. P and W are staged through LDS in chunks of 64 j,
-// read from memory in 512-byte runs per row (the operand layout read straight
-// from memory would fetch 128-byte pieces of 32 rows 7 KB apart). Of a
-// chunk's four 16-j steps wave w takes step w; the four tiles are added
-// through LDS at the end. In the s-th product of a step, lane (i, h)
-// (i = lane % 32, h = lane / 32) feeds j = step + 8 h + s: 8 consecutive
-// complex of row i of each tile. The next chunk's loads are issued before the
-// current chunk's products.
-typedef float f32x16 __attribute__((ext_vector_type(16)));
+// K goes in steps of 16 j: in its s-th product (s < 4) slot g stands for j =
+// step + 4 g + s, so that a lane reads four consecutive complex of its row of P
+// (32 bytes; the four slots a 128-byte run) and four of its column of W.
+// multi_phase_kernel writes the group's phase table once, W = a_kj g_f(z_p) +-
+// b_kj g_b(z_p), zero for j >= 2M and for columns past the group, in the order in
+// which the products read it: [task][sign][step][half of the columns][half of a
+// lane's four][lane] pairs of complex, so that a wave's load is 1 KB in a row.
+//
+// modal_multi_kernel: one block = four waves on the same 16 rows of one sign
+// category of one task. Wave w takes steps w, w + 4, ...; its operands come
+// straight from memory, two steps ahead, and no wave waits for another before the
+// four tiles are added through LDS. Bound by the FP32 matrix rate once the chip
+// is filled evenly (16 tasks at M = 225: 9 us of products, in 736 blocks of 16
+// rows): 19.3 us with its 39 MB of P, 23.9 in blocks of 32 rows with the operands
+// staged through LDS, 24.9 with eight waves per block.
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 __global__ void multi_phase_kernel(const float2* __restrict__ kg, const float2* __restrict__ ab,
                                    const Task* __restrict__ tasks,
                                    const float2* __restrict__ tdz, int zt, int M, int L, int n2p,
                                    int k0, int kcount, int ntasks, float2* __restrict__ W) {
   const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  const long long per_task = 32LL * n2p;
+  const int per_task = 32 * n2p;
   if (t >= (long long)ntasks * per_task) return;
   const int task = (int)(t / per_task);
-  const int rem = (int)(t % per_task);
-  const int c = rem / n2p, j = rem % n2p;
+  const int rem = (int)(t % per_task);  // (step, column half, s / 2, lane, s % 2)
+  const int lane = (rem >> 1) & 63;
+  const int c = ((rem >> 8) & 1) * 16 + (lane & 15);
+  const int j = (rem >> 9) * 16 + 4 * (lane >> 4) + ((rem >> 7) & 1) * 2 + (rem & 1);
   const int ki = c / zt, p = c % zt;
   const int n2 = 2 * M;
   float2 wp = make_float2(0.f, 0.f), wm = wp;
@@ -451,22 +457,15 @@ __global__ void multi_phase_kernel(const float2* __restrict__ kg, const float2* 
     wp = make_float2(fx + bx, fy + by);
     wm = make_float2(fx - bx, fy - by);
   }
-  W[(((long long)task * 2 + 0) * 32 + c) * n2p + j] = wp;
-  W[(((long long)task * 2 + 1) * 32 + c) * n2p + j] = wm;
+  W[((long long)task * 2 + 0) * per_task + rem] = wp;
+  W[((long long)task * 2 + 1) * per_task + rem] = wm;
 }
 
-constexpr int kMultiJ = 64;  // j per staged chunk: four 16-j steps, one per wave
-
-// (up to three waves per SIMD: the staging and operand registers and the
-// three accumulators need about 150 registers)
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 3)))
-modal_multi_kernel(
+__global__ void __launch_bounds__(256) modal_multi_kernel(
     const float4* __restrict__ P, const float4* __restrict__ W, const Task* __restrict__ tasks,
     int zt, int M, int fz, int n2p, int k0, int kcount, int ntasks, int nb_xy, int nb_z,
     float2* __restrict__ spec) {
-  // the chunk's tiles: [0] 32 rows of P, [1] 32 columns of W, 64 j each,
-  // padded by one float4 per row (bank spread); reused for the reduction
-  __shared__ float4 tile[2][32][kMultiJ / 2 + 1];
+  __shared__ float red[4][16][64];  // the waves' tiles: [wave][i, column half, part][lane]
   const int n2 = 2 * M, n3 = 3 * M;
   const int nb = nb_xy + nb_z;
   // Consecutive workgroups go to the eight XCDs in turn; numbering them so
@@ -480,101 +479,85 @@ modal_multi_kernel(
   const int rb = blk % nb;
   const Task tk = tasks[task];
   const bool zrows = rb >= nb_xy;
-  const int r0 = zrows ? n2 + (rb - nb_xy) * 32 : rb * 32;
+  const int r0 = zrows ? n2 + (rb - nb_xy) * 16 : rb * 16;
   const int row_end = zrows ? n3 : n2;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int li = lane & 31, lh = lane >> 5;
-  // staging: thread t copies float4 8 q + t % 8 (q = 0..3) of row t / 8 of
-  // both tiles, so that eight lanes read one 128-byte run per load and a
-  // row's 512 bytes are read by eight lanes (rows past the end repeat the
-  // last row; j past 2M meets zero entries of W, so P there only has to be
-  // finite and its index is clamped to the row's last pair)
-  const int srow = threadIdx.x >> 3, spart = threadIdx.x & 7;
-  const float4* psrc =
-      P + ((long long)tk.layer * n3 + min(r0 + srow, row_end - 1)) * (n2 / 2);
-  const float4* wsrc = W + (((long long)task * 2 + (zrows ? 1 : 0)) * 32 + srow) * (n2p / 2);
-  const int pmax = n2 / 2 - 1, wmax = n2p / 2 - 1;
-  const int nsteps = n2p / 16;
-  const int nchunks = (nsteps + 3) / 4;
-  // three accumulators, so that no operand needs a sign flip:
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int li = lane & 15, lg = lane >> 4;
+  // rows past the end repeat the last one; j past 2M meets zero entries of W, so
+  // P there only has to be finite and its index is clamped to the row's last pair
+  const float4* prow = P + ((long long)tk.layer * n3 + min(r0 + li, row_end - 1)) * (n2 / 2);
+  const float4* wt = W + ((long long)task * 2 + (zrows ? 1 : 0)) * 16 * n2p;
+  const int pmax = n2 / 2 - 1, nsteps = n2p / 16;
+  struct Set {
+    float4 p[2], w[2][2];  // [half of the four], [column half][half of the four]
+  };
+  auto load = [&](Set& o, int i) {  // step wave + 4 i (the last step's again past the end)
+    const int st = min(wave + 4 * i, nsteps - 1);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      o.p[h] = prow[min(8 * st + 2 * lg + h, pmax)];
+#pragma unroll
+      for (int c = 0; c < 2; ++c) o.w[c][h] = wt[st * 256 + (2 * c + h) * 64 + lane];
+    }
+  };
+  // three accumulators per column half, so that no operand needs a sign flip:
   // spec_re = rr - ii, spec_im = im
-  f32x16 rr, ii, im;
+  f32x4 rr[2], ii[2], im[2];
 #pragma unroll
-  for (int r = 0; r < 16; ++r) rr[r] = ii[r] = im[r] = 0.f;
-  // staging registers of one chunk (named scalars, so that they stay in VGPRs)
-  float4 p0, p1, p2, p3, w0, w1, w2, w3;
-#define SCW_MULTI_LOAD(c)                                 \
-  {                                                       \
-    const int i0 = (c) * (kMultiJ / 2) + spart;           \
-    p0 = psrc[min(i0, pmax)];                             \
-    p1 = psrc[min(i0 + 8, pmax)];                         \
-    p2 = psrc[min(i0 + 16, pmax)];                        \
-    p3 = psrc[min(i0 + 24, pmax)];                        \
-    w0 = wsrc[min(i0, wmax)];                             \
-    w1 = wsrc[min(i0 + 8, wmax)];                         \
-    w2 = wsrc[min(i0 + 16, wmax)];                        \
-    w3 = wsrc[min(i0 + 24, wmax)];                        \
-  }
-  SCW_MULTI_LOAD(0);
-  for (int c = 0; c < nchunks; ++c) {
-    __syncthreads();  // the previous tiles have been read
-    tile[0][srow][spart] = p0;
-    tile[0][srow][8 + spart] = p1;
-    tile[0][srow][16 + spart] = p2;
-    tile[0][srow][24 + spart] = p3;
-    tile[1][srow][spart] = w0;
-    tile[1][srow][8 + spart] = w1;
-    tile[1][srow][16 + spart] = w2;
-    tile[1][srow][24 + spart] = w3;
-    __syncthreads();
-    // the next chunk's loads are in flight during this chunk's products (the
-    // last chunk loads itself again)
-    SCW_MULTI_LOAD(min(c + 1, nchunks - 1));
+  for (int c = 0; c < 2; ++c) rr[c] = ii[c] = im[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto step = [&](Set& o, int i) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const float4 a = o.p[h];
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        const float4 b = o.w[c][h];
+        rr[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x, b.x, rr[c], 0, 0, 0);
+        ii[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.y, b.y, ii[c], 0, 0, 0);
+        im[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x, b.y, im[c], 0, 0, 0);
+        rr[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.z, b.z, rr[c], 0, 0, 0);
+        ii[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.w, b.w, ii[c], 0, 0, 0);
+        im[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.y, b.x, im[c], 0, 0, 0);
+        im[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.z, b.w, im[c], 0, 0, 0);
+        im[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.w, b.z, im[c], 0, 0, 0);
+      }
+    }
+    load(o, i + 2);
     __builtin_amdgcn_sched_barrier(0);
-    if (4 * c + wave < nsteps) {
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const float4 a = tile[0][li][8 * wave + 4 * lh + q];
-        const float4 b = tile[1][li][8 * wave + 4 * lh + q];
-        rr = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, b.x, rr, 0, 0, 0);
-        ii = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, b.y, ii, 0, 0, 0);
-        im = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, b.y, im, 0, 0, 0);
-        im = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, b.x, im, 0, 0, 0);
-        rr = __builtin_amdgcn_mfma_f32_32x32x2f32(a.z, b.z, rr, 0, 0, 0);
-        ii = __builtin_amdgcn_mfma_f32_32x32x2f32(a.w, b.w, ii, 0, 0, 0);
-        im = __builtin_amdgcn_mfma_f32_32x32x2f32(a.z, b.w, im, 0, 0, 0);
-        im = __builtin_amdgcn_mfma_f32_32x32x2f32(a.w, b.z, im, 0, 0, 0);
-      }
-    }
+  };
+  Set s0, s1;
+  load(s0, 0);
+  __builtin_amdgcn_sched_barrier(0);
+  load(s1, 1);
+  __builtin_amdgcn_sched_barrier(0);
+  const int mine = (nsteps - wave + 3) / 4;
+  int i = 0;
+  for (; i + 2 <= mine; i += 2) {
+    step(s0, i);
+    step(s1, i + 1);
   }
-#undef SCW_MULTI_LOAD
-  // the four waves' tiles are added through LDS
-  __syncthreads();
-  float* red = reinterpret_cast<float*>(tile);  // [3][32][64]
-  if (wave > 0) {
+  if (i < mine) step(s0, i);
+  // the four waves' tiles are added through LDS, wave w the rows 4 g + w
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      red[((wave - 1) * 32 + r) * 64 + lane] = rr[r] - ii[r];
-      red[((wave - 1) * 32 + 16 + r) * 64 + lane] = im[r];
+  for (int c = 0; c < 2; ++c)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      red[wave][4 * r + 2 * c][lane] = rr[c][r] - ii[c][r];
+      red[wave][4 * r + 2 * c + 1][lane] = im[c][r];
     }
-  }
   __syncthreads();
-  if (wave == 0) {
-    const int ki = li / zt, p = li % zt;
-    if (ki < kcount && p < tk.count) {
-      float2* dst = spec + ((long long)(k0 + ki) * fz + tk.plane0 + p) * n3;
+  const int row = r0 + 4 * lg + wave;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int row = r0 + 8 * (r / 4) + 4 * lh + (r % 4);
-        float x = rr[r] - ii[r], y = im[r];
+  for (int c = 0; c < 2; ++c) {
+    float x = 0.f, y = 0.f;
 #pragma unroll
-        for (int w = 0; w < 3; ++w) {
-          x += red[(w * 32 + r) * 64 + lane];
-          y += red[(w * 32 + 16 + r) * 64 + lane];
-        }
-        if (row < row_end) dst[row] = make_float2(x, y);
-      }
+    for (int w = 0; w < 4; ++w) {
+      x += red[w][4 * wave + 2 * c][lane];
+      y += red[w][4 * wave + 2 * c + 1][lane];
     }
+    const int col = 16 * c + li, ki = col / zt, p = col % zt;
+    if (row < row_end && ki < kcount && p < tk.count)
+      spec[((long long)(k0 + ki) * fz + tk.plane0 + p) * n3 + row] = make_float2(x, y);
   }
 }
 
@@ -1080,7 +1063,7 @@ hipError_t launch_modal_multi(const void* P, const void* kg, const void* ab, con
       reinterpret_cast<float2*>(W));
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const int nb_xy = (2 * M + 31) / 32, nb_z = (M + 31) / 32;
+  const int nb_xy = (2 * M + 15) / 16, nb_z = (M + 15) / 16;
   const long long nblocks = (long long)ntasks * (nb_xy + nb_z);
   modal_multi_kernel<<<(unsigned)((nblocks + 7) / 8 * 8), 256, 0, s>>>(
       reinterpret_cast<const float4*>(P), reinterpret_cast<const float4*>(W), tasks, zt, M, fz,
