@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "scw_internal.h"
 #include "surrogate_device.h"
@@ -38,12 +39,15 @@ __global__ void adam(float* p, const float* g, float* m, float* v, long long n, 
 // Truncated forward DFT of 8 channels of one patch per block:
 //   out[b][i][ky][kx] = sum_y fy[ky][y] sum_x h[b][i][y][x] fx[x][kx]
 // (KY x KX modes; fy is [KY][32], fx is [32][KX], both complex). Grid (4, B),
-// 256 threads. Thread (c, y) = (t / 32, t % 32) first transforms row y of
-// channel c in registers; the column transform then runs over (c, mode).
+// 256 T threads. Thread (c, y) = (t / 32 % 8, t % 32) first transforms row y of
+// channel c in registers, for the t / 256-th T-th of the kx; the column transform
+// then runs over (c, mode). T = 2 while there is at most one block per CU, where
+// each thread's chain of sums is what takes the time (64 patches in bf16
+// products: 11.4 us with T = 1, 9.8 with T = 2).
 // MM selects the mode-major output layout [mode][b][i] (a Fourier layer's
 // spectra, read per mode by the mixing); otherwise [b][i][mode] (the head).
-template <bool BF16, int KY, int KX, bool MM>
-__global__ void __launch_bounds__(256) fused_dft_fwd(const float* __restrict__ h,
+template <bool BF16, int KY, int KX, bool MM, int T>
+__global__ void __launch_bounds__(256 * T) fused_dft_fwd(const float* __restrict__ h,
                                                      const f2* __restrict__ fy,
                                                      const f2* __restrict__ fx,
                                                      f2* __restrict__ H) {
@@ -55,10 +59,12 @@ __global__ void __launch_bounds__(256) fused_dft_fwd(const float* __restrict__ h
   __shared__ f2 hx[8 * HXS];
   __shared__ f2 fys[KY * FYS], fxs[SN * KX];
   const int t = threadIdx.x, b = blockIdx.y, c0 = blockIdx.x * 8;
-  for (int i = t; i < KY * SN; i += 256) fys[(i / SN) * FYS + i % SN] = op<BF16>(fy[i]);
+  for (int i = t; i < KY * SN; i += 256 * T) fys[(i / SN) * FYS + i % SN] = op<BF16>(fy[i]);
   if (BF16)
-    for (int i = t; i < SN * KX; i += 256) fxs[i] = op<BF16>(fx[i]);
-  const int c = t >> 5, y = t & 31;
+    for (int i = t; i < SN * KX; i += 256 * T) fxs[i] = op<BF16>(fx[i]);
+  const int c = (t >> 5) & 7, y = t & 31;
+  const int part = __builtin_amdgcn_readfirstlane(t >> 8);
+  const int kx0 = KX * part / T, kx1 = KX * (part + 1) / T;
   float row[SN];
   const float4* src =
       reinterpret_cast<const float4*>(h + (((long long)b * SW + c0 + c) * SN + y) * SN);
@@ -73,7 +79,7 @@ __global__ void __launch_bounds__(256) fused_dft_fwd(const float* __restrict__ h
   __syncthreads();
   if constexpr (BF16) {  // every product of two rounded operands, as defined
 #pragma unroll 3
-    for (int kx = 0; kx < KX; ++kx) {
+    for (int kx = kx0; kx < kx1; ++kx) {
       float re = 0.f, im = 0.f;
 #pragma unroll
       for (int x = 0; x < SN; ++x) {
@@ -97,7 +103,7 @@ __global__ void __launch_bounds__(256) fused_dft_fwd(const float* __restrict__ h
       dx[x] = row[x] - row[SN - x];
     }
 #pragma unroll 3
-    for (int kx = 0; kx < KX; ++kx) {
+    for (int kx = kx0; kx < kx1; ++kx) {
       const f2 w0 = fx[kx], w16 = fx[(SN / 2) * KX + kx];
       float re = fmaf(row[0], w0.x, row[SN / 2] * w16.x);
       float im = fmaf(row[0], w0.y, row[SN / 2] * w16.y);
@@ -115,7 +121,7 @@ __global__ void __launch_bounds__(256) fused_dft_fwd(const float* __restrict__ h
   // each hx value read serves KG modes
   constexpr int NMODE = KY * KX;
   constexpr int KG = 3, NKG = (KY + KG - 1) / KG;
-  for (int i = t; i < 8 * KX * NKG; i += 256) {
+  for (int i = t; i < 8 * KX * NKG; i += 256 * T) {
     const int cc = i % 8, kx = (i / 8) % KX, g = i / (8 * KX);
     float re[KG], im[KG];
 #pragma unroll
@@ -353,32 +359,34 @@ fused_dft_inv_mfma(
 // The head's mixing, 3 outputs: out[b][o][m] = sum_i A[b][i][m] W[i][o][m].
 // One thread per (patch, mode), modes fastest: every channel's spectra of a
 // patch are read as 64 consecutive modes per wave, the weights (small, cached)
-// likewise, and each spectral value serves the three outputs.
-template <bool BF16>
+// likewise, and each spectral value serves the NO outputs of a thread: all three,
+// or one (blockIdx.z) where that leaves less than two blocks per CU.
+template <bool BF16, int NO>
 __global__ void __launch_bounds__(256) mode_mix_head(const f2* __restrict__ A,
                                                      const f2* __restrict__ Wt, int nmode, int B,
                                                      f2* __restrict__ out) {
   constexpr int O = 3;
+  const int o0 = blockIdx.z * NO;
   const int m = blockIdx.x * 64 + (threadIdx.x & 63);
   const int b = blockIdx.y * 4 + (threadIdx.x >> 6);
   if (m >= nmode || b >= B) return;
   const f2* a = A + (long long)b * SW * nmode + m;
   const f2* w = Wt + m;
-  f2 acc[O];
+  f2 acc[NO];
 #pragma unroll
-  for (int o = 0; o < O; ++o) acc[o] = f2{0.f, 0.f};
+  for (int o = 0; o < NO; ++o) acc[o] = f2{0.f, 0.f};
 #pragma unroll 8
   for (int i = 0; i < SW; ++i) {
     const f2 v = op<BF16>(a[(long long)i * nmode]);
 #pragma unroll
-    for (int o = 0; o < O; ++o) {
-      const f2 c = op<BF16>(w[(i * O + o) * nmode]);
+    for (int o = 0; o < NO; ++o) {
+      const f2 c = op<BF16>(w[(i * O + o0 + o) * nmode]);
       acc[o].x = fmaf(v.x, c.x, fmaf(-v.y, c.y, acc[o].x));
       acc[o].y = fmaf(v.x, c.y, fmaf(v.y, c.x, acc[o].y));
     }
   }
 #pragma unroll
-  for (int o = 0; o < O; ++o) out[((long long)b * O + o) * nmode + m] = acc[o];
+  for (int o = 0; o < NO; ++o) out[((long long)b * O + o0 + o) * nmode + m] = acc[o];
 }
 
 // Per-mode channel mixing of a Fourier layer on the matrix cores:
@@ -464,7 +472,9 @@ __global__ void __launch_bounds__(512) spec_mode_major(const f2* __restrict__ W,
 }
 
 // The lift: h[b][o][p] = sum_c lw[c][o] x[b][c][p] + lb[o], 16 input and 32
-// output channels; grid (B), 512 threads of 2 pixels each.
+// output channels, 2 pixels per thread. Grid (B, P, Q): a block takes 1024 / P
+// pixels and 32 / Q outputs; small batches are split to reach more CUs (one
+// patch: 6.5 us in one block, 4.5 in eight).
 template <bool BF16>
 __global__ void __launch_bounds__(512) lift_kernel(const float* __restrict__ x,
                                                    const float* __restrict__ lw,
@@ -472,9 +482,10 @@ __global__ void __launch_bounds__(512) lift_kernel(const float* __restrict__ x,
                                                    float* __restrict__ h) {
   constexpr int CI = 16;
   __shared__ float lws[CI * SW], lbs[SW];
-  const int t = threadIdx.x, b = blockIdx.x;
-  for (int i = t; i < CI * SW; i += 512) lws[i] = op<BF16>(lw[i]);
-  if (t < SW) lbs[t] = lb[t];
+  const int b = blockIdx.x, t = blockIdx.y * blockDim.x + threadIdx.x;
+  const int no = SW / gridDim.z, o0 = blockIdx.z * no;
+  for (int i = threadIdx.x; i < CI * SW; i += blockDim.x) lws[i] = op<BF16>(lw[i]);
+  if (threadIdx.x < SW) lbs[threadIdx.x] = lb[threadIdx.x];
   float xr[CI][2];
   const float* xb = x + (long long)b * CI * SN * SN;
 #pragma unroll
@@ -486,7 +497,7 @@ __global__ void __launch_bounds__(512) lift_kernel(const float* __restrict__ x,
   __syncthreads();
   float* hb = h + (long long)b * SW * SN * SN + 2 * t;
 #pragma unroll 4
-  for (int o = 0; o < SW; ++o) {
+  for (int o = o0; o < o0 + no; ++o) {
     float a0 = lbs[o], a1 = lbs[o];
 #pragma unroll
     for (int c = 0; c < CI; ++c) {
@@ -522,17 +533,22 @@ hipError_t sur_adam(float* p, const float* g, float* m, float* v, long long n, f
 hipError_t sur_fused_dft_fwd(const float* h, const float* fy, const float* fx, float* H, int B,
                             bool head, bool bf16, hipStream_t s) {
   dim3 grid(SW / 8, B);
-  auto go = [&](auto kern) {
-    kern<<<grid, 256, 0, s>>>(h, reinterpret_cast<const f2*>(fy), reinterpret_cast<const f2*>(fx),
-                              reinterpret_cast<f2*>(H));
+  auto go = [&](auto kern, int T) {
+    kern<<<grid, 256 * T, 0, s>>>(h, reinterpret_cast<const f2*>(fy),
+                                  reinterpret_cast<const f2*>(fx), reinterpret_cast<f2*>(H));
   };
-  if (head) {  // the head's centred 15 x 15 band, [b][i][mode]
-    if (bf16) go(fused_dft_fwd<true, 15, 15, false>);
-    else go(fused_dft_fwd<false, 15, 15, false>);
-  } else {  // a Fourier layer's 17 x 9 half plane, [mode][b][i]
-    if (bf16) go(fused_dft_fwd<true, SKY, SKX, true>);
-    else go(fused_dft_fwd<false, SKY, SKX, true>);
-  }
+  auto pick = [&](auto rounded) {
+    constexpr bool R = decltype(rounded)::value;
+    if (head) {  // the head's centred 15 x 15 band, [b][i][mode]
+      if (B <= 64) go(fused_dft_fwd<R, 15, 15, false, 2>, 2);
+      else go(fused_dft_fwd<R, 15, 15, false, 1>, 1);
+    } else {  // a Fourier layer's 17 x 9 half plane, [mode][b][i]
+      if (B <= 64) go(fused_dft_fwd<R, SKY, SKX, true, 2>, 2);
+      else go(fused_dft_fwd<R, SKY, SKX, true, 1>, 1);
+    }
+  };
+  if (bf16) pick(std::true_type{});
+  else pick(std::false_type{});
   return hipGetLastError();
 }
 // Row-group splits of the inverse half: as many as keep the launch within two
@@ -573,8 +589,15 @@ hipError_t sur_mode_mix(const float* A, const float* W, int nmode, int B, int O,
   f2* o = reinterpret_cast<f2*>(out);
   if (O == 3) {
     dim3 grid((nmode + 63) / 64, (B + 3) / 4);
-    if (bf16) mode_mix_head<true><<<grid, 256, 0, s>>>(a, w, nmode, B, o);
-    else mode_mix_head<false><<<grid, 256, 0, s>>>(a, w, nmode, B, o);
+    auto go = [&](auto kern) { kern<<<grid, 256, 0, s>>>(a, w, nmode, B, o); };
+    if (grid.x * grid.y < 512) {
+      grid.z = 3;
+      if (bf16) go(mode_mix_head<true, 1>);
+      else go(mode_mix_head<false, 1>);
+    } else {
+      if (bf16) go(mode_mix_head<true, 3>);
+      else go(mode_mix_head<false, 3>);
+    }
   } else {
     return hipErrorInvalidValue;
   }
@@ -608,8 +631,10 @@ hipError_t sur_spec_mode_major(const float* W, long long layer_stride_floats, in
 }
 hipError_t sur_lift(const float* x, const float* lw, const float* lb, float* h, int B, bool bf16,
                     hipStream_t s) {
-  if (bf16) lift_kernel<true><<<B, 512, 0, s>>>(x, lw, lb, h);
-  else lift_kernel<false><<<B, 512, 0, s>>>(x, lw, lb, h);
+  const int P = B <= 64 ? 2 : 1, Q = B <= 64 ? 4 : 1;
+  const dim3 grid(B, P, Q);
+  if (bf16) lift_kernel<true><<<grid, 512 / P, 0, s>>>(x, lw, lb, h);
+  else lift_kernel<false><<<grid, 512 / P, 0, s>>>(x, lw, lb, h);
   return hipGetLastError();
 }
 hipError_t sur_encode(const float* n, float* x, int B, hipStream_t s) {

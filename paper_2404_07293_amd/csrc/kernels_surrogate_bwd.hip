@@ -115,12 +115,18 @@ __global__ void __launch_bounds__(256) loss_grad(const float* __restrict__ out,
 }
 
 // ---------------------------------------------------------------- weight gradients
-// out[e] = sum_p part[p][e], e < E: 32 entries x 8 slices of the parts per block.
-__global__ void __launch_bounds__(256) sum_parts(const float* __restrict__ part, int P, int E,
-                                                 float* __restrict__ out) {
+// out[e] = sum_p part[p][e], e < E, for every job: 32 entries x 8 slices of the
+// parts per block, the jobs' blocks one after another (one launch for all of a
+// gradient's sums: apart they took 6 x 3.9 us).
+__global__ void __launch_bounds__(256) sum_parts(const SurSumJobs jobs) {
   __shared__ float red[8][33];
+  int q = 0, blk = blockIdx.x;
+  for (; blk >= (jobs.j[q].E + 31) / 32; ++q) blk -= (jobs.j[q].E + 31) / 32;
+  const float* __restrict__ part = jobs.j[q].part;
+  const int P = jobs.j[q].P, E = jobs.j[q].E;
+  float* __restrict__ out = jobs.j[q].out;
   const int el = threadIdx.x & 31, sl = threadIdx.x >> 5;
-  const int e = blockIdx.x * 32 + el;
+  const int e = blk * 32 + el;
   float s = 0.f;
   if (e < E)
 #pragma unroll 8
@@ -387,15 +393,19 @@ __global__ void __launch_bounds__(256) mode_mix_adjoint_bf16(const f2* __restric
 }
 
 // gG[m][b][o] = sum_y conj(iy[y][ky]) sum_x gz[b][o][y][x] conj(ix[kx][x]), the
-// adjoint of the inverse half's transforms; one patch per block of 8 waves.
-// Rows: a wave transforms its 4 channels, D[y][Re kx | Im kx] over x. The
-// rounded results go to LDS along y, the K of the columns, D[ky][o] per kx.
+// adjoint of the inverse half's transforms; 32 / S channels of one patch per
+// block of 8 waves, grid (B, S). Rows: a wave transforms its 4 / S channels,
+// D[y][Re kx | Im kx] over x. The rounded results go to LDS along y, the K of the
+// columns, D[ky][o] per kx.
 constexpr int T2S = 40;  // LDS row: 32 y + 8 pad (bf16), 16-byte aligned
+template <int S>
 __global__ void __launch_bounds__(512) dft_adjoint_bf16(const float* __restrict__ gz,
                                                         const f2* __restrict__ iy,
                                                         const f2* __restrict__ ix, int B,
                                                         f2* __restrict__ gG) {
-  __shared__ __attribute__((aligned(16))) __bf16 t2[SKX][2][SW][T2S];
+  constexpr int CH = SW / S;
+  __shared__ __attribute__((aligned(16))) __bf16 t2[SKX][2][CH][T2S];
+  const int c0 = blockIdx.y * CH;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, li = lane & 31, lh = lane >> 5;
   const long long b = blockIdx.x;
   const int kxl = li % SKX;  // column li < 18 of the row transform: kx, Re or Im
@@ -413,9 +423,9 @@ __global__ void __launch_bounds__(512) dft_adjoint_bf16(const float* __restrict_
       ai[s][j] = (__bf16)(li < SKY ? -v.y : 0.f);
     }
 #pragma unroll
-  for (int q = 0; q < SW / 8; ++q) {
-    const int o = wave * (SW / 8) + q;
-    const float* row = gz + ((b * SW + o) * SN + li) * SN;
+  for (int q = 0; q < CH / 8; ++q) {
+    const int o = wave * (CH / 8) + q;
+    const float* row = gz + ((b * SW + c0 + o) * SN + li) * SN;
     floatx16 d = {0};
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
@@ -432,12 +442,13 @@ __global__ void __launch_bounds__(512) dft_adjoint_bf16(const float* __restrict_
     }
   }
   __syncthreads();
+  const int lc = li & (CH - 1);  // column li of the product; li >= CH repeats, unused
   for (int kx = wave; kx < SKX; kx += 8) {
     floatx16 cre = {0}, cim = {0};
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
-      const bf16x8 br = *reinterpret_cast<const bf16x8*>(&t2[kx][0][li][16 * s + 8 * lh]);
-      const bf16x8 bi = *reinterpret_cast<const bf16x8*>(&t2[kx][1][li][16 * s + 8 * lh]);
+      const bf16x8 br = *reinterpret_cast<const bf16x8*>(&t2[kx][0][lc][16 * s + 8 * lh]);
+      const bf16x8 bi = *reinterpret_cast<const bf16x8*>(&t2[kx][1][lc][16 * s + 8 * lh]);
       cre = mm16(ar[s], br, cre);
       cim = mm16(ar[s], bi, cim);
       cre = mm16(neg8(ai[s]), bi, cre);
@@ -446,7 +457,8 @@ __global__ void __launch_bounds__(512) dft_adjoint_bf16(const float* __restrict_
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const int ky = drow(r, lh);
-      if (ky < SKY) gG[((long long)(ky * SKX + kx) * B + b) * SW + li] = f2{cre[r], cim[r]};
+      if (ky < SKY && li < CH)
+        gG[((long long)(ky * SKX + kx) * B + b) * SW + c0 + li] = f2{cre[r], cim[r]};
     }
   }
 }
@@ -455,16 +467,18 @@ __global__ void __launch_bounds__(512) dft_adjoint_bf16(const float* __restrict_
 //   out[b][i][y][x] = (Re sum_kx (sum_ky conj(fy[ky][y]) gH[b][m][i]) conj(fx[x][kx])
 //                      + sum_o pw[i][o] gz[b][o][y][x]) GELU'(zp[b][i][y][x])
 // (HEAD: the head's tables and 15 x 15 gF, no pointwise part; zp null: no
-// GELU'). One patch per block of 8 waves. Columns: per kx, D[y][i] over ky,
-// straight from memory; rounded into LDS as rows [y][part][i] of 16 kx (zeros
-// past the last), the operand of the rows: D[i][x] per y.
-template <bool HEAD>
+// GELU'). Block of 8 waves, grid (B, S): 4 / S of a patch's row groups y = 8 g ..
+// + 7. Columns: per kx, D[y][i] over ky, straight from memory; rounded into LDS as
+// rows [y][part][i] of 16 kx (zeros past the last), the operand of the rows:
+// D[i][x] per y, a wave's row of each group.
+template <bool HEAD, int S>
 __global__ void __launch_bounds__(512) dft_fwd_adjoint_bf16(
     const f2* __restrict__ gH, const float* __restrict__ gz, const f2* __restrict__ fy,
     const f2* __restrict__ fx, const float* __restrict__ pw, const float* __restrict__ zp,
     float* __restrict__ out) {
   constexpr int KY = HEAD ? HN : SKY, KX = HEAD ? HN : SKX, KS = KY > 16 ? 2 : 1;
-  __shared__ __attribute__((aligned(16))) __bf16 tt[SN][2][SW][16];
+  constexpr int ROWS = SN / S;  // of this block
+  __shared__ __attribute__((aligned(16))) __bf16 tt[ROWS][2][SW][16];
   const int t = threadIdx.x, wave = t >> 6, lane = t & 63, li = lane & 31, lh = lane >> 5;
   const long long b = blockIdx.x;
   bf16x8 ar[KS], ai[KS];
@@ -478,7 +492,7 @@ __global__ void __launch_bounds__(512) dft_fwd_adjoint_bf16(
       ai[s][j] = (__bf16)(ky < KY ? -w.y : 0.f);
     }
   // zeros past the last kx (kx = 8 of a layer is written over them below)
-  for (int q = t; q < SN * 2 * SW; q += 512)
+  for (int q = t; q < ROWS * 2 * SW; q += 512)
     *reinterpret_cast<u32x4*>(&(&tt[0][0][0][0])[q * 16 + 8]) = u32x4{0u, 0u, 0u, 0u};
   __syncthreads();
   const f2* g0 = gH + b * KY * KX * SW + li;
@@ -505,9 +519,11 @@ __global__ void __launch_bounds__(512) dft_fwd_adjoint_bf16(
     }
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      const int y = drow(r, lh);
-      tt[y][0][li][kx] = (__bf16)cre[r];
-      tt[y][1][li][kx] = (__bf16)cim[r];
+      const int g = r / 4;  // row group of y = drow(r, lh)
+      if (S > 1 && g % S != (int)blockIdx.y) continue;
+      const int yl = 8 * (g / S) + drow(r, lh) % 8;
+      tt[yl][0][li][kx] = (__bf16)cre[r];
+      tt[yl][1][li][kx] = (__bf16)cim[r];
     }
   }
   bf16x8 xr, xi, pa[2];
@@ -523,9 +539,10 @@ __global__ void __launch_bounds__(512) dft_fwd_adjoint_bf16(
     }
   }
   __syncthreads();
-  for (int y = wave; y < SN; y += 8) {
-    const bf16x8 tr = *reinterpret_cast<const bf16x8*>(&tt[y][0][li][8 * lh]);
-    const bf16x8 ti = *reinterpret_cast<const bf16x8*>(&tt[y][1][li][8 * lh]);
+  for (int yl = wave; yl < ROWS; yl += 8) {
+    const int y = 8 * (yl / 8 * S + blockIdx.y) + wave;
+    const bf16x8 tr = *reinterpret_cast<const bf16x8*>(&tt[yl][0][li][8 * lh]);
+    const bf16x8 ti = *reinterpret_cast<const bf16x8*>(&tt[yl][1][li][8 * lh]);
     floatx16 acc = {0}, accp = {0};
     if constexpr (!HEAD) {
 #pragma unroll
@@ -563,7 +580,7 @@ hipError_t sur_loss(const float* out, const float* tgt, long long n, float* part
 }
 
 hipError_t sur_pointwise_grad(const float* h, const float* gz, int ci, int B, bool bf16,
-                              float* part, float* out, hipStream_t s) {
+                              float* part, float* out, SurSumJobs* sums, hipStream_t s) {
   const int units = 4 * B, nblk = std::min(units, kSurPointwiseParts), E = ci * SW + SW;
   auto go = [&](auto kern) { kern<<<nblk, 256, 0, s>>>(h, gz, units, part); };
   if (ci == 32) {
@@ -575,7 +592,14 @@ hipError_t sur_pointwise_grad(const float* h, const float* gz, int ci, int B, bo
   } else {
     return hipErrorInvalidValue;
   }
-  sum_parts<<<(E + 31) / 32, 256, 0, s>>>(part, nblk, E, out);
+  sums->j[sums->n++] = {part, nblk, E, out};
+  return hipGetLastError();
+}
+
+hipError_t sur_sum_parts(const SurSumJobs& jobs, hipStream_t s) {
+  int blocks = 0;
+  for (int q = 0; q < jobs.n; ++q) blocks += (jobs.j[q].E + 31) / 32;
+  if (blocks) sum_parts<<<blocks, 256, 0, s>>>(jobs);
   return hipGetLastError();
 }
 
@@ -594,12 +618,12 @@ hipError_t sur_spec_from_mode_major(const float* gW, long long layer_stride_floa
 }
 
 hipError_t sur_head_grad(const float* F, const float* gout, int B, bool bf16, float* part,
-                         float* out, hipStream_t s) {
+                         float* out, SurSumJobs* sums, hipStream_t s) {
   const int slices = std::min(B, kSurHeadSlices), E = 2 * SW * OUT * HM;
   const dim3 grid((HM + 63) / 64, SW / 4, slices);
   if (bf16) head_grad<true><<<grid, 256, 0, s>>>(c2(F), c2(gout), B, c2(part));
   else head_grad<false><<<grid, 256, 0, s>>>(c2(F), c2(gout), B, c2(part));
-  sum_parts<<<(E + 31) / 32, 256, 0, s>>>(part, slices, E, out);
+  sums->j[sums->n++] = {part, slices, E, out};
   return hipGetLastError();
 }
 
@@ -615,19 +639,34 @@ hipError_t sur_mode_mix_adjoint_bf16(const float* gG, const float* Wm, int B, fl
                                                                            c2(gH));
   return hipGetLastError();
 }
+// Splits of the two transforms' adjoints: as many as keep a launch within two
+// blocks per CU. At 64 patches, 64 blocks took 29 us (forward half) and 11.9 us
+// (inverse half), 256 blocks 13 and 10.5.
 hipError_t sur_dft_adjoint_bf16(const float* gz, const float* iy, const float* ix, int B,
                                 float* gG, hipStream_t s) {
-  dft_adjoint_bf16<<<B, 512, 0, s>>>(gz, c2(iy), c2(ix), B, c2(gG));
+  auto go = [&](auto kern, int splits) {
+    kern<<<dim3(B, splits), 512, 0, s>>>(gz, c2(iy), c2(ix), B, c2(gG));
+  };
+  if (B <= 128) go(dft_adjoint_bf16<4>, 4);
+  else if (B <= 256) go(dft_adjoint_bf16<2>, 2);
+  else go(dft_adjoint_bf16<1>, 1);
   return hipGetLastError();
 }
 hipError_t sur_dft_fwd_adjoint_bf16(const float* gH, const float* gz, const float* fy,
                                     const float* fx, const float* pw, const float* zp, bool head,
                                     int B, float* out, hipStream_t s) {
-  if (head)
-    dft_fwd_adjoint_bf16<true><<<B, 512, 0, s>>>(c2(gH), nullptr, c2(fy), c2(fx), nullptr, zp,
-                                                 out);
-  else
-    dft_fwd_adjoint_bf16<false><<<B, 512, 0, s>>>(c2(gH), gz, c2(fy), c2(fx), pw, zp, out);
+  auto go = [&](auto kern, int splits) {
+    kern<<<dim3(B, splits), 512, 0, s>>>(c2(gH), gz, c2(fy), c2(fx), pw, zp, out);
+  };
+  if (head) {
+    if (B <= 128) go(dft_fwd_adjoint_bf16<true, 4>, 4);
+    else if (B <= 256) go(dft_fwd_adjoint_bf16<true, 2>, 2);
+    else go(dft_fwd_adjoint_bf16<true, 1>, 1);
+  } else {
+    if (B <= 128) go(dft_fwd_adjoint_bf16<false, 4>, 4);
+    else if (B <= 256) go(dft_fwd_adjoint_bf16<false, 2>, 2);
+    else go(dft_fwd_adjoint_bf16<false, 1>, 1);
+  }
   return hipGetLastError();
 }
 

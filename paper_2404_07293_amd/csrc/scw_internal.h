@@ -452,18 +452,29 @@ std::string batch_key(const scw_grid& g);
 // Backward kernels (kernels_surrogate_bwd.hip). Spectral gradients use the
 // forward pass's layouts: gG mode-major [mode][b][o], gH and gF [b][mode][i].
 constexpr int kSurPointwiseParts = 512, kSurHeadSlices = 16;
-// floats of the partial sums that sur_pointwise_grad and sur_head_grad need
-constexpr long long kSurPartFloats = 16LL * 2 * 32 * 3 * 225 > 512LL * 1056
-                                         ? 16LL * 2 * 32 * 3 * 225
-                                         : 512LL * 1056;
+// floats of the partial sums of one sur_pointwise_grad and of sur_head_grad, and
+// of a whole gradient (four layers, the lift, the head)
+constexpr long long kSurPointwisePart = (long long)kSurPointwiseParts * 1056;
+constexpr long long kSurHeadPart = (long long)kSurHeadSlices * 2 * 32 * 3 * 225;
+constexpr long long kSurPartFloats = 5 * kSurPointwisePart + kSurHeadPart;
+// The sums over a gradient's parts: out[e] = sum_p part[p][e], e < E.
+struct SurSumJobs {
+  struct {
+    const float* part;
+    int P, E;
+    float* out;
+  } j[6];
+  int n;
+};
+hipError_t sur_sum_parts(const SurSumJobs& jobs, hipStream_t s);
 // sums[0] = sum |out - tgt|^2, sums[1] = sum |tgt|^2 over n complex values,
 // g = 2 (out - tgt) / sums[1]; part: 512 floats of workspace.
 hipError_t sur_loss(const float* out, const float* tgt, long long n, float* part, float* sums,
                     float* g, hipStream_t s);
 // out = [ci][32] weight gradient of a pointwise map from ci channels h, then
-// the 32 bias gradients.
+// the 32 bias gradients. Its parts go to `part`; the sum is queued in `sums`.
 hipError_t sur_pointwise_grad(const float* h, const float* gz, int ci, int B, bool bf16,
-                              float* part, float* out, hipStream_t s);
+                              float* part, float* out, SurSumJobs* sums, hipStream_t s);
 // gW[m][i][o] = sum_b conj(H[m][b][i]) gG[m][b][o], and its reordering into the
 // parameters' [i][o][m] for `layers` layers layer_stride_floats apart.
 hipError_t sur_spectral_grad(const float* H, const float* gG, int B, bool bf16, float* gW,
@@ -472,7 +483,7 @@ hipError_t sur_spec_from_mode_major(const float* gW, long long layer_stride_floa
                                     float* G, hipStream_t s);
 // out[i][c][m] = sum_b conj(F[b][i][m]) gout[b][c][m]
 hipError_t sur_head_grad(const float* F, const float* gout, int B, bool bf16, float* part,
-                         float* out, hipStream_t s);
+                         float* out, SurSumJobs* sums, hipStream_t s);
 // The adjoint in bf16 products: the head's mixing (gF), a layer's mixing (gH),
 // the inverse half's transforms (gG), and the forward half with the pointwise
 // map and, with zp, GELU' of the pre-activation zp (head: gF and the head's

@@ -63,9 +63,9 @@ struct SurNet {
   DevBuf x, h[NL + 1], z[NL], Hk[NL], G, Wm, F, out, gout, gF, gh, gh2, gG, gH, gWm, part, sums,
       enc_in;
   DevBuf Wb;  // mixing weights as bf16 matrix-core operands (inference)
-  // the parameters change only in sur_set_params and Adam steps; Wb is rebuilt
-  // when its version lags behind theirs
-  unsigned long long params_version = 1, wb_version = 0;
+  // the parameters change only in sur_set_params and Adam steps; Wb and Wm (the
+  // mode-major weights) are rebuilt when their version lags behind theirs
+  unsigned long long params_version = 1, wb_version = 0, wm_version = 0;
 };
 
 namespace {
@@ -127,11 +127,17 @@ const float* cx(const SurNet& n, long long off) { return n.dft.as<float>() + 2 *
 
 // Forward pass; with keep, the per-layer H spectra and pre-activations stay
 // for the backward pass (h[] is always kept).
-int forward(SurNet& n, const float* x, int B, hipStream_t s, bool keep) {
+int forward(SurNet& n, const float* x, int B, hipStream_t s, bool keep, float* out) {
   const Off o;
   const float* P = n.params.as<float>();
-  // mode-major copy of the spectral weights, for the mixing
-  SUR_HIP(sur_spec_mode_major(P + o.spec(0), SZ_LAYER, NM, NL, n.Wm.as<float>(), s));
+  // mode-major copy of the spectral weights, for the mixing; a captured call
+  // makes its own, so that a replay sees the parameters of its time
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  SUR_HIP(hipStreamIsCapturing(s, &capture));
+  if (capture != hipStreamCaptureStatusNone || n.wm_version != n.params_version) {
+    SUR_HIP(sur_spec_mode_major(P + o.spec(0), SZ_LAYER, NM, NL, n.Wm.as<float>(), s));
+    if (capture == hipStreamCaptureStatusNone) n.wm_version = n.params_version;
+  }
   // lift
   SUR_HIP(sur_lift(x, P + o.lw, P + o.lb, n.h[0].as<float>(), B, n.bf16, s));
   for (int k = 0; k < NL; ++k) {
@@ -153,14 +159,14 @@ int forward(SurNet& n, const float* x, int B, hipStream_t s, bool keep) {
   // head: F = hy h hx per channel on the centred 15 x 15 band
   SUR_HIP(sur_fused_dft_fwd(n.h[NL].as<float>(), cx(n, n.o_hy), cx(n, n.o_hx), n.F.as<float>(),
                             B, true, n.bf16, s));
-  SUR_HIP(sur_mode_mix(n.F.as<float>(), P + o.head(), HM, B, OUT, n.out.as<float>(), n.bf16, s));
+  SUR_HIP(sur_mode_mix(n.F.as<float>(), P + o.head(), HM, B, OUT, out, n.bf16, s));
   return SCW_OK;
 }
 
 // Inference in the matrix-core mode with bf16 storage: the same network and
 // the same rounded operands as forward() with n.bf16, every activation and
 // spectrum kept in bf16 (h ping-pongs between the memory of h[0] and h[1]).
-int forward_bf16(SurNet& n, const float* x, int B, hipStream_t s) {
+int forward_bf16(SurNet& n, const float* x, int B, hipStream_t s, float* out) {
   const Off o;
   const float* P = n.params.as<float>();
   if (n.wb_version != n.params_version) {
@@ -179,12 +185,12 @@ int forward_bf16(SurNet& n, const float* x, int B, hipStream_t s) {
     std::swap(ha, hb);
   }
   SUR_HIP(sur_fwd_bf16(ha, cx(n, n.o_hy), cx(n, n.o_hx), n.F.p, B, true, s));
-  SUR_HIP(sur_head_mix_bf16(n.F.p, P + o.head(), B, n.out.as<float>(), s));
+  SUR_HIP(sur_head_mix_bf16(n.F.p, P + o.head(), B, out, s));
   return SCW_OK;
 }
 
-int infer(SurNet& n, const float* x, int B, hipStream_t s) {
-  return n.bf16 ? forward_bf16(n, x, B, s) : forward(n, x, B, s, false);
+int infer(SurNet& n, const float* x, int B, hipStream_t s, float* out) {
+  return n.bf16 ? forward_bf16(n, x, B, s, out) : forward(n, x, B, s, false, out);
 }
 
 // Backward pass from gout (= dL/dout) into grads: per layer the adjoint of its
@@ -199,7 +205,9 @@ int backward(SurNet& n, int B, hipStream_t s) {
   float* part = n.part.as<float>();
   float *gG = n.gG.as<float>(), *gH = n.gH.as<float>(), *gout = n.gout.as<float>();
   float *gz = n.gh.as<float>(), *gnext = n.gh2.as<float>();
-  SUR_HIP(sur_head_grad(n.F.as<float>(), gout, B, n.bf16, part, Gr + o.head(), s));
+  SurSumJobs sums{};
+  SUR_HIP(sur_head_grad(n.F.as<float>(), gout, B, n.bf16, part, Gr + o.head(), &sums, s));
+  part += kSurHeadPart;
   if (n.bf16) {
     float* gF = n.gF.as<float>();
     SUR_HIP(sur_head_mix_adjoint_bf16(gout, P + o.head(), B, gF, s));
@@ -211,7 +219,9 @@ int backward(SurNet& n, int B, hipStream_t s) {
   for (int k = NL - 1; k >= 0; --k) {
     const float* Wm = n.Wm.as<float>() + 2LL * k * NM * W * W;
     const float* zp = k > 0 ? n.z[k - 1].as<float>() : nullptr;
-    SUR_HIP(sur_pointwise_grad(n.h[k].as<float>(), gz, W, B, n.bf16, part, Gr + o.pw(k), s));
+    SUR_HIP(sur_pointwise_grad(n.h[k].as<float>(), gz, W, B, n.bf16, part, Gr + o.pw(k), &sums,
+                               s));
+    part += kSurPointwisePart;
     if (n.bf16)
       SUR_HIP(sur_dft_adjoint_bf16(gz, cx(n, n.o_iy), cx(n, n.o_ix), B, gG, s));
     else
@@ -230,7 +240,8 @@ int backward(SurNet& n, int B, hipStream_t s) {
     std::swap(gz, gnext);
   }
   SUR_HIP(sur_spec_from_mode_major(n.gWm.as<float>(), SZ_LAYER, NL, Gr + o.spec(0), s));
-  SUR_HIP(sur_pointwise_grad(n.x.as<float>(), gz, CIN, B, n.bf16, part, Gr + o.lw, s));
+  SUR_HIP(sur_pointwise_grad(n.x.as<float>(), gz, CIN, B, n.bf16, part, Gr + o.lw, &sums, s));
+  SUR_HIP(sur_sum_parts(sums, s));
   return SCW_OK;
 }
 
@@ -353,8 +364,13 @@ int sur_encode(SurNet& n, const void* n_dev, int B, void* x_dev, hipStream_t s) 
 int sur_forward(SurNet& n, const void* x_dev, int B, void* out_dev, hipStream_t s) {
   int rc = check_batch(n, B);
   if (rc) return rc;
-  if ((rc = infer(n, reinterpret_cast<const float*>(x_dev), B, s))) return rc;
-  SCW_HIP(hipMemcpyAsync(out_dev, n.out.p, (size_t)B * OUT * HM * 8, hipMemcpyDeviceToDevice, s));
+  // the head writes the caller's array, by way of n.out if that is not aligned
+  // to a complex value
+  const bool direct = reinterpret_cast<uintptr_t>(out_dev) % 8 == 0;
+  float* out = direct ? static_cast<float*>(out_dev) : n.out.as<float>();
+  if ((rc = infer(n, reinterpret_cast<const float*>(x_dev), B, s, out))) return rc;
+  if (!direct)
+    SCW_HIP(hipMemcpyAsync(out_dev, out, (size_t)B * OUT * HM * 8, hipMemcpyDeviceToDevice, s));
   return SCW_OK;
 }
 
@@ -363,7 +379,7 @@ int sur_loss_grad(SurNet& n, const void* x_dev, const void* tgt_dev, int B, doub
   int rc = check_batch(n, B);
   if (rc) return rc;
   SCW_HIP(hipMemcpyAsync(n.x.p, x_dev, (size_t)B * CIN * NP * 4, hipMemcpyDeviceToDevice, s));
-  if ((rc = forward(n, n.x.as<float>(), B, s, true))) return rc;
+  if ((rc = forward(n, n.x.as<float>(), B, s, true, n.out.as<float>()))) return rc;
   SCW_HIP(sur_loss(n.out.as<float>(), reinterpret_cast<const float*>(tgt_dev),
                    (long long)B * OUT * HM, n.part.as<float>(), n.sums.as<float>(),
                    n.gout.as<float>(), s));
@@ -407,7 +423,7 @@ int sur_infer_checked(Context& ctx, SurNet& n, const double* n_host, int B, int 
   for (size_t i = 0; i < f.size(); ++i) f[i] = (float)n_host[i];
   SCW_HIP(hipMemcpy(n.enc_in.p, f.data(), f.size() * 4, hipMemcpyHostToDevice));
   SCW_HIP(sur_encode(n.enc_in.as<float>(), n.x.as<float>(), B, nullptr));
-  if ((rc = infer(n, n.x.as<float>(), B, nullptr))) return rc;
+  if ((rc = infer(n, n.x.as<float>(), B, nullptr, n.out.as<float>()))) return rc;
   std::vector<float> o((size_t)B * OUT * HM * 2);
   SCW_HIP(hipMemcpy(o.data(), n.out.p, o.size() * 4, hipMemcpyDeviceToHost));
   for (size_t i = 0; i < o.size(); ++i) out_host[i] = o[i];

@@ -15,11 +15,9 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 // a patch's side, the layers' spectral half plane and the channel count
 constexpr int SN = 32, SKY = 17, SKX = 9, SNM = SKY * SKX, SW = 32;
 
-__device__ __forceinline__ float rbf(float x) {  // round to bf16, nearest even
-  unsigned u = __float_as_uint(x);
-  u = (u + 0x7FFFu + ((u >> 16) & 1u)) & 0xFFFF0000u;
-  return __uint_as_float(u);
-}
+// round to bf16, nearest even, by the hardware's conversion (two values per
+// instruction where the compiler pairs them)
+__device__ __forceinline__ float rbf(float x) { return (float)(__bf16)x; }
 template <bool BF16>
 __device__ __forceinline__ float op(float x) { return BF16 ? rbf(x) : x; }
 template <bool BF16>
