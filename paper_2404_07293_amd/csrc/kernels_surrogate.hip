@@ -509,14 +509,40 @@ __global__ void __launch_bounds__(512) lift_kernel(const float* __restrict__ x,
   }
 }
 
-// complex64 index patches [B][8][32][32] -> channels [B][16][32][32]
-__global__ void encode(const float* n, float* x, long long per_layer_total, int P) {
-  long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;  // over B*8*P
-  if (i >= per_layer_total) return;
-  const long long p = i % P, bl = i / P;  // bl = b*8 + l
-  const long long b = bl / 8, l = bl % 8;
-  x[((b * 16) + 2 * l) * P + p] = (n[2 * i] - 1.45f) / 0.15f;
-  x[((b * 16) + 2 * l + 1) * P + p] = n[2 * i + 1] / 0.05f;
+// complex64 index patches [B][8][32][32] -> channels [B][16][32][32], one
+// (patch, layer) per block and four pixels per thread; VEC: in 16-byte accesses
+// (both arrays aligned), NT: non-temporal. Bound by memory: 537 MB in 88 us,
+// 117 with one pixel per thread.
+template <bool VEC, bool NT>
+__global__ void __launch_bounds__(256) encode(const float* n, float* x) {
+  typedef float float4v __attribute__((ext_vector_type(4)));
+  constexpr int P = SN * SN;
+  const long long bl = blockIdx.x;  // b * 8 + l
+  const int p = 4 * threadIdx.x;
+  const float* src = n + (bl * P + p) * 2;
+  float* re = x + bl * 2 * P + p;  // channel 2 l of patch b, then 2 l + 1
+  float* im = re + P;
+  if constexpr (VEC) {
+    const float4v* s4 = reinterpret_cast<const float4v*>(src);
+    const float4v a = NT ? __builtin_nontemporal_load(s4) : s4[0];
+    const float4v c = NT ? __builtin_nontemporal_load(s4 + 1) : s4[1];
+    const float4v r = {(a.x - 1.45f) / 0.15f, (a.z - 1.45f) / 0.15f, (c.x - 1.45f) / 0.15f,
+                       (c.z - 1.45f) / 0.15f};
+    const float4v i = {a.y / 0.05f, a.w / 0.05f, c.y / 0.05f, c.w / 0.05f};
+    if constexpr (NT) {
+      __builtin_nontemporal_store(r, reinterpret_cast<float4v*>(re));
+      __builtin_nontemporal_store(i, reinterpret_cast<float4v*>(im));
+    } else {
+      *reinterpret_cast<float4v*>(re) = r;
+      *reinterpret_cast<float4v*>(im) = i;
+    }
+  } else {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      re[k] = (src[2 * k] - 1.45f) / 0.15f;
+      im[k] = src[2 * k + 1] / 0.05f;
+    }
+  }
 }
 
 inline unsigned blocks(long long n, int bs = 256) { return (unsigned)((n + bs - 1) / bs); }
@@ -638,8 +664,11 @@ hipError_t sur_lift(const float* x, const float* lw, const float* lb, float* h, 
   return hipGetLastError();
 }
 hipError_t sur_encode(const float* n, float* x, int B, hipStream_t s) {
-  const long long tot = (long long)B * 8 * 1024;
-  encode<<<blocks(tot), 256, 0, s>>>(n, x, tot, 1024);
+  const bool vec = (reinterpret_cast<uintptr_t>(n) | reinterpret_cast<uintptr_t>(x)) % 16 == 0;
+  auto go = [&](auto kern) { kern<<<8 * B, 256, 0, s>>>(n, x); };
+  if (!vec) go(encode<false, false>);
+  else if (sur_past_cache(B)) go(encode<true, true>);
+  else go(encode<true, false>);
   return hipGetLastError();
 }
 

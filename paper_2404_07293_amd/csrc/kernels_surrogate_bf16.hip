@@ -81,10 +81,25 @@ __device__ __forceinline__ float gelu(float z) {
   return fmaf(-az, q * t * e, zp);
 }
 
+// Loads and stores of the activations, non-temporal where the batch does not fit
+// the last-level cache (sur_past_cache); the spectra between them stay there.
+template <bool NT, typename V>
+__device__ __forceinline__ V ld(const V* p) {
+  if constexpr (NT) return __builtin_nontemporal_load(p);
+  else return *p;
+}
+template <bool NT, typename V>
+__device__ __forceinline__ void st(V* p, V v) {
+  if constexpr (NT) __builtin_nontemporal_store(v, p);
+  else *p = v;
+}
+
 // ---------------------------------------------------------------------------
 // Lift: h[b][o][p] = sum_c lw[c][o] x[b][c][p] + lb[o] (16 -> 32 channels),
 // operands rounded, the sum in the order of the FP32 kernel, then stored
 // rounded. One patch per block, 4 pixels per thread.
+typedef float float4v __attribute__((ext_vector_type(4)));
+template <bool NT>
 __global__ void __launch_bounds__(256) lift_bf16(const float* __restrict__ x,
                                                  const float* __restrict__ lw,
                                                  const float* __restrict__ lb,
@@ -98,7 +113,7 @@ __global__ void __launch_bounds__(256) lift_bf16(const float* __restrict__ x,
   const float* xb = x + (long long)b * CI * N * N;
 #pragma unroll
   for (int c = 0; c < CI; ++c) {
-    const float4 v = reinterpret_cast<const float4*>(xb + c * N * N)[t];
+    const float4v v = ld<NT>(reinterpret_cast<const float4v*>(xb + c * N * N) + t);
     xr[c][0] = rb(v.x);
     xr[c][1] = rb(v.y);
     xr[c][2] = rb(v.z);
@@ -382,7 +397,7 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   __builtin_amdgcn_wave_barrier();
 }
-template <bool GELU>
+template <bool GELU, bool NT>
 __global__ void __launch_bounds__(256) inv_bf16(const unsigned* __restrict__ G,
                                                 const bf_t* __restrict__ h,
                                                 const cf* __restrict__ iy,
@@ -407,7 +422,8 @@ __global__ void __launch_bounds__(256) inv_bf16(const unsigned* __restrict__ G,
   auto load_rows = [&](int bb, int j, u32x4* pf) {
     const bf_t* hb = h + (long long)bb * C * N * N + lane_px + 2 * j * N;
 #pragma unroll
-    for (int u = 0; u < 4; ++u) pf[u] = *reinterpret_cast<const u32x4*>(hb + 8 * u * N * N);
+    for (int u = 0; u < 4; ++u)
+      pf[u] = ld<NT>(reinterpret_cast<const u32x4*>(hb + 8 * u * N * N));
   };
   auto load_g = [&](int bb, u32x4* gp) {
     const u32x4* gb = reinterpret_cast<const u32x4*>(G + (long long)bb * LNM * C);
@@ -613,7 +629,7 @@ __global__ void __launch_bounds__(256) inv_bf16(const unsigned* __restrict__ G,
           const int o = 8 * u + (l >> 3);
           const u32x4 v =
               *reinterpret_cast<const u32x4*>(hs + o * 2 * N + (((l & 7) ^ (o & 7)) * 8));
-          *reinterpret_cast<u32x4*>(orow + (long long)o * N * N) = v;
+          st<NT>(reinterpret_cast<u32x4*>(orow + (long long)o * N * N), v);
         }
       }
       wave_sync();  // this row pair's pixels are read before the next are staged
@@ -725,7 +741,8 @@ int resident_blocks(K kern) {
 
 hipError_t sur_lift_bf16(const float* x, const float* lw, const float* lb, void* h, int B,
                          hipStream_t s) {
-  lift_bf16<<<B, 256, 0, s>>>(x, lw, lb, reinterpret_cast<bf_t*>(h));
+  if (sur_past_cache(B)) lift_bf16<true><<<B, 256, 0, s>>>(x, lw, lb, reinterpret_cast<bf_t*>(h));
+  else lift_bf16<false><<<B, 256, 0, s>>>(x, lw, lb, reinterpret_cast<bf_t*>(h));
   return hipGetLastError();
 }
 hipError_t sur_fwd_bf16(const void* h, const float* fy, const float* fx, void* H, int B,
@@ -769,8 +786,8 @@ hipError_t sur_inv_bf16(const void* G, const void* h, const float* iy, const flo
         reinterpret_cast<const cf*>(iy), reinterpret_cast<const cf*>(ix), pw, pb,
         reinterpret_cast<bf_t*>(h_out), B);
   };
-  if (gelu_on) go(inv_bf16<true>);
-  else go(inv_bf16<false>);
+  if (sur_past_cache(B)) gelu_on ? go(inv_bf16<true, true>) : go(inv_bf16<false, true>);
+  else gelu_on ? go(inv_bf16<true, false>) : go(inv_bf16<false, false>);
   return hipGetLastError();
 }
 hipError_t sur_head_mix_bf16(const void* F, const float* W, int B, float* out, hipStream_t s) {

@@ -451,6 +451,11 @@ std::string batch_key(const scw_grid& g);
 // ------------------------------------------------------------------ surrogate kernels
 // Backward kernels (kernels_surrogate_bwd.hip). Spectral gradients use the
 // forward pass's layouts: gG mode-major [mode][b][o], gH and gF [b][mode][i].
+// Whether the large arrays of an inference batch stream past the last-level
+// cache (256 MB): from 1280 patches on a layer's two activations in bf16 no
+// longer fit there with its spectra. Whole bf16 passes, non-temporal and normal:
+// 1024 patches 360 and 353 us, 1536 477 and 488, 4096 1150 and 1267.
+inline bool sur_past_cache(int B) { return B > 1280; }
 constexpr int kSurPointwiseParts = 512, kSurHeadSlices = 16;
 // floats of the partial sums of one sur_pointwise_grad and of sur_head_grad, and
 // of a whole gradient (four layers, the lift, the head)
