@@ -59,23 +59,39 @@ __global__ void __launch_bounds__(256 * T) fused_dft_fwd(const float* __restrict
   __shared__ f2 hx[8 * HXS];
   __shared__ f2 fys[KY * FYS], fxs[SN * KX];
   const int t = threadIdx.x, b = blockIdx.y, c0 = blockIdx.x * 8;
-  for (int i = t; i < KY * SN; i += 256 * T) fys[(i / SN) * FYS + i % SN] = op<BF16>(fy[i]);
-  if (BF16)
-    for (int i = t; i < SN * KX; i += 256 * T) fxs[i] = op<BF16>(fx[i]);
   const int c = (t >> 5) & 7, y = t & 31;
   const int part = __builtin_amdgcn_readfirstlane(t >> 8);
   const int kx0 = KX * part / T, kx1 = KX * (part + 1) / T;
   float row[SN];
   const float4* src =
       reinterpret_cast<const float4*>(h + (((long long)b * SW + c0 + c) * SN + y) * SN);
+  // all loads go out before the first is waited for (tables past their end read
+  // the last entry again)
+  constexpr int NY = (KY * SN + 256 * T - 1) / (256 * T), NX = (SN * KX + 256 * T - 1) / (256 * T);
+  float4 rv[SN / 4];
+  f2 yv[NY], xv[NX];
+#pragma unroll
+  for (int q = 0; q < SN / 4; ++q) rv[q] = src[q];
+#pragma unroll
+  for (int k = 0; k < NY; ++k) yv[k] = fy[min(t + 256 * T * k, KY * SN - 1)];
+  if (BF16)
+#pragma unroll
+    for (int k = 0; k < NX; ++k) xv[k] = fx[min(t + 256 * T * k, SN * KX - 1)];
 #pragma unroll
   for (int q = 0; q < SN / 4; ++q) {
-    const float4 v = src[q];
-    row[4 * q] = op<BF16>(v.x);
-    row[4 * q + 1] = op<BF16>(v.y);
-    row[4 * q + 2] = op<BF16>(v.z);
-    row[4 * q + 3] = op<BF16>(v.w);
+    row[4 * q] = op<BF16>(rv[q].x);
+    row[4 * q + 1] = op<BF16>(rv[q].y);
+    row[4 * q + 2] = op<BF16>(rv[q].z);
+    row[4 * q + 3] = op<BF16>(rv[q].w);
   }
+#pragma unroll
+  for (int k = 0; k < NY; ++k) {
+    const int i = min(t + 256 * T * k, KY * SN - 1);
+    fys[(i / SN) * FYS + i % SN] = op<BF16>(yv[k]);
+  }
+  if (BF16)
+#pragma unroll
+    for (int k = 0; k < NX; ++k) fxs[min(t + 256 * T * k, SN * KX - 1)] = op<BF16>(xv[k]);
   __syncthreads();
   if constexpr (BF16) {  // every product of two rounded operands, as defined
 #pragma unroll 3
@@ -232,7 +248,9 @@ __device__ __forceinline__ int inv_row(int k, int w) {
   if (k == 3 && (w & 3) == 3) return w < 4 ? 0 : SN / 2;
   return w < 4 ? base : SN - base;
 }
-template <bool BF16, int MODE>
+// NT: pixels and outputs non-temporal (batches past the last-level cache: 4096
+// patches 351 us, 367 without).
+template <bool BF16, int MODE, bool NT = false>
 __global__ void __launch_bounds__(INVM_T) __attribute__((amdgpu_waves_per_eu(4)))
 fused_dft_inv_mfma(
     const f2* __restrict__ G, const float* __restrict__ h, const f2* __restrict__ iy,
@@ -263,11 +281,22 @@ fused_dft_inv_mfma(
       }
       gsm[m][ch] = s;
     }
-  } else {
-    const f2* gb = G + (long long)b * SNM * SW;
-    for (int i = t; i < SNM * SW; i += INVM_T) (&gsm[0][0])[i] = op<BF16>(gb[i]);
   }
-  for (int i = t; i < SN * KY; i += INVM_T) iys[i] = op<BF16>(iy[i]);
+  // all loads go out before the first is waited for (arrays past their end read
+  // the last entry again); G's, which the block waits for first, lead (one patch
+  // in FP32: 8.7 us, 11.0 with each staging loop waiting by itself)
+  typedef float float4v __attribute__((ext_vector_type(4)));
+  constexpr int NG = SNM * SW / 2, NGQ = (NG + INVM_T - 1) / INVM_T;
+  constexpr int NYQ = (SN * KY + INVM_T - 1) / INVM_T;
+  float4v gv[NGQ];
+  f2 yv[NYQ];
+  if constexpr (MODE != INV_HEAD) {
+    const float4v* gb = reinterpret_cast<const float4v*>(G + (long long)b * SNM * SW);
+#pragma unroll
+    for (int k = 0; k < NGQ; ++k) gv[k] = gb[min(t + INVM_T * k, NG - 1)];
+  }
+#pragma unroll
+  for (int k = 0; k < NYQ; ++k) yv[k] = iy[min(t + INVM_T * k, SN * KY - 1)];
   // fixed operands: A = pw^T (row o = li, k = i), B = row-transform twiddles
   // (k' < KX: Re ix[k'][x], else -Im ix[k' - KX][x]; column x = li)
   float pwa[SW / 2], ixb[KX];
@@ -286,7 +315,17 @@ fused_dft_inv_mfma(
   float hv[SW / 2];
   if constexpr (MODE != INV_HEAD)
 #pragma unroll
-    for (int s = 0; s < SW / 2; ++s) hv[s] = hb[((2 * s + lh) * SN + inv_row(g0, wave)) * SN + li];
+    for (int s = 0; s < SW / 2; ++s)
+      hv[s] = ld<NT>(&hb[((2 * s + lh) * SN + inv_row(g0, wave)) * SN + li]);
+  if constexpr (MODE != INV_HEAD)
+#pragma unroll
+    for (int k = 0; k < NGQ; ++k) {
+      f2* dst = &gsm[0][0] + 2 * min(t + INVM_T * k, NG - 1);
+      dst[0] = op<BF16>(f2{gv[k].x, gv[k].y});
+      dst[1] = op<BF16>(f2{gv[k].z, gv[k].w});
+    }
+#pragma unroll
+  for (int k = 0; k < NYQ; ++k) iys[min(t + INVM_T * k, SN * KY - 1)] = op<BF16>(yv[k]);
   for (int yc = g0; yc < g0 + groups; ++yc) {
     const int y = inv_row(yc, wave);
     __syncthreads();  // G staged (first group) / the previous group's gy consumed
@@ -333,7 +372,7 @@ fused_dft_inv_mfma(
       if (yc + 1 < g0 + groups)  // rounded (BF16) where used, so the loads stay in flight
 #pragma unroll
         for (int s = 0; s < SW / 2; ++s)
-          hv[s] = hb[((2 * s + lh) * SN + inv_row(yc + 1, wave)) * SN + li];
+          hv[s] = ld<NT>(&hb[((2 * s + lh) * SN + inv_row(yc + 1, wave)) * SN + li]);
     }
 #pragma unroll
     for (int s = 0; s < KX; ++s)
@@ -345,8 +384,8 @@ fused_dft_inv_mfma(
       if constexpr (MODE == INV_LAYER) {
         const float z = acc[r] + pb[o];
         if (z_out) z_out[off] = z;
-        if (apply_gelu) h_out[off] = gelu_fwd_f(z);
-        else if (h_out != z_out) h_out[off] = z;
+        if (apply_gelu) st<NT>(&h_out[off], gelu_fwd_f(z));
+        else if (h_out != z_out) st<NT>(&h_out[off], z);
       } else if (MODE == INV_ADJOINT && zp) {
         h_out[off] = acc[r] * gelu_grad_f(zp[off]);
       } else {
@@ -401,6 +440,10 @@ __global__ void __launch_bounds__(256) mode_mix_head(const f2* __restrict__ A,
 // outputs per half-wave) and uses them for both halves of K; each half-wave
 // writes the 32 outputs of one (patch, mode), one 256-byte run. With BF16 the operands are
 // rounded to bf16 as they are read (their products are exact in FP32).
+// All loads go out together, 16 bytes each for the spectra, and a lane reads both
+// parts of a value at once: 4096 patches in FP32 (321 MB) 77 us, 64 in bf16
+// products 6.2, one 4.9; with the weights read after the spectra were staged, by
+// 8 bytes, 119, 12.4 and 6.7.
 // ADJ is the adjoint, out[b][m][i] = sum_o A[m][b][o] conj(Wm[m][i][o]): a lane
 // then takes channels o = 16 half + s in product s, so that its sixteen
 // weights are one 128-byte run of its row i of Wm.
@@ -410,41 +453,50 @@ __global__ void __launch_bounds__(256) mode_mix_mm(const f2* __restrict__ A,
                                                    const f2* __restrict__ Wm, int nmode, int B,
                                                    f2* __restrict__ out) {
   __shared__ f2 as[MM_G][32][SW + 1];  // [mode][patch][i]
+  typedef float float4v __attribute__((ext_vector_type(4)));
   const int t = threadIdx.x, wave = t >> 6, lane = t & 63, li = lane & 31, lh = lane >> 5;
   const int b0 = blockIdx.x * 32, m0 = blockIdx.y * MM_G;
-  for (int q = t; q < MM_G * 32 * SW; q += 256) {
-    const int mm = q / (32 * SW), bb = (q / SW) % 32, i = q % SW;
-    const int m = m0 + mm, b = b0 + bb;
-    as[mm][bb][i] = (m < nmode && b < B) ? op<BF16>(A[((long long)m * B + b) * SW + i])
-                                         : f2{0.f, 0.f};
-  }
-  __syncthreads();
   const int m = m0 + wave;
-  if (m >= nmode) return;  // no barrier follows
-  const f2* wm = Wm + (long long)m * SW * SW;
+  // the weights' loads go out with the spectra's (a wave past the last mode
+  // reads the last one's)
+  const f2* wm = Wm + (long long)min(m, nmode - 1) * SW * SW;
   f2 wv[SW / 2];
 #pragma unroll
-  for (int s = 0; s < SW / 2; ++s) {
-    if (ADJ) {
-      const f2 w = wm[li * SW + 16 * lh + s];
-      wv[s] = op<BF16>(f2{w.x, -w.y});
-    } else {
-      wv[s] = op<BF16>(wm[(2 * s + lh) * SW + li]);
-    }
+  for (int s = 0; s < SW / 2; ++s)
+    wv[s] = ADJ ? wm[li * SW + 16 * lh + s] : wm[(2 * s + lh) * SW + li];
+  constexpr int NQ = MM_G * 32 * SW / 2 / 256;  // pairs of spectra per thread
+  float4v av[NQ];
+#pragma unroll
+  for (int k = 0; k < NQ; ++k) {
+    const int q = t + 256 * k, mm = q / (16 * SW), bb = (q / 16) % 32, i = 2 * (q % 16);
+    const bool on = m0 + mm < nmode && b0 + bb < B;
+    const long long at = on ? ((long long)(m0 + mm) * B + b0 + bb) * SW + i : 0;
+    av[k] = *reinterpret_cast<const float4v*>(A + at);
+    if (!on) av[k] = float4v{0.f, 0.f, 0.f, 0.f};
   }
-  auto kidx = [&](int s) { return ADJ ? 16 * lh + s : 2 * s + lh; };
+#pragma unroll
+  for (int k = 0; k < NQ; ++k) {
+    const int q = t + 256 * k, mm = q / (16 * SW), bb = (q / 16) % 32, i = 2 * (q % 16);
+    as[mm][bb][i] = op<BF16>(f2{av[k].x, av[k].y});
+    as[mm][bb][i + 1] = op<BF16>(f2{av[k].z, av[k].w});
+  }
+  __syncthreads();
+  if (m >= nmode) return;  // no barrier follows
+#pragma unroll
+  for (int s = 0; s < SW / 2; ++s) wv[s] = op<BF16>(ADJ ? f2{wv[s].x, -wv[s].y} : wv[s]);
+  f2 a[SW / 2];
+#pragma unroll
+  for (int s = 0; s < SW / 2; ++s) a[s] = as[wave][li][ADJ ? 16 * lh + s : 2 * s + lh];
   floatx16 cre = {0}, cim = {0};
 #pragma unroll
   for (int s = 0; s < SW / 2; ++s) {  // real parts of A
-    const float a = as[wave][li][kidx(s)].x;
-    cre = __builtin_amdgcn_mfma_f32_32x32x2f32(a, wv[s].x, cre, 0, 0, 0);
-    cim = __builtin_amdgcn_mfma_f32_32x32x2f32(a, wv[s].y, cim, 0, 0, 0);
+    cre = __builtin_amdgcn_mfma_f32_32x32x2f32(a[s].x, wv[s].x, cre, 0, 0, 0);
+    cim = __builtin_amdgcn_mfma_f32_32x32x2f32(a[s].x, wv[s].y, cim, 0, 0, 0);
   }
 #pragma unroll
   for (int s = 0; s < SW / 2; ++s) {  // imaginary parts of A
-    const float a = as[wave][li][kidx(s)].y;
-    cre = __builtin_amdgcn_mfma_f32_32x32x2f32(a, -wv[s].y, cre, 0, 0, 0);
-    cim = __builtin_amdgcn_mfma_f32_32x32x2f32(a, wv[s].x, cim, 0, 0, 0);
+    cre = __builtin_amdgcn_mfma_f32_32x32x2f32(a[s].y, -wv[s].y, cre, 0, 0, 0);
+    cim = __builtin_amdgcn_mfma_f32_32x32x2f32(a[s].y, wv[s].x, cim, 0, 0, 0);
   }
   f2* dst = out + ((long long)b0 * nmode + m) * SW + li;
 #pragma unroll
@@ -590,6 +642,7 @@ hipError_t sur_fused_dft_inv(const float* G, const float* h, const float* iy, co
         reinterpret_cast<const f2*>(ix), pw, pb, z_out, h_out, gelu ? 1 : 0, nullptr);
   };
   if (bf16) go(fused_dft_inv_mfma<true, INV_LAYER>);
+  else if (sur_past_cache(2 * B)) go(fused_dft_inv_mfma<false, INV_LAYER, true>);
   else go(fused_dft_inv_mfma<false, INV_LAYER>);
   return hipGetLastError();
 }
@@ -659,8 +712,9 @@ hipError_t sur_lift(const float* x, const float* lw, const float* lb, float* h, 
                     hipStream_t s) {
   const int P = B <= 64 ? 2 : 1, Q = B <= 64 ? 4 : 1;
   const dim3 grid(B, P, Q);
-  if (bf16) lift_kernel<true><<<grid, 512 / P, 0, s>>>(x, lw, lb, h);
-  else lift_kernel<false><<<grid, 512 / P, 0, s>>>(x, lw, lb, h);
+  auto go = [&](auto kern) { kern<<<grid, 512 / P, 0, s>>>(x, lw, lb, h); };
+  if (bf16) go(lift_kernel<true>);
+  else go(lift_kernel<false>);
   return hipGetLastError();
 }
 hipError_t sur_encode(const float* n, float* x, int B, hipStream_t s) {

@@ -7,7 +7,7 @@
 // per layer, intermediates of 2-9 MB per 64 patches between them, tiles padded
 // from 9 or 17 columns to 64) and one block per channel for the biases, a loss
 // and gradient took 2.27 ms in bf16 products at 64 patches and 4.93 ms in FP32
-// at 256, against 0.87 and 1.20 ms as here.
+// at 256, against 0.65 and 1.10 ms as here.
 //
 // The bf16 adjoint rounds both operands of every product to bf16 (nearest
 // even) and sums in FP32 on v_mfma_f32_32x32x16_bf16 over K in its natural
@@ -408,6 +408,15 @@ __global__ void __launch_bounds__(512) dft_adjoint_bf16(const float* __restrict_
   const int c0 = blockIdx.y * CH;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, li = lane & 31, lh = lane >> 5;
   const long long b = blockIdx.x;
+  // the pixels' loads lead the tables'
+  float4 gv[CH / 8][4];
+#pragma unroll
+  for (int q = 0; q < CH / 8; ++q) {
+    const float* row = gz + ((b * SW + c0 + wave * (CH / 8) + q) * SN + li) * SN;
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+      gv[q][s] = *reinterpret_cast<const float4*>(row + 16 * (s / 2) + 8 * lh + 4 * (s % 2));
+  }
   const int kxl = li % SKX;  // column li < 18 of the row transform: kx, Re or Im
   const bool imag = li >= SKX;
   bf16x8 bx[2], ar[2], ai[2];
@@ -425,12 +434,10 @@ __global__ void __launch_bounds__(512) dft_adjoint_bf16(const float* __restrict_
 #pragma unroll
   for (int q = 0; q < CH / 8; ++q) {
     const int o = wave * (CH / 8) + q;
-    const float* row = gz + ((b * SW + c0 + o) * SN + li) * SN;
     floatx16 d = {0};
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
-      const float4 v0 = *reinterpret_cast<const float4*>(row + 16 * s + 8 * lh);
-      const float4 v1 = *reinterpret_cast<const float4*>(row + 16 * s + 8 * lh + 4);
+      const float4 v0 = gv[q][2 * s], v1 = gv[q][2 * s + 1];
       const bf16x8 a = {(__bf16)v0.x, (__bf16)v0.y, (__bf16)v0.z, (__bf16)v0.w,
                         (__bf16)v1.x, (__bf16)v1.y, (__bf16)v1.z, (__bf16)v1.w};
       d = mm16(a, bx[s], d);
@@ -481,6 +488,30 @@ __global__ void __launch_bounds__(512) dft_fwd_adjoint_bf16(
   __shared__ __attribute__((aligned(16))) __bf16 tt[ROWS][2][SW][16];
   const int t = threadIdx.x, wave = t >> 6, lane = t & 63, li = lane & 31, lh = lane >> 5;
   const long long b = blockIdx.x;
+  // the loads of the wave's first row (a row ahead below) and of the rows'
+  // operands go out first: they are waited for after the columns
+  float gv[16], zv[16];
+  f2 xw[8];
+  float pv[16];
+  auto load_row = [&](int yl) {
+    const int y = 8 * (yl / 8 * S + blockIdx.y) + wave;
+    if constexpr (!HEAD)
+#pragma unroll
+      for (int j = 0; j < 16; ++j)
+        gv[j] = gz[((b * SW + 16 * (j / 8) + 8 * lh + j % 8) * SN + y) * SN + li];
+    if (zp)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) zv[r] = zp[((b * SW + drow(r, lh)) * SN + y) * SN + li];
+  };
+  load_row(wave);
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    xw[j] = fx[li * KX + min(8 * lh + j, KX - 1)];
+    if constexpr (!HEAD) {
+      pv[j] = pw[li * SW + 8 * lh + j];
+      pv[8 + j] = pw[li * SW + 16 + 8 * lh + j];
+    }
+  }
   bf16x8 ar[KS], ai[KS];
 #pragma unroll
   for (int s = 0; s < KS; ++s)
@@ -530,12 +561,11 @@ __global__ void __launch_bounds__(512) dft_fwd_adjoint_bf16(
 #pragma unroll
   for (int j = 0; j < 8; ++j) {
     const int kx = 8 * lh + j;
-    const f2 w = fx[li * KX + min(kx, KX - 1)];
-    xr[j] = (__bf16)(kx < KX ? w.x : 0.f);
-    xi[j] = (__bf16)(kx < KX ? -w.y : 0.f);
+    xr[j] = (__bf16)(kx < KX ? xw[j].x : 0.f);
+    xi[j] = (__bf16)(kx < KX ? -xw[j].y : 0.f);
     if constexpr (!HEAD) {
-      pa[0][j] = (__bf16)pw[li * SW + kx];
-      pa[1][j] = (__bf16)pw[li * SW + 16 + kx];
+      pa[0][j] = (__bf16)pv[j];
+      pa[1][j] = (__bf16)pv[8 + j];
     }
   }
   __syncthreads();
@@ -550,18 +580,22 @@ __global__ void __launch_bounds__(512) dft_fwd_adjoint_bf16(
         bf16x8 g;
 #pragma unroll
         for (int j = 0; j < 8; ++j)
-          g[j] = (__bf16)gz[((b * SW + 16 * s + 8 * lh + j) * SN + y) * SN + li];
+          g[j] = (__bf16)gv[8 * s + j];
         accp = mm16(pa[s], g, accp);
       }
     }
     acc = mm16(tr, xr, acc);
     acc = mm16(neg8(ti), xi, acc);
+    float zc[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) zc[r] = zp ? zv[r] : 0.f;
+    if (yl + 8 < ROWS) load_row(yl + 8);
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const long long off = ((b * SW + drow(r, lh)) * SN + y) * SN + li;
       float v = acc[r];
       if constexpr (!HEAD) v += accp[r];
-      if (zp) v *= gelu_grad_f(zp[off]);
+      if (zp) v *= gelu_grad_f(zc[r]);
       out[off] = v;
     }
   }
@@ -641,7 +675,8 @@ hipError_t sur_mode_mix_adjoint_bf16(const float* gG, const float* Wm, int B, fl
 }
 // Splits of the two transforms' adjoints: as many as keep a launch within two
 // blocks per CU. At 64 patches, 64 blocks took 29 us (forward half) and 11.9 us
-// (inverse half), 256 blocks 13 and 10.5.
+// (inverse half), 256 blocks with their loads
+// ahead of the tables 10.4 and 10.4.
 hipError_t sur_dft_adjoint_bf16(const float* gz, const float* iy, const float* ix, int B,
                                 float* gG, hipStream_t s) {
   auto go = [&](auto kern, int splits) {

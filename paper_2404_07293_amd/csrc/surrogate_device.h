@@ -15,6 +15,18 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 // a patch's side, the layers' spectral half plane and the channel count
 constexpr int SN = 32, SKY = 17, SKX = 9, SNM = SKY * SKX, SW = 32;
 
+// Loads and stores, non-temporal with NT.
+template <bool NT, typename V>
+__device__ __forceinline__ V ld(const V* p) {
+  if constexpr (NT) return __builtin_nontemporal_load(p);
+  else return *p;
+}
+template <bool NT, typename V>
+__device__ __forceinline__ void st(V* p, V v) {
+  if constexpr (NT) __builtin_nontemporal_store(v, p);
+  else *p = v;
+}
+
 // round to bf16, nearest even, by the hardware's conversion (two values per
 // instruction where the compiler pairs them)
 __device__ __forceinline__ float rbf(float x) { return (float)(__bf16)x; }
