@@ -44,6 +44,46 @@ __device__ __forceinline__ zd zmul(zd a, zd b) {
   return {a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x};
 }
 
+// ---------------------------------------------------------------- exterior
+// Planes outside the sample. The modal sum's launch takes them as blocks after
+// its own (they share no value with it; 150 x 90 x 45 points, a third of the
+// planes outside: 14.0 us a call, 16.9 with a launch of their own);
+// exterior_kernel is that launch where there is no modal sum or more than one
+// volume.
+struct ExtArgs {
+  const ExtPlane* ext;
+  const zd *coef, *ksz;
+  int n_ext;
+};
+template <typename T>
+__device__ inline void exterior_entry(const ExtArgs& x, long long t, int M,
+                                      cx<T>* __restrict__ spec) {
+  const int n3 = 3 * M;
+  if (t >= (long long)x.n_ext * n3) return;
+  const int r = (int)(t % n3);
+  const ExtPlane e = x.ext[t / n3];
+  const int m = r % M;
+  zd val;
+  if (e.kind == 0) {
+    const zd kz = x.ksz[m];
+    const zd gi = zexp_i({kz.x * e.dz, kz.y * e.dz});
+    const zd gr = zexp_i({-kz.x * e.dz, -kz.y * e.dz});
+    const zd pi = zmul(x.coef[r], gi), pr = zmul(x.coef[n3 + r], gr);
+    val = {pi.x + pr.x, pi.y + pr.y};
+  } else {
+    const zd kz = x.ksz[M + m];
+    val = zmul(x.coef[2 * n3 + r], zexp_i({kz.x * e.dz, kz.y * e.dz}));
+  }
+  spec[(long long)e.plane * n3 + r] = {(T)val.x, (T)val.y};
+}
+
+template <typename T>
+__global__ void exterior_kernel(ExtArgs x, int M, long long spec_stride, cx<T>* __restrict__ spec) {
+  x.coef += (long long)blockIdx.y * 9 * M;  // one volume (illumination) per blockIdx.y
+  exterior_entry<T>(x, (long long)blockIdx.x * blockDim.x + threadIdx.x, M,
+                    spec + blockIdx.y * spec_stride);
+}
+
 // ---------------------------------------------------------------- phase
 // f = a g_f(z_p) and bk = b g_b(z_p) of plane p of a task.
 __device__ __forceinline__ void phase_pair(zd g, zd a, zd b, const double* __restrict__ dzp, zd& f,
@@ -104,9 +144,14 @@ template <typename T, int ZT, int RW, bool PH>
 __global__ void __launch_bounds__(256) modal_kernel(
     const cx<T>* __restrict__ P, const cx<T>* __restrict__ w, const zd* __restrict__ kg,
     const zd* __restrict__ a, const zd* __restrict__ b, const double* __restrict__ dz,
-    const Task* __restrict__ tasks, int M, int nb_xy, int nb_z, int jc, cx<T>* __restrict__ spec) {
+    const Task* __restrict__ tasks, int M, int nb_xy, int nb_z, int jc, int nmodal, ExtArgs x,
+    cx<T>* __restrict__ spec) {
   constexpr int NV = 2 * RW * ZT;
   static_assert(NV <= 64 && (NV & (NV - 1)) == 0, "value count must be a power of two <= 64");
+  if ((int)blockIdx.x >= nmodal) {
+    exterior_entry<T>(x, (long long)(blockIdx.x - nmodal) * 256 + threadIdx.x, M, spec);
+    return;
+  }
   extern __shared__ unsigned char smem_raw[];
   cx<T>* sw = reinterpret_cast<cx<T>*>(smem_raw);  // [ZT][jc]
   const int n2 = 2 * M, n3 = 3 * M;
@@ -216,10 +261,15 @@ __device__ __forceinline__ float2 cexpi_f(float re, float im) {
 template <int ZT, int RW>
 __global__ void __launch_bounds__(256) modal_f32_kernel(
     const float4* __restrict__ P, const float2* __restrict__ kgab, const Task* __restrict__ tasks,
-    const float2* __restrict__ tdz, int M, int L, int nb_xy, int nb_z, int jc,
-    float2* __restrict__ spec) {
+    const float2* __restrict__ tdz, int M, int L, int nb_xy, int nb_z, int jc, int nmodal,
+    ExtArgs x, float2* __restrict__ spec) {
   constexpr int NV = 2 * RW * ZT;
   static_assert(NV <= 64 && (NV & (NV - 1)) == 0, "value count must be a power of two <= 64");
+  if ((int)blockIdx.x >= nmodal) {
+    exterior_entry<float>(x, (long long)(blockIdx.x - nmodal) * 256 + threadIdx.x, M,
+                          reinterpret_cast<cx<float>*>(spec));
+    return;
+  }
   extern __shared__ float4 sw4[];  // [ZT][jc / 2]
   float2* sw = reinterpret_cast<float2*>(sw4);
   const int n2 = 2 * M, n3 = 3 * M, h2 = M;  // h2 = float4 per row
@@ -368,7 +418,7 @@ __global__ void __launch_bounds__(256) modal_f32_kernel(
 }
 
 template <int ZT, int RW>
-hipError_t launch_modal_f32_rw(const SynthArgs& a, hipStream_t s) {
+hipError_t launch_modal_f32_rw(const SynthArgs& a, hipStream_t s, const ExtArgs& x) {
   const int n2 = 2 * a.M;
   const int rows_per_block = 4 * RW;
   const int nb_xy = (n2 + rows_per_block - 1) / rows_per_block;
@@ -380,24 +430,25 @@ hipError_t launch_modal_f32_rw(const SynthArgs& a, hipStream_t s) {
   const size_t lds = (size_t)ZT * ((jc / 2 + 63) / 64 * 64) * sizeof(float4);
   const long long nblocks = (long long)a.ntasks * (nb_xy + nb_z);
   if (nblocks == 0) return hipSuccess;
-  modal_f32_kernel<ZT, RW><<<(unsigned)nblocks, 256, lds, s>>>(
+  const long long ext = ((long long)x.n_ext * 3 * a.M + 255) / 256;
+  modal_f32_kernel<ZT, RW><<<(unsigned)(nblocks + ext), 256, lds, s>>>(
       reinterpret_cast<const float4*>(a.P), reinterpret_cast<const float2*>(a.kgab32), a.tasks,
-      reinterpret_cast<const float2*>(a.task_dz32), a.M, a.L, nb_xy, nb_z, jc,
+      reinterpret_cast<const float2*>(a.task_dz32), a.M, a.L, nb_xy, nb_z, jc, (int)nblocks, x,
       reinterpret_cast<float2*>(a.spec));
   return hipGetLastError();
 }
 
 // Rows per wave RW with 2 RW ZT <= 64 accumulated values per lane.
 template <int ZT>
-hipError_t launch_modal_f32(const SynthArgs& a, hipStream_t s) {
+hipError_t launch_modal_f32(const SynthArgs& a, hipStream_t s, const ExtArgs& x) {
   switch (a.modal_rw) {
-    case 2: return launch_modal_f32_rw<ZT, 2>(a, s);
-    case 4: return launch_modal_f32_rw<ZT, 4>(a, s);
+    case 2: return launch_modal_f32_rw<ZT, 2>(a, s, x);
+    case 4: return launch_modal_f32_rw<ZT, 4>(a, s, x);
     case 8:
-      if constexpr (ZT <= 4) return launch_modal_f32_rw<ZT, 8>(a, s);
+      if constexpr (ZT <= 4) return launch_modal_f32_rw<ZT, 8>(a, s, x);
       break;
     case 16:
-      if constexpr (ZT <= 2) return launch_modal_f32_rw<ZT, 16>(a, s);
+      if constexpr (ZT <= 2) return launch_modal_f32_rw<ZT, 16>(a, s, x);
       break;
     default: break;
   }
@@ -559,33 +610,6 @@ __global__ void __launch_bounds__(256) modal_multi_kernel(
     if (row < row_end && ki < kcount && p < tk.count)
       spec[((long long)(k0 + ki) * fz + tk.plane0 + p) * n3 + row] = make_float2(x, y);
   }
-}
-
-// ---------------------------------------------------------------- exterior
-template <typename T>
-__global__ void exterior_kernel(const ExtPlane* __restrict__ ext, int n_ext, int M,
-                                const zd* __restrict__ coef, const zd* __restrict__ ksz,
-                                long long spec_stride, cx<T>* __restrict__ spec) {
-  const int n3 = 3 * M;
-  long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= (long long)n_ext * n3) return;
-  coef += (long long)blockIdx.y * 3 * n3;  // one volume (illumination) per blockIdx.y
-  spec += blockIdx.y * spec_stride;
-  const int r = (int)(t % n3);
-  const ExtPlane e = ext[t / n3];
-  const int m = r % M;
-  zd val;
-  if (e.kind == 0) {
-    const zd kz = ksz[m];
-    const zd gi = zexp_i({kz.x * e.dz, kz.y * e.dz});
-    const zd gr = zexp_i({-kz.x * e.dz, -kz.y * e.dz});
-    const zd pi = zmul(coef[r], gi), pr = zmul(coef[n3 + r], gr);
-    val = {pi.x + pr.x, pi.y + pr.y};
-  } else {
-    const zd kz = ksz[M + m];
-    val = zmul(coef[2 * n3 + r], zexp_i({kz.x * e.dz, kz.y * e.dz}));
-  }
-  spec[(long long)e.plane * n3 + r] = {(T)val.x, (T)val.y};
 }
 
 // ---------------------------------------------------------------- inverse DFT
@@ -954,7 +978,7 @@ hipError_t launch_idft(const SynthArgs& a, hipStream_t s) {
 inline unsigned blocks_for(long long n, int bs) { return (unsigned)((n + bs - 1) / bs); }
 
 template <typename T, int ZT>
-hipError_t launch_modal(const SynthArgs& a, hipStream_t s, bool phases) {
+hipError_t launch_modal(const SynthArgs& a, hipStream_t s, bool phases, const ExtArgs& x) {
   constexpr int RW = (sizeof(T) == 4) ? (ZT <= 4 ? 8 : 4) : (ZT <= 2 ? 4 : 2);
   const int n2 = 2 * a.M;
   const int rows_per_block = 4 * RW;
@@ -967,11 +991,12 @@ hipError_t launch_modal(const SynthArgs& a, hipStream_t s, bool phases) {
   const long long nblocks = (long long)a.ntasks * (nb_xy + nb_z);
   if (nblocks == 0) return hipSuccess;
   auto go = [&](auto kern) {
-    kern<<<(unsigned)nblocks, 256, lds, s>>>(
+    const long long ext = ((long long)x.n_ext * 3 * a.M + 255) / 256;
+    kern<<<(unsigned)(nblocks + ext), 256, lds, s>>>(
         reinterpret_cast<const cx<T>*>(a.P), reinterpret_cast<const cx<T>*>(a.w),
         reinterpret_cast<const zd*>(a.kg), reinterpret_cast<const zd*>(a.a),
         reinterpret_cast<const zd*>(a.b), a.task_dz, a.tasks, a.M, nb_xy, nb_z, jc,
-        reinterpret_cast<cx<T>*>(a.spec));
+        (int)nblocks, x, reinterpret_cast<cx<T>*>(a.spec));
     return hipGetLastError();
   };
   return phases ? go(modal_kernel<T, ZT, RW, true>) : go(modal_kernel<T, ZT, RW, false>);
@@ -984,52 +1009,57 @@ hipError_t launch_synthesis(const SynthArgs& a, hipStream_t s, hipEvent_t* ev) {
   auto mark = [&](int i) -> hipError_t { return ev ? hipEventRecord(ev[i], s) : hipSuccess; };
   if ((e = mark(0)) != hipSuccess) return e;
   const bool modal = (a.stages & kStageModal) != 0;
+  const ExtArgs x{reinterpret_cast<const ExtPlane*>(a.ext_planes),
+                  reinterpret_cast<const zd*>(a.ext), reinterpret_cast<const zd*>(a.ksz),
+                  (a.stages & kStageExterior) ? a.n_ext : 0};
+  // the exterior planes ride with the modal sum, unless the stages are timed
+  const bool ride = modal && a.ntasks > 0 && a.nvol == 1 && !ev;
+  ExtArgs xm = x;
+  if (!ride) xm.n_ext = 0;
   if (!modal) {
     if ((e = mark(1)) != hipSuccess) return e;
-  } else if (a.ntasks > 0 && sizeof(T) == 8) {
-    // The phases of a task are made in the modal sum's blocks where a thread
-    // makes at most six (each block repeats them), in a launch before it
-    // otherwise. 4 tasks of 8 planes: M = 25 12.8 us a call fused, 18.2 with the
-    // launch; M = 81 15.9 and 16.5; M = 121 16.9 and 16.5; 8 tasks at M = 225
-    // 28.2 and 22.2.
-    const bool fused = (long long)a.zt * n2 <= 1536;
-    if (!fused) {
-      phase_kernel<T><<<blocks_for((long long)a.ntasks * a.zt * n2, 256), 256, 0, s>>>(
-          a.tasks, a.task_dz, reinterpret_cast<const zd*>(a.kg),
-          reinterpret_cast<const zd*>(a.a), reinterpret_cast<const zd*>(a.b), n2, a.zt,
-          a.ntasks, reinterpret_cast<cx<T>*>(a.w));
-      if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
-    if ((e = mark(1)) != hipSuccess) return e;
-    switch (a.zt) {
-      case 1: e = launch_modal<T, 1>(a, s, fused); break;
-      case 2: e = launch_modal<T, 2>(a, s, fused); break;
-      case 4: e = launch_modal<T, 4>(a, s, fused); break;
-      case 8: e = launch_modal<T, 8>(a, s, fused); break;
-      default: return hipErrorInvalidValue;
-    }
-    if (e != hipSuccess) return e;
   } else if (a.ntasks > 0) {
-    if ((e = mark(1)) != hipSuccess) return e;
-    switch (a.zt) {
-      case 1: e = launch_modal_f32<1>(a, s); break;
-      case 2: e = launch_modal_f32<2>(a, s); break;
-      case 4: e = launch_modal_f32<4>(a, s); break;
-      case 8: e = launch_modal_f32<8>(a, s); break;
-      default: return hipErrorInvalidValue;
+    if constexpr (sizeof(T) == 8) {
+      // The phases of a task are made in the modal sum's blocks where a thread
+      // makes at most six (each block repeats them), in a launch before it
+      // otherwise. 4 tasks of 8 planes: M = 25 12.8 us a call fused, 18.2 with the
+      // launch; M = 81 15.9 and 16.5; M = 121 16.9 and 16.5; 8 tasks at M = 225
+      // 28.2 and 22.2.
+      const bool fused = (long long)a.zt * n2 <= 1536;
+      if (!fused) {
+        phase_kernel<T><<<blocks_for((long long)a.ntasks * a.zt * n2, 256), 256, 0, s>>>(
+            a.tasks, a.task_dz, reinterpret_cast<const zd*>(a.kg),
+            reinterpret_cast<const zd*>(a.a), reinterpret_cast<const zd*>(a.b), n2, a.zt,
+            a.ntasks, reinterpret_cast<cx<T>*>(a.w));
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+      }
+      if ((e = mark(1)) != hipSuccess) return e;
+      switch (a.zt) {
+        case 1: e = launch_modal<T, 1>(a, s, fused, xm); break;
+        case 2: e = launch_modal<T, 2>(a, s, fused, xm); break;
+        case 4: e = launch_modal<T, 4>(a, s, fused, xm); break;
+        case 8: e = launch_modal<T, 8>(a, s, fused, xm); break;
+        default: return hipErrorInvalidValue;
+      }
+      if (e != hipSuccess) return e;
+    } else {
+      if ((e = mark(1)) != hipSuccess) return e;
+      switch (a.zt) {
+        case 1: e = launch_modal_f32<1>(a, s, xm); break;
+        case 2: e = launch_modal_f32<2>(a, s, xm); break;
+        case 4: e = launch_modal_f32<4>(a, s, xm); break;
+        case 8: e = launch_modal_f32<8>(a, s, xm); break;
+        default: return hipErrorInvalidValue;
+      }
+      if (e != hipSuccess) return e;
     }
-    if (e != hipSuccess) return e;
   } else if ((e = mark(1)) != hipSuccess) {
     return e;
   }
   if ((e = mark(2)) != hipSuccess) return e;
-  if (a.n_ext > 0 && (a.stages & kStageExterior)) {
-    exterior_kernel<T><<<dim3(blocks_for((long long)a.n_ext * 3 * a.M, 256), a.nvol), 256, 0,
-                         s>>>(
-        reinterpret_cast<const ExtPlane*>(a.ext_planes), a.n_ext, a.M,
-        reinterpret_cast<const zd*>(a.ext), reinterpret_cast<const zd*>(a.ksz),
-        (long long)a.fz * 3 * a.M,
-        reinterpret_cast<cx<T>*>(a.spec));
+  if (x.n_ext > 0 && !ride) {
+    exterior_kernel<T><<<dim3(blocks_for((long long)x.n_ext * 3 * a.M, 256), a.nvol), 256, 0, s>>>(
+        x, a.M, (long long)a.fz * 3 * a.M, reinterpret_cast<cx<T>*>(a.spec));
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   if ((e = mark(3)) != hipSuccess) return e;
