@@ -163,6 +163,23 @@ __device__ __forceinline__ int xcd_remap(int b, int nb) {
   return (b % 8) * (nb / 8) + b / 8;
 }
 
+// c += a b with both split: hi.hi + hi.lo + lo.hi
+template <int MODE>
+__device__ __forceinline__ void split_products(u16x8 ah, u16x8 al, u16x8 bh, u16x8 bl,
+                                               floatx16& c) {
+  auto mf = [&](u16x8 a, u16x8 b) {
+    if constexpr (MODE == kBF16)
+      c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a),
+                                                  __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+    else
+      c = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(halfx8, a),
+                                                 __builtin_bit_cast(halfx8, b), c, 0, 0, 0);
+  };
+  mf(ah, bh);
+  mf(ah, bl);
+  mf(al, bh);
+}
+
 template <int MODE>
 __global__ void __launch_bounds__(256) idft_y_kernel(
     const void* __restrict__ amat, const void* __restrict__ bmat,
@@ -252,23 +269,10 @@ __global__ void __launch_bounds__(256) idft_y_kernel(
           const u16x8 bl0 = *reinterpret_cast<const u16x8*>(Bl + o0);
           const u16x8 bh1 = *reinterpret_cast<const u16x8*>(Bh + o1);
           const u16x8 bl1 = *reinterpret_cast<const u16x8*>(Bl + o1);
-          if constexpr (MODE == kBF16) {
-#define MF(a, b, c) c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), \
-                                                                __builtin_bit_cast(bf16x8, b), c, 0, 0, 0)
-            MF(arh[ks], bh0, cr0); MF(arh[ks], bl0, cr0); MF(arl[ks], bh0, cr0);
-            MF(aih[ks], bh0, ci0); MF(aih[ks], bl0, ci0); MF(ail[ks], bh0, ci0);
-            MF(arh[ks], bh1, cr1); MF(arh[ks], bl1, cr1); MF(arl[ks], bh1, cr1);
-            MF(aih[ks], bh1, ci1); MF(aih[ks], bl1, ci1); MF(ail[ks], bh1, ci1);
-#undef MF
-          } else {
-#define MF(a, b, c) c = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(halfx8, a), \
-                                                               __builtin_bit_cast(halfx8, b), c, 0, 0, 0)
-            MF(arh[ks], bh0, cr0); MF(arh[ks], bl0, cr0); MF(arl[ks], bh0, cr0);
-            MF(aih[ks], bh0, ci0); MF(aih[ks], bl0, ci0); MF(ail[ks], bh0, ci0);
-            MF(arh[ks], bh1, cr1); MF(arh[ks], bl1, cr1); MF(arl[ks], bh1, cr1);
-            MF(aih[ks], bh1, ci1); MF(aih[ks], bl1, ci1); MF(ail[ks], bh1, ci1);
-#undef MF
-          }
+          split_products<MODE>(arh[ks], arl[ks], bh0, bl0, cr0);
+          split_products<MODE>(aih[ks], ail[ks], bh0, bl0, ci0);
+          split_products<MODE>(arh[ks], arl[ks], bh1, bl1, cr1);
+          split_products<MODE>(aih[ks], ail[ks], bh1, bl1, ci1);
         }
       }
       const float inv = (MODE == kFP16) ? 1.f / bscale[pc] : 1.f;
@@ -291,9 +295,175 @@ __global__ void __launch_bounds__(256) idft_y_kernel(
   }
 }
 
+// ---------------------------------------------------------------- both passes, split modes
+// The y pass above with the x pass in its blocks: a block forms T for its 64
+// columns, splits it and keeps the operand in LDS, so that it neither goes
+// through memory nor waits for a launch. Per plane/component: the spectrum is in
+// LDS; 64 columns x 4 row groups of threads run the Horner chains as in the x
+// pass and write the operand [hi|lo][k/8][64][8]; after one barrier the waves
+// multiply and store. Spectrum and operand have two buffers each, and the next
+// spectrum is loaded during the products, so that a wave's stores overlap the
+// next plane's chains. The column tiles of the two 128-row halves of 256 rows
+// repeat the x pass (a tenth of the stores' time). Bound by the field's stores:
+// 256 x 256 x 64 points, V = 15 (101 MB): 21.9 us, 29.0 in two launches (FP16:
+// 21.6 and 35.1).
+template <int MODE, int KS>
+__global__ void __launch_bounds__(256) idft_xy_kernel(
+    const c32* __restrict__ spec, const c32* __restrict__ wx, const void* __restrict__ amat, int U,
+    int V, int fx, int fy, int fz, int ngt, int nft, int pcb, c32* __restrict__ E) {
+  static_assert(MODE != kF32, "FP32 operands go through memory");
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+  __shared__ float s_norm[2][32];
+  constexpr int Kp = 16 * KS, C8 = Kp / 8;
+  const int M = U * V;
+  constexpr int bsize = 2 * C8 * FB * 8;  // 16-bit values of one operand buffer
+  unsigned short* bt = reinterpret_cast<unsigned short*>(smem_raw);  // [2][hi|lo][C8][FB][8]
+  c32* S = reinterpret_cast<c32*>(bt + 2 * bsize);                   // [2][V][U]
+  const int n_pc = fz * 3;
+  const int tile = xcd_remap(blockIdx.x, gridDim.x);
+  const int ft = tile % nft;
+  const int gt = (tile / nft) % ngt;
+  const int pg = tile / (nft * ngt);
+  const int pc0 = pg * pcb, pc1 = min(n_pc, pc0 + pcb);
+  const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
+  const int li = lane & 31, lh = lane >> 5;
+  const int g0 = gt * GB + wave * 32, f0 = ft * FB;
+  const int ga = min(g0 + li, fy - 1);  // A row of this lane (rows past fy are not stored)
+  const int col = t % FB, q = t / FB, f = min(f0 + col, fx - 1);
+  typedef float f2v __attribute__((ext_vector_type(2)));
+  for (int i = t; i < M; i += 256) S[i] = spec[(long long)pc0 * M + i];
+  const c32 w = wx[f], sh = wx[fx + f];
+  // A[re|im][hi|lo][Kp/8][fy][8]
+  const unsigned short* A = reinterpret_cast<const unsigned short*>(amat);
+  const long long aq = (long long)Kp * fy;  // elements per (re|im, hi|lo) plane
+  u16x8 arh[KS], arl[KS], aih[KS], ail[KS];
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) {
+    const long long o = ((long long)(2 * ks + lh) * fy + ga) * 8;
+    arh[ks] = *reinterpret_cast<const u16x8*>(A + 0 * aq + o);
+    arl[ks] = *reinterpret_cast<const u16x8*>(A + 1 * aq + o);
+    aih[ks] = *reinterpret_cast<const u16x8*>(A + 2 * aq + o);
+    ail[ks] = *reinterpret_cast<const u16x8*>(A + 3 * aq + o);
+  }
+  // the padding rows 2V .. Kp - 1 stay zero
+  for (int i = t; i < 4 * (Kp - 2 * V) * FB; i += 256) {
+    const int k = 2 * V + i / FB % (Kp - 2 * V), h = i / FB / (Kp - 2 * V);  // (buffer, part)
+    bt[h * (bsize / 2) + ((k / 8) * FB + i % FB) * 8 + k % 8] = 0;
+  }
+  __syncthreads();
+  for (int pc = pc0; pc < pc1; ++pc) {
+    const int buf = (pc - pc0) & 1;
+    const c32* Sb = S + buf * M;
+    float scale = 1.f;
+    if (MODE == kFP16) {
+      if (t < V) {
+        float n = 0.f;
+        for (int u = 0; u < U; ++u) n += fabsf(Sb[t * U + u].x) + fabsf(Sb[t * U + u].y);
+        s_norm[buf][t] = n;
+      }
+      __syncthreads();
+      float mx = 0.f;
+      for (int v = 0; v < V; ++v) mx = fmaxf(mx, s_norm[buf][v]);
+      // largest power of two with scale * max row 1-norm <= 2^14 (bounds |T|)
+      if (mx > 0.f) scale = exp2f(floorf(14.f - log2f(mx)));
+    }
+    unsigned short* Bh = bt + buf * bsize;
+    unsigned short* Bl = Bh + bsize / 2;
+    for (int v0 = q; v0 < V; v0 += 16) {  // four chains at a time
+      const c32* row[4];
+      c32 acc[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {  // rows past V repeat the last and are not kept
+        row[r] = Sb + min(v0 + 4 * r, V - 1) * U;
+        acc[r] = row[r][U - 1];
+      }
+#pragma unroll 2
+      for (int u = U - 2; u >= 0; --u)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[r] = muladd(acc[r], w, row[r][u]);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int v = v0 + 4 * r;
+        if (v >= V) break;
+        const c32 o = mul(acc[r], sh);
+        const float val[2] = {o.x * scale, o.y * scale};
+#pragma unroll
+        for (int part = 0; part < 2; ++part) {
+          const int k = part * V + v, at = ((k / 8) * FB + col) * 8 + k % 8;
+          const unsigned short h = to16(val[part], MODE);
+          Bh[at] = h;
+          Bl[at] = to16(val[part] - from16(h, MODE), MODE);
+        }
+      }
+    }
+    // the next spectrum, into the other buffer (last read before the last barrier)
+    if (pc + 1 < pc1)
+      for (int i = t; i < M; i += 256) S[(buf ^ 1) * M + i] = spec[(long long)(pc + 1) * M + i];
+    __syncthreads();
+    floatx16 cr0 = {0}, ci0 = {0}, cr1 = {0}, ci1 = {0};
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      const int o0 = ((2 * ks + lh) * FB + li) * 8, o1 = o0 + 32 * 8;
+      const u16x8 bh0 = *reinterpret_cast<const u16x8*>(Bh + o0);
+      const u16x8 bl0 = *reinterpret_cast<const u16x8*>(Bl + o0);
+      const u16x8 bh1 = *reinterpret_cast<const u16x8*>(Bh + o1);
+      const u16x8 bl1 = *reinterpret_cast<const u16x8*>(Bl + o1);
+      split_products<MODE>(arh[ks], arl[ks], bh0, bl0, cr0);
+      split_products<MODE>(aih[ks], ail[ks], bh0, bl0, ci0);
+      split_products<MODE>(arh[ks], arl[ks], bh1, bl1, cr1);
+      split_products<MODE>(aih[ks], ail[ks], bh1, bl1, ci1);
+    }
+    const float inv = (MODE == kFP16) ? 1.f / scale : 1.f;
+    const int plane = pc / 3, comp = pc % 3;
+    c32* dst = E + (((long long)comp * fz + plane) * fy) * fx;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int g = g0 + 8 * (r / 4) + 4 * lh + (r % 4);
+      if (g < fy) {
+        if (f0 + li < fx)
+          __builtin_nontemporal_store(f2v{cr0[r] * inv, ci0[r] * inv},
+                                      reinterpret_cast<f2v*>(dst + (long long)g * fx + f0 + li));
+        if (f0 + 32 + li < fx)
+          __builtin_nontemporal_store(
+              f2v{cr1[r] * inv, ci1[r] * inv},
+              reinterpret_cast<f2v*>(dst + (long long)g * fx + f0 + 32 + li));
+      }
+    }
+  }
+}
+
+// two operand buffers (hi and lo, 2 bytes) and two spectra
+size_t xy_lds_bytes(int U, int V, int Kp) {
+  return (size_t)8 * Kp * FB + (size_t)2 * U * V * sizeof(c32);
+}
+
 template <int MODE>
 hipError_t launch_mode(const MfmaArgs& a, hipStream_t s) {
   const int n_pc = a.fz * 3;
+  if constexpr (MODE != kF32) {
+    if (!a.bmat) {  // both passes in one launch (mfma_one_launch)
+      const int ngt = (a.fy + GB - 1) / GB, nft = (a.fx + FB - 1) / FB;
+      // up to three plane/components per block, so that their passes overlap, while
+      // two blocks per CU are left: 256 x 256 x 64 in bf16 25.1 us with one, 21.9
+      // with three; 256 x 256 x 16 8.5 with one, 9.5 with two
+      int pcb = a.pcb > 0 ? a.pcb : (int)std::min(3LL, ((long long)n_pc * ngt * nft + 511) / 512);
+      pcb = std::min(pcb, n_pc);
+      const long long nb = (long long)((n_pc + pcb - 1) / pcb) * ngt * nft;
+      auto go = [&](auto kern) {
+        kern<<<(unsigned)nb, 256, xy_lds_bytes(a.U, a.V, a.Kp), s>>>(
+            reinterpret_cast<const c32*>(a.spec), reinterpret_cast<const c32*>(a.wx), a.amat, a.U,
+            a.V, a.fx, a.fy, a.fz, ngt, nft, pcb, reinterpret_cast<c32*>(a.E));
+        return hipGetLastError();
+      };
+      switch (a.Kp / 16) {
+        case 1: return go(idft_xy_kernel<MODE, 1>);
+        case 2: return go(idft_xy_kernel<MODE, 2>);
+        case 3: return go(idft_xy_kernel<MODE, 3>);
+        case 4: return go(idft_xy_kernel<MODE, 4>);
+        default: return hipErrorInvalidValue;
+      }
+    }
+  }
   {
     const size_t lds = ((size_t)a.U * a.V + (size_t)a.V * XC) * sizeof(c32);
     dim3 grid((a.fx + XC - 1) / XC, n_pc);
@@ -315,6 +485,11 @@ hipError_t launch_mode(const MfmaArgs& a, hipStream_t s) {
 }
 
 }  // namespace
+
+bool mfma_one_launch(int U, int V, int precision) {
+  const int Kp = (2 * V + 15) / 16 * 16;
+  return precision != SCW_FP32 && V <= 32 && xy_lds_bytes(U, V, Kp) <= 60 * 1024;
+}
 
 int mfma_kstep(int precision) { return precision == SCW_FP32 ? 2 : 16; }
 

@@ -62,3 +62,19 @@ def test_image_matches_direct_sums(ctx, precision, U, V, fx, fy):
     t = tol(precision, U, V)
     assert rel(E, E1) <= t
     assert float((I.double() - I1.double()).norm() / I1.double().norm()) <= 3 * t
+
+
+@pytest.mark.parametrize("precision,eps", [("bf16x3", 2.0 ** -16), ("fp16x3", 2.0 ** -20)])
+@pytest.mark.parametrize("U,V,fx,fy,fz", [(3, 1, 1, 1, 1), (5, 7, 63, 127, 3), (3, 9, 64, 128, 4),
+                                          (7, 15, 65, 129, 2), (3, 17, 130, 40, 5),
+                                          (3, 23, 33, 260, 70), (5, 25, 70, 31, 2),
+                                          (3, 31, 200, 150, 60)])
+def test_split_transform_matches_fp32(ctx, precision, eps, U, V, fx, fy, fz):
+    """Every K of the split operands, ragged tiles, and runs of one to three
+    planes per block. A product of two split values keeps the terms down to the
+    square of their 8 or 11 bits, so its relative error is at most 3 eps."""
+    prob = problem(U, V)
+    sol = ctx.solve(prob)
+    grid = W.Grid(fx=fx, fy=fy, fz=fz, z_begin=-0.1, z_end=prob.thickness + 0.1)
+    got, want = sol.synthesize(grid, precision), sol.synthesize(grid, "fp32")
+    assert rel(got, want) <= 3 * eps + tol("fp32", U, V)
