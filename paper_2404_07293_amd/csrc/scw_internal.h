@@ -539,6 +539,11 @@ hipError_t sur_mode_mix_layer(const float* A, const float* Wm, int nmode, int B,
 hipError_t sur_spec_mode_major(const float* W, long long layer_stride_floats, int nmode,
                                int layers, float* Wm, hipStream_t s);
 // h[b][o] = sum_c lw[c][o] x[b][c] + lb[o] over 16 input, 32 output channels.
+// G = the mixing of h's forward transform in one launch, for at most
+// kSurFwdMixBatch patches in FP32 (fy, fx and Wm as for the two launches).
+constexpr int kSurFwdMixBatch = 28;
+hipError_t sur_fwd_mix(const float* h, const float* fy, const float* fx, const float* Wm, int B,
+                       float* G, hipStream_t s);
 hipError_t sur_lift(const float* x, const float* lw, const float* lb, float* h, int B, bool bf16,
                     hipStream_t s);
 hipError_t sur_fused_dft_inv(const float* G, const float* h, const float* iy, const float* ix,

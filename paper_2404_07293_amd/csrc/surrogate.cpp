@@ -144,11 +144,15 @@ int forward(SurNet& n, const float* x, int B, hipStream_t s, bool keep, float* o
     const float* hin = n.h[k].as<float>();
     float* Hk = n.Hk[k].as<float>();
     const bool last = k == NL - 1;
-    // H = fy h fx per channel (the layer's truncated forward transform)
-    SUR_HIP(sur_fused_dft_fwd(hin, cx(n, n.o_fy), cx(n, n.o_fx), Hk, B, false, n.bf16, s));
-    // G[b][m] = H[m][b] W_k[m] per mode over the patches (H mode-major)
-    SUR_HIP(sur_mode_mix_layer(Hk, n.Wm.as<float>() + 2LL * k * NM * W * W, NM, B,
-                               n.G.as<float>(), n.bf16, s));
+    const float* Wm = n.Wm.as<float>() + 2LL * k * NM * W * W;
+    if (!keep && !n.bf16 && B <= kSurFwdMixBatch) {
+      SUR_HIP(sur_fwd_mix(hin, cx(n, n.o_fy), cx(n, n.o_fx), Wm, B, n.G.as<float>(), s));
+    } else {
+      // H = fy h fx per channel (the layer's truncated forward transform)
+      SUR_HIP(sur_fused_dft_fwd(hin, cx(n, n.o_fy), cx(n, n.o_fx), Hk, B, false, n.bf16, s));
+      // G[b][m] = H[m][b] W_k[m] per mode over the patches (H mode-major)
+      SUR_HIP(sur_mode_mix_layer(Hk, Wm, NM, B, n.G.as<float>(), n.bf16, s));
+    }
     // z = Re(iy G ix) + P_k^T h + c_k; h' = GELU(z) except after the last layer
     // the pre-activation is kept only for the backward pass
     float* zk = last ? n.h[k + 1].as<float>() : (keep ? n.z[k].as<float>() : nullptr);
