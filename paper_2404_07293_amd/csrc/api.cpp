@@ -385,7 +385,7 @@ int build_plan(Solution& s, Plan& pl, const scw_grid& g, int precision,
     pl.kp = ((2 * s.V + ks - 1) / ks) * ks;
     if ((rc = build_amat(s, g, precision, pl))) return rc;
     const size_t ebyte = 4;  // f32, or hi + lo 16-bit
-    if (!mfma_one_launch(s.U, s.V, precision) &&
+    if (!mfma_one_launch(s.U, s.V, g.fx, g.fy, g.fz, precision) &&
         ((rc = pl.d_bmat.reserve((size_t)g.fz * 3 * pl.kp * g.fx * ebyte)) ||
          (rc = pl.d_bscale.reserve((size_t)g.fz * 3 * sizeof(float)))))
       return rc;

@@ -304,7 +304,8 @@ __global__ void __launch_bounds__(256) idft_y_kernel(
 // multiply and store. Spectrum and operand have two buffers each, and the next
 // spectrum is loaded during the products, so that a wave's stores overlap the
 // next plane's chains. The column tiles of the two 128-row halves of 256 rows
-// repeat the x pass (a tenth of the stores' time). Bound by the field's stores:
+// repeat the x pass (a tenth of the stores' time; mfma_one_launch has the limit).
+// Bound by the field's stores:
 // 256 x 256 x 64 points, V = 15 (101 MB): 21.9 us, 29.0 in two launches (FP16:
 // 21.6 and 35.1).
 template <int MODE, int KS>
@@ -486,9 +487,16 @@ hipError_t launch_mode(const MfmaArgs& a, hipStream_t s) {
 
 }  // namespace
 
-bool mfma_one_launch(int U, int V, int precision) {
+// The one launch repeats the x pass for every 128 rows and saves a launch and the
+// operand's way through memory. It is taken while the repeated sums are few per
+// point (14 multiply-adds: 512 x 512 x 32 at V = 17, 9 per point, 47.4 us against
+// 49.1; at V = 25, 20 per point, 59.7 and 56.3) or few in all (4e8: 256 x 256 x 64
+// at V = 31, 3.8e8, 33.9 us against 42.3). 512 x 512 x 256 at V = 31 loses a fifth.
+bool mfma_one_launch(int U, int V, int fx, int fy, int fz, int precision) {
   const int Kp = (2 * V + 15) / 16 * 16;
-  return precision != SCW_FP32 && V <= 32 && xy_lds_bytes(U, V, Kp) <= 60 * 1024;
+  const double per_column = 4.0 * ((fy + GB - 1) / GB) * U * V;
+  return precision != SCW_FP32 && V <= 32 && xy_lds_bytes(U, V, Kp) <= 60 * 1024 &&
+         (per_column <= 14.0 * fy || per_column * 3 * fz * fx <= 4e8);
 }
 
 int mfma_kstep(int precision) { return precision == SCW_FP32 ? 2 : 16; }

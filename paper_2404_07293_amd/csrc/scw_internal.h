@@ -386,9 +386,8 @@ struct MfmaArgs {
   void* E;
 };
 int mfma_kstep(int precision);
-// Whether the split modes' two passes run in one launch, without bmat and bscale:
-// where their operand and spectra fit in LDS (a U x V of about 1800 or less).
-bool mfma_one_launch(int U, int V, int precision);
+// Whether the split modes' two passes run in one launch, without bmat and bscale.
+bool mfma_one_launch(int U, int V, int fx, int fy, int fz, int precision);
 
 // ------------------------------------------------------------------ batched synthesis
 struct BatchJob {

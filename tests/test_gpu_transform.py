@@ -68,10 +68,10 @@ def test_image_matches_direct_sums(ctx, precision, U, V, fx, fy):
 @pytest.mark.parametrize("U,V,fx,fy,fz", [(3, 1, 1, 1, 1), (5, 7, 63, 127, 3), (3, 9, 64, 128, 4),
                                           (7, 15, 65, 129, 2), (3, 17, 130, 40, 5),
                                           (3, 23, 33, 260, 70), (5, 25, 70, 31, 2),
-                                          (3, 31, 200, 150, 60)])
+                                          (3, 31, 200, 150, 60), (15, 31, 1000, 130, 70)])
 def test_split_transform_matches_fp32(ctx, precision, eps, U, V, fx, fy, fz):
-    """Every K of the split operands, ragged tiles, and runs of one to three
-    planes per block. A product of two split values keeps the terms down to the
+    """Every K of the split operands, ragged tiles, runs of one to three planes
+    per block, and (the last) the two launches of large repeated sums. A product of two split values keeps the terms down to the
     square of their 8 or 11 bits, so its relative error is at most 3 eps."""
     prob = problem(U, V)
     sol = ctx.solve(prob)
