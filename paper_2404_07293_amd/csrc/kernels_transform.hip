@@ -225,13 +225,18 @@ hipError_t launch(const SynthArgs& s, hipStream_t st) {
   a.sx_step = s.sx_step;
   a.sy_step = s.sy_step;
   a.na2 = s.na2;
-  // rows split over blocks while the launch has less than two blocks per CU and
-  // each wave keeps four groups of rows (a split repeats the x pass)
-  const long long blocks = (long long)a.tiles * (NC == 3 ? 1 : 3) * s.fz * s.nvol;
-  a.splits = 1;
-  while (blocks * a.splits < 512 && a.lay.npy / (a.splits * 2) >= 16) a.splits *= 2;
   const size_t lds = ((size_t)NC * s.V * (s.U / 2 + 1) * 2 + (size_t)(s.U / 2) * 32 +
                       (size_t)NC * s.V * 64) * sizeof(cx<T>);
+  // rows split over blocks while the launch has less than two blocks per CU, each
+  // wave keeps four groups of rows and the blocks stay one round by their LDS (a
+  // split repeats the x pass: 128 x 128 x 64 in FP64 at V = 31, two blocks to a
+  // CU, 20.2 us whole, 25.9 split)
+  const long long blocks = (long long)a.tiles * (NC == 3 ? 1 : 3) * s.fz * s.nvol;
+  const long long slots = 256 * std::max<long long>(1, 160 * 1024 / (long long)std::max<size_t>(lds, 1));
+  a.splits = 1;
+  while (blocks * a.splits < 512 && blocks * a.splits * 2 <= slots &&
+         a.lay.npy / (a.splits * 2) >= 16)
+    a.splits *= 2;
   const dim3 grid(a.tiles * a.splits, (NC == 3 ? 1 : 3) * s.fz, s.nvol);
   auto go = [&](auto kern) {
     kern<<<grid, 256, lds, st>>>(a, reinterpret_cast<cx<T>*>(s.spec),
