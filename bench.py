@@ -82,7 +82,7 @@ def plan_summary(prob, grid):
 
 def source_hash():
     h = hashlib.sha256()
-    for f in ("kernels_synth.hip", "kernels_mfma.hip"):
+    for f in ("kernels_synth.hip", "kernels_transform.hip", "kernels_mfma.hip"):
         p = os.path.join(ROOT, "paper_2404_07293_amd", "csrc", f)
         if os.path.exists(p):
             h.update(open(p, "rb").read())
