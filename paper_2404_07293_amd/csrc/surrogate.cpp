@@ -133,7 +133,10 @@ int forward(SurNet& n, const float* x, int B, hipStream_t s, bool keep, float* o
   // mode-major copy of the spectral weights, for the mixing; a captured call
   // makes its own, so that a replay sees the parameters of its time
   hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-  SUR_HIP(hipStreamIsCapturing(s, &capture));
+  if (hipStreamIsCapturing(s, &capture) != hipSuccess) {  // not known: as if captured
+    (void)hipGetLastError();
+    capture = hipStreamCaptureStatusActive;
+  }
   if (capture != hipStreamCaptureStatusNone || n.wm_version != n.params_version) {
     SUR_HIP(sur_spec_mode_major(P + o.spec(0), SZ_LAYER, NM, NL, n.Wm.as<float>(), s));
     if (capture == hipStreamCaptureStatusNone) n.wm_version = n.params_version;
@@ -368,9 +371,13 @@ int sur_encode(SurNet& n, const void* n_dev, int B, void* x_dev, hipStream_t s) 
 int sur_forward(SurNet& n, const void* x_dev, int B, void* out_dev, hipStream_t s) {
   int rc = check_batch(n, B);
   if (rc) return rc;
-  // the head writes the caller's array, by way of n.out if that is not aligned
-  // to a complex value
-  const bool direct = reinterpret_cast<uintptr_t>(out_dev) % 8 == 0;
+  // the head writes the caller's array, by way of n.out if that is not this
+  // device's memory or not aligned to a complex value
+  hipPointerAttribute_t at{};
+  const bool known = hipPointerGetAttributes(&at, out_dev) == hipSuccess;
+  if (!known) (void)hipGetLastError();
+  const bool direct = known && at.type == hipMemoryTypeDevice && at.device == n.ctx->device &&
+                      reinterpret_cast<uintptr_t>(out_dev) % 8 == 0;
   float* out = direct ? static_cast<float*>(out_dev) : n.out.as<float>();
   if ((rc = infer(n, reinterpret_cast<const float*>(x_dev), B, s, out))) return rc;
   if (!direct)

@@ -42,7 +42,8 @@ def test_large_batches_equal_small_ones(ctx, bf16, small, large):  # noqa: F811
 
 
 def test_unaligned_arrays(ctx):  # noqa: F811
-    """Arrays aligned to a float only: same values by the other accesses."""
+    """Arrays aligned to a float only, and an output in host memory: same values
+    by the other accesses."""
     import torch
     from paper_2404_07293_amd.surrogate import Surrogate
     net, B = Surrogate(ctx, max_batch=2, seed=5), 2
@@ -61,6 +62,11 @@ def test_unaligned_arrays(ctx):  # noqa: F811
     assert net.lib.scw_sur_forward(net.handle, ctypes.c_void_p(x.data_ptr()), B,
                                    ctypes.c_void_p(ob.data_ptr() + 4), st) == 0
     assert torch.equal(ob[1:], torch.view_as_real(out).reshape(-1))
+    host = torch.empty(out.shape, dtype=out.dtype, pin_memory=True)
+    assert net.lib.scw_sur_forward(net.handle, ctypes.c_void_p(x.data_ptr()), B,
+                                   ctypes.c_void_p(host.data_ptr()), st) == 0
+    torch.cuda.synchronize()
+    assert torch.equal(host, out.cpu())
     net.free()
 
 
