@@ -1095,6 +1095,16 @@ int scw_batch_plan(scw_ctx* ctx, scw_solution* const* jobs, int njobs, const scw
     return rc;
   SCW_HIP(hipDeviceGetAttribute(&b->cus, hipDeviceAttributeMultiprocessorCount, ctx->c.device));
   Context::BatchShape sh{std::min(32, std::max(2, grid->fy / 16)), 4, 1};
+  // Eight-point transforms where a smaller radix would do: 1024 jobs of 64 x 64 x 8
+  // at U up to 17 165.6 us with P = 8, 169.2 with 4 (but 500 jobs of 33 x 64 x 5 at
+  // U up to 9 67.8 and 66.2); 1000 of 64 x 16 x 8 117 with P = 8, 123 with 2. Small
+  // items are grabbed several at a time once every block has four of them, since
+  // the counter serves one at a time: the latter 81.5 us by fours; 64 x 32 x 8 97.2
+  // by twos, 119 singly.
+  if (sh.P < 8 && grid->fy >= 8 && (sh.P < 4 || b->mmax > 81) &&
+      (32 * (size_t)(grid->fy / sh.P) + 3 * (size_t)b->mmax) * 8 <= 48 * 1024)
+    sh.P = 8;
+  if (b->n_items >= 16 * b->cus) sh.chunk = grid->fy <= 16 ? 4 : grid->fy <= 32 ? 2 : 1;
   auto it = ctx->c.tuned_batch.find(batch_key(*grid));
   if (it != ctx->c.tuned_batch.end()) sh = it->second;
   if ((rc = batch_set_shape(b.get(), sh.P, sh.blocks_per_cu, sh.chunk))) return rc;
