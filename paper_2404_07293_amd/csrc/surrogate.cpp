@@ -64,8 +64,10 @@ struct SurNet {
       enc_in;
   DevBuf Wb;  // mixing weights as bf16 matrix-core operands (inference)
   // the parameters change only in sur_set_params and Adam steps; Wb and Wm (the
-  // mode-major weights) are rebuilt when their version lags behind theirs
+  // mode-major weights) are rebuilt when their version lags behind theirs, and in
+  // every call once an Adam step was captured, as its replays pass no host code
   unsigned long long params_version = 1, wb_version = 0, wm_version = 0;
+  bool step_captured = false;
 };
 
 namespace {
@@ -125,6 +127,14 @@ int build_dft(SurNet& n) {
 
 const float* cx(const SurNet& n, long long off) { return n.dft.as<float>() + 2 * off; }
 
+// Whether work enqueued on s is captured (not known: as if it were).
+bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &st) == hipSuccess) return st != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  return true;
+}
+
 // Forward pass; with keep, the per-layer H spectra and pre-activations stay
 // for the backward pass (h[] is always kept).
 int forward(SurNet& n, const float* x, int B, hipStream_t s, bool keep, float* out) {
@@ -132,14 +142,10 @@ int forward(SurNet& n, const float* x, int B, hipStream_t s, bool keep, float* o
   const float* P = n.params.as<float>();
   // mode-major copy of the spectral weights, for the mixing; a captured call
   // makes its own, so that a replay sees the parameters of its time
-  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(s, &capture) != hipSuccess) {  // not known: as if captured
-    (void)hipGetLastError();
-    capture = hipStreamCaptureStatusActive;
-  }
-  if (capture != hipStreamCaptureStatusNone || n.wm_version != n.params_version) {
+  const bool captured = capturing(s);
+  if (captured || n.step_captured || n.wm_version != n.params_version) {
     SUR_HIP(sur_spec_mode_major(P + o.spec(0), SZ_LAYER, NM, NL, n.Wm.as<float>(), s));
-    if (capture == hipStreamCaptureStatusNone) n.wm_version = n.params_version;
+    if (!captured) n.wm_version = n.params_version;
   }
   // lift
   SUR_HIP(sur_lift(x, P + o.lw, P + o.lb, n.h[0].as<float>(), B, n.bf16, s));
@@ -176,7 +182,7 @@ int forward(SurNet& n, const float* x, int B, hipStream_t s, bool keep, float* o
 int forward_bf16(SurNet& n, const float* x, int B, hipStream_t s, float* out) {
   const Off o;
   const float* P = n.params.as<float>();
-  if (n.wb_version != n.params_version) {
+  if (n.step_captured || n.wb_version != n.params_version) {
     SUR_HIP(sur_mix_weights_bf16(P + o.spec(0), SZ_LAYER, NL, n.Wb.p, s));
     n.wb_version = n.params_version;
   }
@@ -412,6 +418,7 @@ int sur_train_step(SurNet& n, const void* x_dev, const void* tgt_dev, int B, flo
                    double* loss, hipStream_t s) {
   int rc = sur_loss_grad(n, x_dev, tgt_dev, B, loss, nullptr, s);
   if (rc) return rc;
+  if (capturing(s)) n.step_captured = true;
   n.step++;
   n.params_version++;
   SCW_HIP(sur_adam(n.params.as<float>(), n.grads.as<float>(), n.adam_m.as<float>(),
