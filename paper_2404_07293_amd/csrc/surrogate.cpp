@@ -135,18 +135,23 @@ bool capturing(hipStream_t s) {
   return true;
 }
 
+// Whether a call has to make a copy of the weights, last made for `version`,
+// again. A captured call makes its own, so that a replay sees the parameters of
+// its time, and leaves the version, as nothing has been made yet.
+bool stale(const SurNet& n, unsigned long long version, bool captured) {
+  return captured || n.step_captured || version != n.params_version;
+}
+
 // Forward pass; with keep, the per-layer H spectra and pre-activations stay
 // for the backward pass (h[] is always kept).
 int forward(SurNet& n, const float* x, int B, hipStream_t s, bool keep, float* out) {
   const Off o;
   const float* P = n.params.as<float>();
-  // mode-major copy of the spectral weights, for the mixing; a captured call
-  // makes its own, so that a replay sees the parameters of its time
+  // mode-major copy of the spectral weights, for the mixing
   const bool captured = capturing(s);
-  if (captured || n.step_captured || n.wm_version != n.params_version) {
+  if (stale(n, n.wm_version, captured))
     SUR_HIP(sur_spec_mode_major(P + o.spec(0), SZ_LAYER, NM, NL, n.Wm.as<float>(), s));
-    if (!captured) n.wm_version = n.params_version;
-  }
+  if (!captured) n.wm_version = n.params_version;
   // lift
   SUR_HIP(sur_lift(x, P + o.lw, P + o.lb, n.h[0].as<float>(), B, n.bf16, s));
   for (int k = 0; k < NL; ++k) {
@@ -182,10 +187,10 @@ int forward(SurNet& n, const float* x, int B, hipStream_t s, bool keep, float* o
 int forward_bf16(SurNet& n, const float* x, int B, hipStream_t s, float* out) {
   const Off o;
   const float* P = n.params.as<float>();
-  if (n.step_captured || n.wb_version != n.params_version) {
+  const bool captured = capturing(s);
+  if (stale(n, n.wb_version, captured))
     SUR_HIP(sur_mix_weights_bf16(P + o.spec(0), SZ_LAYER, NL, n.Wb.p, s));
-    n.wb_version = n.params_version;
-  }
+  if (!captured) n.wb_version = n.params_version;
   void* ha = n.h[0].p;
   void* hb = n.h[1].p;
   SUR_HIP(sur_lift_bf16(x, P + o.lw, P + o.lb, ha, B, s));
