@@ -28,6 +28,18 @@ int fail(int code, const std::string& msg) {
   return code;
 }
 
+// The allocation of this thread that fails next, counted down (0: none). Only
+// scw_internal_fail_allocation sets it.
+static thread_local int t_fail_in = 0;
+
+hipError_t device_malloc(void** p, size_t n) {
+  // a size that no device has: the failure and the error it leaves are the runtime's own
+  if (t_fail_in > 0 && --t_fail_in == 0) n = (size_t)1 << 60;
+  const hipError_t e = hipMalloc(p, n);
+  if (e != hipSuccess) (void)hipGetLastError();
+  return e;
+}
+
 namespace {
 
 int elem_bytes(int precision) { return precision == SCW_FP64 ? 16 : 8; }
@@ -417,6 +429,15 @@ int check_grid(const scw_grid* g) {
 using namespace scw;
 
 extern "C" {
+
+// For tests, not in the header: the k-th device allocation of the calling
+// thread from now fails (0: none). Returns how many were still to go before
+// the one set earlier, 0 when it has failed.
+int scw_internal_fail_allocation(int k) {
+  const int left = t_fail_in;
+  t_fail_in = std::max(0, k);
+  return left;
+}
 
 const char* scw_last_error(void) { return g_err.c_str(); }
 

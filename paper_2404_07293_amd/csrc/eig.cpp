@@ -13,18 +13,24 @@
 
 namespace scw {
 
+int blas_fail(const char* call, int status) {
+  const rocblas_status st = static_cast<rocblas_status>(status);
+  const bool memory = st == rocblas_status_memory_error;
+  if (memory) (void)hipGetLastError();
+  return fail(memory ? SCW_ENOMEM : SCW_EHIP,
+              std::string(call) + ": " + rocblas_status_to_string(st));
+}
+
 int blas_handle(Context& ctx, hipStream_t st, void** out) {
   if (!ctx.blas) {
     rocblas_handle h = nullptr;
     const rocblas_status r = rocblas_create_handle(&h);
-    if (r != rocblas_status_success)
-      return fail(SCW_EHIP, std::string("rocblas_create_handle: ") + rocblas_status_to_string(r));
+    if (r != rocblas_status_success) return blas_fail("rocblas_create_handle", r);
     ctx.blas = h;
   }
   rocblas_handle h = static_cast<rocblas_handle>(ctx.blas);
   const rocblas_status r = rocblas_set_stream(h, st);
-  if (r != rocblas_status_success)
-    return fail(SCW_EHIP, std::string("rocblas_set_stream: ") + rocblas_status_to_string(r));
+  if (r != rocblas_status_success) return blas_fail("rocblas_set_stream", r);
   *out = h;
   return SCW_OK;
 }
@@ -92,9 +98,7 @@ int device_eig_batched(Context& ctx, int n, int count, double* A, double* w, dou
       reinterpret_cast<const rocblas_double_complex*>(dZ.p), n, (rocblas_stride)nn,
       reinterpret_cast<const rocblas_double_complex*>(A), n, (rocblas_stride)nn, &zero,
       reinterpret_cast<rocblas_double_complex*>(X), n, (rocblas_stride)nn, count);
-  if (bs != rocblas_status_success)
-    return fail(SCW_EHIP, std::string("rocblas_zgemm_strided_batched: ") +
-                              rocblas_status_to_string(bs));
+  if (bs != rocblas_status_success) return blas_fail("rocblas_zgemm_strided_batched", bs);
   SCW_HIP(launch_eig_normalize(n, (long long)count * n, X, st));
   SCW_HIP(hipStreamSynchronize(st));
   return SCW_OK;

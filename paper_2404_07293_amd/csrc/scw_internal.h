@@ -34,6 +34,10 @@ int fail(int code, const std::string& msg);
   } while (0)
 
 // ------------------------------------------------------------------ device memory
+// hipMalloc, for every device allocation of the library. A failure leaves no
+// error behind: the runtime would report it at the next launch check, here, where
+// the caller goes on with less memory, or in the user's next call.
+hipError_t device_malloc(void** p, size_t n);
 struct DevBuf {
   void* p = nullptr;
   size_t bytes = 0;
@@ -51,7 +55,7 @@ struct DevBuf {
     if (n <= bytes) return SCW_OK;
     release();
     if (n == 0) return SCW_OK;
-    if (hipMalloc(&p, n) != hipSuccess) {
+    if (device_malloc(&p, n) != hipSuccess) {
       p = nullptr;
       return fail(SCW_ENOMEM, "hipMalloc of " + std::to_string(n) + " bytes failed");
     }
@@ -268,6 +272,9 @@ int device_eig_batched(Context& ctx, int n, int count, double* A, double* w, dou
                        hipStream_t st);
 // The context's rocBLAS handle (created on first use), bound to stream st.
 int blas_handle(Context& ctx, hipStream_t st, void** out);
+// Fails with a rocBLAS or rocSOLVER status: SCW_ENOMEM where its workspace could
+// not be had (and no error left in the runtime), else SCW_EHIP.
+int blas_fail(const char* call, int status);
 size_t eig_hessenberg_work(int n);  // bytes of workspace per matrix
 hipError_t launch_eig_hessenberg(int n, int count, double* A, double* Z, double* work,
                                  hipStream_t s);

@@ -398,11 +398,10 @@ rocblas_double_complex* zp(const DevBuf& b, size_t off = 0) {
 }
 }  // namespace
 
-#define SCW_BLAS(call)                                                                   \
-  do {                                                                                   \
-    rocblas_status st_ = (call);                                                         \
-    if (st_ != rocblas_status_success)                                                   \
-      return fail(SCW_EHIP, std::string(#call) + ": " + rocblas_status_to_string(st_));  \
+#define SCW_BLAS(call)                                                  \
+  do {                                                                  \
+    rocblas_status st_ = (call);                                        \
+    if (st_ != rocblas_status_success) return blas_fail(#call, st_);    \
   } while (0)
 
 // The connection route's 6M x 6M system (Eq. 29) on the device, from the
