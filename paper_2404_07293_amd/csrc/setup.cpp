@@ -960,6 +960,10 @@ static int device_eig_group(Context& ctx, const scw_problem* const* probs, Solut
       SCW_HIP(hipMemcpyAsync(cat_C.as<char>() + off, ps[i]->d_C.p, b, hipMemcpyDeviceToDevice, st));
       off += b;
     }
+    for (int i = 0; i < n; ++i) {  // (a free waits for the copies)
+      ps[i]->d_A.release();
+      ps[i]->d_C.release();
+    }
     A = &cat_A;
     C = &cat_C;
   }
@@ -1452,7 +1456,9 @@ int solve_problem(Context& ctx, const scw_problem& p, Solution& s, int n_waves,
 int solve_problems(Context& ctx, const scw_problem* probs, int n, Solution** sols) {
   // in rounds of problems whose device eigendecompositions share launches:
   // problems of one round with the same matrix order form one batch
-  const size_t kRoundBytes = (size_t)24 << 30;  // device A, C and eigensolver workspace
+  // per layer A, C, X, A C, and the eigensolver's Z, row-major copy and rotation
+  // record (three quarters of a block): seven 2M x 2M blocks
+  const size_t kRoundBytes = (size_t)24 << 30;
   int i0 = 0;
   while (i0 < n) {
     std::vector<std::unique_ptr<PendingSolve>> ps;
@@ -1460,7 +1466,7 @@ int solve_problems(Context& ctx, const scw_problem* probs, int n, Solution** sol
     int i1 = i0;
     while (i1 < n) {
       const size_t nn = 4 * (size_t)probs[i1].U * probs[i1].V * probs[i1].U * probs[i1].V;
-      const size_t need = nn * 16 * 6 * (size_t)std::max(1, probs[i1].nz);
+      const size_t need = nn * 16 * 7 * (size_t)std::max(1, probs[i1].nz);
       if (i1 > i0 && bytes + need > kRoundBytes) break;
       bytes += need;
       ++i1;
