@@ -512,67 +512,82 @@ __global__ void __launch_bounds__(256) mode_mix_mm(const f2* __restrict__ A,
 // its kx, then a thread per (ky, channel) the columns and a thread per (ky,
 // output) the mixing, whose weights are loaded first of all. Each launch of a
 // small batch costs its latency, and every block reads the whole patch again, so
-// this pays while the blocks have a CU each: one patch 8.4 us, 10.9 in two
-// launches; a call with 28 patches 101 us, 107.
+// this pays while the blocks have a CU each: one patch 7.6 us, 10.9 in two
+// launches; a call with 28 patches 99 us, 105.
+//
+// Every sum has the terms and the order of fused_dft_fwd and mode_mix_mm (whose
+// FP32 products add their two K slots one after the other), so that a patch's
+// result has the same bits in every batch, and as in the training forward pass.
 constexpr int FM_T = 18 * 32;
-// v[i] summed over eight lanes, into lane i of the eight.
-template <int N>
-__device__ __forceinline__ void halve8(float* v, int lane) {
-  if constexpr (N > 1) {
-    constexpr int H = N / 2;
-    const bool up = (lane & H) != 0;
-#pragma unroll
-    for (int i = 0; i < H; ++i) {
-      const float send = up ? v[i] : v[i + H];
-      v[i] = (up ? v[i + H] : v[i]) + __shfl_xor(send, H, 64);
-    }
-    halve8<H>(v, lane);
-  }
-}
 __global__ void __launch_bounds__(FM_T) fwd_mix(const float* __restrict__ h,
                                                 const f2* __restrict__ fy,
                                                 const f2* __restrict__ fx,
                                                 const f2* __restrict__ Wm,
                                                 f2* __restrict__ G) {
-  constexpr int HS = SN + 1;
+  constexpr int HS = SN + 1, RS = SN + 4;  // row strides against bank conflicts
   __shared__ f2 hx[SW * HS], fys[SKY * HS], Hs[SKY * HS];
+  __shared__ __attribute__((aligned(16))) float rows[8][SN * RS];
   const int t = threadIdx.x, kx = blockIdx.x, ch = t & 31, ky = t >> 5;
   const long long b = blockIdx.y;
   // Rows: eight lanes read a row of 128 bytes, a wave (the ninth has none) eight
-  // rows per load and sixteen such groups.
+  // rows per load and sixteen such groups: the 32 rows of four channels.
   constexpr int NR = 16;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63, part = lane & 7;
-  float4 rv[NR];
+  typedef float float4v __attribute__((ext_vector_type(4)));
+  float4v rv[NR];
   if (wave < 8) {
-    const float4* src = reinterpret_cast<const float4*>(
+    const float4v* src = reinterpret_cast<const float4v*>(
         h + (b * SW * SN + wave * NR * 8 + (lane >> 3)) * SN + 4 * part);
 #pragma unroll
     for (int k = 0; k < NR; ++k) rv[k] = src[k * 8 * SN / 4];
   }
-  f2 xv[4];  // the twiddles of this lane's four pixels
-#pragma unroll
-  for (int e = 0; e < 4; ++e) xv[e] = fx[(4 * part + e) * SKX + kx];
   const f2 yv = fy[min(t, SKY * SN - 1)];  // past the end: the last entry again
   const int m = min(ky, SKY - 1) * SKX + kx;
   f2 wv[SW];
+  auto weights = [&](int i0) {  // half of them: with all from the start registers would spill
 #pragma unroll
-  for (int i = 0; i < SW; ++i) wv[i] = Wm[((long long)m * SW + i) * SW + ch];
+    for (int i = 0; i < SW / 2; ++i) wv[i0 + i] = Wm[((long long)m * SW + i0 + i) * SW + ch];
+  };
+  weights(0);
   if (t < SKY * SN) fys[(t / SN) * HS + t % SN] = yv;
   if (wave < 8) {
+    // Through LDS a lane gets a whole row, the upper half-wave the same rows for
+    // the imaginary part: with the twiddles of x and 32 - x conjugate, Re takes
+    // row[x] + row[32 - x] and Im the difference.
+    const int y = lane & 31;
+    const bool imag = lane >= 32;
+    const float sign = imag ? -1.f : 1.f;
+    float w[SN / 2 + 1];
 #pragma unroll
-    for (int k0 = 0; k0 < NR; k0 += 8) {
-      float re[8], im[8];
-#pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        const float4 v = rv[k0 + k];
-        re[k] = fmaf(v.x, xv[0].x, v.y * xv[1].x) + fmaf(v.z, xv[2].x, v.w * xv[3].x);
-        im[k] = fmaf(v.x, xv[0].y, v.y * xv[1].y) + fmaf(v.z, xv[2].y, v.w * xv[3].y);
-      }
-      halve8<8>(re, lane);
-      halve8<8>(im, lane);  // lane part holds group k0 + part
-      const int r = (wave * NR + k0 + part) * 8 + (lane >> 3);
-      hx[(r / SN) * HS + r % SN] = f2{re[0], im[0]};
+    for (int x = 0; x <= SN / 2; ++x) {
+      const f2 v = fx[x * SKX + kx];  // wave-uniform
+      w[x] = imag ? v.y : v.x;
     }
+    float* stage = rows[wave];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      if (c == 2) weights(SW / 2);
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        *reinterpret_cast<float4v*>(stage + (8 * k + (lane >> 3)) * RS + 4 * part) = rv[4 * c + k];
+      wave_sync();
+      float row[SN];
+#pragma unroll
+      for (int q = 0; q < SN / 4; ++q) {
+        const float4v v = *reinterpret_cast<const float4v*>(stage + y * RS + 4 * q);
+        row[4 * q] = v.x;
+        row[4 * q + 1] = v.y;
+        row[4 * q + 2] = v.z;
+        row[4 * q + 3] = v.w;
+      }
+      float s = fmaf(row[0], w[0], row[SN / 2] * w[SN / 2]);
+#pragma unroll
+      for (int x = 1; x < SN / 2; ++x) s = fmaf(fmaf(sign, row[SN - x], row[x]), w[x], s);
+      reinterpret_cast<float*>(hx + (wave * 4 + c) * HS + y)[imag] = s;
+      wave_sync();  // the rows are read before the next are staged
+    }
+  } else {
+    weights(SW / 2);
   }
   __syncthreads();
   if (ky < SKY) {  // columns, rows yy and 32 - yy together
@@ -593,12 +608,17 @@ __global__ void __launch_bounds__(FM_T) fwd_mix(const float* __restrict__ h,
   }
   __syncthreads();
   if (ky < SKY) {
+    const f2* hs = Hs + ky * HS;
     f2 g = {0.f, 0.f};
 #pragma unroll
-    for (int i = 0; i < SW; ++i) {
-      const f2 v = Hs[ky * HS + i];
-      g.x = fmaf(v.x, wv[i].x, fmaf(-v.y, wv[i].y, g.x));
-      g.y = fmaf(v.x, wv[i].y, fmaf(v.y, wv[i].x, g.y));
+    for (int i = 0; i < SW; ++i) {  // real parts of H
+      g.x = fmaf(hs[i].x, wv[i].x, g.x);
+      g.y = fmaf(hs[i].x, wv[i].y, g.y);
+    }
+#pragma unroll
+    for (int i = 0; i < SW; ++i) {  // imaginary parts
+      g.x = fmaf(hs[i].y, -wv[i].y, g.x);
+      g.y = fmaf(hs[i].y, wv[i].x, g.y);
     }
     G[(b * SNM + m) * SW + ch] = g;
   }

@@ -27,6 +27,12 @@ __device__ __forceinline__ void st(V* p, V v) {
   else *p = v;
 }
 
+// Orders one wave's LDS accesses between phases that pass values across lanes.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // round to bf16, nearest even, by the hardware's conversion (two values per
 // instruction where the compiler pairs them)
 __device__ __forceinline__ float rbf(float x) { return (float)(__bf16)x; }
