@@ -519,10 +519,17 @@ int solve_stable_device(Context& ctx, int G, Solution* const* sols,
     for (int m = 0; m < M; ++m) msz[m] = -s.sz_top[m];
     half_space_diagonals(s, s.sz_bot, hd.data() + (size_t)g * 4 * M);
     half_space_diagonals(s, msz, hd.data() + (size_t)(G + g) * 4 * M);
-    for (int q = 0; q < 2; ++q)  // X, Y: layers L apart in their place of XYlu
-      SCW_HIP(hipMemcpy2DAsync(dXYlu.as<zc>() + ((size_t)q * G + g) * nn, 2 * gn * 16,
-                               (q ? dY : dX) + (size_t)g * L * nn, nn * 16, nn * 16, L,
-                               hipMemcpyDeviceToDevice, st));
+    for (int q = 0; q < 2; ++q) {  // X, Y: layers 2 G apart in their place of XYlu
+      zc* dst = dXYlu.as<zc>() + ((size_t)q * G + g) * nn;
+      const zc* src = (q ? dY : dX) + (size_t)g * L * nn;
+      if (G > 1)  // (a group's workspace keeps the pitch below 1 GB)
+        SCW_HIP(hipMemcpy2DAsync(dst, 2 * gn * 16, src, nn * 16, nn * 16, L,
+                                 hipMemcpyDeviceToDevice, st));
+      else  // blocks of any size: M = 4096 alone passes the 2 GB that a pitch may have
+        for (int l = 0; l < L; ++l)
+          SCW_HIP(hipMemcpyAsync(dst + (size_t)l * 2 * nn, src + (size_t)l * nn, nn * 16,
+                                 hipMemcpyDeviceToDevice, st));
+    }
   }
   SCW_HIP(hipMemcpyAsync(dE.p, E.data(), E.size() * 16, hipMemcpyHostToDevice, st));
   SCW_HIP(hipMemcpyAsync(dhd.p, hd.data(), hd.size() * 16, hipMemcpyHostToDevice, st));
@@ -1328,14 +1335,17 @@ int solve_boundary(Context& ctx, const scw_problem* const* probs, Solution** sol
 }
 
 // How many problems from the first of `n` can share the device elimination:
-// the same shape, one after another on the device, in about 4 GB of
-// workspace (6 blocks per layer and 2 x 2 for the top system).
+// the same shape, one after another on the device, in about 4 GB of workspace
+// (4 blocks per layer, 6 of the recursion and 4 of the top system) and, as their
+// 2 L LU factorisations go in one batch, in the 65536 blocks that a launch takes
+// in its second and third dimension.
 int boundary_group(const scw_problem* const* probs, Solution** sols, PendingSolve** ps, int n) {
   if (probs[0]->route != SCW_ROUTE_STABLE_DEVICE) return 1;
   const size_t nn = 4 * (size_t)sols[0]->M * sols[0]->M;
   const size_t each = nn * 16 * (4 * (size_t)sols[0]->L + 10);
   int g = 1;
   while (g < n && (size_t)(g + 1) * each <= ((size_t)4 << 30) &&
+         2LL * sols[0]->L * (g + 1) <= 65535 &&
          probs[g]->route == SCW_ROUTE_STABLE_DEVICE && sols[g]->M == sols[0]->M &&
          sols[g]->L == sols[0]->L && sols[g]->K == sols[0]->K && ps[g]->dX && ps[0]->dX &&
          ps[g]->dX == ps[0]->dX + (size_t)g * sols[0]->L * nn &&
