@@ -236,8 +236,10 @@ int choose_shape(const Solution& s, const scw_grid& g, int precision,
   // FP32 and FP64 transform by conjugate pairs wherever its tables fit: a quarter
   // to an eighth of the direct sum's work for any fy, and no operand through
   // memory. Transforms alone, pairs against the factored pass: 8 x 128 x 128 x
-  // 64 points, V = 15: 40 us, 72; 256 x 256 x 128, V = 21: 44.6 us, 45; against
-  // the direct sums, 150 x 90 x 45, V = 9: 8.0 us, 19.1.
+  // 64 points, V = 15: 40 us, 72; 256 x 256 x 128, V = 21: 44.6 us, 45 (whole
+  // calls, the modal sum of a 300 MB matrix included: 94.0 by pairs, 94.2 and 94.8
+  // by the factored pass with 32 and 64 columns); against the direct sums,
+  // 150 x 90 x 45, V = 9: 8.0 us, 19.1.
   // The tables grow with fx and fy, the field also with fz: grids so thin that
   // the tables would be the larger keep the other transforms.
   int kind = cfg.transform;
@@ -1118,13 +1120,14 @@ int scw_batch_plan(scw_ctx* ctx, scw_solution* const* jobs, int njobs, const scw
   Context::BatchShape sh{std::min(32, std::max(2, grid->fy / 16)), 4, 1};
   // Eight-point transforms where a smaller radix would do: 1024 jobs of 64 x 64 x 8
   // at U up to 17 165.6 us with P = 8, 169.2 with 4 (but 500 jobs of 33 x 64 x 5 at
-  // U up to 9 67.8 and 66.2); 1000 of 64 x 16 x 8 117 with P = 8, 123 with 2. Small
+  // U up to 9 67.8 and 66.2); 1000 of 64 x 16 x 8 117 with P = 8, 123 with 2. Not
+  // the best past U = 17: 4096 jobs of 64 x 64 x 8 at U from 9 to 25 638 us with
+  // P = 8, 733 with 4, 590 with 16, which the tuner finds. Small
   // items are grabbed several at a time once every block has four of them, since
   // the counter serves one at a time: the latter 81.5 us by fours; 64 x 32 x 8 97.2
   // by twos, 119 singly.
-  if (sh.P < 8 && grid->fy >= 8 && (sh.P < 4 || b->mmax > 81) &&
-      (32 * (size_t)(grid->fy / sh.P) + 3 * (size_t)b->mmax) * 8 <= 48 * 1024)
-    sh.P = 8;
+  // (Their tables fit: fy is at most 64 where P is below 8.)
+  if (sh.P < 8 && grid->fy >= 8 && (sh.P < 4 || b->mmax > 81)) sh.P = 8;
   if (b->n_items >= 16 * b->cus) sh.chunk = grid->fy <= 16 ? 4 : grid->fy <= 32 ? 2 : 1;
   auto it = ctx->c.tuned_batch.find(batch_key(*grid));
   if (it != ctx->c.tuned_batch.end()) sh = it->second;
