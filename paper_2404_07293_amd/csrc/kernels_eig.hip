@@ -1,8 +1,10 @@
 // Batched FP64 complex non-symmetric eigensolver for the per-layer 2M x 2M
 // products A C (Sec. 3.2, Sec. 4.2: the eigendecomposition step). Every
-// matrix of a batch is independent, so each kernel gives one workgroup (or,
-// for the eigenvectors, one wavefront) to one matrix or vector, and a batch of
-// layers, wavelengths or patches fills the chip.
+// matrix of a batch is independent: the two chains of dependent steps (the
+// reduction's panels and the QR iteration) have one workgroup per matrix, so
+// that a batch of layers, wavelengths or patches fills the chip; what the chains
+// leave behind (their reflectors and rotations on the rest of H and on Z, and the
+// eigenvectors) is spread over many workgroups to a matrix.
 //
 // Steps, each a published method restated for this layout:
 //   1. Householder reduction to upper Hessenberg form H = Q^H A Q in panels of

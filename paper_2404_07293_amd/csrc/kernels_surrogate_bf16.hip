@@ -26,11 +26,11 @@
 #include <algorithm>
 
 #include "scw_internal.h"
+#include "surrogate_device.h"
 
 namespace scw {
 namespace {
 
-typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned short bf_t;
@@ -81,18 +81,8 @@ __device__ __forceinline__ float gelu(float z) {
   return fmaf(-az, q * t * e, zp);
 }
 
-// Loads and stores of the activations, non-temporal where the batch does not fit
-// the last-level cache (sur_past_cache); the spectra between them stay there.
-template <bool NT, typename V>
-__device__ __forceinline__ V ld(const V* p) {
-  if constexpr (NT) return __builtin_nontemporal_load(p);
-  else return *p;
-}
-template <bool NT, typename V>
-__device__ __forceinline__ void st(V* p, V v) {
-  if constexpr (NT) __builtin_nontemporal_store(v, p);
-  else *p = v;
-}
+// NT: the activations' loads and stores are non-temporal, where the batch does
+// not fit the last-level cache (sur_past_cache); the spectra between them stay there.
 
 // ---------------------------------------------------------------------------
 // Lift: h[b][o][p] = sum_c lw[c][o] x[b][c][p] + lb[o] (16 -> 32 channels),
@@ -393,10 +383,6 @@ constexpr int IV_GY8 = C * N * 8;           // offset of gy8 in the shared words
 constexpr int IV_WORDS = C * N * 8 + C * N; // gy and gy8 (9216 words, 36 KB)
 constexpr int IV_GQ = (LNM * C / 4 + 255) / 256;  // 16-byte chunks of G per thread
 static_assert(LKX * LKY * IV_GR <= IV_WORDS, "staged G exceeds the shared words");
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-}
 template <bool GELU, bool NT>
 __global__ void __launch_bounds__(256) inv_bf16(const unsigned* __restrict__ G,
                                                 const bf_t* __restrict__ h,

@@ -458,13 +458,13 @@ BatchArgs batch_args(const scw_batch* b, void* E);
 std::string batch_key(const scw_grid& g);
 
 // ------------------------------------------------------------------ surrogate kernels
-// Backward kernels (kernels_surrogate_bwd.hip). Spectral gradients use the
-// forward pass's layouts: gG mode-major [mode][b][o], gH and gF [b][mode][i].
 // Whether the large arrays of an inference batch stream past the last-level
 // cache (256 MB): from 1280 patches on a layer's two activations in bf16 no
 // longer fit there with its spectra. Whole bf16 passes, non-temporal and normal:
 // 1024 patches 360 and 353 us, 1536 477 and 488, 4096 1150 and 1267.
 inline bool sur_past_cache(int B) { return B > 1280; }
+// Backward kernels (kernels_surrogate_bwd.hip). Spectral gradients use the
+// forward pass's layouts: gG mode-major [mode][b][o], gH and gF [b][mode][i].
 constexpr int kSurPointwiseParts = 512, kSurHeadSlices = 16;
 // floats of the partial sums of one sur_pointwise_grad and of sur_head_grad, and
 // of a whole gradient (four layers, the lift, the head)
@@ -544,12 +544,12 @@ hipError_t sur_mode_mix_layer(const float* A, const float* Wm, int nmode, int B,
 // layer_stride_floats apart.
 hipError_t sur_spec_mode_major(const float* W, long long layer_stride_floats, int nmode,
                                int layers, float* Wm, hipStream_t s);
-// h[b][o] = sum_c lw[c][o] x[b][c] + lb[o] over 16 input, 32 output channels.
 // G = the mixing of h's forward transform in one launch, for at most
 // kSurFwdMixBatch patches in FP32 (fy, fx and Wm as for the two launches).
 constexpr int kSurFwdMixBatch = 28;
 hipError_t sur_fwd_mix(const float* h, const float* fy, const float* fx, const float* Wm, int B,
                        float* G, hipStream_t s);
+// h[b][o] = sum_c lw[c][o] x[b][c] + lb[o] over 16 input, 32 output channels.
 hipError_t sur_lift(const float* x, const float* lw, const float* lb, float* h, int B, bool bf16,
                     hipStream_t s);
 hipError_t sur_fused_dft_inv(const float* G, const float* h, const float* iy, const float* ix,

@@ -1,5 +1,4 @@
-// Device helpers shared by the surrogate's FP32-storage kernels and its
-// backward pass.
+// Device helpers shared by the surrogate's kernels.
 #pragma once
 #include <hip/hip_runtime.h>
 
