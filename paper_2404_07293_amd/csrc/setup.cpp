@@ -545,14 +545,32 @@ int solve_stable_device(Context& ctx, int G, Solution* const* sols,
   auto zx = [](const zc* p) {
     return reinterpret_cast<rocblas_double_complex*>(const_cast<zc*>(p));
   };
+  // b <- (LU)^-1 b of `count` systems of order n. A single large problem's systems
+  // go one by one: rocSOLVER's triangular solves of one system are the faster ones
+  // there, those of a batch everywhere else. Boundary solves of 8 layers, one by
+  // one and batched: 2M = 450 44.7 and 45.0 ms, 578 53.1 and 59.8, 882 90.9 and
+  // 102; 242 23.7 and 23.0; two problems of 882 (4 layers) 73.4 and 66.5.
+  const bool one_by_one = G == 1 && n2 >= 512;
+  auto substitute = [&](int n, int k, rocblas_double_complex* lu, rocblas_int* pv,
+                        rocblas_double_complex* b, rocblas_stride sb, int count) -> int {
+    if (!one_by_one) {
+      SCW_BLAS(rocsolver_zgetrs_strided_batched(h, N, n, k, lu, n, (rocblas_stride)n * n, pv,
+                                                (rocblas_stride)n, b, n, sb, count));
+      return SCW_OK;
+    }
+    for (int i = 0; i < count; ++i)
+      SCW_BLAS(rocsolver_zgetrs(h, N, n, k, lu + (size_t)i * n * n, n, pv + (size_t)i * n,
+                                b + (size_t)i * sb, n));
+    return SCW_OK;
+  };
   SCW_BLAS(rocsolver_zgetrf_strided_batched(h, n2, n2, zp(dXYlu), n2, snn, xypiv,
                                             (rocblas_stride)n2, info, 2 * L * G));
   for (int l = L - 1; l >= 0; --l) {
     SCW_HIP(hipMemcpyAsync(dA.p, dF.p, gn * 16 * 2, hipMemcpyDeviceToDevice, st));
     // A1 = X^-1 Fe, A2 = Y^-1 Fh with the factors of the batched call
-    SCW_BLAS(rocsolver_zgetrs_strided_batched(
-        h, N, n2, n2, zp(dXYlu, (size_t)(2 * l) * gn), n2, snn,
-        xypiv + (size_t)(2 * l) * G * n2, (rocblas_stride)n2, zp(dA), n2, snn, 2 * G));
+    if ((rc = substitute(n2, n2, zp(dXYlu, (size_t)(2 * l) * gn),
+                         xypiv + (size_t)(2 * l) * G * n2, zp(dA), snn, 2 * G)))
+      return rc;
     // G_t, G_b in place; t = G_t^-1; r = G_b t
     double* A2 = dA.as<double>() + 2 * gn;
     SCW_HIP(launch_half_sum_diff(dA.as<double>(), A2, (long long)gn, st));
@@ -561,8 +579,7 @@ int solve_stable_device(Context& ctx, int G, Solution* const* sols,
     SCW_HIP(launch_eye(reinterpret_cast<double*>(tl), n2, st, G));
     SCW_BLAS(rocsolver_zgetrf_strided_batched(h, n2, n2, zp(dA), n2, snn, piv, (rocblas_stride)n2,
                                               info + (size_t)(2 * L + l) * G, G));
-    SCW_BLAS(rocsolver_zgetrs_strided_batched(h, N, n2, n2, zp(dA), n2, snn, piv,
-                                              (rocblas_stride)n2, zx(tl), n2, snn, G));
+    if ((rc = substitute(n2, n2, zp(dA), piv, zx(tl), snn, G))) return rc;
     SCW_BLAS(rocblas_zgemm_strided_batched(h, N, N, n2, n2, n2, &one, zp(dA, gn), n2, snn, zx(tl),
                                            n2, snn, &zero, zx(rl), n2, snn, G));
     // F_l = [X (I + E r E); Y (I - E r E)]
@@ -592,9 +609,7 @@ int solve_stable_device(Context& ctx, int G, Solution* const* sols,
                             dF.as<double>() + 2 * gn, n2, G, dS.as<double>(), st));
   SCW_BLAS(rocsolver_zgetrf_strided_batched(h, n4, n4, zp(dS), n4, (rocblas_stride)n4 * n4, piv,
                                             (rocblas_stride)n4, info + (size_t)3 * L * G, G));
-  SCW_BLAS(rocsolver_zgetrs_strided_batched(h, N, n4, K, zp(dS), n4, (rocblas_stride)n4 * n4, piv,
-                                            (rocblas_stride)n4, zp(drhs), n4,
-                                            (rocblas_stride)n4k, G));
+  if ((rc = substitute(n4, K, zp(dS), piv, zp(drhs), (rocblas_stride)n4k, G))) return rc;
   std::vector<rocblas_int> hinfo((size_t)(3 * L + 1) * G);
   SCW_HIP(hipMemcpyAsync(hinfo.data(), info, hinfo.size() * sizeof(rocblas_int),
                          hipMemcpyDeviceToHost, st));
