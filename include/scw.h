@@ -210,7 +210,8 @@ int scw_solve_batch(scw_ctx* ctx, const scw_problem* probs, int n, scw_solution*
  *   w_dev      device complex128 [count][n]: the eigenvalues;
  *   X_dev      device complex128 [count][n][n], column-major: column j is a
  *              unit-norm eigenvector of eigenvalue j.
- * Workspace (about 3 count n^2 x 16 bytes) is allocated and freed by the call,
+ * Workspace (about 3 count n^2 x 16 bytes, 5 up to n = 64 and a few KB a
+ * matrix) is allocated and freed by the call,
  * which blocks until the result is ready. Errors: SCW_EINVAL for a bad size
  * or null pointer; SCW_ELAPACK when the QR iteration of a matrix does not
  * converge (the message names the matrix); SCW_ENOMEM, SCW_EHIP. */

@@ -35,6 +35,40 @@ int blas_handle(Context& ctx, hipStream_t st, void** out) {
   return SCW_OK;
 }
 
+namespace {
+// The eigensolver's workspace, one allocation (each costs microseconds) of six
+// regions, each for all matrices: Z, the row-major copy, the states, the sweep
+// headers, the reduction's panels where they need more than the row-major copy's
+// region (free until the iteration is done), and the rotations. Matrices that
+// stay in LDS get room for the rotations of a whole iteration, as another launch
+// costs more than their sweeps (100 matrices of order 8: 377 us a call, 562 in
+// four launches; 16 of order 50: 3.86 ms, 4.23).
+struct EigWork {
+  size_t part[6];  // bytes per matrix
+  size_t capr;
+  int caps;
+  explicit EigWork(int n) {
+    const size_t nn = (size_t)n * n;
+    capr = n <= 64 ? 2 * nn + 64 : nn / 2 + n;
+    caps = 4 * n + 64;
+    const size_t hess = eig_hessenberg_work(n);
+    const size_t p[6] = {nn * 16, nn * 16, 8 * sizeof(int), (size_t)caps * 16,
+                         hess > nn * 16 ? hess : 0, capr * 24};
+    std::copy(p, p + 6, part);
+  }
+  size_t at(size_t count, int k) const {  // offset of region k, 256-byte aligned
+    size_t o = 0;
+    for (int i = 0; i < k; ++i) o += (part[i] * count + 255) / 256 * 256;
+    return o;
+  }
+};
+}  // namespace
+
+size_t eig_matrix_bytes(int n) {
+  const EigWork wk(n);
+  return wk.at(1, 6);
+}
+
 int device_eig_batched(Context& ctx, int n, int count, double* A, double* w, double* X,
                        hipStream_t st) {
   if (n < 1 || n > kEigMaxN || count < 1)
@@ -43,39 +77,34 @@ int device_eig_batched(Context& ctx, int n, int count, double* A, double* w, dou
   if (!A || !w || !X) return fail(SCW_EINVAL, "batched eigensolver: null pointer");
   SCW_HIP(hipSetDevice(ctx.device));
   const size_t nn = (size_t)n * n;
-  DevBuf dZ, dTt, dstate, drot, dhdr;
-  int rc;
+  const EigWork wk(n);
   // A usual iteration has about 1.25 n^2 rotations per matrix and takes three
-  // launches with this record; another launch costs tens of microseconds, so
-  // less is taken where memory is short.
+  // launches with a record of n^2 / 2; another launch costs tens of microseconds,
+  // so less is taken where memory is short.
   EigRecord rec{};
-  size_t capr = nn / 2 + n;
-  rec.caps = 4 * n + 64;
-  if ((rc = dZ.reserve(nn * 16 * count)) || (rc = dTt.reserve(nn * 16 * count)) ||
-      (rc = dstate.reserve(sizeof(int) * 8 * count)) ||
-      (rc = dhdr.reserve((size_t)rec.caps * 16 * count)))
-    return rc;
-  while ((rc = drot.reserve(capr * 24 * count)) == SCW_ENOMEM && capr > (size_t)n)
+  size_t capr = wk.capr;
+  rec.caps = wk.caps;
+  const size_t o_tt = wk.at(count, 1), o_state = wk.at(count, 2), o_hdr = wk.at(count, 3),
+               o_hess = wk.part[4] ? wk.at(count, 4) : o_tt, o_rot = wk.at(count, 5);
+  DevBuf work;
+  int rc;
+  while ((rc = work.reserve(o_rot + capr * 24 * count)) == SCW_ENOMEM && capr > (size_t)n)
     capr = std::max<size_t>(n, capr / 4);
   if (rc) return rc;
+  char* base = work.as<char>();
+  double* Z = reinterpret_cast<double*>(base);
+  double* Tt = reinterpret_cast<double*>(base + o_tt);
+  double* hwork = reinterpret_cast<double*>(base + o_hess);
   rec.capr = (int)capr;
-  rec.state = dstate.as<int>();
-  rec.rots = drot.as<double>();
-  rec.rotc = drot.as<double>() + 2 * capr * count;
-  rec.hdr = dhdr.as<int>();
-  // the row-major copy's buffer is free until the iteration is done; small
-  // matrices need more for the reduction's panels than it holds
-  DevBuf dhess;
-  double* hwork = dTt.as<double>();
-  if (eig_hessenberg_work(n) > nn * 16) {
-    if ((rc = dhess.reserve(eig_hessenberg_work(n) * count))) return rc;
-    hwork = dhess.as<double>();
-  }
-  SCW_HIP(launch_eig_hessenberg(n, count, A, dZ.as<double>(), hwork, st));
+  rec.state = reinterpret_cast<int*>(base + o_state);
+  rec.hdr = reinterpret_cast<int*>(base + o_hdr);
+  rec.rots = reinterpret_cast<double*>(base + o_rot);
+  rec.rotc = rec.rots + 2 * capr * count;
+  SCW_HIP(launch_eig_hessenberg(n, count, A, Z, hwork, st));
   SCW_HIP(launch_eig_schur_begin(n, count, rec.state, st));
   std::vector<int> state(8 * (size_t)count);
   for (bool done = false; !done;) {
-    SCW_HIP(launch_eig_schur(n, count, A, dZ.as<double>(), w, rec, st));
+    SCW_HIP(launch_eig_schur(n, count, A, Z, w, rec, st));
     SCW_HIP(hipMemcpyAsync(state.data(), rec.state, state.size() * sizeof(int),
                            hipMemcpyDeviceToHost, st));
     SCW_HIP(hipStreamSynchronize(st));
@@ -88,14 +117,14 @@ int device_eig_batched(Context& ctx, int n, int count, double* A, double* w, dou
                                    std::to_string(b) + " did not converge at eigenvalue " +
                                    std::to_string(state[8 * (size_t)b + 3] - 1));
   // the Schur factor's eigenvectors overwrite A once it is copied row-major
-  SCW_HIP(launch_eig_vectors(n, count, A, dTt.as<double>(), w, A, st));
+  SCW_HIP(launch_eig_vectors(n, count, A, Tt, w, A, st));
   void* hv = nullptr;
   if ((rc = blas_handle(ctx, st, &hv))) return rc;
   rocblas_handle h = static_cast<rocblas_handle>(hv);
   const rocblas_double_complex one = {1.0, 0.0}, zero = {0.0, 0.0};
   const rocblas_status bs = rocblas_zgemm_strided_batched(
       h, rocblas_operation_none, rocblas_operation_none, n, n, n, &one,
-      reinterpret_cast<const rocblas_double_complex*>(dZ.p), n, (rocblas_stride)nn,
+      reinterpret_cast<const rocblas_double_complex*>(Z), n, (rocblas_stride)nn,
       reinterpret_cast<const rocblas_double_complex*>(A), n, (rocblas_stride)nn, &zero,
       reinterpret_cast<rocblas_double_complex*>(X), n, (rocblas_stride)nn, count);
   if (bs != rocblas_status_success) return blas_fail("rocblas_zgemm_strided_batched", bs);

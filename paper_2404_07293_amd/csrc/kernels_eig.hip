@@ -1142,9 +1142,9 @@ hipError_t launch_eig_hessenberg(int n, int count, double* A, double* Z, double*
   double2* a = reinterpret_cast<double2*>(A);
   double2* z = reinterpret_cast<double2*>(Z);
   double2* w = reinterpret_cast<double2*>(work);
-  eig_hessenberg_kernel<<<count, 1024, lds, s>>>(n, a, w);
+  if (n > 2) eig_hessenberg_kernel<<<count, 1024, lds, s>>>(n, a, w);
   eig_hess_apply_kernel<<<dim3((n + 63) / 64, count, 2), 256, 0, s>>>(n, a, z, w);
-  eig_hess_clear_kernel<<<dim3(n, count), 256, 0, s>>>(n, a);
+  if (n > 2) eig_hess_clear_kernel<<<dim3(n, count), 256, 0, s>>>(n, a);
   return hipGetLastError();
 }
 

@@ -270,6 +270,8 @@ constexpr int kEigMaxN = SCW_EIG_MAX_N;
 // [count][n] and unit-norm eigenvectors X [count][n][n]. Blocks until done.
 int device_eig_batched(Context& ctx, int n, int count, double* A, double* w, double* X,
                        hipStream_t st);
+// Workspace that a call takes per matrix where memory is not short.
+size_t eig_matrix_bytes(int n);
 // The context's rocBLAS handle (created on first use), bound to stream st.
 int blas_handle(Context& ctx, hipStream_t st, void** out);
 // Fails with a rocBLAS or rocSOLVER status: SCW_ENOMEM where its workspace could

@@ -1481,8 +1481,7 @@ int solve_problem(Context& ctx, const scw_problem& p, Solution& s, int n_waves,
 int solve_problems(Context& ctx, const scw_problem* probs, int n, Solution** sols) {
   // in rounds of problems whose device eigendecompositions share launches:
   // problems of one round with the same matrix order form one batch
-  // per layer A, C, X, A C, and the eigensolver's Z, row-major copy and rotation
-  // record (three quarters of a block): seven 2M x 2M blocks
+  // of up to this size: per layer A, C, X, A C and the eigensolver's workspace
   const size_t kRoundBytes = (size_t)24 << 30;
   int i0 = 0;
   while (i0 < n) {
@@ -1490,8 +1489,9 @@ int solve_problems(Context& ctx, const scw_problem* probs, int n, Solution** sol
     size_t bytes = 0;
     int i1 = i0;
     while (i1 < n) {
-      const size_t nn = 4 * (size_t)probs[i1].U * probs[i1].V * probs[i1].U * probs[i1].V;
-      const size_t need = nn * 16 * 7 * (size_t)std::max(1, probs[i1].nz);
+      const size_t n2 = 2 * (size_t)std::max(1, probs[i1].U) * std::max(1, probs[i1].V);
+      const size_t need = (4 * n2 * n2 * 16 + eig_matrix_bytes((int)std::min<size_t>(n2, kEigMaxN))) *
+                          (size_t)std::max(1, probs[i1].nz);
       if (i1 > i0 && bytes + need > kRoundBytes) break;
       bytes += need;
       ++i1;

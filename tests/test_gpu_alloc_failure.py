@@ -83,6 +83,22 @@ def test_eigensolver_goes_on_with_a_shorter_record(ctx):
     assert not failed and survived == 1
 
 
+@pytest.mark.parametrize("n", [2, 3, 8, 16, 40, 64])
+def test_small_matrices_with_a_shorter_record(ctx, n):
+    """Orders whose whole iteration is recorded in one launch, and with the record
+    that is taken when that does not fit: several launches, the same rotations."""
+    import torch
+    rng = np.random.default_rng(n)
+    A = torch.from_numpy(rng.standard_normal((5, n, n)) +
+                         1j * rng.standard_normal((5, n, n))).cuda()
+    norm = float(torch.linalg.matrix_norm(A, ord=2).max())
+    for k in (0, 1):  # no allocation, the first one
+        w, X = _failing(ctx, k, lambda: ctx.eig_batched(A))[0]
+        r = A @ X.contiguous() - X * w[:, None, :]
+        assert float(torch.linalg.vector_norm(r, dim=1).max()) <= 1e-12 * norm * n
+        assert float((torch.linalg.vector_norm(X, dim=1) - 1).abs().max()) <= 1e-14 * n
+
+
 def test_solve_batch_goes_on_in_smaller_groups(ctx):
     """Three problems that share an elimination: each of the group's allocations
     may fail and leave smaller groups. 1e-10, as other orders of rounding."""
