@@ -41,7 +41,7 @@ namespace {
 // headers, the reduction's panels where they need more than the row-major copy's
 // region (free until the iteration is done), and the rotations. Matrices that
 // stay in LDS get room for the rotations of a whole iteration, as another launch
-// costs more than their sweeps (100 matrices of order 8: 377 us a call, 562 in
+// costs more than their sweeps (100 matrices of order 8: 370 us a call, 562 in
 // four launches; 16 of order 50: 3.86 ms, 4.23).
 struct EigWork {
   size_t part[6];  // bytes per matrix

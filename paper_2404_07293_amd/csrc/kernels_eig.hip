@@ -299,7 +299,7 @@ eig_hessenberg_kernel(int n, double2* __restrict__ Aall, double2* __restrict__ w
 #pragma unroll
       for (int p = 0; p < NB; ++p) w[p] = Wb[(size_t)p * n + c];
 #pragma unroll 1
-      for (int q = 0; q < NB; ++q) {
+      for (int q = 0; q < jn; ++q) {
         const double2 vc = cconj(V[(size_t)q * n + c]);
 #pragma unroll
         for (int p = 0; p < NB; ++p) w[p] = csub(w[p], cmul(s_S[p][q], vc));
